@@ -84,6 +84,8 @@ static void upload_values(pamg_hierarchy* h, DevVals<T>& V, const std::vector<La
     if (h->smoother == PAMG_SMOOTHER_HYBRID_GS || h->smoothed_p) {   // smoothed: host-built hierarchies only
         V.gsa.assign(nl, nullptr);
         V.gst.assign(nl, nullptr);
+        V.gsw_f.assign(nl, nullptr);
+        V.gsw_b.assign(nl, nullptr);
         V.zt.assign(nl, nullptr);
         V.sa_pv.assign(nl, nullptr);
         V.sa_tv.assign(nl, nullptr);
@@ -101,6 +103,11 @@ static void upload_values(pamg_hierarchy* h, DevVals<T>& V, const std::vector<La
                     V.gsa[l] = upload<T>(h, lay[l - m].gs.ainv, s);
                 }
                 V.gst[l] = dalloc<T>(h, n, s);
+                if (gs_dense_level(h, l)) {
+                    const size_t w = (size_t)h->idx[l].gs_nblk * gs_dense_block(h->gs_block);
+                    V.gsw_f[l] = dalloc<T>(h, w, s);
+                    V.gsw_b[l] = dalloc<T>(h, w, s);
+                }
             }
             if (h->smoothed_p) {
                 V.sa_pv[l] = upload<T>(h, lay[l - m].sa_pv, s);
@@ -125,6 +132,29 @@ static void upload_values(pamg_hierarchy* h, DevVals<T>& V, const std::vector<La
     V.dbg_in = dalloc<T>(h, maxn, s);
     V.dbg_in2 = dalloc<T>(h, maxn, s);
     V.built = true;
+}
+
+bool gs_dense_level(const pamg_hierarchy* h, int l) {
+    const DevLevelIdx& I = h->idx[l];
+    return h->smoother == PAMG_SMOOTHER_HYBRID_GS && l < h->L && I.nnz >= (long long)kGsDenseRow * I.n;
+}
+
+void build_gs_dense(pamg_hierarchy* h, int l, hipStream_t s) {
+    const DevLevelIdx& I = h->idx[l];
+    DevVals<double>& V = h->f64;
+    const int ns = gs_strips(h->gs_block);
+    const dim3 g((unsigned)(I.gs_nblk * ns * (kGsTile / kGsInvCols)));
+    hipLaunchKernelGGL((k_gs_invert<false>), g, dim3(64), 0, s, I.n, h->gs_block, ns, (const int*)I.ci,
+                       (const double*)V.v[l], I.gs_fresh, (const double*)V.gsa[l], V.gsw_f[l]);
+    hipLaunchKernelGGL((k_gs_invert<true>), g, dim3(64), 0, s, I.n, h->gs_block, ns, (const int*)I.ci,
+                       (const double*)V.v[l], I.gs_fresh, (const double*)V.gsa[l], V.gsw_b[l]);
+    if (h->f32.built) {
+        const long long w = (long long)I.gs_nblk * gs_dense_block(h->gs_block);
+        hipLaunchKernelGGL((k_convert<double, float>), dim3(vec_grid(w)), dim3(kBlock), 0, s, w,
+                           (const double*)V.gsw_f[l], h->f32.gsw_f[l]);
+        hipLaunchKernelGGL((k_convert<double, float>), dim3(vec_grid(w)), dim3(kBlock), 0, s, w,
+                           (const double*)V.gsw_b[l], h->f32.gsw_b[l]);
+    }
 }
 
 // Matrix bytes of one pass over a level in the tile format: values, 16-bit
@@ -265,6 +295,9 @@ void upload_hierarchy(pamg_hierarchy* h, const std::vector<LayoutLevel>& lay, bo
     }
     upload_values<double>(h, h->f64, lay, db, s);
     if (build_f32) upload_values<float>(h, h->f32, lay, db, s);
+    if (h->smoother == PAMG_SMOOTHER_HYBRID_GS)
+        for (int l = 0; l < h->L; ++l)
+            if (gs_dense_level(h, l)) build_gs_dense(h, l, s);
     const int n0 = h->idx[0].n;
     int maxn = 0;
     for (auto& I : h->idx) maxn = std::max(maxn, I.n);
@@ -491,46 +524,44 @@ static int coarse_partials(int nL) { return nL > kCoarseRowsMin ? coarse_rows_gr
 // ---------------------------------------------------------------- schedule
 
 // One hybrid Gauss-Seidel sweep at level l from x_old into x_new (zero: from
-// x_old = 0, the first pre-smoothing sweep, which needs no residual pass).
-template <int MAXB, typename T, typename RT, int RB>
-static void launch_hgs_rb(pamg_hierarchy* h, DevVals<T>& V, int l, const RT* r, const T* x_old, T* x_new,
-                          bool backward, bool zero, const int* done, hipStream_t s) {
-    const DevLevelIdx& I = h->idx[l];
-    const T winv = (T)(1.0 / h->omega);
-    const dim3 g(I.gs_nblk), blk(MAXB);
-    if (zero) {
-        hipLaunchKernelGGL((k_hgs<MAXB, T, RT, false, true, RB>), g, blk, 0, s, I.n, h->gs_block, (const int*)I.ci,
-                           (const T*)V.v[l], I.gs_fresh, (const T*)V.gsa[l], I.gs_df, I.gs_maxd, r,
-                           (const T*)nullptr, x_new, winv, done);
-        return;
-    }
-    // t = r - A x_old through the row tiles
-    launch_resid<T, T, T, RT>(I, V.v[l], x_old, r, V.gst[l], s);
-    if (backward)
-        hipLaunchKernelGGL((k_hgs<MAXB, T, T, true, false, RB>), g, blk, 0, s, I.n, h->gs_block, (const int*)I.ci,
-                           (const T*)V.v[l], I.gs_fresh, (const T*)V.gsa[l], I.gs_db, I.gs_maxd, (const T*)V.gst[l],
-                           x_old, x_new, winv, done);
-    else
-        hipLaunchKernelGGL((k_hgs<MAXB, T, T, false, false, RB>), g, blk, 0, s, I.n, h->gs_block, (const int*)I.ci,
-                           (const T*)V.v[l], I.gs_fresh, (const T*)V.gsa[l], I.gs_df, I.gs_maxd, (const T*)V.gst[l],
-                           x_old, x_new, winv, done);
-}
-
-// One sweep.  A level whose rows average kGsWideRow entries or more
-// (smoothed coarse levels) loads the in-block entries past the registers
-// kGsWideBatch at a time instead of kGsBatch, at the price of registers (two
-// waves per SIMD): with blocks of 256 rows (many in-block entries per row),
-// or with one-wave blocks when the level's waves fit the chip in one round.
+// x_old = 0, the first pre-smoothing sweep, which needs no residual pass):
+// the product with the inverted blocks on levels with long rows, the
+// substitution on the others.
 template <int MAXB, typename T, typename RT>
 static void launch_hgs(pamg_hierarchy* h, DevVals<T>& V, int l, const RT* r, const T* x_old, T* x_new, bool backward,
                        bool zero, const int* done, hipStream_t s) {
     const DevLevelIdx& I = h->idx[l];
-    constexpr long long kWideWaves = 256LL * 4 * 2;  // CUs x SIMDs x waves per SIMD of the wide form
-    const bool long_rows = I.nnz >= (long long)kGsWideRow * I.n;
-    if (long_rows && (MAXB > kGsSmallBlock || (long long)I.gs_nblk * (MAXB / 64) <= kWideWaves))
-        launch_hgs_rb<MAXB, T, RT, kGsWideBatch>(h, V, l, r, x_old, x_new, backward, zero, done, s);
+    const T winv = (T)(1.0 / h->omega);
+    // t = r - A x_old through the row tiles
+    if (!zero) launch_resid<T, T, T, RT>(I, V.v[l], x_old, r, V.gst[l], s);
+    const T* t = V.gst[l];
+    if (V.gsw_f[l]) {
+        const int nb = h->gs_block, ns = gs_strips(nb);
+        const int g = I.gs_nblk * ns;
+        if (zero)
+            LAUNCH((k_hgs_dense<T, RT, false, true>), g, 0, s, I.n, nb, ns, (const T*)V.gsw_f[l], r,
+                   (const T*)nullptr, x_new, winv, done);
+        else if (backward)
+            LAUNCH((k_hgs_dense<T, T, true, false>), g, 0, s, I.n, nb, ns, (const T*)V.gsw_b[l], t, x_old, x_new,
+                   winv, done);
+        else
+            LAUNCH((k_hgs_dense<T, T, false, false>), g, 0, s, I.n, nb, ns, (const T*)V.gsw_f[l], t, x_old, x_new,
+                   winv, done);
+        return;
+    }
+    const dim3 g(I.gs_nblk), blk(MAXB);
+    if (zero)
+        hipLaunchKernelGGL((k_hgs<MAXB, T, RT, false, true>), g, blk, 0, s, I.n, h->gs_block, (const int*)I.ci,
+                           (const T*)V.v[l], I.gs_fresh, (const T*)V.gsa[l], I.gs_df, I.gs_maxd, r,
+                           (const T*)nullptr, x_new, winv, done);
+    else if (backward)
+        hipLaunchKernelGGL((k_hgs<MAXB, T, T, true, false>), g, blk, 0, s, I.n, h->gs_block, (const int*)I.ci,
+                           (const T*)V.v[l], I.gs_fresh, (const T*)V.gsa[l], I.gs_db, I.gs_maxd, t, x_old, x_new,
+                           winv, done);
     else
-        launch_hgs_rb<MAXB, T, RT, kGsBatch>(h, V, l, r, x_old, x_new, backward, zero, done, s);
+        hipLaunchKernelGGL((k_hgs<MAXB, T, T, false, false>), g, blk, 0, s, I.n, h->gs_block, (const int*)I.ci,
+                           (const T*)V.v[l], I.gs_fresh, (const T*)V.gsa[l], I.gs_df, I.gs_maxd, t, x_old, x_new,
+                           winv, done);
 }
 
 // `sweeps` hybrid Gauss-Seidel sweeps at level l on A_l x = r: forward from

@@ -52,6 +52,7 @@ struct DevVals {
     std::vector<T*> r, zp;            // V-cycle workspace: r_l (l >= 1), zp_l (l < L)
     std::vector<T*> gsa, zt;          // hybrid GS: 1 / a_ii and a second iterate buffer (l < L)
     std::vector<T*> gst;              // hybrid GS: residual of the old iterate (l < L)
+    std::vector<T*> gsw_f, gsw_b;     // hybrid GS: inverted blocks (levels with long rows; else null)
     std::vector<T*> sa_pv, sa_tv;     // smoothed prolongator: values of P and P^T (l < L)
     T* zc = nullptr;                  // hybrid GS: coarsest-level solution
     T* ainv = nullptr;                // dense A_L^{-1}
@@ -168,6 +169,11 @@ inline T* dalloc(pamg_hierarchy* h, size_t count, hipStream_t s = nullptr) {
     h->info.device_bytes += bytes;
     return static_cast<T*>(p);
 }
+
+// Hybrid Gauss-Seidel levels whose blocks are inverted (kernels_gs.hpp), and
+// the inversion from the level's current values (both precisions).
+bool gs_dense_level(const pamg_hierarchy* h, int l);
+void build_gs_dense(pamg_hierarchy* h, int l, hipStream_t s);
 
 inline int vec_grid(long long n) {
     long long g = (n + kBlock - 1) / kBlock;

@@ -25,14 +25,13 @@ constexpr int kGsSmallBlock = 64;     // blocks of <= 64 rows run one wave per w
 constexpr int kGsFresh = 16;          // in-block entries of a row held in registers
 static_assert(kGsFresh % 4 == 0, "the substitution reads its slots in groups of four");
 constexpr int kGsBatch = 8;           // entries past those loaded together in a depth step
-constexpr int kGsWideBatch = 32;      // the same on levels with long rows (few blocks, registers to spare)
-constexpr int kGsWideRow = 64;        // mean row length from which a level takes the wide batch
+constexpr int kGsDenseRow = 64;       // mean row length from which a level's blocks are inverted (k_hgs_dense)
 
 // One sweep from t = r - A x_old (ZERO: x_old = 0 and t = r, the first
 // pre-smoothing sweep).  Row i of the block: d_i = (t_i - sum_{fresh j}
 // a_ij d_j) / a_ii with fresh = in the block and earlier (forward) / later
 // (backward), in column order; x_new = x_old + d / omega.
-template <int MAXB, typename T, typename TT, bool BACKWARD, bool ZERO, int RB = kGsBatch>
+template <int MAXB, typename T, typename TT, bool BACKWARD, bool ZERO>
 static __global__ __launch_bounds__(MAXB) void k_hgs(
     int n, int nb, const int* __restrict__ ci, const T* __restrict__ av, const int2* __restrict__ fr,
     const T* __restrict__ ainv, const uint8_t* __restrict__ depth, const int* __restrict__ maxd,
@@ -93,43 +92,150 @@ static __global__ __launch_bounds__(MAXB) void k_hgs(
                     for (int u = 0; u < 4; ++u) fresh += fa[g + u] * dj[u];
                 }
             }
-            // entries past the registers: RB at a time, loaded together at
-            // clamped indices, added in order.  The wide form (long coarse
-            // rows, registers to spare) also issues the batch's LDS reads
-            // together (a slot past the row adds exactly +0); the narrow one
-            // keeps a branch per entry, which holds the level-0 kernels'
-            // registers down
-            for (int k0 = kf + kGsFresh; k0 < kf + nf; k0 += RB) {
-                T ab[RB];
-                int cb[RB];
+            // entries past the registers: kGsBatch at a time, loaded together
+            // at clamped indices, added in order, a branch per entry (it
+            // holds the level-0 kernels' registers down)
+            for (int k0 = kf + kGsFresh; k0 < kf + nf; k0 += kGsBatch) {
+                T ab[kGsBatch];
+                int cb[kGsBatch];
 #pragma unroll
-                for (int u = 0; u < RB; ++u) {
+                for (int u = 0; u < kGsBatch; ++u) {
                     const int k = min(k0 + u, kf + nf - 1);
                     ab[u] = av[k];
                     cb[u] = ci[k] - b0;
                 }
-                if constexpr (RB > kGsBatch) {
 #pragma unroll
-                    for (int u = 0; u < RB; ++u) {
-                        ab[u] = k0 + u < kf + nf ? ab[u] : T(0);
-                        cb[u] = k0 + u < kf + nf ? cb[u] : 0;
-                    }
-                    T db[RB];
-#pragma unroll
-                    for (int u = 0; u < RB; ++u) db[u] = s_d[cb[u]];
-#pragma unroll
-                    for (int u = 0; u < RB; ++u) fresh += ab[u] * db[u];
-                } else {
-#pragma unroll
-                    for (int u = 0; u < RB; ++u)
-                        if (k0 + u < kf + nf) fresh += ab[u] * s_d[cb[u]];
-                }
+                for (int u = 0; u < kGsBatch; ++u)
+                    if (k0 + u < kf + nf) fresh += ab[u] * s_d[cb[u]];
             }
             s_d[t] = (ti - fresh) * ai;
         }
         __syncthreads();
     }
     if (own) x_new[i] = xi + s_d[t] * omega_inv;
+}
+
+// ----------------------------------------------------------------------------
+// Levels with long rows (kGsDenseRow entries or more on average: smoothed
+// Galerkin levels).  A block of 256 such rows is almost a dense triangle (59
+// to 72 in-block entries before a row, mean depth 188 to 202 of 255), so its
+// substitution is a chain of about 200 steps, each waiting on memory for the
+// row's entries: 780 us a sweep on a level of 23,032 rows, whatever its size.
+// The triangles are inverted instead, once at setup: W = (L_pp + D_pp)^-1
+// (backward: (U_pp + D_pp)^-1), and a sweep is one product d = W t, with no
+// chain and about the substitution's bytes (a row of W holds at most its
+// position in the block: 160 values on average, against 60 to 70 values and
+// columns).  On levels with short rows the substitution stays: level 0 of the
+// 27-point operator holds 3 to 4 in-block entries a row, so W would be twice
+// the whole matrix (45 us a sweep there, against 47 us for W's bytes alone).
+//
+// W is stored in 64 x 64 tiles, column-major inside a tile, so that the 64
+// lanes of a wave (one row each) read 512 consecutive bytes per column; only
+// the tiles on and below (backward: above) the diagonal are kept.
+constexpr int kGsTile = 64;
+constexpr int kGsInvCols = 16;        // columns of W one wave computes
+
+inline int gs_strips(int nb) { return (nb + kGsTile - 1) / kGsTile; }
+inline long long gs_dense_block(int nb) {            // values of W per block and direction
+    const long long ns = gs_strips(nb);
+    return ns * (ns + 1) / 2 * kGsTile * kGsTile;
+}
+// First value of tile (row strip s, column strip q) inside a block's W.
+template <bool BACKWARD>
+__device__ __forceinline__ int gs_tile_offset(int ns, int s, int q) {
+    return (BACKWARD ? s * ns - s * (s - 1) / 2 + (q - s) : s * (s + 1) / 2 + q) * (kGsTile * kGsTile);
+}
+
+// Columns c0 .. c0 + 15 of W for block p (grid: blocks x 16-column groups, one
+// wave each): substitution on columns of the identity, rows in order, the
+// wave's four 16-lane groups taking every fourth in-block entry of a row and
+// meeting in a fixed butterfly.  Rows and columns past the block are zero.
+template <bool BACKWARD>
+static __global__ __launch_bounds__(64) void k_gs_invert(int n, int nb, int ns, const int* __restrict__ ci,
+                                                         const double* __restrict__ av, const int2* __restrict__ fr,
+                                                         const double* __restrict__ ainv, double* __restrict__ W) {
+    __shared__ double S[kGsMaxBlock][kGsInvCols + 1];
+    const int groups = ns * (kGsTile / kGsInvCols);
+    const int p = blockIdx.x / groups, c0 = (blockIdx.x % groups) * kGsInvCols;
+    const int lane = threadIdx.x, c = lane % kGsInvCols, part = lane / kGsInvCols;
+    const int b0 = p * nb, m = min(n - b0, nb);
+    for (int e = lane; e < ns * kGsTile * kGsInvCols; e += 64) S[e / kGsInvCols][e % kGsInvCols] = 0.0;
+    __syncthreads();
+    // forward: rows from the group's first column down; backward: from its last column up
+    const int first = BACKWARD ? min(c0 + kGsInvCols, m) - 1 : c0;
+    const int count = BACKWARD ? first + 1 : m - c0;
+    for (int u = 0; u < count; ++u) {
+        const int i = BACKWARD ? first - u : first + u;
+        const int2 f = fr[b0 + i];
+        const int before = f.y & 0xff, after = (f.y >> 8) & 0xff, diag = (f.y >> 16) & 1;
+        const int k0 = BACKWARD ? f.x + before + diag : f.x, k1 = k0 + (BACKWARD ? after : before);
+        double s = 0.0;
+#pragma unroll 4
+        for (int k = k0 + part; k < k1; k += 4) s += av[k] * S[ci[k] - b0][c];
+        s += __shfl_xor(s, 16, 64);
+        s += __shfl_xor(s, 32, 64);
+        if (part == 0) S[i][c] = ((i == c0 + c ? 1.0 : 0.0) - s) * ainv[b0 + i];
+        __syncthreads();
+    }
+    double* Wp = W + (size_t)p * (ns * (ns + 1) / 2 * kGsTile * kGsTile);
+    const int q = c0 / kGsTile;
+    for (int s = BACKWARD ? 0 : q; s < (BACKWARD ? q + 1 : ns); ++s) {
+        double* T = Wp + gs_tile_offset<BACKWARD>(ns, s, q) + (c0 % kGsTile) * kGsTile;
+        for (int cc = 0; cc < kGsInvCols; ++cc) T[cc * kGsTile + lane] = S[s * kGsTile + lane][cc];
+    }
+}
+
+// One sweep with the inverted blocks from t = r - A x_old (ZERO: x_old = 0,
+// t = r): x_new = x_old + (W t) / omega.  One workgroup per 64-row strip of a
+// block (90 blocks of 256 rows fill the chip four ways); wave g takes columns
+// g, g + 4, ... of each tile, the 16 loads of a tile issued together and the
+// next tile's before this one is used; the four waves' sums meet in LDS in a
+// fixed order.
+template <typename T, typename TT, bool BACKWARD, bool ZERO>
+static __global__ __launch_bounds__(kBlock) void k_hgs_dense(int n, int nb, int ns, const T* __restrict__ W,
+                                                             const TT* __restrict__ tin, const T* __restrict__ x_old,
+                                                             T* __restrict__ x_new, T omega_inv,
+                                                             const int* __restrict__ done) {
+    if (*done) return;
+    constexpr int G = kBlock / 64, C = kGsTile / G;
+    __shared__ T s_t[kGsMaxBlock];
+    __shared__ T s_part[G][kGsTile];
+    const int p = blockIdx.x / ns, s = blockIdx.x % ns;
+    const int b0 = p * nb, m = min(n - b0, nb);
+    const int lane = threadIdx.x & 63, g = threadIdx.x >> 6;
+    const int q0 = BACKWARD ? s : 0, q1 = BACKWARD ? ns : s + 1;
+    const T* __restrict__ Wp = W + (size_t)p * (ns * (ns + 1) / 2 * kGsTile * kGsTile) +
+                               gs_tile_offset<BACKWARD>(ns, s, q0) + g * kGsTile + lane;
+    T a[C];
+#pragma unroll
+    for (int u = 0; u < C; ++u) a[u] = Wp[u * G * kGsTile];
+    s_t[threadIdx.x] = (int)threadIdx.x < m ? (T)tin[b0 + threadIdx.x] : T(0);
+    const int i = s * kGsTile + lane;
+    const bool own = g == 0 && i < m;
+    T xi = 0;
+    if constexpr (!ZERO) xi = own ? x_old[b0 + i] : T(0);
+    __syncthreads();
+    T acc = 0;
+    for (int q = q0; q < q1; ++q) {
+        T cur[C];
+#pragma unroll
+        for (int u = 0; u < C; ++u) cur[u] = a[u];
+        Wp += kGsTile * kGsTile;
+        if (q + 1 < q1) {
+#pragma unroll
+            for (int u = 0; u < C; ++u) a[u] = Wp[u * G * kGsTile];
+        }
+#pragma unroll
+        for (int u = 0; u < C; ++u) acc += cur[u] * s_t[q * kGsTile + u * G + g];
+    }
+    s_part[g][lane] = acc;
+    __syncthreads();
+    if (own) {
+        T d = s_part[0][lane];
+#pragma unroll
+        for (int u = 1; u < G; ++u) d += s_part[u][lane];
+        x_new[b0 + i] = xi + d * omega_inv;
+    }
 }
 
 // Dense coarsest solve e = A_L^-1 r: one wave per row of the symmetric

@@ -227,6 +227,7 @@ static void update_values(pamg_hierarchy* h, const double* val, bool on_device, 
                 hipLaunchKernelGGL((k_convert<double, float>), dim3(vec_grid(I.n)), dim3(kBlock), 0, s,
                                    (long long)I.n, (const double*)V.gsa[j], h->f32.gsa[j]);
         }
+        if (gs_dense_level(h, j)) build_gs_dense(h, j, s);
     }
     HIP_CHECK(hipGetLastError());
     h->values_updated = true;
