@@ -8,12 +8,17 @@
 // (N = n rounded up to 64; the padding carries an identity diagonal, so the
 // factor and the inverse of the padded matrix are block-diagonal with the
 // wanted ones in the top-left corner):
-//   factor:  for each block column k: unblocked Cholesky of the diagonal tile
-//            and its triangular inverse in LDS; panel L_ik = A_ik L_kk^{-T};
-//            trailing update A_ij -= L_ik L_jk^T  (j <= i);
-//   inverse: X = L^{-1} by block forward substitution on the identity
-//            (X_ic = L_ii^{-1} X_ic, then X_mc -= L_mi X_ic for m > i);
-//            A^{-1} = X^T X on the lower block triangle, mirrored.
+//   for each block column k, two launches:
+//            panel L_ik = A_ik L_kk^{-T} and block row k of
+//            X = L^{-1} (X_kc = L_kk^{-1} X_kc, the block forward substitution
+//            on the identity); trailing update A_ij -= L_ik L_jk^T (j <= i)
+//            and X_mc -= L_mk X_kc (m > k), and in it the Cholesky factor of
+//            the next diagonal tile and its triangular inverse, in registers;
+//   then     A^{-1} = X^T X on the lower block triangle, mirrored.
+// The two halves need the same panel, so they share its launches (with five
+// launches a block column the substitution alone took 34 us of them).
+// n = 2675: 8.7 -> 2.8 ms (a block column: panel 13 us, update 43 us, of
+// which the next diagonal tile's serial factorization is the longer part).
 // Every tile product runs on the matrix cores (v_mfma_f64_16x16x4_f64): one
 // wave per 16-row strip of the 64 x 64 output tile, four 16-column tiles.
 // All sums have a fixed order, so the result is deterministic.
@@ -80,71 +85,128 @@ __global__ __launch_bounds__(kDenseThreads) void k_dense_eye(int N, double* __re
     if (i < N) X[(size_t)i * N + i] = 1.0;
 }
 
-// Diagonal tile kb: unblocked Cholesky in LDS (lower), written back with
-// zeros above the diagonal, and its triangular inverse into Dinv[kb].  A
-// pivot that is not positive sets *bad and is replaced by 1 so that the rest
-// stays finite; the host then reports the matrix as not positive definite.
-__global__ __launch_bounds__(kDenseThreads) void k_dense_potrf_tile(double* __restrict__ M, int N, int kb,
-                                                                    double* __restrict__ Dinv, int* __restrict__ bad) {
-    __shared__ double S[kT][kTP];
-    __shared__ double T[kT][kTP];
-    const int tid = threadIdx.x;
+// Diagonal tile kb: Cholesky factor (written back with zeros above the
+// diagonal) and its triangular inverse into Dinv[kb].  A pivot that is not
+// positive sets *bad and is replaced by 1 so that the rest stays finite; the
+// host then reports the matrix as not positive definite.
+//
+// This tile is the serial part of the factorization (one workgroup, one after
+// the other), so it is bound by the latency of its 64 column steps.  A thread
+// of the 16 x 16 grid holds 4 x 4 entries of the tile and of the inverse in
+// registers (rows ty + 16 a, columns tx + 16 b); a step exchanges only the
+// pivot column and one row of the inverse through LDS (two buffers, one
+// barrier), and both triangles are eliminated together: A_ic -= (a_ij / d_j)
+// a_cj and T_i -= (a_ij / d_j) T_j.  The square roots of the pivots stay out
+// of the chain and scale L and T at the end.  In LDS with three barriers a
+// step, and the inverse afterwards by one thread per column, the tile took
+// 126 us (5.3 of the 8.7 ms of n = 2675); now the update that contains it
+// takes 43 us.
+__device__ __forceinline__ void potrf_tile(double* M, int N, int kb, double* Dinv, int* bad) {
+    __shared__ double s_col[2][kT];     // column j of the tile (rows >= j)
+    __shared__ double s_row[2][kT];     // row j of the inverse
+    __shared__ double s_piv[kT];
+    const int tx = threadIdx.x % 16, ty = threadIdx.x / 16;
     double* G = M + (size_t)kb * kT * N + (size_t)kb * kT;
-    load_tile(S, G, N);
-    __syncthreads();
-    for (int j = 0; j < kT; ++j) {
-        if (tid == 0) {
-            double d = S[j][j];
-            if (!(d > 0.0)) {
-                *bad = 1;
-                d = 1.0;
+    double A[4][4], T[4][4];
+#pragma unroll
+    for (int a = 0; a < 4; ++a)
+#pragma unroll
+        for (int b = 0; b < 4; ++b) {
+            const int r = ty + 16 * a, c = tx + 16 * b;
+            A[a][b] = G[(size_t)r * N + c];
+            T[a][b] = r == c ? 1.0 : 0.0;
+        }
+#pragma unroll
+    for (int J = 0; J < 4; ++J) {
+#pragma unroll 1                        // (unrolled, the code outgrows the instruction cache)
+        for (int jj = 0; jj < 16; ++jj) {
+            const int j = 16 * J + jj, buf = j & 1;
+            if (tx == jj) {
+#pragma unroll
+                for (int a = 0; a < 4; ++a) s_col[buf][ty + 16 * a] = A[a][J];
             }
-            S[j][j] = sqrt(d);
-        }
-        __syncthreads();
-        const double djj = S[j][j];
-        for (int i = j + 1 + tid; i < kT; i += kDenseThreads) S[i][j] /= djj;
-        __syncthreads();
-        for (int e = tid; e < kT * kT; e += kDenseThreads) {
-            const int r = e / kT, c = e % kT;
-            if (c > j && r >= c) S[r][c] -= S[r][j] * S[c][j];
-        }
-        __syncthreads();
-    }
-    // column c of the inverse by forward substitution (one thread per column)
-    if (tid < kT) {
-        const int c = tid;
-        for (int i = 0; i < c; ++i) T[i][c] = 0.0;
-        T[c][c] = 1.0 / S[c][c];
-        for (int i = c + 1; i < kT; ++i) {
-            double s = 0.0;
-            for (int m = c; m < i; ++m) s += S[i][m] * T[m][c];
-            T[i][c] = -s / S[i][i];
+            if (ty == jj) {
+#pragma unroll
+                for (int b = 0; b < 4; ++b) s_row[buf][tx + 16 * b] = T[J][b];
+            }
+            __syncthreads();
+            double d = s_col[buf][j];
+            const bool spd = d > 0.0;
+            if (!spd) d = 1.0;
+            if (threadIdx.x == 0) {
+                s_piv[j] = d;
+                if (!spd) *bad = 1;
+            }
+            double li[4], ac[4], tr[4];
+            const double rd = 1.0 / d;
+#pragma unroll
+            for (int u = 0; u < 4; ++u) {
+                li[u] = s_col[buf][ty + 16 * u];
+                ac[u] = s_col[buf][tx + 16 * u];
+                tr[u] = s_row[buf][tx + 16 * u];
+            }
+            // an entry past its range contributes a zero factor (selected
+            // after the loads, which are issued together)
+#pragma unroll
+            for (int u = 0; u < 4; ++u) {
+                li[u] = ty + 16 * u > j ? li[u] * rd : 0.0;
+                ac[u] = tx + 16 * u > j ? ac[u] : 0.0;
+            }
+#pragma unroll
+            for (int a = 0; a < 4; ++a)
+#pragma unroll
+                for (int b = 0; b < 4; ++b) {
+                    A[a][b] -= li[a] * ac[b];
+                    T[a][b] -= li[a] * tr[b];
+                }
+            // no second barrier: the next step writes the other buffer, and
+            // this one only after the next barrier
         }
     }
     __syncthreads();
     double* D = Dinv + (size_t)kb * kT * kT;
-    for (int e = tid; e < kT * kT; e += kDenseThreads) {
-        const int r = e / kT, c = e % kT;
-        G[(size_t)r * N + c] = c <= r ? S[r][c] : 0.0;
-        D[e] = T[r][c];
+    double pc[4], pr[4];
+#pragma unroll
+    for (int u = 0; u < 4; ++u) {
+        pc[u] = sqrt(s_piv[tx + 16 * u]);
+        pr[u] = sqrt(s_piv[ty + 16 * u]);
     }
+#pragma unroll
+    for (int a = 0; a < 4; ++a)
+#pragma unroll
+        for (int b = 0; b < 4; ++b) {
+            const int r = ty + 16 * a, c = tx + 16 * b;
+            G[(size_t)r * N + c] = c < r ? A[a][b] / pc[b] : c == r ? pc[b] : 0.0;
+            D[r * kT + c] = c <= r ? T[a][b] / pr[a] : 0.0;
+        }
 }
 
-// Panel: L_ik = A_ik L_kk^{-T} for the row tiles i = kb+1+blockIdx.x.
-__global__ __launch_bounds__(kDenseThreads) void k_dense_panel(double* __restrict__ M, int N, int kb,
-                                                               const double* __restrict__ Dinv) {
+// The first diagonal tile; k_dense_update factors the others.
+__global__ __launch_bounds__(kDenseThreads) void k_dense_potrf_first(double* __restrict__ M, int N,
+                                                                     double* __restrict__ Dinv, int* __restrict__ bad) {
+    potrf_tile(M, N, 0, Dinv, bad);
+}
+
+// Blocks 0 .. t-1, the panel: L_ik = A_ik L_kk^{-T} for the row tiles
+// i = kb+1+block; blocks t .. t+kb, block row kb of X = L^{-1}:
+// X_kc = L_kk^{-1} X_kc for c = block - t.
+__global__ __launch_bounds__(kDenseThreads) void k_dense_panel(double* __restrict__ M, double* __restrict__ X, int N,
+                                                               int kb, int t, const double* __restrict__ Dinv) {
     __shared__ double Dk[kT][kTP];
     __shared__ double A[kT][kTP];
     const int wave = threadIdx.x / 64, lane = threadIdx.x % 64;
-    const int ib = kb + 1 + blockIdx.x;
-    double* G = M + (size_t)ib * kT * N + (size_t)kb * kT;
+    const int u = blockIdx.x;
+    double* G = u < t ? M + (size_t)(kb + 1 + u) * kT * N + (size_t)kb * kT
+                      : X + (size_t)kb * kT * N + (size_t)(u - t) * kT;
     load_tile(Dk, Dinv + (size_t)kb * kT * kT, kT);
     load_tile(A, G, N);
     __syncthreads();
     d4 acc[4];
     zero(acc);
-    strip_product(acc, wave, lane, [&](int r, int k) { return A[r][k]; }, [&](int k, int c) { return Dk[c][k]; });
+    if (u < t)
+        strip_product(acc, wave, lane, [&](int r, int k) { return A[r][k]; }, [&](int k, int c) { return Dk[c][k]; });
+    else
+        strip_product(acc, wave, lane, [&](int r, int k) { return Dk[r][k]; }, [&](int k, int c) { return A[k][c]; });
 #pragma unroll
     for (int ct = 0; ct < 4; ++ct)
 #pragma unroll
@@ -160,66 +222,46 @@ __device__ __forceinline__ void tri_index(long long p, int& i, int& j) {
     j = (int)(p - (long long)r * (r + 1) / 2);
 }
 
-// Trailing update: A_ij -= L_ik L_jk^T for kb < j <= i (one tile per block).
-__global__ __launch_bounds__(kDenseThreads) void k_dense_syrk(double* __restrict__ M, int N, int kb) {
-    __shared__ double Pi[kT][kTP];
-    __shared__ double Pj[kT][kTP];
+// Blocks 0 .. T-1, T = t (t + 1) / 2, the trailing update A_ij -= L_ik L_jk^T
+// for kb < j <= i (one tile per block); the others, X_mc -= L_mk X_kc for
+// m = kb+1 .. kb+t and c = 0 .. kb (block T + (m - kb - 1) * (kb + 1) + c).
+// Block 0 holds the next diagonal tile, which no other block touches: it
+// factors it straight away, beside the rest of the update.
+__global__ __launch_bounds__(kDenseThreads) void k_dense_update(double* M, double* X, int N, int kb, long long T,
+                                                                double* Dinv, int* bad) {
+    __shared__ double P[kT][kTP];
+    __shared__ double Q[kT][kTP];
     const int wave = threadIdx.x / 64, lane = threadIdx.x % 64;
-    int i, j;
-    tri_index(blockIdx.x, i, j);
-    const int ib = kb + 1 + i, jb = kb + 1 + j;
-    load_tile(Pi, M + (size_t)ib * kT * N + (size_t)kb * kT, N);
-    load_tile(Pj, M + (size_t)jb * kT * N + (size_t)kb * kT, N);
-    __syncthreads();
     d4 acc[4];
     zero(acc);
-    strip_product(acc, wave, lane, [&](int r, int k) { return Pi[r][k]; }, [&](int k, int c) { return Pj[c][k]; });
-    double* G = M + (size_t)ib * kT * N + (size_t)jb * kT;
+    double* G;
+    if (blockIdx.x < T) {
+        int i, j;
+        tri_index(blockIdx.x, i, j);
+        const int ib = kb + 1 + i, jb = kb + 1 + j;
+        load_tile(P, M + (size_t)ib * kT * N + (size_t)kb * kT, N);
+        load_tile(Q, M + (size_t)jb * kT * N + (size_t)kb * kT, N);
+        __syncthreads();
+        strip_product(acc, wave, lane, [&](int r, int k) { return P[r][k]; }, [&](int k, int c) { return Q[c][k]; });
+        G = M + (size_t)ib * kT * N + (size_t)jb * kT;
+    } else {
+        const int u = (int)(blockIdx.x - T);
+        const int m = kb + 1 + u / (kb + 1), c0 = u % (kb + 1);
+        load_tile(P, M + (size_t)m * kT * N + (size_t)kb * kT, N);
+        load_tile(Q, X + (size_t)kb * kT * N + (size_t)c0 * kT, N);
+        __syncthreads();
+        strip_product(acc, wave, lane, [&](int r, int k) { return P[r][k]; }, [&](int k, int c) { return Q[k][c]; });
+        G = X + (size_t)m * kT * N + (size_t)c0 * kT;
+    }
 #pragma unroll
     for (int ct = 0; ct < 4; ++ct)
 #pragma unroll
         for (int q = 0; q < 4; ++q) G[(size_t)res_row(wave, lane, q) * N + res_col(lane, ct)] -= acc[ct][q];
-}
-
-// X_ic = L_ii^{-1} X_ic for the block columns c = blockIdx.x <= i.
-__global__ __launch_bounds__(kDenseThreads) void k_dense_trmm(double* __restrict__ X, int N, int ib,
-                                                              const double* __restrict__ Dinv) {
-    __shared__ double Di[kT][kTP];
-    __shared__ double B[kT][kTP];
-    const int wave = threadIdx.x / 64, lane = threadIdx.x % 64;
-    double* G = X + (size_t)ib * kT * N + (size_t)blockIdx.x * kT;
-    load_tile(Di, Dinv + (size_t)ib * kT * kT, kT);
-    load_tile(B, G, N);
-    __syncthreads();
-    d4 acc[4];
-    zero(acc);
-    strip_product(acc, wave, lane, [&](int r, int k) { return Di[r][k]; }, [&](int k, int c) { return B[k][c]; });
-#pragma unroll
-    for (int ct = 0; ct < 4; ++ct)
-#pragma unroll
-        for (int q = 0; q < 4; ++q) G[(size_t)res_row(wave, lane, q) * N + res_col(lane, ct)] = acc[ct][q];
-}
-
-// X_mc -= L_mi X_ic for m = ib+1 .. nb-1 and c = 0 .. ib
-// (blockIdx.x = (m - ib - 1) * (ib + 1) + c).
-__global__ __launch_bounds__(kDenseThreads) void k_dense_fwd_update(double* __restrict__ X, const double* __restrict__ M,
-                                                                    int N, int ib) {
-    __shared__ double Lm[kT][kTP];
-    __shared__ double B[kT][kTP];
-    const int wave = threadIdx.x / 64, lane = threadIdx.x % 64;
-    const int m = ib + 1 + (int)(blockIdx.x / (ib + 1));
-    const int c = (int)(blockIdx.x % (ib + 1));
-    load_tile(Lm, M + (size_t)m * kT * N + (size_t)ib * kT, N);
-    load_tile(B, X + (size_t)ib * kT * N + (size_t)c * kT, N);
-    __syncthreads();
-    d4 acc[4];
-    zero(acc);
-    strip_product(acc, wave, lane, [&](int r, int k) { return Lm[r][k]; }, [&](int k, int cc) { return B[k][cc]; });
-    double* G = X + (size_t)m * kT * N + (size_t)c * kT;
-#pragma unroll
-    for (int ct = 0; ct < 4; ++ct)
-#pragma unroll
-        for (int q = 0; q < 4; ++q) G[(size_t)res_row(wave, lane, q) * N + res_col(lane, ct)] -= acc[ct][q];
+    if (blockIdx.x == 0) {
+        __threadfence_block();
+        __syncthreads();                // the tile is written
+        potrf_tile(M, N, kb + 1, Dinv, bad);
+    }
 }
 
 // A^{-1}_ab = sum_{k >= a} X_ka^T X_kb for a >= b (one tile per block),
@@ -289,30 +331,23 @@ void coarse_inverse_device(DenseWork& w, int n, const int* rp, const int* ci, co
     const int rows_grid = (N + kDenseThreads - 1) / kDenseThreads;
     hipLaunchKernelGGL(k_dense_scatter, dim3(rows_grid), dim3(kDenseThreads), 0, s, n, N, rp, ci, v, dM);
     hipLaunchKernelGGL(k_dense_eye, dim3(rows_grid), dim3(kDenseThreads), 0, s, N, dX);
+    hipLaunchKernelGGL(k_dense_potrf_first, dim3(1), dim3(kDenseThreads), 0, s, dM, N, dD, dflag);
     for (int kb = 0; kb < nb; ++kb) {
-        hipLaunchKernelGGL(k_dense_potrf_tile, dim3(1), dim3(kDenseThreads), 0, s, dM, N, kb, dD, dflag);
         const int t = nb - kb - 1;
-        if (t > 0) {
-            hipLaunchKernelGGL(k_dense_panel, dim3(t), dim3(kDenseThreads), 0, s, dM, N, kb, (const double*)dD);
-            hipLaunchKernelGGL(k_dense_syrk, dim3((unsigned)((long long)t * (t + 1) / 2)), dim3(kDenseThreads), 0,
-                               s, dM, N, kb);
-        }
+        hipLaunchKernelGGL(k_dense_panel, dim3(t + kb + 1), dim3(kDenseThreads), 0, s, dM, dX, N, kb, t,
+                           (const double*)dD);
+        const long long T = (long long)t * (t + 1) / 2;
+        if (t > 0)
+            hipLaunchKernelGGL(k_dense_update, dim3((unsigned)(T + (long long)t * (kb + 1))), dim3(kDenseThreads), 0,
+                               s, dM, dX, N, kb, T, dD, dflag);
     }
+    hipLaunchKernelGGL(k_dense_xtx, dim3((unsigned)((long long)nb * (nb + 1) / 2)), dim3(kDenseThreads), 0, s,
+                       (const double*)dX, N, nb, n, ainv);
     HIP_CHECK(hipGetLastError());
     int bad = 0;
     HIP_CHECK(hipMemcpyAsync(&bad, dflag, sizeof(int), hipMemcpyDeviceToHost, s));
     HIP_CHECK(hipStreamSynchronize(s));
     if (bad) throw Error(PAMG_E_NOT_SPD, "coarsest matrix is not positive definite");
-    for (int ib = 0; ib < nb; ++ib) {
-        hipLaunchKernelGGL(k_dense_trmm, dim3(ib + 1), dim3(kDenseThreads), 0, s, dX, N, ib, (const double*)dD);
-        if (ib + 1 < nb)
-            hipLaunchKernelGGL(k_dense_fwd_update, dim3((unsigned)((long long)(nb - 1 - ib) * (ib + 1))),
-                               dim3(kDenseThreads), 0, s, dX, (const double*)dM, N, ib);
-    }
-    hipLaunchKernelGGL(k_dense_xtx, dim3((unsigned)((long long)nb * (nb + 1) / 2)), dim3(kDenseThreads), 0, s,
-                       (const double*)dX, N, nb, n, ainv);
-    HIP_CHECK(hipGetLastError());
-    HIP_CHECK(hipStreamSynchronize(s));
 }
 
 }  // namespace pamg
