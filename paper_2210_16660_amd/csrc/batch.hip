@@ -106,11 +106,9 @@ static void launch_down_b(const DevLevelIdx& I, int v, const T* vd, const void* 
         constexpr int U = decltype(u)::value, CPL = decltype(c)::value;
         const int grid = unit_grid(I.nc, kBlock / (kW / CPL));
         if (r_is_f64)
-            hipLaunchKernelGGL((kb_down<U, CPL, T, double>), dim3(grid), dim3(kBlock), 0, s, I.nc, (const int*)I.rp,
-                               (const int*)I.ci, vd, (const double*)r, p, (const int*)I.aggptr, rc, done);
+            hipLaunchKernelGGL((kb_down<U, CPL, T, double>), dim3(grid), dim3(kBlock), 0, s, I.nc, I.row_idx(), (const int*)I.ci, vd, (const double*)r, p, (const int*)I.aggptr, rc, done);
         else
-            hipLaunchKernelGGL((kb_down<U, CPL, T, T>), dim3(grid), dim3(kBlock), 0, s, I.nc, (const int*)I.rp,
-                               (const int*)I.ci, vd, (const T*)r, p, (const int*)I.aggptr, rc, done);
+            hipLaunchKernelGGL((kb_down<U, CPL, T, T>), dim3(grid), dim3(kBlock), 0, s, I.nc, I.row_idx(), (const int*)I.ci, vd, (const T*)r, p, (const int*)I.aggptr, rc, done);
     });
 }
 
@@ -122,12 +120,10 @@ static void launch_up_b(const DevLevelIdx& I, const DevLevelIdx& F, int v, const
         constexpr int U = decltype(u)::value, CPL = decltype(c)::value;
         const int grid = unit_grid(I.n, kBlock / (kW / CPL));
         if (rf_is_f64)
-            hipLaunchKernelGGL((kb_up<U, CPL, T, T, double>), dim3(grid), dim3(kBlock), 0, s, I.n, (const int*)I.rp,
-                               (const int*)I.ci, av, zp, r, dinv, (const int*)F.aggptr, (const double*)r_f, dinv_f,
+            hipLaunchKernelGGL((kb_up<U, CPL, T, T, double>), dim3(grid), dim3(kBlock), 0, s, I.n, I.row_idx(), (const int*)I.ci, av, zp, r, dinv, (const int*)F.aggptr, (const double*)r_f, dinv_f,
                                p_f, zp_f, done);
         else
-            hipLaunchKernelGGL((kb_up<U, CPL, T, T, T>), dim3(grid), dim3(kBlock), 0, s, I.n, (const int*)I.rp,
-                               (const int*)I.ci, av, zp, r, dinv, (const int*)F.aggptr, (const T*)r_f, dinv_f, p_f,
+            hipLaunchKernelGGL((kb_up<U, CPL, T, T, T>), dim3(grid), dim3(kBlock), 0, s, I.n, I.row_idx(), (const int*)I.ci, av, zp, r, dinv, (const int*)F.aggptr, (const T*)r_f, dinv_f, p_f,
                                zp_f, done);
     });
 }
@@ -206,7 +202,7 @@ static int enqueue_vcycle_b(BatchEngine* E, DevVals<T>& V, const double* dv, con
     const int g = unit_grid(I0.n, up0_rows_per_block<T>());
     T* zout;
     if constexpr (std::is_same<T, float>::value) zout = E->Z32; else zout = E->Z;
-    hipLaunchKernelGGL((kb_up0<T>), dim3(g), dim3(kBlock), 0, s, I0.n, (const int*)I0.rp, (const int*)I0.ci,
+    hipLaunchKernelGGL((kb_up0<T>), dim3(g), dim3(kBlock), 0, s, I0.n, I0.row_idx(), (const int*)I0.ci,
                        (const T*)V.v[0], (const T*)E->zp[0], (const T*)r0, (const T*)V.dinv[0], zout, dv,
                        E->partial, done);
     return g;
@@ -222,13 +218,11 @@ static void enqueue_iteration_b(BatchEngine* E, DevVals<T>& V, int krylov, int p
     const DevLevelIdx& I0 = h->idx[0];
     const int gk = unit_grid(I0.n, kKrylovRowsPerBlock);
     if (std::is_same<T, float>::value && h->L > 0)
-        hipLaunchKernelGGL(kb_krylov_pq<float>, dim3(gk), dim3(kBlock), 0, s, I0.n, (const int*)I0.rp,
-                           (const int*)I0.ci, (const double*)h->f64.v[0], (const float*)E->Z32,
+        hipLaunchKernelGGL(kb_krylov_pq<float>, dim3(gk), dim3(kBlock), 0, s, I0.n, I0.row_idx(), (const int*)I0.ci, (const double*)h->f64.v[0], (const float*)E->Z32,
                            (const double*)E->P[parity], E->P[1 - parity], E->Q, (const double*)E->R,
                            (const BatchState*)E->st, E->partial, done);
     else
-        hipLaunchKernelGGL(kb_krylov_pq<double>, dim3(gk), dim3(kBlock), 0, s, I0.n, (const int*)I0.rp,
-                           (const int*)I0.ci, (const double*)h->f64.v[0], (const double*)E->Z,
+        hipLaunchKernelGGL(kb_krylov_pq<double>, dim3(gk), dim3(kBlock), 0, s, I0.n, I0.row_idx(), (const int*)I0.ci, (const double*)h->f64.v[0], (const double*)E->Z,
                            (const double*)E->P[parity], E->P[1 - parity], E->Q, (const double*)E->R,
                            (const BatchState*)E->st, E->partial, done);
     hipLaunchKernelGGL(kb_fin_alpha, dim3(1), dim3(kFinThreads), 0, s, E->st, (const double*)E->partial, gk);
@@ -491,7 +485,7 @@ void batch_true_residual(BatchEngine* E, int restart_mask, double* relres, hipSt
     pamg_hierarchy* h = E->h;
     const DevLevelIdx& I0 = h->idx[0];
     const int g = unit_grid(I0.n, kBlock / kW);
-    hipLaunchKernelGGL(kb_resid, dim3(g), dim3(kBlock), 0, s, I0.n, (const int*)I0.rp, (const int*)I0.ci,
+    hipLaunchKernelGGL(kb_resid, dim3(g), dim3(kBlock), 0, s, I0.n, I0.row_idx(), (const int*)I0.ci,
                        (const double*)h->f64.v[0], (const double*)E->X, (const double*)E->B, E->Y,
                        restart_mask ? E->R : (double*)nullptr, restart_mask ? E->R32 : (float*)nullptr, restart_mask,
                        E->partial_b);

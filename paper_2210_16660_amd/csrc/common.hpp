@@ -63,6 +63,24 @@ struct TileDict {
     int32_t max_len = 0;            // longest dictionary of the level
 };
 
+// Sliced rows of a large level (the layout of the ks_* kernels): tiles of at
+// most kSlice consecutive rows, whole aggregates, with one column dictionary
+// each; in a tile the rows are sorted by length (longest first, ties in row
+// order) and stored step by step: entry k of the q-th row is at base +
+// kSlice k + q, padded to the longest row (padding: column 0, value 0).
+struct SellRows {
+    std::vector<int32_t> tiles;     // 8 ints per tile: first row, end row, base, first dictionary entry,
+                                    // dictionary length, first coarse row, end coarse row, 0
+    std::vector<uint32_t> slot;     // per sorted position: row - first row of its tile | length << 16
+    std::vector<int32_t> rowpos;    // per row: its first entry (entry k: rowpos + kSlice k)
+    std::vector<int32_t> ci;        // columns, padded
+    std::vector<int32_t> col;       // the dictionaries, tile after tile
+    std::vector<uint16_t> local;    // per (padded) entry: position of its column in its tile's dictionary
+    int32_t max_len = 0;            // longest dictionary
+    int32_t xcd[9] = {};            // first tile of each of 8 equal shares of the rows, and the end
+    int64_t entries() const { return (int64_t)ci.size(); }
+};
+
 // A CSR matrix's row tiles (<= kTileRows rows and <= items * kBlock entries,
 // or one longer row; 4 ints per tile: k0, k1, r0, r1) with their column
 // dictionaries (tiles of >= kDictItems items per thread): the layout of the
@@ -99,6 +117,9 @@ struct LayoutLevel {
     std::vector<double> dinv, p;    // permuted
     std::vector<int32_t> aggptr;    // n_{l+1}+1: members of coarse row I are rows [aggptr[I], aggptr[I+1])
     int items = 8;                  // tile capacity of this level: items * kBlock entries
+    // the largest levels (sell_applies): sliced rows, uploaded in place of
+    // ci, v, vd and the tiles below
+    SellRows sell;
     std::vector<int32_t> down_tiles;  // 4 ints per restriction tile: k0, k1, c0, c1 (l < L)
     std::vector<int32_t> up_tiles;    // 4 ints per row tile: k0, k1, r0, r1
     // Column dictionaries of the tiles: the distinct columns of a tile's
@@ -118,6 +139,13 @@ constexpr int kBlock = 256;          // threads per workgroup of the tile kernel
 constexpr int kMaxItems = 16;        // matrix entries per thread per tile (largest tiles)
 constexpr int kDictItems = 8;        // tiles of at least this many items per thread use column dictionaries
 constexpr int kDictMaxLarge = 2048;  // longest dictionary accepted for the largest tiles (prefetch slots)
+constexpr int kSlice = 256;          // most rows of a sliced tile: one per thread of a workgroup
+constexpr int kSellWaves = 6;        // waves per SIMD (workgroups per CU) the sliced kernels are compiled for
+constexpr int kSellGrid = 256 * kSellWaves;  // their workgroups: what the chip holds at once
+constexpr int kSellStep = 8;         // entries of a row loaded together
+constexpr int kSellDict = 2048;      // longest dictionary of a tile (16 KB in FP64)
+constexpr int kSellMinRows = 2 * kSellGrid * kSlice;  // 786,432: two full rounds of the chip
+constexpr int kSellMaxRow = 128;     // longest row (a lane walks its row alone)
 constexpr int kTileRows = kBlock;    // at most one row (or aggregate) per thread in a tile
 constexpr int kMaxAggSteps = 4;      // composed aggregates hold at most 2^4 fine rows
 constexpr int kTargetTiles = 1024;   // small levels shrink their tiles to keep >= this many
@@ -136,6 +164,25 @@ std::vector<LayoutLevel> build_layout(const HostHierarchy& H);
 int first_tile_items(int64_t nnz);
 void make_tiles(const std::vector<int32_t>& rp, const std::vector<int32_t>& aggptr, int32_t n, int32_t nc,
                 int32_t cap, std::vector<int32_t>& up, std::vector<int32_t>& down);
+
+// Whether a level of n rows, nnz entries and longest row maxrow is stored in
+// sliced rows.
+bool sell_applies(int64_t n, int64_t nnz, int64_t maxrow);
+// Tiles of an n-row level (aggptr: aggregate boundaries they respect, nc = 0:
+// none), 4 ints each: first row, end row, first coarse row, end coarse row;
+// and the same with every tile halved whose dictionary (dlen) is too long
+// (returns whether there was one).
+std::vector<int32_t> sell_tiles(const std::vector<int32_t>& aggptr, int32_t n, int32_t nc);
+bool split_sell_tiles(std::vector<int32_t>& tiles, const std::vector<int32_t>& aggptr, int32_t nc,
+                      const std::vector<int32_t>& dlen);
+// Empty when the padded entries exceed 32-bit positions.
+SellRows sell_rows(const std::vector<int32_t>& rp, const std::vector<int32_t>& ci, const std::vector<int32_t>& aggptr,
+                   int32_t n, int32_t nc);
+// First tile of each of 8 equal shares of the n rows (tiles: stride ints per
+// tile, the first row first).
+void sell_shares(const std::vector<int32_t>& tiles, int stride, int32_t n, int32_t xcd[9]);
+// Values in CSR order as the slices store them.
+std::vector<double> sell_values(const SellRows& S, const std::vector<int32_t>& rp, const std::vector<double>& v);
 
 // Smoothed prolongator of level l in hierarchical numbering (P and P^T).
 void sa_layout(const HostCSR& P, const LayoutLevel& fine, const LayoutLevel& coarse, LayoutLevel& out);

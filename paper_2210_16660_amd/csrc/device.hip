@@ -63,17 +63,18 @@ static void upload_values(pamg_hierarchy* h, DevVals<T>& V, const std::vector<La
                 V.vd[l] = D.vd;
                 V.p[l] = D.p;
             } else {
-                V.v[l] = convert_copy<T>(h, D.v, D.nnz, s);
+                V.v[l] = convert_copy<T>(h, D.v, D.nent, s);
                 V.dinv[l] = convert_copy<T>(h, D.dinv, D.n, s);
-                V.vd[l] = convert_copy<T>(h, D.vd, D.nnz, s);
+                V.vd[l] = convert_copy<T>(h, D.vd, D.nent, s);
                 V.p[l] = convert_copy<T>(h, D.p, D.n, s);
             }
         } else {
             const LayoutLevel& Ly = lay[l - m];
-            V.v[l] = upload<T>(h, Ly.v, s);
+            const bool sell = !Ly.sell.tiles.empty();
+            V.v[l] = sell ? upload<T>(h, sell_values(Ly.sell, Ly.rp, Ly.v), s) : upload<T>(h, Ly.v, s);
             V.dinv[l] = upload<T>(h, Ly.dinv, s);
             if (l + 1 < nl) {
-                V.vd[l] = upload<T>(h, Ly.vd, s);
+                V.vd[l] = sell ? upload<T>(h, sell_values(Ly.sell, Ly.rp, Ly.vd), s) : upload<T>(h, Ly.vd, s);
                 V.p[l] = upload<T>(h, Ly.p, s);
             }
         }
@@ -144,9 +145,9 @@ void build_gs_dense(pamg_hierarchy* h, int l, hipStream_t s) {
     DevVals<double>& V = h->f64;
     const int ns = gs_strips(h->gs_block);
     const dim3 g((unsigned)(I.gs_nblk * ns * (kGsTile / kGsInvCols)));
-    hipLaunchKernelGGL((k_gs_invert<false>), g, dim3(64), 0, s, I.n, h->gs_block, ns, (const int*)I.ci,
+    hipLaunchKernelGGL((k_gs_invert<false>), g, dim3(64), 0, s, I.n, h->gs_block, ns, I.row_idx(), (const int*)I.ci,
                        (const double*)V.v[l], I.gs_fresh, (const double*)V.gsa[l], V.gsw_f[l]);
-    hipLaunchKernelGGL((k_gs_invert<true>), g, dim3(64), 0, s, I.n, h->gs_block, ns, (const int*)I.ci,
+    hipLaunchKernelGGL((k_gs_invert<true>), g, dim3(64), 0, s, I.n, h->gs_block, ns, I.row_idx(), (const int*)I.ci,
                        (const double*)V.v[l], I.gs_fresh, (const double*)V.gsa[l], V.gsw_b[l]);
     if (h->f32.built) {
         const long long w = (long long)I.gs_nblk * gs_dense_block(h->gs_block);
@@ -159,8 +160,11 @@ void build_gs_dense(pamg_hierarchy* h, int l, hipStream_t s) {
 
 // Matrix bytes of one pass over a level in the tile format: values, 16-bit
 // dictionary positions, the tiles' dictionaries, descriptors (16 B) and spans
-// (8 B), and the row pointer.
+// (8 B), and the row pointer; sliced rows: the same with their padding, tile
+// descriptors of 32 B and row slots in place of the row pointer.
 static uint64_t matrix_bytes(const DevLevelIdx& I, bool down, uint64_t s) {
+    if (I.sell)
+        return (uint64_t)I.nent * (2 + s) + 4 * (uint64_t)I.sell_dlen + 32 * (uint64_t)I.sv.ntiles + 4 * (uint64_t)I.n;
     const uint64_t dict = (uint64_t)(down ? I.down_dlen : I.up_dlen);
     const uint64_t nt = (uint64_t)(down ? I.n_down : I.n_up);
     return (uint64_t)I.nnz * (2 + s) + 4 * dict + 24 * nt + 4 * ((uint64_t)I.n + 1);
@@ -228,6 +232,16 @@ void upload_hierarchy(pamg_hierarchy* h, const std::vector<LayoutLevel>& lay, bo
         };
         dict(D.up_dict, I.up_span, I.up_col, I.up_loc, I.up_dmax, I.up_dlen);
         dict(D.down_dict, I.down_span, I.down_col, I.down_loc, I.down_dmax, I.down_dlen);
+        I.nent = D.nent;
+        if (D.sell.n_tiles) {
+            const DevSell& S = D.sell;
+            I.sell = true;
+            I.sv = {reinterpret_cast<const int4*>(S.tiles), S.n_tiles, {}, S.slot, S.col, S.loc};
+            std::copy(S.xcd, S.xcd + 9, I.sv.xcd);
+            I.rowpos = S.rowpos;
+            I.sell_dmax = std::max(1, S.max_len);
+            I.sell_dlen = S.len;
+        }
         if (h->smoother == PAMG_SMOOTHER_HYBRID_GS) {
             I.gs_df = D.gs_df;
             I.gs_db = D.gs_db;
@@ -244,9 +258,20 @@ void upload_hierarchy(pamg_hierarchy* h, const std::vector<LayoutLevel>& lay, bo
         I.nc = (l + 1 < nl) ? (int)lay[l + 1 - m].dinv.size() : 0;
         I.items = Ly.items;
         I.rp = upload<int>(h, Ly.rp, s);
-        I.ci = upload<int>(h, Ly.ci, s);
+        I.ci = upload<int>(h, Ly.sell.tiles.empty() ? Ly.ci : Ly.sell.ci, s);
+        I.nent = Ly.sell.tiles.empty() ? I.nnz : Ly.sell.entries();
         I.perm = upload<int>(h, Ly.perm, s);
         I.iperm = upload<int>(h, Ly.iperm, s);
+        if (!Ly.sell.tiles.empty()) {
+            const SellRows& S = Ly.sell;
+            I.sell = true;
+            I.sv = {reinterpret_cast<const int4*>(upload<int>(h, S.tiles, s)), (int)(S.tiles.size() / 8), {},
+                    upload<uint32_t>(h, S.slot, s), upload<int>(h, S.col, s), upload<uint16_t>(h, S.local, s)};
+            std::copy(S.xcd, S.xcd + 9, I.sv.xcd);
+            I.rowpos = upload<int>(h, S.rowpos, s);
+            I.sell_dmax = std::max(1, (int)S.max_len);
+            I.sell_dlen = (long long)S.col.size();
+        }
         I.up_tiles = reinterpret_cast<const int4*>(upload<int>(h, Ly.up_tiles, s));
         I.n_up = (int)Ly.up_tiles.size() / 4;
         I.up_span = reinterpret_cast<const int2*>(upload<int>(h, Ly.up_dict.span, s));
@@ -380,27 +405,35 @@ static void with_items(int items, F&& f) {
     }
 }
 
+// rc = P^T (r - M g): the down-sweep (M = A D^-1, g = r), or the residual of a
+// smoothed z and its restriction (M = A, g = z).
+template <typename T, typename RT, typename GT>
+static void launch_restrict(const DevLevelIdx& I, const T* m, const RT* r, const GT* g, const T* p, T* rc,
+                            const int* done, hipStream_t s) {
+    if (I.sell) {
+        LAUNCH((ks_down<T, RT, GT>), I.down_grid(), sell_lds_bytes<T>(I.sell_dmax), s, m, r, g, p,
+               (const int*)I.aggptr, I.sv, rc, done);
+        return;
+    }
+    with_items(I.items, [&](auto it) {
+        constexpr int IT = decltype(it)::value;
+        LAUNCH((k_down<IT, T, RT, GT>), I.down_grid(), (tile_lds_bytes<IT, T>(I.down_dmax)), s, (const int*)I.rp,
+               (const int*)I.ci, m, r, g, p, (const int*)I.aggptr, I.down_tiles, I.n_down, I.down_span, I.down_col,
+               I.down_loc, rc, done);
+    });
+}
+
 template <typename T, typename RT>
 static void launch_down(const DevLevelIdx& I, const T* vd, const RT* r, const T* p, T* rc, const int* done,
                         hipStream_t s) {
-    with_items(I.items, [&](auto it) {
-        constexpr int IT = decltype(it)::value;
-        LAUNCH((k_down<IT, T, RT, RT>), tile_grid(I.n_down), (tile_lds_bytes<IT, T>(I.down_dmax)), s, (const int*)I.rp,
-               (const int*)I.ci, vd, r, r, p, (const int*)I.aggptr, I.down_tiles, I.n_down, I.down_span, I.down_col,
-               I.down_loc, rc, done);
-    });
+    launch_restrict<T, RT, RT>(I, vd, r, r, p, rc, done, s);
 }
 
 // Residual of a smoothed z and its restriction: rc = P^T (r - A z).
 template <typename T, typename RT>
 static void launch_resid_restrict(const DevLevelIdx& I, const T* v, const RT* r, const T* z, const T* p, T* rc,
                                   const int* done, hipStream_t s) {
-    with_items(I.items, [&](auto it) {
-        constexpr int IT = decltype(it)::value;
-        LAUNCH((k_down<IT, T, RT, T>), tile_grid(I.n_down), (tile_lds_bytes<IT, T>(I.down_dmax)), s, (const int*)I.rp,
-               (const int*)I.ci, v, r, z, p, (const int*)I.aggptr, I.down_tiles, I.n_down, I.down_span, I.down_col,
-               I.down_loc, rc, done);
-    });
+    launch_restrict<T, RT, T>(I, v, r, z, p, rc, done, s);
 }
 
 // F: the finer level (l - 1) prolongated into, or nullptr at level 0 (OUT).
@@ -410,44 +443,57 @@ static void launch_up(const DevLevelIdx& I, const T* v, const T* zp, const RT* r
                       typename std::common_type<ZO>::type* z_out, const double* dv,
                       double* partial, const int* done, hipStream_t s) {
     const int* aggptr_f = F ? (const int*)F->aggptr : nullptr;
+    const auto launch = [&](auto mode, auto zo) {
+        constexpr int M = decltype(mode)::value;
+        using Z = decltype(zo);
+        if (I.sell) {
+            LAUNCH((ks_up<T, RT, RTF, M, Z>), I.row_grid(), sell_lds_bytes<T>(I.sell_dmax), s, v, zp, r,
+                   dinv, I.sv, aggptr_f, r_f, dinv_f, p_f, zp_f, (Z*)z_out, dv, partial, done);
+            return;
+        }
+        with_items(I.items, [&](auto it) {
+            constexpr int IT = decltype(it)::value;
+            LAUNCH((k_up<IT, T, RT, RTF, M, Z>), I.row_grid(), (tile_lds_bytes<IT, T>(I.up_dmax)), s, (const int*)I.rp,
+                   (const int*)I.ci, v, zp, r, dinv, I.up_tiles, I.n_up, I.up_span, I.up_col, I.up_loc, aggptr_f, r_f,
+                   dinv_f, p_f, zp_f, (Z*)z_out, dv, partial, done);
+        });
+    };
+    if constexpr (OUT)
+        launch(std::integral_constant<int, kUpOut>{}, ZO());
+    else if (F->max_agg <= 2)
+        launch(std::integral_constant<int, kUpPair>{}, double());
+    else
+        launch(std::integral_constant<int, kUpWide>{}, double());
+}
+
+// A level's row-tile product with epilogue EPI: kSpmvPlain y = A x or b - A x
+// (with the partials of y . y), kSpmvSmooth the l1-Jacobi step
+// y = x + D^-1 (b - A x).
+template <int EPI, typename T, typename XT, typename YT, typename BT>
+static void launch_rows(const DevLevelIdx& I, const T* v, const XT* x, const BT* b, const T* d, YT* y, double* partial,
+                        const int* done, hipStream_t s) {
+    if (I.sell) {
+        LAUNCH((ks_spmv<T, XT, YT, BT, EPI>), I.row_grid(), sell_lds_bytes<T>(I.sell_dmax), s, v, x, b, d,
+               y, I.sv, partial, done);
+        return;
+    }
     with_items(I.items, [&](auto it) {
         constexpr int IT = decltype(it)::value;
-        if constexpr (OUT) {
-            LAUNCH((k_up<IT, T, RT, RTF, kUpOut, ZO>), tile_grid(I.n_up), (tile_lds_bytes<IT, T>(I.up_dmax)), s, (const int*)I.rp,
-                   (const int*)I.ci, v, zp, r, dinv, I.up_tiles, I.n_up, I.up_span, I.up_col, I.up_loc, aggptr_f,
-                   r_f, dinv_f, p_f, zp_f, z_out, dv, partial, done);
-        } else if (F->max_agg <= 2) {
-            LAUNCH((k_up<IT, T, RT, RTF, kUpPair>), tile_grid(I.n_up), (tile_lds_bytes<IT, T>(I.up_dmax)), s, (const int*)I.rp,
-                   (const int*)I.ci, v, zp, r, dinv, I.up_tiles, I.n_up, I.up_span, I.up_col, I.up_loc, aggptr_f,
-                   r_f, dinv_f, p_f, zp_f, z_out, dv, partial, done);
-        } else {
-            LAUNCH((k_up<IT, T, RT, RTF, kUpWide>), tile_grid(I.n_up), (tile_lds_bytes<IT, T>(I.up_dmax)), s, (const int*)I.rp,
-                   (const int*)I.ci, v, zp, r, dinv, I.up_tiles, I.n_up, I.up_span, I.up_col, I.up_loc, aggptr_f,
-                   r_f, dinv_f, p_f, zp_f, z_out, dv, partial, done);
-        }
+        LAUNCH((k_spmv<IT, T, XT, YT, BT, EPI>), I.row_grid(), (tile_lds_bytes<IT, T>(I.up_dmax)), s, (const int*)I.rp,
+               (const int*)I.ci, v, x, b, d, y, I.up_tiles, I.n_up, I.up_span, I.up_col, I.up_loc, partial, done);
     });
 }
 
 template <typename T, typename XT>
 static void launch_spmv(const DevLevelIdx& I, const T* v, const XT* x, const double* b, double* y, double* partial,
                         hipStream_t s) {
-    with_items(I.items, [&](auto it) {
-        constexpr int IT = decltype(it)::value;
-        LAUNCH((k_spmv<IT, T, XT, double>), tile_grid(I.n_up), (tile_lds_bytes<IT, T>(I.up_dmax)), s, (const int*)I.rp,
-               (const int*)I.ci, v, x, b, (const T*)nullptr, y, I.up_tiles, I.n_up, I.up_span, I.up_col, I.up_loc,
-               partial, (const int*)nullptr);
-    });
+    launch_rows<kSpmvPlain, T, XT, double, double>(I, v, x, b, nullptr, y, partial, nullptr, s);
 }
 
 // y = b - A x through the row tiles, any vector types; no partials.
 template <typename T, typename XT, typename YT, typename BT>
 static void launch_resid(const DevLevelIdx& I, const T* v, const XT* x, const BT* b, YT* y, hipStream_t s) {
-    with_items(I.items, [&](auto it) {
-        constexpr int IT = decltype(it)::value;
-        LAUNCH((k_spmv<IT, T, XT, YT, BT>), tile_grid(I.n_up), (tile_lds_bytes<IT, T>(I.up_dmax)), s, (const int*)I.rp,
-               (const int*)I.ci, v, x, b, (const T*)nullptr, y, I.up_tiles, I.n_up, I.up_span, I.up_col, I.up_loc,
-               (double*)nullptr, (const int*)nullptr);
-    });
+    launch_rows<kSpmvPlain, T, XT, YT, BT>(I, v, x, b, nullptr, y, nullptr, nullptr, s);
 }
 
 // The l1-Jacobi step from x on a level: y = x + D^-1 (b - A x), through the
@@ -455,12 +501,7 @@ static void launch_resid(const DevLevelIdx& I, const T* v, const XT* x, const BT
 template <typename T, typename BT>
 static void launch_smooth(const DevLevelIdx& I, const T* v, const T* x, const BT* b, const T* dinv, T* y,
                           const int* done, hipStream_t s) {
-    with_items(I.items, [&](auto it) {
-        constexpr int IT = decltype(it)::value;
-        LAUNCH((k_spmv<IT, T, T, T, BT, kSpmvSmooth>), tile_grid(I.n_up), (tile_lds_bytes<IT, T>(I.up_dmax)), s,
-               (const int*)I.rp, (const int*)I.ci, v, x, b, dinv, y, I.up_tiles, I.n_up, I.up_span, I.up_col,
-               I.up_loc, (double*)nullptr, done);
-    });
+    launch_rows<kSpmvSmooth, T, T, T, BT>(I, v, x, b, dinv, y, nullptr, done, s);
 }
 
 // y = z + M x with a tiled matrix M (the prolongated correction z + P e).
@@ -495,9 +536,14 @@ template <typename ZT>
 static void launch_krylov(const DevLevelIdx& I, const double* v, const ZT* z, const double* p_old, double* p_new,
                           double* q, const double* r, const SolveState* st, double* partial, const int* done,
                           hipStream_t s) {
+    if (I.sell) {
+        LAUNCH((ks_krylov_pq<ZT>), I.row_grid(), sell_lds_bytes<double>(I.sell_dmax), s, v, z, p_old,
+               p_new, q, r, I.sv, st, partial, done);
+        return;
+    }
     with_items(I.items, [&](auto it) {
         constexpr int IT = decltype(it)::value;
-        LAUNCH((k_krylov_pq<IT, ZT>), tile_grid(I.n_up), (tile_lds_bytes<IT, double>(I.up_dmax)), s, (const int*)I.rp,
+        LAUNCH((k_krylov_pq<IT, ZT>), I.row_grid(), (tile_lds_bytes<IT, double>(I.up_dmax)), s, (const int*)I.rp,
                (const int*)I.ci, v, z, p_old, p_new, q, r, I.up_tiles, I.n_up, I.up_span, I.up_col, I.up_loc, st,
                partial, done);
     });
@@ -551,15 +597,15 @@ static void launch_hgs(pamg_hierarchy* h, DevVals<T>& V, int l, const RT* r, con
     }
     const dim3 g(I.gs_nblk), blk(MAXB);
     if (zero)
-        hipLaunchKernelGGL((k_hgs<MAXB, T, RT, false, true>), g, blk, 0, s, I.n, h->gs_block, (const int*)I.ci,
+        hipLaunchKernelGGL((k_hgs<MAXB, T, RT, false, true>), g, blk, 0, s, I.n, h->gs_block, I.row_idx(), (const int*)I.ci,
                            (const T*)V.v[l], I.gs_fresh, (const T*)V.gsa[l], I.gs_df, I.gs_maxd, r,
                            (const T*)nullptr, x_new, winv, done);
     else if (backward)
-        hipLaunchKernelGGL((k_hgs<MAXB, T, T, true, false>), g, blk, 0, s, I.n, h->gs_block, (const int*)I.ci,
+        hipLaunchKernelGGL((k_hgs<MAXB, T, T, true, false>), g, blk, 0, s, I.n, h->gs_block, I.row_idx(), (const int*)I.ci,
                            (const T*)V.v[l], I.gs_fresh, (const T*)V.gsa[l], I.gs_db, I.gs_maxd, t, x_old, x_new,
                            winv, done);
     else
-        hipLaunchKernelGGL((k_hgs<MAXB, T, T, false, false>), g, blk, 0, s, I.n, h->gs_block, (const int*)I.ci,
+        hipLaunchKernelGGL((k_hgs<MAXB, T, T, false, false>), g, blk, 0, s, I.n, h->gs_block, I.row_idx(), (const int*)I.ci,
                            (const T*)V.v[l], I.gs_fresh, (const T*)V.gsa[l], I.gs_df, I.gs_maxd, t, x_old, x_new,
                            winv, done);
 }
@@ -682,7 +728,7 @@ static int enqueue_vcycle_sa(pamg_hierarchy* h, DevVals<T>& V, const double* r0,
     const DevLevelIdx& I0 = h->idx[0];
     launch_up<T, double, double, true>(I0, V.v[0], V.zp[0], r0, V.dinv[0], nullptr, (const double*)nullptr, nullptr,
                                        nullptr, nullptr, z_out, dv, h->partial, done, s);
-    return tile_grid(I0.n_up);
+    return I0.row_grid();
 }
 
 // The l1-Jacobi cycle with tentative prolongators; r0 of type R0 (the FP64
@@ -727,7 +773,7 @@ static int enqueue_vcycle_plain(pamg_hierarchy* h, DevVals<T>& V, const R0* r0, 
     const DevLevelIdx& I0 = h->idx[0];
     launch_up<T, R0, R0, true, ZO>(I0, V.v[0], V.zp[0], r0, V.dinv[0], nullptr, (const R0*)nullptr, nullptr, nullptr,
                                    nullptr, z_out, dv, h->partial, done, s);
-    return tile_grid(I0.n_up);
+    return I0.row_grid();
 }
 
 // z_out = B r0 on level 0 (r0, z_out FP64, hierarchical order); the level-0
@@ -775,7 +821,7 @@ static void enqueue_iteration(pamg_hierarchy* h, DevVals<T>& V, int krylov, int 
     else
         launch_krylov<double>(I, h->f64.v[0], h->z, h->p[parity], h->p[1 - parity], h->q, h->r, h->st, h->partial,
                               done, s);
-    LAUNCH(k_fin_alpha, 1, 0, s, h->st, (const double*)h->partial, tile_grid(I.n_up));
+    LAUNCH(k_fin_alpha, 1, 0, s, h->st, (const double*)h->partial, I.row_grid());
     const int gv = vec_grid(I.n);
     LAUNCH(k_krylov_update, gv, 0, s, I.n, h->x, h->r, (const double*)h->p[1 - parity], (const double*)h->q,
            (const SolveState*)h->st, h->partial, done);
@@ -817,7 +863,7 @@ static void read_state(pamg_hierarchy* h, hipStream_t s) {
 // ||b - A x|| / ||b|| for the hierarchical-order x, b; uses dbg0 as scratch.
 static double true_relres(pamg_hierarchy* h, hipStream_t s) {
     const DevLevelIdx& I = h->idx[0];
-    const int g = tile_grid(I.n_up);
+    const int g = I.row_grid();
     launch_spmv<double, double>(I, h->f64.v[0], h->x, h->b, h->dbg0, h->partial_b, s);
     double part[kMaxGrid];        // g <= kMaxGrid; no heap allocation on the solve path
     HIP_CHECK(hipMemcpyAsync(part, h->partial_b, sizeof(double) * g, hipMemcpyDeviceToHost, s));
@@ -848,7 +894,7 @@ static void begin_solve(pamg_hierarchy* h, const double* b_user, const double* x
         LAUNCH((k_gather<double, double>), gv, 0, s, n, (const int*)I0.iperm, x0_user, h->x);
         launch_spmv<double, double>(I0, h->f64.v[0], h->x, h->b, h->r, h->partial, s);
         LAUNCH(k_fin_init, 1, 0, s, h->st, (const double*)h->partial_b, gv, (const double*)h->partial,
-               tile_grid(I0.n_up));
+               I0.row_grid());
     } else {
         LAUNCH(k_fill, gv, 0, s, (long long)n, h->x, 0.0);
         LAUNCH(k_norm2, gv, 0, s, n, (const double*)h->b, h->r, h->partial);
@@ -872,7 +918,7 @@ static void restart_solve(pamg_hierarchy* h, hipStream_t s) {
     const DevLevelIdx& I0 = h->idx[0];
     launch_spmv<double, double>(I0, h->f64.v[0], h->x, h->b, h->r, h->partial, s);
     LAUNCH(k_fin_init, 1, 0, s, h->st, (const double*)h->partial_b, 0, (const double*)h->partial,
-           tile_grid(I0.n_up));
+           I0.row_grid());
     read_state_async(h, s);
 }
 
@@ -994,7 +1040,7 @@ struct ScratchView {
 // or the single-level coarse product, the vector kernels.
 static size_t solve_partials(const pamg_hierarchy* h) {
     const DevLevelIdx& I0 = h->idx[0];
-    size_t need = 2 * (size_t)tile_grid(I0.n_up);
+    size_t need = 2 * (size_t)I0.row_grid();
     need = std::max(need, (size_t)vec_grid(I0.n));
     if (h->L == 0) need = std::max(need, (size_t)coarse_partials(h->idx[0].n));
     return need;
@@ -1517,11 +1563,13 @@ void ensure_host_levels(pamg_hierarchy* h) {
     for (int l = 0; l < upto; ++l) {
         const DevLevelIdx& I = h->idx[l];
         const int n = I.n, nc = I.nc;
-        std::vector<int32_t> rp, ci, perm, iperm, aggptr, ciperm;
+        std::vector<int32_t> rp, ci, perm, iperm, aggptr, ciperm, rowpos;
         std::vector<double> v, dinv, p;
         get(rp, I.rp, (size_t)n + 1);
-        get(ci, I.ci, (size_t)I.nnz);
-        get(v, h->f64.v[l], (size_t)I.nnz);
+        get(ci, I.ci, (size_t)I.nent);
+        get(v, h->f64.v[l], (size_t)I.nent);
+        if (I.sell) get(rowpos, I.rowpos, (size_t)n);
+        const int64_t step = I.sell ? kSlice : 1;
         get(perm, I.perm, (size_t)n);
         get(iperm, I.iperm, (size_t)n);
         get(dinv, h->f64.dinv[l], (size_t)n);
@@ -1542,7 +1590,9 @@ void ensure_host_levels(pamg_hierarchy* h) {
             for (int64_t i = b; i < e; ++i) {
                 const int32_t ip = perm[i];
                 row.clear();
-                for (int32_t k = rp[ip]; k < rp[ip + 1]; ++k) row.emplace_back(iperm[ci[k]], v[k]);
+                const int64_t o0 = I.sell ? rowpos[ip] : rp[ip];
+                for (int32_t k = 0; k < rp[ip + 1] - rp[ip]; ++k)
+                    row.emplace_back(iperm[ci[o0 + k * step]], v[o0 + k * step]);
                 std::sort(row.begin(), row.end(), [](const std::pair<int32_t, double>& x,
                                                      const std::pair<int32_t, double>& y) { return x.first < y.first; });
                 const int32_t o = H.A.rp[i];

@@ -637,6 +637,132 @@ __global__ void k_spans(int ntiles, const long long* doff, const int* dlen, int*
     }
 }
 
+// Column dictionary of each sliced tile (rows tiles[t].x .. .y; CSR): its
+// distinct columns, ascending (count pass: their number, or kSellDict + 1 when
+// there are more; fill pass: the columns at the tile's offset and the 16-bit
+// position of every stored entry of its slices).  The distinct columns are
+// collected in an open-addressing table in LDS, at most half full: a tile
+// stops inserting once kDictStop columns are in it, and the inserts of one
+// step in flight then add at most kSB more.
+constexpr int kDictHash = 8192;                 // table slots
+constexpr int kDictStop = kSellDict + kSB;      // a tile with this many columns is split anyway
+static_assert(2 * (kDictStop + kSB) <= kDictHash, "the table must stay at most half full");
+
+// Insert the columns of entries [k0, k0 + m) into the table (all slots -1).
+__device__ inline void dict_insert(int* table, int* count, const int* ci, int k0, int m) {
+    for (int u0 = 0; u0 < m; u0 += kSB) {
+        const int u = u0 + threadIdx.x;
+        const bool room = *(volatile int*)count < kDictStop;
+        if (u < m && room) {
+            const int c = ci[k0 + u];
+            unsigned h = ((unsigned)c * 2654435761u) >> 19;     // 13 bits
+            for (;;) {
+                const int old = atomicCAS(&table[h], -1, c);
+                if (old == c) break;
+                if (old == -1) {
+                    atomicAdd(count, 1);
+                    break;
+                }
+                h = (h + 1) & (kDictHash - 1);
+            }
+        }
+        __syncthreads();
+    }
+}
+
+__global__ __launch_bounds__(kSB) void k_dict_count(int ntiles, const int4* tiles, const int* rp, const int* ci,
+                                                    int* dlen) {
+    __shared__ int table[kDictHash];
+    __shared__ int count;
+    for (int t = blockIdx.x; t < ntiles; t += gridDim.x) {
+        const int k0 = rp[tiles[t].x], m = rp[tiles[t].y] - k0;
+        for (int u = threadIdx.x; u < kDictHash; u += kSB) table[u] = -1;
+        if (threadIdx.x == 0) count = 0;
+        __syncthreads();
+        dict_insert(table, &count, ci, k0, m);
+        if (threadIdx.x == 0) dlen[t] = count <= kSellDict ? count : kSellDict + 1;
+        __syncthreads();
+    }
+}
+
+// kSlice times the longest row of each tile (rows tiles[t].x .. .y).
+__global__ __launch_bounds__(kSB) void k_sell_sizes(int ntiles, const int4* tiles, const int* rp, int* size) {
+    __shared__ int longest;
+    for (int t = blockIdx.x; t < ntiles; t += gridDim.x) {
+        const int4 d = tiles[t];
+        if (threadIdx.x == 0) longest = 0;
+        __syncthreads();
+        const int i = d.x + (int)threadIdx.x;
+        if (i < d.y) atomicMax(&longest, rp[i + 1] - rp[i]);
+        __syncthreads();
+        if (threadIdx.x == 0) size[t] = kSlice * longest;
+        __syncthreads();
+    }
+}
+
+// Each sliced tile from its CSR rows: the rows sorted by length (longest
+// first, ties in row order), their entries step by step (padding: column 0,
+// value 0), each row's first entry, the dictionary and every entry's position
+// in it.
+__global__ __launch_bounds__(kSB) void k_sell_fill(int ntiles, const int4* tiles, const int* rp, const int* ci,
+                                                   const double* v, uint32_t* slot, int* rowpos, int* ci2, double* v2,
+                                                   int* dcol, uint16_t* loc) {
+    static_assert(kSlice == kSB, "one thread per row of a tile");
+    __shared__ int table[kDictHash];
+    __shared__ int uq[kSellDict];
+    __shared__ int key[kSlice];
+    __shared__ int count;
+    for (int t = blockIdx.x; t < ntiles; t += gridDim.x) {
+        const int4 d = tiles[2 * t];
+        const int total = tiles[2 * t + 1].x, rows = d.y - d.x;
+        const int k0 = rp[d.x], m = rp[d.y] - k0;
+        const int j = threadIdx.x;
+        for (int u = j; u < kDictHash; u += kSB) table[u] = -1;
+        if (j == 0) count = 0;
+        key[j] = j < rows ? (kSellMaxRow - (rp[d.x + j + 1] - rp[d.x + j])) << 16 | j : INT_MAX;
+        __syncthreads();
+        lds_bitonic(key, kSlice);
+        dict_insert(table, &count, ci, k0, m);
+        // compact (any order), then sort: the result does not depend on it
+        if (j == 0) count = 0;
+        __syncthreads();
+        for (int u = j; u < kDictHash; u += kSB)
+            if (table[u] >= 0) uq[atomicAdd(&count, 1)] = table[u];
+        int P = 1;
+        while (P < total) P <<= 1;
+        for (int u = total + j; u < P; u += kSB) uq[u] = INT_MAX;
+        __syncthreads();
+        lds_bitonic(uq, P);
+        for (int u = j; u < total; u += kSB) dcol[d.w + u] = uq[u];
+        const int steps = kSellMaxRow - (key[0] >> 16);
+        const bool own = j < rows;
+        const int len = own ? kSellMaxRow - (key[j] >> 16) : 0, i = d.x + (own ? key[j] & 0xffff : 0);
+        if (own) {
+            slot[d.x + j] = (uint32_t)(i - d.x) | (uint32_t)len << 16;
+            rowpos[i] = d.z + j;
+        }
+        const int r = rp[i];
+        for (int k = 0; k < steps; ++k) {
+            const size_t o = (size_t)d.z + (size_t)k * kSlice + j;
+            int col = 0, b = 0;
+            double a = 0.0;
+            if (k < len) {
+                col = ci[r + k];
+                a = v[r + k];
+                int e = total;
+                while (b < e) {
+                    const int h = (b + e) >> 1;
+                    if (uq[h] < col) b = h + 1; else e = h;
+                }
+            }
+            ci2[o] = col;
+            v2[o] = a;
+            loc[o] = (uint16_t)b;
+        }
+        __syncthreads();
+    }
+}
+
 // ------------------------------------------------------ aggregate composition
 
 // The pairwise levels composed into one kept level (at most kMaxAggSteps).
@@ -844,26 +970,27 @@ namespace {
 // Per row of a level with blocks of nb rows: 1 / a_ii and the range of the
 // row's entries whose columns lie in its block (first such entry; the counts
 // before and after the row; whether a_ii is stored), as the host schedule.
-__global__ void k_gs_rows(int n, int nb, const int* __restrict__ rp, const int* __restrict__ ci,
+__global__ void k_gs_rows(int n, int nb, RowIdx R, const int* __restrict__ ci,
                           const double* __restrict__ v, double* __restrict__ ainv, int* __restrict__ fresh,
                           int* __restrict__ bad) {
     for (int i = blockIdx.x * blockDim.x + threadIdx.x; i < n; i += gridDim.x * blockDim.x) {
         const int b0 = i / nb * nb, b1 = min(n, b0 + nb);
         int first = -1, before = 0, after = 0, diag = 0;
         double a = 0.0;
-        for (int k = rp[i]; k < rp[i + 1]; ++k) {
-            const int j = ci[k];
+        const int o = R.start(i), len = R.len(i), st = R.stride();
+        for (int k = 0; k < len; ++k) {
+            const int j = ci[o + k * st];
             if (j >= b0 && j < b1 && first < 0) first = k;
             if (j >= b0 && j < i) ++before;
             if (j > i && j < b1) ++after;
             if (j == i) {
-                if (!(v[k] > 0.0)) *bad = 1;
-                a = 1.0 / v[k];
+                if (!(v[o + k * st] > 0.0)) *bad = 1;
+                a = 1.0 / v[o + k * st];
                 diag = 1;
             }
         }
         ainv[i] = a;
-        fresh[2 * (size_t)i] = first < 0 ? rp[i] : first;
+        fresh[2 * (size_t)i] = R.rp[i] + (first < 0 ? 0 : first);
         fresh[2 * (size_t)i + 1] = before | after << 8 | diag << 16;
     }
 }
@@ -871,15 +998,16 @@ __global__ void k_gs_rows(int n, int nb, const int* __restrict__ rp, const int* 
 // Per block: each row's depth in the block's forward (earlier rows) and
 // backward (later rows) dependency graph, and the block's largest depths; one
 // thread walks its block's rows in order, as the host schedule.
-__global__ void k_gs_depths(int n, int nb, int nblk, const int* __restrict__ rp, const int* __restrict__ ci,
+__global__ void k_gs_depths(int n, int nb, int nblk, RowIdx R, const int* __restrict__ ci,
                             uint8_t* __restrict__ df, uint8_t* __restrict__ db, int* __restrict__ maxd) {
     for (int p = blockIdx.x * blockDim.x + threadIdx.x; p < nblk; p += gridDim.x * blockDim.x) {
         const int b0 = p * nb, b1 = min(n, b0 + nb);
         int mf = 0, mb = 0;
         for (int i = b0; i < b1; ++i) {
             int d = 0;
-            for (int k = rp[i]; k < rp[i + 1]; ++k) {
-                const int j = ci[k];
+            const int o = R.start(i), len = R.len(i), st = R.stride();
+            for (int k = 0; k < len; ++k) {
+                const int j = ci[o + k * st];
                 if (j >= b0 && j < i) d = max(d, (int)df[j] + 1);
             }
             df[i] = (uint8_t)d;
@@ -887,8 +1015,9 @@ __global__ void k_gs_depths(int n, int nb, int nblk, const int* __restrict__ rp,
         }
         for (int i = b1 - 1; i >= b0; --i) {
             int d = 0;
-            for (int k = rp[i]; k < rp[i + 1]; ++k) {
-                const int j = ci[k];
+            const int o = R.start(i), len = R.len(i), st = R.stride();
+            for (int k = 0; k < len; ++k) {
+                const int j = ci[o + k * st];
                 if (j > i && j < b1) d = max(d, (int)db[j] + 1);
             }
             db[i] = (uint8_t)d;
@@ -912,10 +1041,11 @@ void device_gs_schedule(pamg_hierarchy* h, DevLevelOut& D, int nb, hipStream_t s
     Temps T{h->ctx, s, {}};
     int* bad = T.get<int>(1);
     HIP_CHECK(hipMemsetAsync(bad, 0, sizeof(int), s));
-    hipLaunchKernelGGL(k_gs_rows, dim3(grid_for(n, kSB)), dim3(kSB), 0, s, n, nb, (const int*)D.rp, (const int*)D.ci,
+    const RowIdx R{D.rp, D.sell.rowpos};
+    hipLaunchKernelGGL(k_gs_rows, dim3(grid_for(n, kSB)), dim3(kSB), 0, s, n, nb, R, (const int*)D.ci,
                        (const double*)D.v, D.gs_ainv, D.gs_fresh, bad);
-    hipLaunchKernelGGL(k_gs_depths, dim3(grid_for(nblk, 64)), dim3(64), 0, s, n, nb, nblk, (const int*)D.rp,
-                       (const int*)D.ci, D.gs_df, D.gs_db, D.gs_maxd);
+    hipLaunchKernelGGL(k_gs_depths, dim3(grid_for(nblk, 64)), dim3(64), 0, s, n, nb, nblk, R, (const int*)D.ci,
+                       D.gs_df, D.gs_db, D.gs_maxd);
     HIP_CHECK(hipGetLastError());
     if (read1(bad, s)) throw Error(PAMG_E_NOT_SPD, "non-positive diagonal on a coarse level (Gauss-Seidel smoother)");
 }
@@ -1078,26 +1208,99 @@ std::unique_ptr<DeviceBuild> device_build(pamg_hierarchy* h, const pamg_csr& A, 
                            (const int*)L.rp, len);
         scan<int>(T, n, len, rp2, s);
         T.release(len);
+        // the permuted CSR: the level's own arrays, or the source of its sliced rows
+        bool sell = sell_applies(n, L.nnz, L.maxrow);
         D.rp = dalloc<int>(h, (size_t)n + 1, s);
-        D.ci = dalloc<int>(h, L.nnz, s);
-        D.v = dalloc<double>(h, L.nnz, s);
         D.dinv = dalloc<double>(h, n, s);
         D.p = dalloc<double>(h, n, s);
+        int* ci2 = sell ? T.get<int>(L.nnz) : dalloc<int>(h, L.nnz, s);
+        double* v2 = sell ? T.get<double>(L.nnz) : dalloc<double>(h, L.nnz, s);
         hipLaunchKernelGGL(k_reorder, dim3(grid_rows(n)), dim3(64), 0, s, n, (const int*)D.iperm,
                            (const int*)D.perm, (const int*)L.rp, (const int*)L.ci, (const double*)L.v,
-                           (const double*)L.dinv, (const double*)kcp[j], (const long long*)rp2, D.ci, D.v, D.dinv,
-                           D.p);
+                           (const double*)L.dinv, (const double*)kcp[j], (const long long*)rp2, ci2, v2, D.dinv, D.p);
         hipLaunchKernelGGL(k_to_int, dim3(grid_for(n + 1, kSB)), dim3(kSB), 0, s, (long long)n + 1,
                            (const long long*)rp2, D.rp);
         T.release(rp2);
-        D.vd = dalloc<double>(h, L.nnz, s);
-        hipLaunchKernelGGL(k_vd, dim3(grid_for(L.nnz, kSB)), dim3(kSB), 0, s, L.nnz, (const int*)D.ci,
-                           (const double*)D.v, (const double*)D.dinv, D.vd);
-        // tiles (host partition of the row pointer) and dictionaries
         std::vector<int32_t> rp_h, ap_h;
         to_host(rp_h, D.rp, (size_t)n + 1, s);
         to_host(ap_h, D.aggptr, (size_t)nc + 1, s);
         for (int32_t c = 0; c < nc; ++c) D.max_agg = std::max(D.max_agg, ap_h[c + 1] - ap_h[c]);
+        D.nent = L.nnz;
+        if (sell) {
+            // tiles (host partition of the aggregates), halved until every dictionary fits
+            DevSell& S = D.sell;
+            std::vector<int32_t> tiles = sell_tiles(ap_h, n, nc), dlen;
+            for (;;) {
+                const int nt = (int)(tiles.size() / 4);
+                int4* td = T.get<int4>(nt);
+                int* dl = T.get<int>(nt);
+                to_device(reinterpret_cast<int*>(td), tiles.data(), tiles.size(), s);
+                hipLaunchKernelGGL(k_dict_count, dim3(grid_rows(nt)), dim3(kSB), 0, s, nt, (const int4*)td,
+                                   (const int*)D.rp, (const int*)ci2, dl);
+                to_host(dlen, dl, (size_t)nt, s);
+                T.release(td);
+                T.release(dl);
+                if (!split_sell_tiles(tiles, ap_h, nc, dlen)) break;
+            }
+            const int nt = (int)dlen.size();
+            int4* td = T.get<int4>(nt);
+            int* size = T.get<int>(nt);
+            to_device(reinterpret_cast<int*>(td), tiles.data(), tiles.size(), s);
+            hipLaunchKernelGGL(k_sell_sizes, dim3(grid_rows(nt)), dim3(kSB), 0, s, nt, (const int4*)td,
+                               (const int*)D.rp, size);
+            std::vector<int32_t> size_h;
+            to_host(size_h, size, (size_t)nt, s);
+            T.release(td);
+            T.release(size);
+            std::vector<int32_t> full(8 * (size_t)nt, 0);
+            long long at = 0;
+            for (int t = 0; t < nt && at < (1ll << 31); ++t) {
+                const int32_t* q = &tiles[4 * (size_t)t];
+                const int32_t d[8] = {q[0], q[1], (int32_t)at, (int32_t)S.len, dlen[t], q[2], q[3], 0};
+                std::copy(d, d + 8, full.begin() + 8 * (size_t)t);
+                S.max_len = std::max(S.max_len, dlen[t]);
+                S.len += dlen[t];
+                at += size_h[t];
+            }
+            if (at < (1ll << 31)) {
+                S.n_tiles = nt;
+                D.nent = at;
+                sell_shares(full, 8, n, S.xcd);
+                S.tiles = dalloc<int>(h, full.size(), s);
+                to_device(S.tiles, full.data(), full.size(), s);
+                S.slot = dalloc<uint32_t>(h, n, s);
+                S.rowpos = dalloc<int>(h, n, s);
+                S.col = dalloc<int>(h, S.len, s);
+                S.loc = dalloc<uint16_t>(h, at, s);
+                D.ci = dalloc<int>(h, at, s);
+                D.v = dalloc<double>(h, at, s);
+                hipLaunchKernelGGL(k_sell_fill, dim3(grid_rows(nt)), dim3(kSB), 0, s, nt, (const int4*)S.tiles,
+                                   (const int*)D.rp, (const int*)ci2, (const double*)v2, S.slot, S.rowpos, D.ci, D.v,
+                                   S.col, S.loc);
+            } else {
+                sell = false;                   // more padded entries than 32-bit positions
+            }
+            if (!sell) {
+                D.ci = dalloc<int>(h, L.nnz, s);
+                D.v = dalloc<double>(h, L.nnz, s);
+                HIP_CHECK(hipMemcpyAsync(D.ci, ci2, sizeof(int) * L.nnz, hipMemcpyDeviceToDevice, s));
+                HIP_CHECK(hipMemcpyAsync(D.v, v2, sizeof(double) * L.nnz, hipMemcpyDeviceToDevice, s));
+            }
+            T.release(ci2);
+            T.release(v2);
+        } else {
+            D.ci = ci2;
+            D.v = v2;
+        }
+        D.vd = dalloc<double>(h, D.nent, s);
+        hipLaunchKernelGGL(k_vd, dim3(grid_for(D.nent, kSB)), dim3(kSB), 0, s, D.nent, (const int*)D.ci,
+                           (const double*)D.v, (const double*)D.dinv, D.vd);
+        D.items = first_tile_items(L.nnz);
+        if (sell) {
+            cip = D.iperm;
+            continue;
+        }
+        // tiles (host partition of the row pointer) and dictionaries
         int items = first_tile_items(L.nnz);
         std::vector<int32_t> up, down;
         int* dl_up = nullptr;

@@ -18,6 +18,16 @@ struct DevDict {
     int max_len = 0;
 };
 
+// Sliced rows of a level (SellRows on the device; ci is the level's).
+struct DevSell {
+    int *tiles = nullptr, *rowpos = nullptr, *col = nullptr;
+    uint32_t* slot = nullptr;
+    uint16_t* loc = nullptr;
+    long long len = 0;          // dictionary entries
+    int n_tiles = 0, max_len = 0;
+    int32_t xcd[9] = {};
+};
+
 // One device-built level in hierarchical numbering (LayoutLevel on the
 // device); its arrays belong to the hierarchy's allocation list.
 struct DevLevelOut {
@@ -27,6 +37,8 @@ struct DevLevelOut {
     int *up_tiles = nullptr, *down_tiles = nullptr;
     double *v = nullptr, *vd = nullptr, *dinv = nullptr, *p = nullptr;
     DevDict up_dict, down_dict;
+    DevSell sell;                       // n_tiles > 0: ci, v and vd are in its order, and there are no other tiles
+    long long nent = 0;                 // stored entries (with the padding of sliced rows)
     // hybrid Gauss-Seidel schedule (GsLevel on the device; device_gs_schedule)
     uint8_t *gs_df = nullptr, *gs_db = nullptr;
     int *gs_maxd = nullptr, *gs_fresh = nullptr;

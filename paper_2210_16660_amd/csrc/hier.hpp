@@ -9,7 +9,7 @@
 #include <string>
 #include <vector>
 
-#include "kernels.hpp"
+#include "kernels_sell.hpp"
 
 #define HIP_CHECK(call)                                                                              \
     do {                                                                                             \
@@ -92,6 +92,18 @@ struct DevLevelIdx {
     const uint16_t *up_loc = nullptr, *down_loc = nullptr;
     int up_dmax = 1, down_dmax = 1;     // longest dictionary (dynamic LDS of the tile kernels)
     long long up_dlen = 0, down_dlen = 0;  // total dictionary entries
+    // the largest levels: sliced rows (ci and the values in their padded
+    // order; none of the tiles above)
+    bool sell = false;
+    SellView sv{};
+    const int* rowpos = nullptr;        // first entry of each row (sliced rows; else null)
+    int sell_dmax = 1;                  // longest dictionary (dynamic LDS)
+    long long sell_dlen = 0;            // total dictionary entries
+    long long nent = 0;                 // stored entries: nnz, or with the padding of sliced rows
+    // workgroups of the level's tile launches (row_grid: the partials of its reductions)
+    int row_grid() const { return sell ? sell_grid(sv.ntiles) : tile_grid(n_up); }
+    int down_grid() const { return sell ? sell_grid(sv.ntiles) : tile_grid(n_down); }
+    RowIdx row_idx() const { return {rp, rowpos}; }
     // hybrid Gauss-Seidel schedule (l < L): per-row depths, per-block largest depths
     const uint8_t *gs_df = nullptr, *gs_db = nullptr;
     const int* gs_maxd = nullptr;

@@ -60,6 +60,16 @@ __device__ __forceinline__ T prolong_value(T d, T r, T p, T z) {
     return fma(p, z, dr);
 }
 
+// Where a level stores the entries of a row: entry k of row i is at
+// start(i) + k * stride() (CSR, or sliced rows when pos is set).
+struct RowIdx {
+    const int* rp;
+    const int* pos;
+    __device__ __forceinline__ int len(int i) const { return rp[i + 1] - rp[i]; }
+    __device__ __forceinline__ int start(int i) const { return pos ? pos[i] : rp[i]; }
+    __device__ __forceinline__ int stride() const { return pos ? kSlice : 1; }
+};
+
 // Tiles handled by this workgroup: first, first+stride, ... < end.
 struct TileWalk {
     int first, stride, end;

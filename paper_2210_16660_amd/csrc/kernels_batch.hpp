@@ -110,21 +110,23 @@ inline int unit_grid(long long nunits, int gpb) {
     return g < 1 ? 1 : (int)g;
 }
 
-// s[q] += sum over row entries [kb, ke) of a_k x[c_k][col0 + q], in entry order.
+// s[q] += sum over row i's entries, in entry order, of a_k x[c_k][col0 + q].
 // (The lanes of a group load the same index and value; plain loads keep the
 // line in L2 for the group's next entries: non-temporal loads made the
 // 16-column engine 1.6x slower.)
 template <int U, int CPL, typename T, typename XT>
-__device__ __forceinline__ void row_accumulate(int kb, int ke, const int* __restrict__ ci, const T* __restrict__ av,
-                                               const XT* __restrict__ x, int col0, T (&s)[CPL]) {
-    int k = kb;
-    for (; k + U <= ke; k += U) {
+__device__ __forceinline__ void row_accumulate(const RowIdx& R, int i, const int* __restrict__ ci,
+                                               const T* __restrict__ av, const XT* __restrict__ x, int col0,
+                                               T (&s)[CPL]) {
+    const int len = R.len(i), st = R.stride();
+    int o = R.start(i), k = 0;
+    for (; k + U <= len; k += U, o += U * st) {
         int c[U];
         T a[U];
 #pragma unroll
-        for (int u = 0; u < U; ++u) c[u] = ci[k + u];
+        for (int u = 0; u < U; ++u) c[u] = ci[o + u * st];
 #pragma unroll
-        for (int u = 0; u < U; ++u) a[u] = av[k + u];
+        for (int u = 0; u < U; ++u) a[u] = av[o + u * st];
         Vec<XT, CPL> xv[U];
 #pragma unroll
         for (int u = 0; u < U; ++u) xv[u] = vload<XT, CPL>(x + (size_t)c[u] * kW + col0);
@@ -133,9 +135,9 @@ __device__ __forceinline__ void row_accumulate(int kb, int ke, const int* __rest
 #pragma unroll
             for (int q = 0; q < CPL; ++q) s[q] += a[u] * (T)xv[u].v[q];
     }
-    for (; k < ke; ++k) {
-        const Vec<XT, CPL> xv = vload<XT, CPL>(x + (size_t)ci[k] * kW + col0);
-        const T a = av[k];
+    for (; k < len; ++k, o += st) {
+        const Vec<XT, CPL> xv = vload<XT, CPL>(x + (size_t)ci[o] * kW + col0);
+        const T a = av[o];
 #pragma unroll
         for (int q = 0; q < CPL; ++q) s[q] += a * (T)xv.v[q];
     }
@@ -145,7 +147,7 @@ __device__ __forceinline__ void row_accumulate(int kb, int ke, const int* __rest
 
 // Down-sweep: rc[I] = sum_{m in G_I} p_m (r_m - (A D^-1 r)_m), per column.
 template <int U, int CPL, typename T, typename RT>
-static __global__ __launch_bounds__(kBlock) void kb_down(int nc, const int* __restrict__ rp, const int* __restrict__ ci,
+static __global__ __launch_bounds__(kBlock) void kb_down(int nc, RowIdx rows, const int* __restrict__ ci,
                                                   const T* __restrict__ vd, const RT* __restrict__ r,
                                                   const T* __restrict__ p, const int* __restrict__ aggptr,
                                                   T* __restrict__ rc, const int* __restrict__ done) {
@@ -162,7 +164,7 @@ static __global__ __launch_bounds__(kBlock) void kb_down(int nc, const int* __re
             T s[CPL];
 #pragma unroll
             for (int q = 0; q < CPL; ++q) s[q] = 0;
-            row_accumulate<U, CPL, T, RT>(rp[m], rp[m + 1], ci, vd, r, col0, s);
+            row_accumulate<U, CPL, T, RT>(rows, m, ci, vd, r, col0, s);
             const Vec<RT, CPL> rm = vload<RT, CPL>(r + (size_t)m * kW + col0);
             const T pm = p[m];
 #pragma unroll
@@ -178,7 +180,7 @@ static __global__ __launch_bounds__(kBlock) void kb_down(int nc, const int* __re
 // Up-sweep at level l > 0: z = zp + D^-1 (r - A zp), prolongated into level
 // l-1: zp_f[m] = dinv_f[m] r_f[m] + p_f[m] z for the members m of row i.
 template <int U, int CPL, typename T, typename RT, typename RTF>
-static __global__ __launch_bounds__(kBlock) void kb_up(int n, const int* __restrict__ rp, const int* __restrict__ ci,
+static __global__ __launch_bounds__(kBlock) void kb_up(int n, RowIdx rows, const int* __restrict__ ci,
                                                 const T* __restrict__ av, const T* __restrict__ zp,
                                                 const RT* __restrict__ r, const T* __restrict__ dinv,
                                                 const int* __restrict__ aggptr_f, const RTF* __restrict__ r_f,
@@ -192,7 +194,7 @@ static __global__ __launch_bounds__(kBlock) void kb_up(int n, const int* __restr
         T s[CPL];
 #pragma unroll
         for (int q = 0; q < CPL; ++q) s[q] = 0;
-        row_accumulate<U, CPL, T, T>(rp[i], rp[i + 1], ci, av, zp, col0, s);
+        row_accumulate<U, CPL, T, T>(rows, i, ci, av, zp, col0, s);
         const Vec<T, CPL> zpi = vload<T, CPL>(zp + (size_t)i * kW + col0);
         const Vec<RT, CPL> ri = vload<RT, CPL>(r + (size_t)i * kW + col0);
         const T di = dinv[i];
@@ -222,7 +224,7 @@ constexpr int up0_rows_per_block() { return kBlock / (kW / up0_cols<T>()); }
 // z is written in the cycle's precision T: with the FP32 cycle z is a float
 // (exactly its FP64 widening), so the Krylov pass gathers 64-byte rows.
 template <typename T>
-static __global__ __launch_bounds__(kBlock) void kb_up0(int n, const int* __restrict__ rp, const int* __restrict__ ci,
+static __global__ __launch_bounds__(kBlock) void kb_up0(int n, RowIdx rows, const int* __restrict__ ci,
                                                  const T* __restrict__ av, const T* __restrict__ zp,
                                                  const T* __restrict__ r, const T* __restrict__ dinv,
                                                  T* __restrict__ z_out, const double* __restrict__ dv,
@@ -239,7 +241,7 @@ static __global__ __launch_bounds__(kBlock) void kb_up0(int n, const int* __rest
         T s[CPL];
 #pragma unroll
         for (int q = 0; q < CPL; ++q) s[q] = 0;
-        row_accumulate<8, CPL, T, T>(rp[i], rp[i + 1], ci, av, zp, col0, s);
+        row_accumulate<8, CPL, T, T>(rows, i, ci, av, zp, col0, s);
         const size_t e = (size_t)i * kW + col0;
         const Vec<T, CPL> zv = vload<T, CPL>(zp + e);
         const T di = dinv[i];
@@ -440,7 +442,7 @@ constexpr int kKrylovCols = 4;
 constexpr int kKrylovRowsPerBlock = kBlock / (kW / kKrylovCols);
 
 template <typename ZT>
-static __global__ __launch_bounds__(kBlock) void kb_krylov_pq(int n, const int* __restrict__ rp, const int* __restrict__ ci,
+static __global__ __launch_bounds__(kBlock) void kb_krylov_pq(int n, RowIdx rows, const int* __restrict__ ci,
                                                        const double* __restrict__ av, const ZT* __restrict__ z,
                                                        const double* __restrict__ p_old, double* __restrict__ p_new,
                                                        double* __restrict__ q, const double* __restrict__ r,
@@ -466,7 +468,7 @@ static __global__ __launch_bounds__(kBlock) void kb_krylov_pq(int n, const int* 
         double s[CPL];
 #pragma unroll
         for (int c = 0; c < CPL; ++c) s[c] = 0.0;
-        row_accumulate<8, CPL, double, ZT>(rp[i], rp[i + 1], ci, av, z, col0, s);
+        row_accumulate<8, CPL, double, ZT>(rows, i, ci, av, z, col0, s);
         const size_t e = (size_t)i * kW + col0;
         const Vec<ZT, CPL> zi = vload<ZT, CPL>(z + e);
         const Vec<double, CPL> po = vload<double, CPL>(p_old + e);
@@ -730,7 +732,7 @@ static __global__ __launch_bounds__(kBlock) void kb_store(int n, const int* __re
 
 // Y = B - A X (all columns) and per-column partials of y.y; with `commit`
 // set, columns in `mask` also take Y as their recurrence residual R.
-static __global__ __launch_bounds__(kBlock) void kb_resid(int n, const int* __restrict__ rp, const int* __restrict__ ci,
+static __global__ __launch_bounds__(kBlock) void kb_resid(int n, RowIdx rows, const int* __restrict__ ci,
                                                    const double* __restrict__ av, const double* __restrict__ X,
                                                    const double* __restrict__ B, double* __restrict__ Y,
                                                    double* __restrict__ R, float* __restrict__ R32, int mask,
@@ -743,7 +745,7 @@ static __global__ __launch_bounds__(kBlock) void kb_resid(int n, const int* __re
     const bool commit = R != nullptr && ((mask >> lane) & 1);
     for (int i = w.first; i < w.end; i += w.stride) {
         double s[1] = {0.0};
-        row_accumulate<4, 1, double, double>(rp[i], rp[i + 1], ci, av, X, lane, s);
+        row_accumulate<4, 1, double, double>(rows, i, ci, av, X, lane, s);
         const size_t e = (size_t)i * kW + lane;
         const double y = B[e] - s[0];
         Y[e] = y;

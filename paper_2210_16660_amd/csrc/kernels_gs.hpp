@@ -33,7 +33,7 @@ constexpr int kGsDenseRow = 64;       // mean row length from which a level's bl
 // (backward), in column order; x_new = x_old + d / omega.
 template <int MAXB, typename T, typename TT, bool BACKWARD, bool ZERO>
 static __global__ __launch_bounds__(MAXB) void k_hgs(
-    int n, int nb, const int* __restrict__ ci, const T* __restrict__ av, const int2* __restrict__ fr,
+    int n, int nb, RowIdx R, const int* __restrict__ ci, const T* __restrict__ av, const int2* __restrict__ fr,
     const T* __restrict__ ainv, const uint8_t* __restrict__ depth, const int* __restrict__ maxd,
     const TT* __restrict__ tin, const T* __restrict__ x_old, T* __restrict__ x_new, T omega_inv,
     const int* __restrict__ done) {
@@ -43,13 +43,16 @@ static __global__ __launch_bounds__(MAXB) void k_hgs(
     const int b0 = p * nb, b1 = min(n, b0 + nb);
     const int i = b0 + t;
     const bool own = t < nb && i < b1;
+    const int st = R.stride();
     int dep = -1, nf = 0, kf = 0;
     T ti = 0, xi = 0, ai = 0;
     if (own) {
         const int2 f = fr[i];
         const int before = f.y & 0xff, after = (f.y >> 8) & 0xff, diag = (f.y >> 16) & 1;
         nf = BACKWARD ? after : before;
-        kf = BACKWARD ? f.x + before + diag : f.x;
+        // in-block entries of the row: kf, kf + st, ...
+        const int k = f.x - R.rp[i] + (BACKWARD ? before + diag : 0);
+        kf = R.start(i) + k * st;
         ti = (T)tin[i];
         ai = ainv[i];
         dep = depth[i];
@@ -63,7 +66,7 @@ static __global__ __launch_bounds__(MAXB) void k_hgs(
     const int kb = nf > 0 ? kf : 0, kl = nf > 0 ? nf - 1 : 0;
 #pragma unroll
     for (int u = 0; u < kGsFresh; ++u) {
-        const int k = kb + min(u, kl);
+        const int k = kb + min(u, kl) * st;
         fa[u] = av[k];
         fq[u] = ci[k];
     }
@@ -95,18 +98,18 @@ static __global__ __launch_bounds__(MAXB) void k_hgs(
             // entries past the registers: kGsBatch at a time, loaded together
             // at clamped indices, added in order, a branch per entry (it
             // holds the level-0 kernels' registers down)
-            for (int k0 = kf + kGsFresh; k0 < kf + nf; k0 += kGsBatch) {
+            for (int k0 = kGsFresh; k0 < nf; k0 += kGsBatch) {
                 T ab[kGsBatch];
                 int cb[kGsBatch];
 #pragma unroll
                 for (int u = 0; u < kGsBatch; ++u) {
-                    const int k = min(k0 + u, kf + nf - 1);
+                    const int k = kf + min(k0 + u, nf - 1) * st;
                     ab[u] = av[k];
                     cb[u] = ci[k] - b0;
                 }
 #pragma unroll
                 for (int u = 0; u < kGsBatch; ++u)
-                    if (k0 + u < kf + nf) fresh += ab[u] * s_d[cb[u]];
+                    if (k0 + u < nf) fresh += ab[u] * s_d[cb[u]];
             }
             s_d[t] = (ti - fresh) * ai;
         }
@@ -151,7 +154,7 @@ __device__ __forceinline__ int gs_tile_offset(int ns, int s, int q) {
 // wave's four 16-lane groups taking every fourth in-block entry of a row and
 // meeting in a fixed butterfly.  Rows and columns past the block are zero.
 template <bool BACKWARD>
-static __global__ __launch_bounds__(64) void k_gs_invert(int n, int nb, int ns, const int* __restrict__ ci,
+static __global__ __launch_bounds__(64) void k_gs_invert(int n, int nb, int ns, RowIdx R, const int* __restrict__ ci,
                                                          const double* __restrict__ av, const int2* __restrict__ fr,
                                                          const double* __restrict__ ainv, double* __restrict__ W) {
     __shared__ double S[kGsMaxBlock][kGsInvCols + 1];
@@ -168,10 +171,14 @@ static __global__ __launch_bounds__(64) void k_gs_invert(int n, int nb, int ns, 
         const int i = BACKWARD ? first - u : first + u;
         const int2 f = fr[b0 + i];
         const int before = f.y & 0xff, after = (f.y >> 8) & 0xff, diag = (f.y >> 16) & 1;
-        const int k0 = BACKWARD ? f.x + before + diag : f.x, k1 = k0 + (BACKWARD ? after : before);
+        const int o = R.start(b0 + i) + (f.x - R.rp[b0 + i] + (BACKWARD ? before + diag : 0)) * R.stride();
+        const int nf = BACKWARD ? after : before;
         double s = 0.0;
 #pragma unroll 4
-        for (int k = k0 + part; k < k1; k += 4) s += av[k] * S[ci[k] - b0][c];
+        for (int u4 = part; u4 < nf; u4 += 4) {
+            const int k = o + u4 * R.stride();
+            s += av[k] * S[ci[k] - b0][c];
+        }
         s += __shfl_xor(s, 16, 64);
         s += __shfl_xor(s, 32, 64);
         if (part == 0) S[i][c] = ((i == c0 + c ? 1.0 : 0.0) - s) * ainv[b0 + i];

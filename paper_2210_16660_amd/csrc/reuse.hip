@@ -74,13 +74,24 @@ static __global__ __launch_bounds__(kBlock) void k_scale_columns(long long nnz, 
 }
 
 // Hybrid Gauss-Seidel: 1 / a_ii of every row (device order).
-static __global__ __launch_bounds__(kBlock) void k_diag_inverse(int n, const int* __restrict__ rp,
-                                                         const int* __restrict__ ci, const double* __restrict__ v,
-                                                         double* __restrict__ ainv) {
+static __global__ __launch_bounds__(kBlock) void k_diag_inverse(int n, RowIdx R, const int* __restrict__ ci,
+                                                         const double* __restrict__ v, double* __restrict__ ainv) {
     const int stride = gridDim.x * kBlock;
-    for (int i = blockIdx.x * kBlock + threadIdx.x; i < n; i += stride)
-        for (int k = rp[i]; k < rp[i + 1]; ++k)
-            if (ci[k] == i) ainv[i] = 1.0 / v[k];
+    for (int i = blockIdx.x * kBlock + threadIdx.x; i < n; i += stride) {
+        const int o = R.start(i), len = R.len(i), st = R.stride();
+        for (int k = 0; k < len; ++k)
+            if (ci[o + k * st] == i) ainv[i] = 1.0 / v[o + k * st];
+    }
+}
+
+// Values in the level's stored order: v_k = vc[idx_k], 0 for padding (idx_k < 0).
+static __global__ __launch_bounds__(kBlock) void k_gather_entries(long long nent, const int* __restrict__ idx,
+                                                           const double* __restrict__ vc, double* __restrict__ v) {
+    const long long stride = (long long)gridDim.x * kBlock;
+    for (long long k = (long long)blockIdx.x * kBlock + threadIdx.x; k < nent; k += stride) {
+        const int q = idx[k];
+        v[k] = q >= 0 ? vc[q] : 0.0;
+    }
 }
 
 
@@ -153,7 +164,20 @@ static void build_plan(pamg_hierarchy* h, hipStream_t s) {
         HIP_CHECK(hipMemcpy(perm.data(), I.perm, sizeof(int32_t) * I.n, hipMemcpyDeviceToHost));
         HIP_CHECK(hipMemcpy(iperm.data(), I.iperm, sizeof(int32_t) * I.n, hipMemcpyDeviceToHost));
         R->crp.push_back(to_device(A.rp));
-        R->hperm.push_back(to_device(entry_order(A, perm, iperm)));
+        std::vector<int32_t> order = entry_order(A, perm, iperm);
+        if (I.sell) {
+            // the level's entries as its slices store them
+            std::vector<int32_t> rp(I.n + 1), rowpos(I.n), padded(I.nent, -1);
+            HIP_CHECK(hipMemcpy(rp.data(), I.rp, sizeof(int32_t) * (I.n + 1), hipMemcpyDeviceToHost));
+            HIP_CHECK(hipMemcpy(rowpos.data(), I.rowpos, sizeof(int32_t) * I.n, hipMemcpyDeviceToHost));
+            parallel_ranges(I.n, [&](int, int64_t b, int64_t e) {
+                for (int64_t i = b; i < e; ++i)
+                    for (int32_t k = rp[i]; k < rp[i + 1]; ++k)
+                        padded[rowpos[i] + (int64_t)(k - rp[i]) * kSlice] = order[k];
+            });
+            order.swap(padded);
+        }
+        R->hperm.push_back(to_device(order));
         R->dcan.push_back(static_cast<double*>(dalloc_plan(sizeof(double) * std::max<size_t>(1, I.n))));
     }
     const HostCSR& A0 = h->host.lev[0].A;
@@ -204,24 +228,24 @@ static void update_values(pamg_hierarchy* h, const double* val, bool on_device, 
         const double* vc = R.vcan[R.kept_pw[j]];
         hipLaunchKernelGGL(k_l1_inverse, dim3(vec_grid(I.n)), dim3(kBlock), 0, s, I.n, (const int*)R.crp[j], vc,
                            R.dcan[j]);
-        hipLaunchKernelGGL((k_gather<double, double>), dim3(vec_grid(I.nnz)), dim3(kBlock), 0, s, (int)I.nnz,
+        hipLaunchKernelGGL(k_gather_entries, dim3(vec_grid(I.nent)), dim3(kBlock), 0, s, I.nent,
                            (const int*)R.hperm[j], vc, V.v[j]);
         hipLaunchKernelGGL((k_gather<double, double>), dim3(vec_grid(I.n)), dim3(kBlock), 0, s, I.n,
                            (const int*)I.iperm, (const double*)R.dcan[j], V.dinv[j]);
         if (j < h->L)
-            hipLaunchKernelGGL(k_scale_columns, dim3(vec_grid(I.nnz)), dim3(kBlock), 0, s, I.nnz, (const int*)I.ci,
+            hipLaunchKernelGGL(k_scale_columns, dim3(vec_grid(I.nent)), dim3(kBlock), 0, s, I.nent, (const int*)I.ci,
                                (const double*)V.v[j], (const double*)V.dinv[j], V.vd[j]);
         const bool gs = h->smoother == PAMG_SMOOTHER_HYBRID_GS && j < h->L;
         if (gs)
-            hipLaunchKernelGGL(k_diag_inverse, dim3(vec_grid(I.n)), dim3(kBlock), 0, s, I.n, (const int*)I.rp,
-                               (const int*)I.ci, (const double*)V.v[j], V.gsa[j]);
+            hipLaunchKernelGGL(k_diag_inverse, dim3(vec_grid(I.n)), dim3(kBlock), 0, s, I.n, I.row_idx(), (const int*)I.ci,
+                               (const double*)V.v[j], V.gsa[j]);
         if (h->f32.built) {
-            hipLaunchKernelGGL((k_convert<double, float>), dim3(vec_grid(I.nnz)), dim3(kBlock), 0, s, I.nnz,
+            hipLaunchKernelGGL((k_convert<double, float>), dim3(vec_grid(I.nent)), dim3(kBlock), 0, s, I.nent,
                                (const double*)V.v[j], h->f32.v[j]);
             hipLaunchKernelGGL((k_convert<double, float>), dim3(vec_grid(I.n)), dim3(kBlock), 0, s, (long long)I.n,
                                (const double*)V.dinv[j], h->f32.dinv[j]);
             if (j < h->L)
-                hipLaunchKernelGGL((k_convert<double, float>), dim3(vec_grid(I.nnz)), dim3(kBlock), 0, s, I.nnz,
+                hipLaunchKernelGGL((k_convert<double, float>), dim3(vec_grid(I.nent)), dim3(kBlock), 0, s, I.nent,
                                    (const double*)V.vd[j], h->f32.vd[j]);
             if (gs)
                 hipLaunchKernelGGL((k_convert<double, float>), dim3(vec_grid(I.n)), dim3(kBlock), 0, s,

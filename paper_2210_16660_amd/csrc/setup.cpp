@@ -1071,6 +1071,154 @@ void make_tiles(const std::vector<int32_t>& rp, const std::vector<int32_t>& aggp
     }
 }
 
+bool sell_applies(int64_t n, int64_t nnz, int64_t maxrow) {
+    return first_tile_items(nnz) >= kDictItems && n >= kSellMinRows && maxrow <= kSellMaxRow;
+}
+
+// Equal tiles, their number a multiple of the workgroups the chip holds (a
+// level one tile over would run as long as one with twice the tiles): about
+// n / (k kSellGrid) rows with the smallest k that fits a slice.
+std::vector<int32_t> sell_tiles(const std::vector<int32_t>& aggptr, int32_t n, int32_t nc) {
+    const int64_t k = (n + (int64_t)kSellGrid * kSlice - 1) / ((int64_t)kSellGrid * kSlice);
+    const int64_t count = k * kSellGrid;
+    std::vector<int32_t> tiles;
+    int32_t r = 0, c = 0;
+    for (int64_t t = 1; r < n; ++t) {
+        // up to the share's end, never more than a slice
+        const int32_t want = t < count ? (int32_t)((int64_t)n * t / count) : n;
+        int32_t e = std::min(std::max(want, r + 1), r + kSlice), ce = c;
+        if (nc > 0) {
+            ce = c + 1;
+            while (ce < nc && aggptr[ce + 1] <= e) ++ce;
+            e = aggptr[ce];
+        }
+        tiles.insert(tiles.end(), {r, e, c, ce});
+        r = e;
+        c = ce;
+    }
+    return tiles;
+}
+
+bool split_sell_tiles(std::vector<int32_t>& tiles, const std::vector<int32_t>& aggptr, int32_t nc,
+                      const std::vector<int32_t>& dlen) {
+    std::vector<int32_t> out;
+    bool any = false;
+    for (size_t t = 0; t < dlen.size(); ++t) {
+        const int32_t r0 = tiles[4 * t], r1 = tiles[4 * t + 1], c0 = tiles[4 * t + 2], c1 = tiles[4 * t + 3];
+        if (dlen[t] <= kSellDict) {
+            out.insert(out.end(), {r0, r1, c0, c1});
+            continue;
+        }
+        any = true;
+        if (nc == 0) {
+            const int32_t m = r0 + (r1 - r0) / 2;
+            out.insert(out.end(), {r0, m, 0, 0, m, r1, 0, 0});
+        } else {
+            const int32_t c = c0 + (c1 - c0) / 2;
+            out.insert(out.end(), {r0, aggptr[c], c0, c, aggptr[c], r1, c, c1});
+        }
+    }
+    tiles.swap(out);
+    return any;
+}
+void sell_shares(const std::vector<int32_t>& tiles, int stride, int32_t n, int32_t xcd[9]) {
+    const int32_t nt = (int32_t)(tiles.size() / stride);
+    for (int32_t x = 0, t = 0; x < 8; ++x) {
+        while (t < nt && tiles[(size_t)stride * t] < (int64_t)n * x / 8) ++t;
+        xcd[x] = t;
+    }
+    xcd[8] = nt;
+}
+
+// a tile that cannot be halved again (one row, or one aggregate) always fits
+static_assert((kSellMaxRow << kMaxAggSteps) <= kSellDict, "an aggregate of the longest rows");
+
+SellRows sell_rows(const std::vector<int32_t>& rp, const std::vector<int32_t>& ci, const std::vector<int32_t>& aggptr,
+                   int32_t n, int32_t nc) {
+    SellRows S;
+    std::vector<int32_t> tiles = sell_tiles(aggptr, n, nc);
+    struct alignas(64) PosBuf {  // one cache line (or more) per thread
+        std::vector<int32_t> pos;
+    };
+    std::vector<PosBuf> pbuf(num_threads());
+    std::vector<std::vector<int32_t>> dict;
+    std::vector<uint16_t> local(ci.size());
+    for (;;) {
+        const int64_t nt = (int64_t)tiles.size() / 4;
+        dict.assign(nt, {});
+        std::vector<int32_t> dlen(nt, 0);
+        parallel_chunks(nt, 4, [&](int th, int64_t b, int64_t e) {
+            std::vector<int32_t>& pos = pbuf[th].pos;
+            if (pos.empty()) pos.assign(n, -1);
+            for (int64_t t = b; t < e; ++t) {
+                const int32_t k0 = rp[tiles[4 * t]], k1 = rp[tiles[4 * t + 1]];
+                std::vector<int32_t>& u = dict[t];
+                for (int32_t k = k0; k < k1; ++k)
+                    if (pos[ci[k]] < 0) {
+                        pos[ci[k]] = 0;
+                        u.push_back(ci[k]);
+                    }
+                std::sort(u.begin(), u.end());
+                for (size_t j = 0; j < u.size(); ++j) pos[u[j]] = (int32_t)j;
+                for (int32_t k = k0; k < k1; ++k) local[k] = (uint16_t)pos[ci[k]];
+                for (int32_t c : u) pos[c] = -1;
+                dlen[t] = (int32_t)u.size();
+            }
+        });
+        if (!split_sell_tiles(tiles, aggptr, nc, dlen)) break;
+    }
+    const int64_t nt = (int64_t)tiles.size() / 4;
+    int64_t total = 0, at = 0;
+    S.tiles.resize(8 * nt);
+    for (int64_t t = 0; t < nt; ++t) {
+        const int32_t r0 = tiles[4 * t], r1 = tiles[4 * t + 1], len = (int32_t)dict[t].size();
+        int32_t longest = 0;
+        for (int32_t i = r0; i < r1; ++i) longest = std::max(longest, rp[i + 1] - rp[i]);
+        const int32_t d[8] = {r0, r1, (int32_t)at, (int32_t)total, len, tiles[4 * t + 2], tiles[4 * t + 3], 0};
+        std::copy(d, d + 8, S.tiles.begin() + 8 * t);
+        S.max_len = std::max(S.max_len, len);
+        total += len;
+        at += (int64_t)kSlice * longest;
+        if (at >= (int64_t(1) << 31)) return SellRows();
+    }
+    sell_shares(S.tiles, 8, n, S.xcd);
+    S.col.resize(total);
+    S.slot.resize(n);
+    S.rowpos.resize(n);
+    S.ci.assign(at, 0);
+    S.local.assign(at, 0);
+    parallel_ranges(nt, [&](int, int64_t b, int64_t e) {
+        std::vector<int32_t> order;
+        for (int64_t t = b; t < e; ++t) {
+            std::copy(dict[t].begin(), dict[t].end(), S.col.begin() + S.tiles[8 * t + 3]);
+            const int32_t r0 = S.tiles[8 * t], rows = S.tiles[8 * t + 1] - r0;
+            order.resize(rows);
+            std::iota(order.begin(), order.end(), 0);
+            const auto len = [&](int32_t j) { return rp[r0 + j + 1] - rp[r0 + j]; };
+            std::stable_sort(order.begin(), order.end(), [&](int32_t x, int32_t y) { return len(x) > len(y); });
+            for (int32_t q = 0; q < rows; ++q) {
+                const int32_t i = r0 + order[q], o = S.tiles[8 * t + 2] + q;
+                S.slot[r0 + q] = (uint32_t)order[q] | (uint32_t)len(order[q]) << 16;
+                S.rowpos[i] = o;
+                for (int32_t k = rp[i]; k < rp[i + 1]; ++k) {
+                    S.ci[o + (int64_t)(k - rp[i]) * kSlice] = ci[k];
+                    S.local[o + (int64_t)(k - rp[i]) * kSlice] = local[k];
+                }
+            }
+        }
+    });
+    return S;
+}
+
+std::vector<double> sell_values(const SellRows& S, const std::vector<int32_t>& rp, const std::vector<double>& v) {
+    std::vector<double> out(S.entries(), 0.0);
+    parallel_ranges((int64_t)S.rowpos.size(), [&](int, int64_t b, int64_t e) {
+        for (int64_t i = b; i < e; ++i)
+            for (int32_t k = rp[i]; k < rp[i + 1]; ++k) out[S.rowpos[i] + (int64_t)(k - rp[i]) * kSlice] = v[k];
+    });
+    return out;
+}
+
 // Row tiles of an n-row matrix with ncols columns, capacity chosen as for a
 // level's own matrix: the first capacity whose dictionaries fit the
 // prefetch slots (halving from first_tile_items), dictionaries only for
@@ -1169,7 +1317,11 @@ std::vector<LayoutLevel> build_layout(const HostHierarchy& H) {
         });
         int items = first_tile_items((int64_t)L.rp[n]);
         const int32_t nc = l + 1 < nl ? H.lev[l + 1].A.n : 0;
-        for (;;) {
+        L.items = items;
+        int32_t maxrow = 0;
+        for (int32_t i = 0; i < n; ++i) maxrow = std::max(maxrow, L.rp[i + 1] - L.rp[i]);
+        if (sell_applies(n, L.rp[n], maxrow)) L.sell = sell_rows(L.rp, L.ci, L.aggptr, n, nc);
+        while (L.sell.tiles.empty()) {
             L.items = items;
             const int32_t cap = items * kBlock;
             make_tiles(L.rp, L.aggptr, n, nc, cap, L.up_tiles, L.down_tiles);
