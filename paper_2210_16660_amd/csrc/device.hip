@@ -13,6 +13,7 @@
 
 #include "hier.hpp"
 #include "kernels_gs.hpp"
+#include "kernels_tail.hpp"
 #include "dsetup.hpp"
 
 namespace pamg {
@@ -135,6 +136,8 @@ static void upload_values(pamg_hierarchy* h, DevVals<T>& V, const std::vector<La
     V.built = true;
 }
 
+static int tail_level(const pamg_hierarchy* h);
+
 bool gs_dense_level(const pamg_hierarchy* h, int l) {
     const DevLevelIdx& I = h->idx[l];
     return h->smoother == PAMG_SMOOTHER_HYBRID_GS && l < h->L && I.nnz >= (long long)kGsDenseRow * I.n;
@@ -171,15 +174,15 @@ static uint64_t matrix_bytes(const DevLevelIdx& I, bool down, uint64_t s) {
 }
 
 static uint64_t vcycle_bytes(const pamg_hierarchy* h, int s) {
-    // sum over l < L of the two matrix passes + (10 n_l + 2 n_{l+1}) s, plus the coarse solve
+    // sum over l < tail of the two matrix passes + (10 n_l + 2 n_{l+1}) s, plus the dense product of the tail
     uint64_t B = 0;
-    for (int l = 0; l < h->L; ++l) {
+    for (int l = 0; l < h->tail; ++l) {
         const DevLevelIdx& I = h->idx[l];
         const uint64_t n = I.n, nc = h->idx[l + 1].n;
         B += matrix_bytes(I, true, s) + matrix_bytes(I, false, s) + (10 * n + 2 * nc) * s;
     }
-    const uint64_t nL = h->idx[h->L].n;
-    B += (nL * nL + 2 * nL) * s;
+    const uint64_t nt = h->idx[h->tail].n;
+    B += (nt * nt + 2 * nt) * s;
     return B;
 }
 
@@ -323,6 +326,15 @@ void upload_hierarchy(pamg_hierarchy* h, const std::vector<LayoutLevel>& lay, bo
     if (h->smoother == PAMG_SMOOTHER_HYBRID_GS)
         for (int l = 0; l < h->L; ++l)
             if (gs_dense_level(h, l)) build_gs_dense(h, l, s);
+    h->tail = tail_level(h);
+    const size_t nt = (size_t)h->idx[h->tail].n;
+    h->f64.tail = h->tail < h->L ? dalloc<double>(h, nt * nt, s) : h->f64.ainv;
+    if (build_f32) h->f32.tail = h->tail < h->L ? dalloc<float>(h, nt * nt, s) : h->f32.ainv;
+    {
+        std::unique_ptr<TailWork> w = tail_work(h, s);
+        build_tail(h, *w, s);
+        HIP_CHECK(hipStreamSynchronize(s));
+    }
     const int n0 = h->idx[0].n;
     int maxn = 0;
     for (auto& I : h->idx) maxn = std::max(maxn, I.n);
@@ -534,18 +546,18 @@ static void launch_tiled(const DevTiled& M, const T* v, const T* x, const BT* b,
 
 template <typename ZT>
 static void launch_krylov(const DevLevelIdx& I, const double* v, const ZT* z, const double* p_old, double* p_new,
-                          double* q, const double* r, const SolveState* st, double* partial, const int* done,
-                          hipStream_t s) {
+                          double* q, const double* r, SolveState* st, const double* zpart, int zcount,
+                          double* partial, const int* done, hipStream_t s) {
     if (I.sell) {
         LAUNCH((ks_krylov_pq<ZT>), I.row_grid(), sell_lds_bytes<double>(I.sell_dmax), s, v, z, p_old,
-               p_new, q, r, I.sv, st, partial, done);
+               p_new, q, r, I.sv, st, zpart, zcount, partial, done);
         return;
     }
     with_items(I.items, [&](auto it) {
         constexpr int IT = decltype(it)::value;
         LAUNCH((k_krylov_pq<IT, ZT>), I.row_grid(), (tile_lds_bytes<IT, double>(I.up_dmax)), s, (const int*)I.rp,
                (const int*)I.ci, v, z, p_old, p_new, q, r, I.up_tiles, I.n_up, I.up_span, I.up_col, I.up_loc, st,
-               partial, done);
+               zpart, zcount, partial, done);
     });
 }
 
@@ -553,19 +565,82 @@ template <typename T, typename RT, typename RTF, bool OUT>
 static void launch_coarse(int nL, const T* ainv, const RT* r, const int* aggptr_f, const RTF* r_f, const T* dinv_f,
                           const T* p_f, T* zp_f, double* z_out, const double* dv, double* partial, const int* done,
                           hipStream_t s) {
-    if (nL > kCoarseRowsMin) {
-        hipLaunchKernelGGL((k_coarse_rows<T, RT, RTF, OUT>), dim3(coarse_rows_grid(nL)), dim3(kBlock), 0, s, nL, ainv,
-                           r, aggptr_f, r_f, dinv_f, p_f, zp_f, z_out, dv, partial, done);
-        return;
+    hipLaunchKernelGGL((k_coarse_rows<T, RT, RTF, OUT>), dim3(coarse_rows_grid(nL)), dim3(kBlock), 0, s, nL, ainv, r,
+                       aggptr_f, r_f, dinv_f, p_f, zp_f, z_out, dv, partial, done);
+}
+
+// ---------------------------------------------------------------- dense tail
+// The cycle from a small level t down to the coarsest and back is one linear
+// operator of n_t unknowns, B_t; on the levels below about a thousand rows its
+// two sweeps a level are nothing but launches (4.6 to 6.5 us each), while B_t
+// as a dense matrix is one product like the coarsest level's.  With
+// E = I - A D^-1 (the residual after pre-smoothing from zero), P the level's
+// prolongator and B_L = A_L^-1,
+//   B_l = D^-1 + E^T (D^-1 + P B_{l+1} P^T E)
+// built in FP64 after the coarsest inverse (A is symmetric: column j of E is
+// read from row j), two sparse times dense products a level, and rounded once
+// for the FP32 cycle.
+//
+// The line (tail_level): up to kTailRows rows (8 MB, which the XCDs' L2s hold)
+// where B_t has at most kTailShare times the operator's entries, up to twice
+// the rows where it has no more than the operator.  32^3: 22 launches an
+// iteration become 14; at 2048 rows the product takes 8 us against 10 to 13 us
+// for the two launches of a level.  (serve.hip charges the bound.)
+
+static int tail_level(const pamg_hierarchy* h) {
+    if (h->smoother != PAMG_SMOOTHER_L1_JACOBI || h->smoothed_p) return h->L;
+    int t = h->L;
+    while (t > 1) {
+        const long long n = h->idx[t - 1].n;
+        if (n > 2 * kTailRows || n * n > (n > kTailRows ? 1 : kTailShare) * h->idx[0].nnz) break;
+        --t;
     }
-    const int G = coarse_groups(nL);
-    const size_t lds = (size_t)(1 + G) * nL * sizeof(T);
-    hipLaunchKernelGGL((k_coarse<T, RT, RTF, OUT>), dim3(1), dim3(kCoarseThreads), lds, s, nL, G, ainv, r, aggptr_f,
-                       r_f, dinv_f, p_f, zp_f, z_out, dv, partial, done);
+    return t;
+}
+
+std::unique_ptr<TailWork> tail_work(pamg_hierarchy* h, hipStream_t s) {
+    std::unique_ptr<TailWork> w(new TailWork());
+    if (h->tail >= h->L) return w;
+    w->ctx = h->ctx;
+    auto get = [&](size_t bytes) {
+        void* p = ctx_alloc(h->ctx, bytes, s);
+        w->bufs.push_back({p, bytes});
+        return p;
+    };
+    const size_t n = h->idx[h->tail].n, nc = h->idx[h->tail + 1].n;
+    w->G = static_cast<double*>(get(n * nc * sizeof(double)));
+    w->own = static_cast<int*>(get(n * sizeof(int)));
+    if (h->tail + 1 < h->L) {
+        w->B[0] = static_cast<double*>(get(nc * nc * sizeof(double)));
+        w->B[1] = static_cast<double*>(get(nc * nc * sizeof(double)));
+    }
+    return w;
+}
+
+void build_tail(pamg_hierarchy* h, TailWork& w, hipStream_t s) {
+    DevVals<double>& V = h->f64;
+    const double* Bc = V.ainv;
+    for (int l = h->L - 1; l >= h->tail; --l) {
+        const DevLevelIdx& I = h->idx[l];
+        const int n = I.n, nc = I.nc;
+        double* Bl = l == h->tail ? V.tail : w.B[l & 1];
+        LAUNCH(k_tail_owners, vec_grid(nc), 0, s, nc, (const int*)I.aggptr, w.own);
+        LAUNCH(k_tail_g, nc, nc * sizeof(double), s, n, nc, (const int*)I.rp, (const int*)I.ci, (const double*)V.v[l],
+               (const double*)V.dinv[l], (const double*)V.p[l], (const int*)w.own, Bc, w.G);
+        LAUNCH(k_tail_b, n, 0, s, n, (const int*)I.rp, (const int*)I.ci, (const double*)V.v[l],
+               (const double*)V.dinv[l], (const double*)V.p[l], (const int*)w.own, (const double*)w.G, Bl);
+        Bc = Bl;
+    }
+    if (h->f32.built && h->tail < h->L) {
+        const long long nn = (long long)h->idx[h->tail].n * h->idx[h->tail].n;
+        hipLaunchKernelGGL((k_convert<double, float>), dim3(vec_grid(nn)), dim3(kBlock), 0, s, nn,
+                           (const double*)V.tail, h->f32.tail);
+    }
+    HIP_CHECK(hipGetLastError());
 }
 
 // number of partials the coarsest level leaves when it writes z (single level)
-static int coarse_partials(int nL) { return nL > kCoarseRowsMin ? coarse_rows_grid(nL) : 1; }
+static int coarse_partials(int nL) { return coarse_rows_grid(nL); }
 
 // ---------------------------------------------------------------- schedule
 
@@ -737,7 +812,7 @@ static int enqueue_vcycle_sa(pamg_hierarchy* h, DevVals<T>& V, const double* r0,
 template <typename T, typename R0, typename ZO = double>
 static int enqueue_vcycle_plain(pamg_hierarchy* h, DevVals<T>& V, const R0* r0, ZO* z_out, const double* dv,
                                 const int* done, hipStream_t s) {
-    const int L = h->L;
+    const int L = h->tail;                  // from here on one dense product
     for (int l = 0; l < L; ++l) {
         const DevLevelIdx& I = h->idx[l];
         if (l == 0)
@@ -748,17 +823,17 @@ static int enqueue_vcycle_plain(pamg_hierarchy* h, DevVals<T>& V, const R0* r0, 
     const int nL = h->idx[L].n;
     if constexpr (std::is_same<ZO, double>::value) {
         if (L == 0) {
-            launch_coarse<T, R0, R0, true>(nL, V.ainv, r0, nullptr, (const R0*)nullptr, nullptr, nullptr, nullptr,
+            launch_coarse<T, R0, R0, true>(nL, V.tail, r0, nullptr, (const R0*)nullptr, nullptr, nullptr, nullptr,
                                            z_out, dv, h->partial, done, s);
             return coarse_partials(nL);
         }
     }
     const DevLevelIdx& F = h->idx[L - 1];
     if (L - 1 == 0)
-        launch_coarse<T, T, R0, false>(nL, V.ainv, V.r[L], F.aggptr, r0, V.dinv[0], V.p[0], V.zp[0], nullptr,
+        launch_coarse<T, T, R0, false>(nL, V.tail, V.r[L], F.aggptr, r0, V.dinv[0], V.p[0], V.zp[0], nullptr,
                                        nullptr, nullptr, done, s);
     else
-        launch_coarse<T, T, T, false>(nL, V.ainv, V.r[L], F.aggptr, V.r[L - 1], V.dinv[L - 1], V.p[L - 1],
+        launch_coarse<T, T, T, false>(nL, V.tail, V.r[L], F.aggptr, V.r[L - 1], V.dinv[L - 1], V.p[L - 1],
                                       V.zp[L - 1], nullptr, nullptr, nullptr, done, s);
     for (int l = L - 1; l >= 1; --l) {
         const DevLevelIdx& I = h->idx[l];
@@ -780,18 +855,20 @@ static int enqueue_vcycle_plain(pamg_hierarchy* h, DevVals<T>& V, const R0* r0, 
 // up-sweep also writes the partials of z . dv.  Returns the number of partials.
 // The FP32 cycle first rounds r0 to FP32 once (r32): its level-0 kernels then
 // gather 4-byte values, with the same results.
+// r32_current: r32 holds r0's rounding already.
 // z32_out (FP32 cycle with tentative prolongators and l1-Jacobi, L >= 1
 // only; else null): z written there in FP32, exactly, instead of z_out.
 template <typename T>
 static int enqueue_vcycle(pamg_hierarchy* h, DevVals<T>& V, const double* r0, double* z_out, const double* dv,
-                          const int* done, hipStream_t s, float* z32_out = nullptr) {
+                          const int* done, hipStream_t s, float* z32_out = nullptr, bool r32_current = false) {
     const int L = h->L;
     if (h->smoother == PAMG_SMOOTHER_HYBRID_GS && L > 0) return enqueue_vcycle_gs<T>(h, V, r0, z_out, dv, done, s);
     if (h->smoothed_p && L > 0) return enqueue_vcycle_sa<T>(h, V, r0, z_out, dv, done, s);
     if constexpr (std::is_same<T, float>::value) {
         if (h->r32) {
             const long long n0 = h->idx[0].n;
-            hipLaunchKernelGGL((k_convert<double, float>), dim3(vec_grid(n0)), dim3(kBlock), 0, s, n0, r0, h->r32);
+            if (!r32_current)
+                hipLaunchKernelGGL((k_convert<double, float>), dim3(vec_grid(n0)), dim3(kBlock), 0, s, n0, r0, h->r32);
             if (z32_out && L > 0)
                 return enqueue_vcycle_plain<float, float, float>(h, V, (const float*)h->r32, z32_out, dv, done, s);
             return enqueue_vcycle_plain<float, float>(h, V, (const float*)h->r32, z_out, dv, done, s);
@@ -807,30 +884,33 @@ static bool cycle_z32(const pamg_hierarchy* h) {
            h->smoother == PAMG_SMOOTHER_L1_JACOBI && !h->smoothed_p;
 }
 
+// r32_current: r32 is the rounding of r (the iteration before wrote both).
 template <typename T>
-static void enqueue_iteration(pamg_hierarchy* h, DevVals<T>& V, int krylov, int parity, hipStream_t s) {
+static void enqueue_iteration(pamg_hierarchy* h, DevVals<T>& V, int krylov, int parity, bool r32_current,
+                              hipStream_t s) {
     const int* done = &h->st->done;
     const double* dv = (krylov == PAMG_KRYLOV_CG) ? h->r : h->q;
     const bool z32 = cycle_z32<T>(h);
-    const int cnt = enqueue_vcycle<T>(h, V, h->r, h->z, dv, done, s, z32 ? h->z32 : nullptr);
-    LAUNCH(k_fin_beta, 1, 0, s, h->st, (const double*)h->partial, cnt);
+    // partials: z . dv in partial, p.q and p.r in partial_b, r.r in partial
+    const int cnt = enqueue_vcycle<T>(h, V, h->r, h->z, dv, done, s, z32 ? h->z32 : nullptr, r32_current);
     const DevLevelIdx& I = h->idx[0];
+    const double* zpart = h->partial;
     if (z32)
-        launch_krylov<float>(I, h->f64.v[0], h->z32, h->p[parity], h->p[1 - parity], h->q, h->r, h->st, h->partial,
-                             done, s);
+        launch_krylov<float>(I, h->f64.v[0], h->z32, h->p[parity], h->p[1 - parity], h->q, h->r, h->st, zpart, cnt,
+                             h->partial_b, done, s);
     else
-        launch_krylov<double>(I, h->f64.v[0], h->z, h->p[parity], h->p[1 - parity], h->q, h->r, h->st, h->partial,
-                              done, s);
-    LAUNCH(k_fin_alpha, 1, 0, s, h->st, (const double*)h->partial, I.row_grid());
+        launch_krylov<double>(I, h->f64.v[0], h->z, h->p[parity], h->p[1 - parity], h->q, h->r, h->st, zpart, cnt,
+                              h->partial_b, done, s);
     const int gv = vec_grid(I.n);
-    LAUNCH(k_krylov_update, gv, 0, s, I.n, h->x, h->r, (const double*)h->p[1 - parity], (const double*)h->q,
-           (const SolveState*)h->st, h->partial, done);
+    float* r32 = std::is_same<T, float>::value ? h->r32 : nullptr;
+    LAUNCH(k_krylov_update, gv, 0, s, I.n, h->x, h->r, r32, (const double*)h->p[1 - parity], (const double*)h->q,
+           h->st, (const double*)h->partial_b, I.row_grid(), h->partial, done);
     LAUNCH(k_fin_norm, 1, 0, s, h->st, (const double*)h->partial, gv);
 }
 
 template <typename T>
 static void enqueue_block(pamg_hierarchy* h, DevVals<T>& V, int krylov, int k, hipStream_t s) {
-    for (int j = 0; j < k; ++j) enqueue_iteration<T>(h, V, krylov, j & 1, s);
+    for (int j = 0; j < k; ++j) enqueue_iteration<T>(h, V, krylov, j & 1, j > 0, s);
 }
 
 template <typename T>
@@ -1339,7 +1419,8 @@ static void time_op_impl(pamg_hierarchy* h, DevVals<T>& V, int op, int l, int re
         // matrix (FP64), z, p_old, q_old, r reads; p_new, q writes
         *bytes = M8 + 6 * n * 8;
         launch = [=]() {
-            launch_krylov<double>(I, h->f64.v[0], h->z, h->p[0], h->p[1], h->q, h->r, h->st, h->partial, nodone, s);
+            launch_krylov<double>(I, h->f64.v[0], h->z, h->p[0], h->p[1], h->q, h->r, h->st, h->partial, I.row_grid(),
+                                  h->partial_b, nodone, s);
         };
     } else if (op == PAMG_OP_SMOOTH) {
         // one backward hybrid Gauss-Seidel sweep: CSR (int32 columns), own r,

@@ -56,6 +56,7 @@ struct DevVals {
     std::vector<T*> sa_pv, sa_tv;     // smoothed prolongator: values of P and P^T (l < L)
     T* zc = nullptr;                  // hybrid GS: coarsest-level solution
     T* ainv = nullptr;                // dense A_L^{-1}
+    T* tail = nullptr;                // dense cycle operator of level `tail` (the coarsest: ainv)
     T* dbg_in = nullptr;              // scratch in this precision (max n)
     T* dbg_in2 = nullptr;
 };
@@ -142,6 +143,7 @@ struct pamg_hierarchy {
     int sweeps = 1, gs_block = 256;
     double omega = 1.0;
     bool smoothed_p = false;                  // smoothed prolongators (general sparse P)
+    int tail = 0;                             // level from which the l1-Jacobi cycle is one dense product (<= L)
     std::vector<pamg::DevLevelIdx> idx;
     pamg::DevVals<double> f64;
     pamg::DevVals<float> f32;
@@ -233,6 +235,24 @@ struct DenseWork {
         if (ctx) ctx_free_all(ctx, bufs);
     }
 };
+constexpr int kTailRows = 1024;       // the dense operator of the cycle's last levels (tail_level)
+constexpr int kTailShare = 5;
+// Device workspace of build_tail (allocated before anything it is used for is
+// changed): the dense operators of two neighbouring levels, a product between
+// them and the aggregate of every row.
+struct TailWork {
+    pamg_context* ctx = nullptr;
+    std::vector<DevAlloc> bufs;
+    double *B[2] = {nullptr, nullptr}, *G = nullptr;
+    int* own = nullptr;
+    ~TailWork() {
+        if (ctx) ctx_free_all(ctx, bufs);
+    }
+};
+std::unique_ptr<TailWork> tail_work(pamg_hierarchy* h, hipStream_t s);
+// The dense operator of the l1-Jacobi cycle from level h->tail on, from the
+// levels' current values and the coarsest inverse (both precisions).
+void build_tail(pamg_hierarchy* h, TailWork& w, hipStream_t s);
 std::unique_ptr<DenseWork> dense_work(pamg_context* ctx, int n, hipStream_t s);
 void coarse_inverse_device(DenseWork& w, int n, const int* rp, const int* ci, const double* v, double* ainv,
                            hipStream_t s);

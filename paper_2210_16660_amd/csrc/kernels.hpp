@@ -70,6 +70,12 @@ struct RowIdx {
     __device__ __forceinline__ int stride() const { return pos ? kSlice : 1; }
 };
 
+// a and b (uniform) have both been asked for when either is waited for: their
+// loads are not moved behind a branch below.  (The converged flag and the first descriptor, row or partials of a kernel are
+// loads of their own, written by other XCDs; waiting for one after the other
+// cost 0.6 us of the 4 us that a launch on a small level takes.)
+__device__ __forceinline__ void issued(int& a, int& b) { asm volatile("" : "+s"(a), "+s"(b)); }
+
 // Tiles handled by this workgroup: first, first+stride, ... < end.
 struct TileWalk {
     int first, stride, end;
@@ -251,7 +257,7 @@ static __global__ __launch_bounds__(kBlock, 4) void k_down(
     const RT* __restrict__ r, const GT* __restrict__ g, const T* __restrict__ p, const int* __restrict__ aggptr,
     const int4* __restrict__ tiles, int ntiles,
     const int2* __restrict__ span, const int* __restrict__ ucol, const uint16_t* __restrict__ loc, T* __restrict__ rc, const int* __restrict__ done) {
-    if (*done) return;
+    int dn = *done;
     PAMG_TILE_LDS(T, ITEMS)
     __shared__ T s_u[kBlock];
     __shared__ T s_red[kBlock / 64];
@@ -261,7 +267,11 @@ static __global__ __launch_bounds__(kBlock, 4) void k_down(
     TileNext nx;
     if (w.first < w.end) {
         next_desc(nx, w.first, tiles, span, DICT);
-        if constexpr (DICT) next_cols(nx, ucol);
+        issued(dn, nx.d.x);
+    }
+    if (dn) return;
+    if constexpr (DICT) {
+        if (w.first < w.end) next_cols(nx, ucol);
     }
     for (int t = w.first; t < w.end; t += w.stride) {
         const int4 d = nx.d;
@@ -366,7 +376,7 @@ static __global__ __launch_bounds__(kBlock, 4) void k_up(
     ZO* __restrict__ z_out, const double* __restrict__ dv, double* __restrict__ partial,
     const int* __restrict__ done) {
     constexpr bool TO_OUT = MODE == kUpOut;
-    if (*done) return;
+    int dn = *done;
     PAMG_TILE_LDS(T, ITEMS)
     __shared__ T s_red[kBlock / 64];
     __shared__ double s_redd[kBlock / 64];
@@ -379,7 +389,11 @@ static __global__ __launch_bounds__(kBlock, 4) void k_up(
     TileNext nx;
     if (w.first < w.end) {
         next_desc(nx, w.first, tiles, span, DICT);
-        if constexpr (DICT) next_cols(nx, ucol);
+        issued(dn, nx.d.x);
+    }
+    if (dn) return;
+    if constexpr (DICT) {
+        if (w.first < w.end) next_cols(nx, ucol);
     }
     for (int t = w.first; t < w.end; t += w.stride) {
         const int4 d = nx.d;
@@ -500,70 +514,18 @@ static __global__ __launch_bounds__(kBlock, 4) void k_up(
 }
 
 // ----------------------------------------------------------------------------
-// Coarsest level: z = A_L^-1 r with the dense symmetric inverse, one
-// workgroup of 1024 threads: the columns j are split into G groups whose
-// partial sums meet in LDS (fixed order), then each row I prolongates into
-// level L-1 as in k_up, or (single-level hierarchy) writes z.
-// Dynamic LDS: (1 + G) * nL values, G = 16 (nL <= 256), 4 (nL <= 1024), else 1.
-constexpr int kCoarseThreads = 1024;
-inline int coarse_groups(int nL) { return nL <= 256 ? 16 : (nL <= 1024 ? 4 : 1); }
-
-template <typename T, typename RT, typename RTF, bool TO_OUT>
-static __global__ __launch_bounds__(kCoarseThreads) void k_coarse(
-    int nL, int G, const T* __restrict__ ainv, const RT* __restrict__ r,
-    const int* __restrict__ aggptr_f, const RTF* __restrict__ r_f, const T* __restrict__ dinv_f,
-    const T* __restrict__ p_f, T* __restrict__ zp_f,
-    double* __restrict__ z_out, const double* __restrict__ dv, double* __restrict__ partial,
-    const int* __restrict__ done) {
-    if (*done) return;
-    extern __shared__ __align__(16) unsigned char s_raw[];
-    T* s_r = reinterpret_cast<T*>(s_raw);
-    T* s_part = s_r + nL;
-    __shared__ double s_redd[kCoarseThreads / 64];
-    const int tid = threadIdx.x;
-    for (int i = tid; i < nL; i += kCoarseThreads) s_r[i] = (T)r[i];
-    __syncthreads();
-    const int per = kCoarseThreads / G;          // threads per column group
-    const int g = tid / per, lt = tid % per;
-    const int j0 = (int)((long long)nL * g / G), j1 = (int)((long long)nL * (g + 1) / G);
-    for (int I = lt; I < nL; I += per) {
-        T s = 0;
-        for (int j = j0; j < j1; ++j) s += ainv[(size_t)j * nL + I] * s_r[j];
-        s_part[(size_t)g * nL + I] = s;
-    }
-    __syncthreads();
-    double dot = 0.0;
-    for (int I = tid; I < nL; I += kCoarseThreads) {
-        T z = 0;
-        for (int q = 0; q < G; ++q) z += s_part[(size_t)q * nL + I];
-        if constexpr (TO_OUT) {
-            z_out[I] = (double)z;
-            dot += (double)z * dv[I];
-        } else {
-            for (int m = aggptr_f[I]; m < aggptr_f[I + 1]; ++m) zp_f[m] = prolong_value(dinv_f[m], (T)r_f[m], p_f[m], z);
-        }
-    }
-    if constexpr (TO_OUT) {
-        dot = wave_sum(dot);
-        if ((tid & 63) == 0) s_redd[tid >> 6] = dot;
-        __syncthreads();
-        if (tid == 0) {
-            double t = 0.0;
-            for (int q = 0; q < kCoarseThreads / 64; ++q) t += s_redd[q];
-            partial[0] = t;
-        }
-    }
-}
-
-// ----------------------------------------------------------------------------
-// Coarsest level when it is large (a stalled coarsening can leave thousands of
-// rows): the same product and prolongation as k_coarse, one wave per row.  The
-// inverse is symmetric, so row I is read along its length (coalesced, 64
-// consecutive columns per load) and the lanes' partial sums meet in a wave
-// butterfly (fixed order); ceil(nL / 4) workgroups of four waves, so even a
-// coarsest level of a few thousand rows spreads over the whole chip.
-constexpr int kCoarseRowsMin = 512;          // above this size the coarsest runs on many workgroups
+// The dense end of the cycle: z = M r with the coarsest level's inverse, or the
+// dense operator of the last levels, then the prolongation into the next finer
+// level as in k_up, or (single-level hierarchy) z out.  One wave per row: M is
+// symmetric, so row I is read along its length (coalesced, 64 consecutive
+// columns per load) and the lanes' partial sums meet in a wave butterfly (fixed
+// order); ceil(nL / 4) workgroups of four waves spread even a few hundred rows
+// over the chip (one workgroup took 13 us at 130 rows, this form about 5).  The
+// prolongation's operands are loaded ahead of the product.
+constexpr int kCoarseThreads = 1024;         // the 16-column engine's single-workgroup product
+constexpr int kCoarseRowsMin = 512;          // above this size that engine's runs on many workgroups
 constexpr int kCoarseRowsPerBlock = kBlock / 64;
+static_assert((1 << kMaxAggSteps) <= 64, "one lane per member of an aggregate");
 inline int coarse_rows_grid(int nL) { return (nL + kCoarseRowsPerBlock - 1) / kCoarseRowsPerBlock; }
 
 template <typename T, typename RT, typename RTF, bool TO_OUT>
@@ -578,23 +540,32 @@ static __global__ __launch_bounds__(kBlock) void k_coarse_rows(
     const int tid = threadIdx.x, wave = tid / 64, lane = tid % 64;
     const int I = blockIdx.x * kCoarseRowsPerBlock + wave;
     T s = 0;
+    int m = 0;
+    bool own = false;                       // lane j < members: fine row m = aggptr_f[I] + j (at most 2^4)
+    T rf = 0, df = 0, pf = 0;
     if (I < nL) {
+        if constexpr (!TO_OUT) {
+            m = aggptr_f[I] + lane;
+            own = m < aggptr_f[I + 1];
+            if (own) {
+                rf = (T)r_f[m];
+                df = dinv_f[m];
+                pf = p_f[m];
+            }
+        }
         const T* __restrict__ row = ainv + (size_t)I * nL;
-#pragma unroll 4
+#pragma unroll 8
         for (int j = lane; j < nL; j += 64) s += row[j] * (T)r[j];
     }
     const T z = wave_sum(s);
     double dot = 0.0;
-    if (I < nL) {
-        if constexpr (TO_OUT) {
-            if (lane == 0) {
-                z_out[I] = (double)z;
-                dot = (double)z * dv[I];
-            }
-        } else {
-            for (int m = aggptr_f[I] + lane; m < aggptr_f[I + 1]; m += 64)
-                zp_f[m] = prolong_value(dinv_f[m], (T)r_f[m], p_f[m], z);
+    if constexpr (TO_OUT) {
+        if (I < nL && lane == 0) {
+            z_out[I] = (double)z;
+            dot = (double)z * dv[I];
         }
+    } else {
+        if (own) zp_f[m] = prolong_value(df, rf, pf, z);
     }
     if constexpr (TO_OUT) {
         if (lane == 0) s_dot[wave] = dot;
@@ -749,12 +720,80 @@ static __global__ __launch_bounds__(kBlock, 4) void k_spmv(
 }
 
 // ----------------------------------------------------------------------------
+// The workgroup's sum of s, fixed order, valid in every thread.
+__device__ __forceinline__ double block_total(double s, double* s_red) {
+    s = wave_sum(s);
+    __syncthreads();
+    if ((threadIdx.x & 63) == 0) s_red[threadIdx.x >> 6] = s;
+    __syncthreads();
+    double t = 0.0;
+#pragma unroll
+    for (int i = 0; i < kBlock / 64; ++i) t += s_red[i];
+    return t;
+}
+
+// Fixed-order sum of `count` <= kMaxGrid partials by one workgroup, valid in
+// every thread; all loads are issued together (one after another they cost 4 us
+// at 1500 partials).  reduce_pairs: of the even and of the odd entries of
+// 2 count values.
+constexpr int kPartialSlots = kMaxGrid / kBlock;
+__device__ __forceinline__ double reduce_partials(const double* __restrict__ partial, int count, double* s_red) {
+    double v[kPartialSlots];
+#pragma unroll
+    for (int u = 0; u < kPartialSlots; ++u) {
+        const int i = u * kBlock + (int)threadIdx.x;
+        v[u] = u * kBlock < count && i < count ? partial[i] : 0.0;
+    }
+    double s = 0.0;
+#pragma unroll
+    for (int u = 0; u < kPartialSlots; ++u) s += v[u];
+    return block_total(s, s_red);
+}
+__device__ __forceinline__ double2 reduce_pairs(const double* __restrict__ partial, int count, double* s_red) {
+    const double2* __restrict__ p = reinterpret_cast<const double2*>(partial);
+    double2 v[kPartialSlots];
+#pragma unroll
+    for (int u = 0; u < kPartialSlots; ++u) {
+        const int i = u * kBlock + (int)threadIdx.x;
+        v[u] = u * kBlock < count && i < count ? p[i] : make_double2(0.0, 0.0);
+    }
+    double2 s = make_double2(0.0, 0.0);
+#pragma unroll
+    for (int u = 0; u < kPartialSlots; ++u) {
+        s.x += v[u].x;
+        s.y += v[u].y;
+    }
+    s.x = block_total(s.x, s_red);
+    s.y = block_total(s.y, s_red);
+    return s;
+}
+
+// The scalars of the recurrence are formed by the kernels that use them: every
+// workgroup sums the few partials (at most 2048, from L2) in the same fixed
+// order and workgroup 0 also writes the state, fields that no workgroup of the
+// same launch reads.  Kernels of their own for them cost 4.5 us each, launch
+// and a chain of two loads, 9 of about 95 us per iteration on 32^3.
+
+// beta (and rho for PCG) from the partials of z . dv.
+__device__ __forceinline__ double krylov_beta(SolveState* st, const double* __restrict__ zpart, int zcount,
+                                              double* s_red) {
+    const double d = reduce_partials(zpart, zcount, s_red);
+    const bool cg = st->krylov == PAMG_KRYLOV_CG;      // d = r.z; FCG: d = z.q_old
+    const double beta = st->first ? 0.0 : cg ? d / st->rho_old : -d / st->delta_old;
+    if (blockIdx.x == 0 && threadIdx.x == 0) {
+        st->beta = beta;
+        if (cg) st->rho = d;
+    }
+    return beta;
+}
+
 // Krylov step, part 1: p = z + beta p_old (p = z on the first iteration),
 // q = A p computed as A z + beta q_old (the same vector in exact arithmetic,
 // so that only z is gathered: one dictionary gather per tile instead of two;
 // q holds q_old on entry and each row's element is read before its owner
 // overwrites it), partials of p.q and p.r.  On the first iteration (and after
-// a restart) q = A z.  z is FP64, or FP32 when it comes from the FP32 cycle
+// a restart) q = A z.  zpart: the partials of z . dv, from which beta follows.
+// z is FP64, or FP32 when it comes from the FP32 cycle
 // (whose z values are FP32 numbers: the same sums, half the gathered bytes).
 template <int ITEMS, typename ZT = double>
 static __global__ __launch_bounds__(kBlock, 4) void k_krylov_pq(
@@ -763,21 +802,26 @@ static __global__ __launch_bounds__(kBlock, 4) void k_krylov_pq(
     double* __restrict__ q, const double* __restrict__ r,
     const int4* __restrict__ tiles, int ntiles,
     const int2* __restrict__ span, const int* __restrict__ ucol, const uint16_t* __restrict__ loc,
-    const SolveState* __restrict__ st, double* __restrict__ partial, const int* __restrict__ done) {
-    if (*done) return;
+    SolveState* __restrict__ st, const double* __restrict__ zpart, int zcount, double* __restrict__ partial,
+    const int* __restrict__ done) {
+    int dn = *done;
     PAMG_TILE_LDS(double, ITEMS)
     __shared__ double s_red[kBlock / 64];
     const int tid = threadIdx.x;
-    const bool first = st->first != 0;
-    const double beta = st->beta;
     const TileWalk w = tile_walk(ntiles);
     double pq = 0.0, pr = 0.0;
     constexpr bool DICT = tile_uses_dict<ITEMS>();
     TileNext nx;
     if (w.first < w.end) {
         next_desc(nx, w.first, tiles, span, DICT);
-        if constexpr (DICT) next_cols(nx, ucol);
+        issued(dn, nx.d.x);
     }
+    if (dn) return;
+    if constexpr (DICT) {
+        if (w.first < w.end) next_cols(nx, ucol);
+    }
+    const bool first = st->first != 0;
+    const double beta = krylov_beta(st, zpart, zcount, s_red);
     for (int t = w.first; t < w.end; t += w.stride) {
         const int4 d = nx.d;
         const int2 sp = nx.sp;
@@ -857,72 +901,49 @@ static __global__ __launch_bounds__(kBlock, 4) void k_krylov_pq(
     }
 }
 
-// Krylov step, part 2: x += alpha p, r -= alpha q, partial of r.r.
+// Krylov step, part 2: alpha from the partials of p.q and p.r (part_pq, two per
+// workgroup of the pass before), x += alpha p, r -= alpha q, partial of r.r;
+// r32 (the FP32 cycle, else null): r rounded to FP32, the next cycle's level-0
+// residual.
 static __global__ __launch_bounds__(kBlock) void k_krylov_update(
-    int n, double* __restrict__ x, double* __restrict__ r, const double* __restrict__ p,
-    const double* __restrict__ q, const SolveState* __restrict__ st, double* __restrict__ partial,
-    const int* __restrict__ done) {
-    if (*done) return;
+    int n, double* __restrict__ x, double* __restrict__ r, float* __restrict__ r32, const double* __restrict__ p,
+    const double* __restrict__ q, SolveState* __restrict__ st, const double* __restrict__ part_pq, int pq_count,
+    double* __restrict__ partial, const int* __restrict__ done) {
+    const int dn = *done;                   // with the partials' loads in flight
     __shared__ double s_red[kBlock / 64];
-    const double alpha = st->alpha;
+    const double2 pp = reduce_pairs(part_pq, pq_count, s_red);
+    const double pq = pp.x, pr = pp.y;
+    if (dn) return;
+    const bool cg = st->krylov == PAMG_KRYLOV_CG;
+    const double rho = st->rho;
+    const double alpha = (cg ? rho : pr) / pq;
+    const bool ok = pq > 0.0;
+    if (blockIdx.x == 0 && threadIdx.x == 0) {
+        st->delta = pq;
+        st->gamma = pr;
+        if (ok) {
+            st->alpha = alpha;
+            if (cg) st->rho_old = rho;
+            st->delta_old = pq;
+            st->first = 0;
+        } else {
+            // every workgroup stops here, whether it sees done or forms pq itself
+            st->status = (pq != pq) ? PAMG_E_NUMERIC : PAMG_E_NOT_SPD;
+            st->done = 1;
+        }
+    }
+    if (!ok) return;
     double rr = 0.0;
     const int stride = gridDim.x * kBlock;
     for (int i = blockIdx.x * kBlock + threadIdx.x; i < n; i += stride) {
         x[i] += alpha * p[i];
         const double ri = r[i] - alpha * q[i];
         r[i] = ri;
+        if (r32) r32[i] = (float)ri;
         rr += ri * ri;
     }
     rr = block_sum(rr, s_red);
     if (threadIdx.x == 0) partial[blockIdx.x] = rr;
-}
-
-// Fixed-order sum of `count` partials spaced `stride` apart (one workgroup).
-__device__ __forceinline__ double reduce_partials(const double* __restrict__ partial, int count, int stride,
-                                                  double* s_red) {
-    double s = 0.0;
-    for (int i = threadIdx.x; i < count; i += kBlock) s += partial[(size_t)i * stride];
-    return block_sum(s, s_red);
-}
-
-// beta (and rho for PCG) from the partials of z.dv written by the level-0 up-sweep.
-static __global__ __launch_bounds__(kBlock) void k_fin_beta(SolveState* __restrict__ st, const double* __restrict__ partial,
-                                                     int count) {
-    if (st->done) return;
-    __shared__ double s_red[kBlock / 64];
-    const double d = reduce_partials(partial, count, 1, s_red);
-    if (threadIdx.x == 0) {
-        if (st->krylov == PAMG_KRYLOV_CG) {        // d = r.z
-            st->rho = d;
-            st->beta = st->first ? 0.0 : d / st->rho_old;
-        } else {                                    // d = z.q_old
-            st->beta = st->first ? 0.0 : -d / st->delta_old;
-        }
-    }
-}
-
-// delta = p.q, gamma = p.r, alpha.
-static __global__ __launch_bounds__(kBlock) void k_fin_alpha(SolveState* __restrict__ st, const double* __restrict__ partial,
-                                                      int count) {
-    if (st->done) return;
-    __shared__ double s_red[kBlock / 64];
-    const double pq = reduce_partials(partial, count, 2, s_red);
-    __syncthreads();
-    const double pr = reduce_partials(partial + 1, count, 2, s_red);
-    if (threadIdx.x == 0) {
-        st->delta = pq;
-        st->gamma = pr;
-        if (!(pq > 0.0)) {
-            st->status = (pq != pq) ? PAMG_E_NUMERIC : PAMG_E_NOT_SPD;
-            st->done = 1;
-            return;
-        }
-        const double num = (st->krylov == PAMG_KRYLOV_CG) ? st->rho : pr;
-        st->alpha = num / pq;
-        if (st->krylov == PAMG_KRYLOV_CG) st->rho_old = st->rho;
-        st->delta_old = pq;
-        st->first = 0;
-    }
 }
 
 // ||r||, iteration count and the stopping test ||r|| <= tol ||b||.
@@ -930,7 +951,7 @@ static __global__ __launch_bounds__(kBlock) void k_fin_norm(SolveState* __restri
                                                      int count) {
     if (st->done) return;
     __shared__ double s_red[kBlock / 64];
-    const double rr = reduce_partials(partial, count, 1, s_red);
+    const double rr = reduce_partials(partial, count, s_red);
     if (threadIdx.x == 0) {
         st->rr = rr;
         const double rn = sqrt(rr);
@@ -958,9 +979,9 @@ static __global__ __launch_bounds__(kBlock) void k_fin_init(SolveState* __restri
                                                      int bb_count, const double* __restrict__ rr_part, int rr_count) {
     __shared__ double s_red[kBlock / 64];
     double bb = 0.0;
-    if (bb_count > 0) bb = reduce_partials(bb_part, bb_count, 1, s_red);
+    if (bb_count > 0) bb = reduce_partials(bb_part, bb_count, s_red);
     __syncthreads();
-    const double rr = reduce_partials(rr_part, rr_count, 1, s_red);
+    const double rr = reduce_partials(rr_part, rr_count, s_red);
     if (threadIdx.x == 0) {
         if (bb_count > 0) {
             st->bb = bb;

@@ -295,7 +295,8 @@ template <typename ZT = double>
 static __global__ __launch_bounds__(kBlock, kSellWaves) void ks_krylov_pq(
     const double* __restrict__ av, const ZT* __restrict__ z, const double* __restrict__ p_old,
     double* __restrict__ p_new, double* __restrict__ q, const double* __restrict__ r, SellView V,
-    const SolveState* __restrict__ st, double* __restrict__ partial, const int* __restrict__ done) {
+    SolveState* __restrict__ st, const double* __restrict__ zpart, int zcount, double* __restrict__ partial,
+    const int* __restrict__ done) {
     if (*done) return;
     extern __shared__ __align__(16) unsigned char s_dyn[];
     double* s_x = reinterpret_cast<double*>(s_dyn);
@@ -303,7 +304,7 @@ static __global__ __launch_bounds__(kBlock, kSellWaves) void ks_krylov_pq(
     __shared__ double s_red[kBlock / 64];
     const int tid = threadIdx.x;
     const bool first = st->first != 0;
-    const double beta = st->beta;
+    const double beta = krylov_beta(st, zpart, zcount, s_red);
     double pq = 0.0, pr = 0.0;
     sell_walk<double>(
         V, av, s_x, s_sum, [&](int c) { return (double)z[c]; },

@@ -215,6 +215,7 @@ static void update_values(pamg_hierarchy* h, const double* val, bool on_device, 
     // workspace of the coarsest factorization, before any value is changed
     const DevLevelIdx& CL = h->idx[h->L];
     std::unique_ptr<DenseWork> dw = dense_work(h->ctx, CL.n, s);
+    std::unique_ptr<TailWork> tw = tail_work(h, s);
     // the pairwise Galerkin chain
     for (int m = 0; m + 1 < R.npw; ++m) {
         const int ne = (int)R.nnz[m + 1];
@@ -262,6 +263,7 @@ static void update_values(pamg_hierarchy* h, const double* val, bool on_device, 
         hipLaunchKernelGGL((k_convert<double, float>), dim3(vec_grid(nn)), dim3(kBlock), 0, s, nn,
                            (const double*)V.ainv, h->f32.ainv);
     }
+    build_tail(h, *tw, s);
     HIP_CHECK(hipStreamSynchronize(s));
 }
 

@@ -142,12 +142,20 @@ static double ms_between(Clock::time_point a, Clock::time_point b) {
 // as a batch, and is charged then.
 static uint64_t dense_bytes(uint64_t nL, int prec) { return nL * nL * (prec == PAMG_PREC_F32 ? 12 : 8); }
 
+// Bound of the dense operator of the cycle's last levels (device.hip,
+// tail_level), whose size the hierarchy fixes.
+static uint64_t tail_bytes(const pamg_csr& A, int prec) {
+    const uint64_t n = (uint64_t)A.n, nnz = (uint64_t)A.nnz, rows = kTailRows;
+    const uint64_t entries = std::max(std::min(kTailShare * nnz, rows * rows), std::min(nnz, 4 * rows * rows));
+    return std::min(entries, n * n) * (prec == PAMG_PREC_F32 ? 12 : 8);
+}
+
 static uint64_t estimate_core(const pamg_csr& A, int prec) {
     const double cx = 2.3;
     const double n = (double)A.n, nnz = (double)A.nnz;
     double hier = cx * (nnz * (4 + 8 + 8) + n * 80) + 96.0 * n + (1 << 18);
     if (prec == PAMG_PREC_F32) hier += cx * (nnz * 8 + n * 32) + 4.0 * n;
-    return (uint64_t)hier;
+    return (uint64_t)hier + tail_bytes(A, prec);
 }
 
 // ... plus the dense inverse of a coarsest level of the usual size (at most
