@@ -51,9 +51,21 @@ static void with_variant(int v, F&& f) {
     }
 }
 
+// log2 of the narrowest width (4, 8 or 16) that holds nrhs columns: the vectors
+// and the gathers of a batch then carry few idle columns.  5 right-hand sides on
+// the 61^3 varying-coefficient operator, 19 FP64 iterations: 9.9 ms at width 16,
+// 6.9 ms at 8.  A row of 4 columns is 16 bytes in FP32 and 32 in FP64, already
+// less than the 64 a gather fetches, so there is no narrower one.
+static int width_log(int nrhs) { return nrhs <= 4 ? 2 : nrhs <= 8 ? 3 : 4; }
+
+// Columns per lane of a variant (tuned at 16 columns) at another width: the
+// same lanes per row where the row has that many columns.
+static inline int cpl_at(int cpl, int lw) { return std::max(1, cpl << lw >> 4); }
+
 struct BatchEngine {
     pamg_hierarchy* h = nullptr;
     int prec = 0;
+    int lw = 4;                               // log2 of the width the vectors are laid out in (n x 2^lw)
     std::vector<void*> r, zp;                 // V-cycle vectors per level (n_l x 16, V-cycle precision)
     void* zc = nullptr;                       // coarse result scratch (n_L x 16)
     double *X = nullptr, *R = nullptr, *Z = nullptr, *P[2] = {nullptr, nullptr}, *Q = nullptr, *B = nullptr,
@@ -68,7 +80,7 @@ struct BatchEngine {
     void** ptr_host = nullptr;                // pinned staging for the pointer tables (2 * kW)
     hipStream_t cap_stream = nullptr;
     hipGraphExec_t graph[2] = {nullptr, nullptr};
-    int graph_k[2] = {0, 0};
+    int graph_k[2] = {0, 0}, graph_lw[2] = {0, 0};
     std::vector<int> cfg_down, cfg_up;        // variant per level
     std::vector<DevAlloc> allocs;             // from the hierarchy's context
     uint64_t bytes = 0;
@@ -99,31 +111,63 @@ static T* balloc(BatchEngine* E, size_t count, hipStream_t s) {
 
 // ---------------------------------------------------------------- schedule
 
-template <typename T>
-static void launch_down_b(const DevLevelIdx& I, int v, const T* vd, const void* r, bool r_is_f64, const T* p, T* rc,
-                          const int* done, hipStream_t s) {
+// f(unroll, columns per lane, rows a workgroup) of variant v at width 2^lw.
+template <typename F>
+static void with_variant_at(int v, int lw, F&& f) {
+    using std::integral_constant;
     with_variant(v, [&](auto u, auto c) {
-        constexpr int U = decltype(u)::value, CPL = decltype(c)::value;
-        const int grid = unit_grid(I.nc, kBlock / (kW / CPL));
-        if (r_is_f64)
-            hipLaunchKernelGGL((kb_down<U, CPL, T, double>), dim3(grid), dim3(kBlock), 0, s, I.nc, I.row_idx(), (const int*)I.ci, vd, (const double*)r, p, (const int*)I.aggptr, rc, done);
+        constexpr int C16 = decltype(c)::value;
+        const int rows16 = kBlock / (kW / C16);
+        if (lw == 4)
+            f(u, c, rows16);
+        else if (lw == 3)
+            f(u, integral_constant<int, (C16 > 1 ? C16 / 2 : 1)>{}, kBlock * cpl_at(C16, 3) / 8);
         else
-            hipLaunchKernelGGL((kb_down<U, CPL, T, T>), dim3(grid), dim3(kBlock), 0, s, I.nc, I.row_idx(), (const int*)I.ci, vd, (const T*)r, p, (const int*)I.aggptr, rc, done);
+            f(u, integral_constant<int, (C16 > 3 ? C16 / 4 : 1)>{}, kBlock * cpl_at(C16, 2) / 4);
+    });
+}
+
+// f(columns per lane) of the fixed-shape level-0 kernels.
+template <typename F>
+static void with_fixed(int lw, F&& f) {
+    using std::integral_constant;
+    if (lw == 4)
+        f(integral_constant<int, 4>{});
+    else if (lw == 3)
+        f(integral_constant<int, 2>{});
+    else
+        f(integral_constant<int, 1>{});
+}
+
+template <typename T>
+static void launch_down_b(const DevLevelIdx& I, int v, int lw, const T* vd, const void* r, bool r_is_f64, const T* p,
+                          T* rc, const int* done, hipStream_t s) {
+    with_variant_at(v, lw, [&](auto u, auto c, int rows) {
+        constexpr int U = decltype(u)::value, CPL = decltype(c)::value;
+        const int grid = unit_grid(I.nc, rows);
+        if (r_is_f64)
+            hipLaunchKernelGGL((kb_down<U, CPL, T, double>), dim3(grid), dim3(kBlock), 0, s, I.nc, lw, I.row_idx(),
+                               (const int*)I.ci, vd, (const double*)r, p, (const int*)I.aggptr, rc, done);
+        else
+            hipLaunchKernelGGL((kb_down<U, CPL, T, T>), dim3(grid), dim3(kBlock), 0, s, I.nc, lw, I.row_idx(),
+                               (const int*)I.ci, vd, (const T*)r, p, (const int*)I.aggptr, rc, done);
     });
 }
 
 template <typename T>
-static void launch_up_b(const DevLevelIdx& I, const DevLevelIdx& F, int v, const T* av, const T* zp, const T* r,
-                        const T* dinv, const void* r_f, bool rf_is_f64, const T* dinv_f, const T* p_f, T* zp_f,
-                        const int* done, hipStream_t s) {
-    with_variant(v, [&](auto u, auto c) {
+static void launch_up_b(const DevLevelIdx& I, const DevLevelIdx& F, int v, int lw, const T* av, const T* zp,
+                        const T* r, const T* dinv, const void* r_f, bool rf_is_f64, const T* dinv_f, const T* p_f,
+                        T* zp_f, const int* done, hipStream_t s) {
+    with_variant_at(v, lw, [&](auto u, auto c, int rows) {
         constexpr int U = decltype(u)::value, CPL = decltype(c)::value;
-        const int grid = unit_grid(I.n, kBlock / (kW / CPL));
+        const int grid = unit_grid(I.n, rows);
         if (rf_is_f64)
-            hipLaunchKernelGGL((kb_up<U, CPL, T, T, double>), dim3(grid), dim3(kBlock), 0, s, I.n, I.row_idx(), (const int*)I.ci, av, zp, r, dinv, (const int*)F.aggptr, (const double*)r_f, dinv_f,
+            hipLaunchKernelGGL((kb_up<U, CPL, T, T, double>), dim3(grid), dim3(kBlock), 0, s, I.n, lw, I.row_idx(),
+                               (const int*)I.ci, av, zp, r, dinv, (const int*)F.aggptr, (const double*)r_f, dinv_f,
                                p_f, zp_f, done);
         else
-            hipLaunchKernelGGL((kb_up<U, CPL, T, T, T>), dim3(grid), dim3(kBlock), 0, s, I.n, I.row_idx(), (const int*)I.ci, av, zp, r, dinv, (const int*)F.aggptr, (const T*)r_f, dinv_f, p_f,
+            hipLaunchKernelGGL((kb_up<U, CPL, T, T, T>), dim3(grid), dim3(kBlock), 0, s, I.n, lw, I.row_idx(),
+                               (const int*)I.ci, av, zp, r, dinv, (const int*)F.aggptr, (const T*)r_f, dinv_f, p_f,
                                zp_f, done);
     });
 }
@@ -154,13 +198,13 @@ static int enqueue_vcycle_b(BatchEngine* E, DevVals<T>& V, const double* dv, con
     for (int l = 0; l < L; ++l) {
         const DevLevelIdx& I = h->idx[l];
         if (l == 0)
-            launch_down_b<T>(I, E->cfg_down[0], V.vd[0], r0, r0_f64, V.p[0], (T*)E->r[1], done, s);
+            launch_down_b<T>(I, E->cfg_down[0], E->lw, V.vd[0], r0, r0_f64, V.p[0], (T*)E->r[1], done, s);
         else
-            launch_down_b<T>(I, E->cfg_down[l], V.vd[l], E->r[l], false, V.p[l], (T*)E->r[l + 1], done, s);
+            launch_down_b<T>(I, E->cfg_down[l], E->lw, V.vd[l], E->r[l], false, V.p[l], (T*)E->r[l + 1], done, s);
     }
     const int nL = h->idx[L].n;
     if (L == 0) {
-        hipLaunchKernelGGL((kb_coarse<T, double, double, true>), dim3(1), dim3(kCoarseThreads), 0, s, nL,
+        hipLaunchKernelGGL((kb_coarse<T, double, double, true>), dim3(1), dim3(kCoarseThreads), 0, s, nL, E->lw,
                            (const T*)V.ainv, (const double*)E->R, (T*)E->zc, (const int*)nullptr,
                            (const double*)nullptr, (const T*)nullptr, (const T*)nullptr, (T*)nullptr, E->Z, dv,
                            E->partial, done);
@@ -168,23 +212,23 @@ static int enqueue_vcycle_b(BatchEngine* E, DevVals<T>& V, const double* dv, con
     }
     const DevLevelIdx& F = h->idx[L - 1];
     if (nL > coarse_rows_min_b<T>()) {
-        const dim3 g(coarse_rows_grid_b<T>(nL));
+        const dim3 g(coarse_rows_grid_b(nL));
         if (L - 1 == 0)
-            hipLaunchKernelGGL((kb_coarse_rows<T, T, double>), g, dim3(kBlock), 0, s, nL, (const T*)V.ainv,
+            hipLaunchKernelGGL((kb_coarse_rows<T, T, double>), g, dim3(kBlock), 0, s, nL, E->lw, (const T*)V.ainv,
                                (const T*)E->r[L], (const int*)F.aggptr, (const double*)E->R, (const T*)V.dinv[0],
                                (const T*)V.p[0], (T*)E->zp[0], (double*)nullptr, done);
         else
-            hipLaunchKernelGGL((kb_coarse_rows<T, T, T>), g, dim3(kBlock), 0, s, nL, (const T*)V.ainv,
+            hipLaunchKernelGGL((kb_coarse_rows<T, T, T>), g, dim3(kBlock), 0, s, nL, E->lw, (const T*)V.ainv,
                                (const T*)E->r[L], (const int*)F.aggptr, (const T*)E->r[L - 1],
                                (const T*)V.dinv[L - 1], (const T*)V.p[L - 1], (T*)E->zp[L - 1], (double*)nullptr,
                                done);
     } else if (L - 1 == 0)
-        hipLaunchKernelGGL((kb_coarse<T, T, double, false>), dim3(1), dim3(kCoarseThreads), 0, s, nL,
+        hipLaunchKernelGGL((kb_coarse<T, T, double, false>), dim3(1), dim3(kCoarseThreads), 0, s, nL, E->lw,
                            (const T*)V.ainv, (const T*)E->r[L], (T*)E->zc, (const int*)F.aggptr, (const double*)E->R,
                            (const T*)V.dinv[0], (const T*)V.p[0], (T*)E->zp[0], (double*)nullptr,
                            (const double*)nullptr, (double*)nullptr, done);
     else
-        hipLaunchKernelGGL((kb_coarse<T, T, T, false>), dim3(1), dim3(kCoarseThreads), 0, s, nL, (const T*)V.ainv,
+        hipLaunchKernelGGL((kb_coarse<T, T, T, false>), dim3(1), dim3(kCoarseThreads), 0, s, nL, E->lw, (const T*)V.ainv,
                            (const T*)E->r[L], (T*)E->zc, (const int*)F.aggptr, (const T*)E->r[L - 1],
                            (const T*)V.dinv[L - 1], (const T*)V.p[L - 1], (T*)E->zp[L - 1], (double*)nullptr,
                            (const double*)nullptr, (double*)nullptr, done);
@@ -192,19 +236,22 @@ static int enqueue_vcycle_b(BatchEngine* E, DevVals<T>& V, const double* dv, con
         const DevLevelIdx& I = h->idx[l];
         const DevLevelIdx& Fi = h->idx[l - 1];
         if (l - 1 == 0)
-            launch_up_b<T>(I, Fi, E->cfg_up[l], V.v[l], (const T*)E->zp[l], (const T*)E->r[l], V.dinv[l], r0, r0_f64,
+            launch_up_b<T>(I, Fi, E->cfg_up[l], E->lw, V.v[l], (const T*)E->zp[l], (const T*)E->r[l], V.dinv[l], r0, r0_f64,
                            V.dinv[0], V.p[0], (T*)E->zp[0], done, s);
         else
-            launch_up_b<T>(I, Fi, E->cfg_up[l], V.v[l], (const T*)E->zp[l], (const T*)E->r[l], V.dinv[l],
+            launch_up_b<T>(I, Fi, E->cfg_up[l], E->lw, V.v[l], (const T*)E->zp[l], (const T*)E->r[l], V.dinv[l],
                            E->r[l - 1], false, V.dinv[l - 1], V.p[l - 1], (T*)E->zp[l - 1], done, s);
     }
     const DevLevelIdx& I0 = h->idx[0];
-    const int g = unit_grid(I0.n, up0_rows_per_block<T>());
+    const int g = unit_grid(I0.n, kFixedRows);
     T* zout;
     if constexpr (std::is_same<T, float>::value) zout = E->Z32; else zout = E->Z;
-    hipLaunchKernelGGL((kb_up0<T>), dim3(g), dim3(kBlock), 0, s, I0.n, I0.row_idx(), (const int*)I0.ci,
-                       (const T*)V.v[0], (const T*)E->zp[0], (const T*)r0, (const T*)V.dinv[0], zout, dv,
-                       E->partial, done);
+    with_fixed(E->lw, [&](auto c) {
+        constexpr int CPL = decltype(c)::value;
+        hipLaunchKernelGGL((kb_up0<CPL, T>), dim3(g), dim3(kBlock), 0, s, I0.n, I0.row_idx(), (const int*)I0.ci,
+                           (const T*)V.v[0], (const T*)E->zp[0], (const T*)r0, (const T*)V.dinv[0], zout, dv,
+                           E->partial, done);
+    });
     return g;
 }
 
@@ -214,23 +261,30 @@ static void enqueue_iteration_b(BatchEngine* E, DevVals<T>& V, int krylov, int p
     const int* done = &E->st->all_done;
     const double* dv = (krylov == PAMG_KRYLOV_CG) ? E->R : E->Q;
     const int cnt = enqueue_vcycle_b<T>(E, V, dv, done, s);
-    hipLaunchKernelGGL(kb_fin_beta, dim3(1), dim3(kFinThreads), 0, s, E->st, (const double*)E->partial, cnt);
+    const int lw = E->lw;
+    const dim3 fin(kFinParts << lw), vec(kRowGroups << lw);
+    hipLaunchKernelGGL(kb_fin_beta, dim3(1), fin, 0, s, lw, E->st, (const double*)E->partial, cnt);
     const DevLevelIdx& I0 = h->idx[0];
-    const int gk = unit_grid(I0.n, kKrylovRowsPerBlock);
-    if (std::is_same<T, float>::value && h->L > 0)
-        hipLaunchKernelGGL(kb_krylov_pq<float>, dim3(gk), dim3(kBlock), 0, s, I0.n, I0.row_idx(), (const int*)I0.ci, (const double*)h->f64.v[0], (const float*)E->Z32,
-                           (const double*)E->P[parity], E->P[1 - parity], E->Q, (const double*)E->R,
-                           (const BatchState*)E->st, E->partial, done);
-    else
-        hipLaunchKernelGGL(kb_krylov_pq<double>, dim3(gk), dim3(kBlock), 0, s, I0.n, I0.row_idx(), (const int*)I0.ci, (const double*)h->f64.v[0], (const double*)E->Z,
-                           (const double*)E->P[parity], E->P[1 - parity], E->Q, (const double*)E->R,
-                           (const BatchState*)E->st, E->partial, done);
-    hipLaunchKernelGGL(kb_fin_alpha, dim3(1), dim3(kFinThreads), 0, s, E->st, (const double*)E->partial, gk);
-    const int g = unit_grid(I0.n, kBlock / kW);
-    hipLaunchKernelGGL(kb_update, dim3(g), dim3(kBlock), 0, s, I0.n, E->X, E->R, E->R32,
+    const int gk = unit_grid(I0.n, kFixedRows);
+    with_fixed(lw, [&](auto c) {
+        constexpr int CPL = decltype(c)::value;
+        if (std::is_same<T, float>::value && h->L > 0)
+            hipLaunchKernelGGL((kb_krylov_pq<CPL, float>), dim3(gk), dim3(kBlock), 0, s, I0.n, I0.row_idx(),
+                               (const int*)I0.ci, (const double*)h->f64.v[0], (const float*)E->Z32,
+                               (const double*)E->P[parity], E->P[1 - parity], E->Q, (const double*)E->R,
+                               (const BatchState*)E->st, E->partial, done);
+        else
+            hipLaunchKernelGGL((kb_krylov_pq<CPL, double>), dim3(gk), dim3(kBlock), 0, s, I0.n, I0.row_idx(),
+                               (const int*)I0.ci, (const double*)h->f64.v[0], (const double*)E->Z,
+                               (const double*)E->P[parity], E->P[1 - parity], E->Q, (const double*)E->R,
+                               (const BatchState*)E->st, E->partial, done);
+    });
+    hipLaunchKernelGGL(kb_fin_alpha, dim3(1), fin, 0, s, lw, E->st, (const double*)E->partial, gk);
+    const int g = unit_grid(I0.n, kRowGroups);
+    hipLaunchKernelGGL(kb_update, dim3(g), vec, 0, s, I0.n, lw, E->X, E->R, E->R32,
                        (const double*)E->P[1 - parity], (const double*)E->Q, (const BatchState*)E->st, E->partial,
                        done);
-    hipLaunchKernelGGL(kb_fin_norm, dim3(1), dim3(kFinThreads), 0, s, E->st, (const double*)E->partial, g);
+    hipLaunchKernelGGL(kb_fin_norm, dim3(1), fin, 0, s, lw, E->st, (const double*)E->partial, g);
 }
 
 template <typename T>
@@ -275,9 +329,9 @@ static void autotune(BatchEngine* E, DevVals<T>& V, hipStream_t s) {
         for (int v = 0; v < kNumVariants; ++v) {
             const float t = time_variant([&]() {
                 if (l == 0)
-                    launch_down_b<T>(I, v, V.vd[0], r0, r0_f64, V.p[0], (T*)E->r[1], nodone, s);
+                    launch_down_b<T>(I, v, 4, V.vd[0], r0, r0_f64, V.p[0], (T*)E->r[1], nodone, s);
                 else
-                    launch_down_b<T>(I, v, V.vd[l], E->r[l], false, V.p[l], (T*)E->r[l + 1], nodone, s);
+                    launch_down_b<T>(I, v, 4, V.vd[l], E->r[l], false, V.p[l], (T*)E->r[l + 1], nodone, s);
             }, s);
             if (t < best) { best = t; E->cfg_down[l] = v; }
         }
@@ -287,10 +341,10 @@ static void autotune(BatchEngine* E, DevVals<T>& V, hipStream_t s) {
         for (int v = 0; v < kNumVariants; ++v) {
             const float t = time_variant([&]() {
                 if (l - 1 == 0)
-                    launch_up_b<T>(I, Fi, v, V.v[l], (const T*)E->zp[l], (const T*)E->r[l], V.dinv[l], r0, r0_f64,
+                    launch_up_b<T>(I, Fi, v, 4, V.v[l], (const T*)E->zp[l], (const T*)E->r[l], V.dinv[l], r0, r0_f64,
                                    V.dinv[0], V.p[0], (T*)E->zp[0], nodone, s);
                 else
-                    launch_up_b<T>(I, Fi, v, V.v[l], (const T*)E->zp[l], (const T*)E->r[l], V.dinv[l], E->r[l - 1],
+                    launch_up_b<T>(I, Fi, v, 4, V.v[l], (const T*)E->zp[l], (const T*)E->r[l], V.dinv[l], E->r[l - 1],
                                    false, V.dinv[l - 1], V.p[l - 1], (T*)E->zp[l - 1], nodone, s);
             }, s);
             if (t < best) { best = t; E->cfg_up[l] = v; }
@@ -369,7 +423,7 @@ BatchEngine* get_engine(pamg_hierarchy* h, int prec, hipStream_t s) {
 
 static hipGraphExec_t block_graph(BatchEngine* E, int krylov, int k) {
     hipGraphExec_t& ex = E->graph[krylov];
-    if (ex && E->graph_k[krylov] == k) return ex;
+    if (ex && E->graph_k[krylov] == k && E->graph_lw[krylov] == E->lw) return ex;
     if (ex) {
         HIP_CHECK(hipGraphExecDestroy(ex));
         ex = nullptr;
@@ -384,6 +438,7 @@ static hipGraphExec_t block_graph(BatchEngine* E, int krylov, int k) {
     HIP_CHECK(hipGraphInstantiate(&ex, g, nullptr, nullptr, 0));
     HIP_CHECK(hipGraphDestroy(g));
     E->graph_k[krylov] = k;
+    E->graph_lw[krylov] = E->lw;
     return ex;
 }
 
@@ -457,10 +512,10 @@ void batch_load(BatchEngine* E, const double* const* src, const double* tol, con
     E->st_host->all_done = 0;
     HIP_CHECK(hipMemcpyAsync(E->st, E->st_host, sizeof(BatchState), hipMemcpyHostToDevice, s));
     HIP_CHECK(hipMemcpyAsync((void*)E->src_dev, E->ptr_host, kW * sizeof(void*), hipMemcpyHostToDevice, s));
-    const int g = std::min(kMaxGrid, std::max(1, (I0.n + 15) / 16));
-    hipLaunchKernelGGL(kb_load, dim3(g), dim3(kBlock), 0, s, I0.n, (const int*)I0.iperm,
+    const int g = unit_grid(I0.n, kRowGroups);
+    hipLaunchKernelGGL(kb_load, dim3(g), dim3(kRowGroups << E->lw), 0, s, I0.n, E->lw, (const int*)I0.iperm,
                        (const double* const*)E->src_dev, E->B, E->R, E->R32, E->X, E->partial_b);
-    hipLaunchKernelGGL(kb_fin_init, dim3(1), dim3(kFinThreads), 0, s, E->st, (const double*)E->partial_b, g,
+    hipLaunchKernelGGL(kb_fin_init, dim3(1), dim3(kFinParts << E->lw), 0, s, E->lw, E->st, (const double*)E->partial_b, g,
                        (const double*)E->partial_b, g, mask);
     HIP_CHECK(hipGetLastError());
     batch_read_state(E, s);
@@ -472,8 +527,8 @@ void batch_store(BatchEngine* E, double* const* dst, hipStream_t s) {
     const DevLevelIdx& I0 = h->idx[0];
     for (int c = 0; c < kW; ++c) E->ptr_host[kW + c] = (void*)dst[c];
     HIP_CHECK(hipMemcpyAsync((void*)E->dst_dev, E->ptr_host + kW, kW * sizeof(void*), hipMemcpyHostToDevice, s));
-    const int g = std::min(kMaxGrid, std::max(1, (I0.n + 15) / 16));
-    hipLaunchKernelGGL(kb_store, dim3(g), dim3(kBlock), 0, s, I0.n, (const int*)I0.perm, (double* const*)E->dst_dev,
+    const int g = unit_grid(I0.n, kRowGroups);
+    hipLaunchKernelGGL(kb_store, dim3(g), dim3(kRowGroups << E->lw), 0, s, I0.n, E->lw, (const int*)I0.perm, (double* const*)E->dst_dev,
                        (const double*)E->X, (const BatchState*)E->st);
     HIP_CHECK(hipGetLastError());
     HIP_CHECK(hipStreamSynchronize(s));
@@ -484,22 +539,23 @@ void batch_store(BatchEngine* E, double* const* dst, hipStream_t s) {
 void batch_true_residual(BatchEngine* E, int restart_mask, double* relres, hipStream_t s) {
     pamg_hierarchy* h = E->h;
     const DevLevelIdx& I0 = h->idx[0];
-    const int g = unit_grid(I0.n, kBlock / kW);
-    hipLaunchKernelGGL(kb_resid, dim3(g), dim3(kBlock), 0, s, I0.n, I0.row_idx(), (const int*)I0.ci,
+    const int g = unit_grid(I0.n, kRowGroups), W = 1 << E->lw;
+    hipLaunchKernelGGL(kb_resid, dim3(g), dim3(kRowGroups << E->lw), 0, s, I0.n, E->lw, I0.row_idx(), (const int*)I0.ci,
                        (const double*)h->f64.v[0], (const double*)E->X, (const double*)E->B, E->Y,
                        restart_mask ? E->R : (double*)nullptr, restart_mask ? E->R32 : (float*)nullptr, restart_mask,
                        E->partial_b);
-    std::vector<double> part((size_t)g * kW);
+    std::vector<double> part((size_t)g * W);
     HIP_CHECK(hipMemcpyAsync(part.data(), E->partial_b, part.size() * sizeof(double), hipMemcpyDeviceToHost, s));
     HIP_CHECK(hipStreamSynchronize(s));
-    for (int c = 0; c < kW; ++c) {
+    for (int c = W; c < kW; ++c) relres[c] = 0.0;
+    for (int c = 0; c < W; ++c) {
         double t = 0.0;
-        for (int b = 0; b < g; ++b) t += part[(size_t)b * kW + c];
+        for (int b = 0; b < g; ++b) t += part[(size_t)b * W + c];
         const double bn = E->st_host->col[c].bnorm;
         relres[c] = bn > 0 ? std::sqrt(t) / bn : 0.0;
     }
     if (restart_mask) {
-        hipLaunchKernelGGL(kb_fin_init, dim3(1), dim3(kFinThreads), 0, s, E->st, (const double*)E->partial_b, 0,
+        hipLaunchKernelGGL(kb_fin_init, dim3(1), dim3(kFinParts << E->lw), 0, s, E->lw, E->st, (const double*)E->partial_b, 0,
                            (const double*)E->partial_b, g, restart_mask);
         HIP_CHECK(hipGetLastError());
         batch_read_state(E, s);
@@ -521,6 +577,11 @@ int solve_batch(pamg_hierarchy* h, int nrhs, const double* B, int64_t ldb, doubl
     const int krylov = o.krylov == PAMG_KRYLOV_CG ? PAMG_KRYLOV_CG : PAMG_KRYLOV_FCG;
     BatchEngine* E = get_engine(h, prec, s);
     batch_read_state(E, s);
+    struct Width {                                   // back to 16 however the solve ends
+        BatchEngine* E;
+        ~Width() { E->lw = 4; }
+    } width{E};
+    E->lw = width_log(nrhs);
     const double* src[kW];
     double tol[kW];
     int maxit[kW], fixed[kW];
@@ -609,11 +670,11 @@ static void debug_batch_impl(BatchEngine* E, DevVals<T>& V, int op, const double
         // the kernel the cycle runs at this size (a single-level hierarchy
         // always takes the single-workgroup product)
         if (L >= 1 && I.n > coarse_rows_min_b<T>())
-            hipLaunchKernelGGL((kb_coarse_rows<T, T, double, true>), dim3(coarse_rows_grid_b<T>(I.n)), dim3(kBlock), 0,
-                               s, I.n, (const T*)V.ainv, (const T*)rin, (const int*)nullptr, (const double*)nullptr,
+            hipLaunchKernelGGL((kb_coarse_rows<T, T, double, true>), dim3(coarse_rows_grid_b(I.n)), dim3(kBlock), 0,
+                               s, I.n, 4, (const T*)V.ainv, (const T*)rin, (const int*)nullptr, (const double*)nullptr,
                                (const T*)nullptr, (const T*)nullptr, (T*)nullptr, E->Z, nodone);
         else
-            hipLaunchKernelGGL((kb_coarse<T, T, double, true>), dim3(1), dim3(kCoarseThreads), 0, s, I.n,
+            hipLaunchKernelGGL((kb_coarse<T, T, double, true>), dim3(1), dim3(kCoarseThreads), 0, s, I.n, 4,
                                (const T*)V.ainv, (const T*)rin, (T*)E->Y, (const int*)nullptr, (const double*)nullptr,
                                (const T*)nullptr, (const T*)nullptr, (T*)nullptr, E->Z, (const double*)E->Z,
                                E->partial, nodone);
@@ -718,7 +779,7 @@ void batch_config(pamg_hierarchy* h, int prec, int32_t* cfg) {
         cfg[4 * l + 0] = variant_unroll(E->cfg_down[l]);
         cfg[4 * l + 1] = variant_cpl(E->cfg_down[l]);
         cfg[4 * l + 2] = l > 0 ? variant_unroll(E->cfg_up[l]) : 8;     // level 0: the fixed-shape kb_up0
-        cfg[4 * l + 3] = l > 0 ? variant_cpl(E->cfg_up[l]) : (prec == PAMG_PREC_F32 ? up0_cols<float>() : up0_cols<double>());
+        cfg[4 * l + 3] = l > 0 ? variant_cpl(E->cfg_up[l]) : kW / kFixedLanes;
     }
 }
 

@@ -1,11 +1,13 @@
 // Multi-right-hand-side kernels: the same V-cycle and Krylov steps applied to
-// kW = 16 independent right-hand sides at once.
+// W = 4, 8 or 16 (at most kW) independent right-hand sides at once.
 //
-// Vectors are n x 16, row-major, in hierarchical order: the 16 values of a
-// row are one 128-byte (FP64) or 64-byte (FP32) line, so every gathered
+// Vectors are n x W, row-major, in hierarchical order: with W = 16 the values
+// of a row are one 128-byte (FP64) or 64-byte (FP32) line, so every gathered
 // neighbour is one line and every matrix entry is read once per 16 columns.
-// A row is handled by a group of kW/CPL lanes, each lane owning CPL adjacent
-// columns.  Per column the arithmetic is a fixed sequence (entries in CSR
+// The width is a launch argument (lw = log2 W): a batch of few right-hand sides
+// moves few columns (five columns of 227 thousand rows, FP64: 10.9 ms a solve
+// at width 16).  A row is handled by a group of W/CPL lanes, each lane owning
+// CPL adjacent columns.  Per column the arithmetic is a fixed sequence (entries in CSR
 // order, members in order), independent of the unroll depth U, of CPL and
 // of the other columns: a column's result does not depend on what else is
 // in the batch.  Reductions are per-workgroup partials combined in a fixed
@@ -85,6 +87,16 @@ __device__ __forceinline__ void vstore(T* p, const Vec<T, C>& a) {
     }
 }
 
+// The row group of this thread and its first column: W / CPL lanes a group.
+template <int CPL>
+struct LaneGroup {
+    static constexpr int kLog = CPL == 4 ? 2 : CPL == 2 ? 1 : 0;
+    int g, col0, gpb;
+    __device__ __forceinline__ explicit LaneGroup(int lw)
+        : g((int)threadIdx.x >> (lw - kLog)), col0(((int)threadIdx.x & ((1 << (lw - kLog)) - 1)) * CPL),
+          gpb((int)blockDim.x >> (lw - kLog)) {}
+};
+
 // Units (rows or coarse rows) handled by one row group: first, +stride, < end;
 // units are split into contiguous per-XCD chunks as in tile_walk.
 __device__ __forceinline__ TileWalk unit_walk(int nunits, int gpb, int g) {
@@ -116,7 +128,7 @@ inline int unit_grid(long long nunits, int gpb) {
 // 16-column engine 1.6x slower.)
 template <int U, int CPL, typename T, typename XT>
 __device__ __forceinline__ void row_accumulate(const RowIdx& R, int i, const int* __restrict__ ci,
-                                               const T* __restrict__ av, const XT* __restrict__ x, int col0,
+                                               const T* __restrict__ av, const XT* __restrict__ x, int lw, int col0,
                                                T (&s)[CPL]) {
     const int len = R.len(i), st = R.stride();
     int o = R.start(i), k = 0;
@@ -129,14 +141,14 @@ __device__ __forceinline__ void row_accumulate(const RowIdx& R, int i, const int
         for (int u = 0; u < U; ++u) a[u] = av[o + u * st];
         Vec<XT, CPL> xv[U];
 #pragma unroll
-        for (int u = 0; u < U; ++u) xv[u] = vload<XT, CPL>(x + (size_t)c[u] * kW + col0);
+        for (int u = 0; u < U; ++u) xv[u] = vload<XT, CPL>(x + ((size_t)c[u] << lw) + col0);
 #pragma unroll
         for (int u = 0; u < U; ++u)
 #pragma unroll
             for (int q = 0; q < CPL; ++q) s[q] += a[u] * (T)xv[u].v[q];
     }
     for (; k < len; ++k, o += st) {
-        const Vec<XT, CPL> xv = vload<XT, CPL>(x + (size_t)ci[o] * kW + col0);
+        const Vec<XT, CPL> xv = vload<XT, CPL>(x + ((size_t)ci[o] << lw) + col0);
         const T a = av[o];
 #pragma unroll
         for (int q = 0; q < CPL; ++q) s[q] += a * (T)xv.v[q];
@@ -147,14 +159,14 @@ __device__ __forceinline__ void row_accumulate(const RowIdx& R, int i, const int
 
 // Down-sweep: rc[I] = sum_{m in G_I} p_m (r_m - (A D^-1 r)_m), per column.
 template <int U, int CPL, typename T, typename RT>
-static __global__ __launch_bounds__(kBlock) void kb_down(int nc, RowIdx rows, const int* __restrict__ ci,
+static __global__ __launch_bounds__(kBlock) void kb_down(int nc, int lw, RowIdx rows, const int* __restrict__ ci,
                                                   const T* __restrict__ vd, const RT* __restrict__ r,
                                                   const T* __restrict__ p, const int* __restrict__ aggptr,
                                                   T* __restrict__ rc, const int* __restrict__ done) {
     if (*done) return;
-    constexpr int LPR = kW / CPL, GPB = kBlock / LPR;
-    const int g = threadIdx.x / LPR, col0 = (threadIdx.x % LPR) * CPL;
-    const TileWalk w = unit_walk(nc, GPB, g);
+    const LaneGroup<CPL> lg(lw);
+    const int col0 = lg.col0;
+    const TileWalk w = unit_walk(nc, lg.gpb, lg.g);
     for (int I = w.first; I < w.end; I += w.stride) {
         const int m0 = aggptr[I], m1 = aggptr[I + 1];
         T acc[CPL];
@@ -164,8 +176,8 @@ static __global__ __launch_bounds__(kBlock) void kb_down(int nc, RowIdx rows, co
             T s[CPL];
 #pragma unroll
             for (int q = 0; q < CPL; ++q) s[q] = 0;
-            row_accumulate<U, CPL, T, RT>(rows, m, ci, vd, r, col0, s);
-            const Vec<RT, CPL> rm = vload<RT, CPL>(r + (size_t)m * kW + col0);
+            row_accumulate<U, CPL, T, RT>(rows, m, ci, vd, r, lw, col0, s);
+            const Vec<RT, CPL> rm = vload<RT, CPL>(r + ((size_t)m << lw) + col0);
             const T pm = p[m];
 #pragma unroll
             for (int q = 0; q < CPL; ++q) acc[q] += pm * ((T)rm.v[q] - s[q]);
@@ -173,67 +185,65 @@ static __global__ __launch_bounds__(kBlock) void kb_down(int nc, RowIdx rows, co
         Vec<T, CPL> o;
 #pragma unroll
         for (int q = 0; q < CPL; ++q) o.v[q] = acc[q];
-        vstore<T, CPL>(rc + (size_t)I * kW + col0, o);
+        vstore<T, CPL>(rc + ((size_t)I << lw) + col0, o);
     }
 }
 
 // Up-sweep at level l > 0: z = zp + D^-1 (r - A zp), prolongated into level
 // l-1: zp_f[m] = dinv_f[m] r_f[m] + p_f[m] z for the members m of row i.
 template <int U, int CPL, typename T, typename RT, typename RTF>
-static __global__ __launch_bounds__(kBlock) void kb_up(int n, RowIdx rows, const int* __restrict__ ci,
+static __global__ __launch_bounds__(kBlock) void kb_up(int n, int lw, RowIdx rows, const int* __restrict__ ci,
                                                 const T* __restrict__ av, const T* __restrict__ zp,
                                                 const RT* __restrict__ r, const T* __restrict__ dinv,
                                                 const int* __restrict__ aggptr_f, const RTF* __restrict__ r_f,
                                                 const T* __restrict__ dinv_f, const T* __restrict__ p_f,
                                                 T* __restrict__ zp_f, const int* __restrict__ done) {
     if (*done) return;
-    constexpr int LPR = kW / CPL, GPB = kBlock / LPR;
-    const int g = threadIdx.x / LPR, col0 = (threadIdx.x % LPR) * CPL;
-    const TileWalk w = unit_walk(n, GPB, g);
+    const LaneGroup<CPL> lg(lw);
+    const int col0 = lg.col0;
+    const TileWalk w = unit_walk(n, lg.gpb, lg.g);
     for (int i = w.first; i < w.end; i += w.stride) {
         T s[CPL];
 #pragma unroll
         for (int q = 0; q < CPL; ++q) s[q] = 0;
-        row_accumulate<U, CPL, T, T>(rows, i, ci, av, zp, col0, s);
-        const Vec<T, CPL> zpi = vload<T, CPL>(zp + (size_t)i * kW + col0);
-        const Vec<RT, CPL> ri = vload<RT, CPL>(r + (size_t)i * kW + col0);
+        row_accumulate<U, CPL, T, T>(rows, i, ci, av, zp, lw, col0, s);
+        const Vec<T, CPL> zpi = vload<T, CPL>(zp + ((size_t)i << lw) + col0);
+        const Vec<RT, CPL> ri = vload<RT, CPL>(r + ((size_t)i << lw) + col0);
         const T di = dinv[i];
         T z[CPL];
 #pragma unroll
         for (int q = 0; q < CPL; ++q) z[q] = zpi.v[q] + di * ((T)ri.v[q] - s[q]);
         for (int m = aggptr_f[i]; m < aggptr_f[i + 1]; ++m) {
-            const Vec<RTF, CPL> rf = vload<RTF, CPL>(r_f + (size_t)m * kW + col0);
+            const Vec<RTF, CPL> rf = vload<RTF, CPL>(r_f + ((size_t)m << lw) + col0);
             const T df = dinv_f[m], pf = p_f[m];
             Vec<T, CPL> o;
 #pragma unroll
             for (int q = 0; q < CPL; ++q) o.v[q] = prolong_value(df, (T)rf.v[q], pf, z[q]);
-            vstore<T, CPL>(zp_f + (size_t)m * kW + col0, o);
+            vstore<T, CPL>(zp_f + ((size_t)m << lw) + col0, o);
         }
     }
 }
 
-// Level-0 up-sweep: z = zp + D^-1 (r - A zp) written in FP64, with per-column
-// partials of z . dv.  Fixed shape, whatever the tuning (its partial sums
-// must not depend on it): unroll 8 and four columns per lane (one 16-byte
-// load in FP32, two in FP64).
-template <typename T>
-constexpr int up0_cols() { return 4; }
-template <typename T>
-constexpr int up0_rows_per_block() { return kBlock / (kW / up0_cols<T>()); }
+// Level-0 up-sweep: z = zp + D^-1 (r - A zp), with per-column partials of
+// z . dv.  Fixed shape, whatever the tuning and the width (its partial sums
+// must not depend on them): kFixedRows rows a workgroup, four lanes a row
+// (W / 4 columns per lane, one 16-byte load in FP32 at W = 16, two in FP64),
+// unroll 8.  z is written in the cycle's precision T: with the FP32 cycle z is
+// a float (exactly its FP64 widening), so the Krylov pass gathers half lines.
+constexpr int kFixedLanes = 4;
+constexpr int kFixedRows = kBlock / kFixedLanes;
 
-// z is written in the cycle's precision T: with the FP32 cycle z is a float
-// (exactly its FP64 widening), so the Krylov pass gathers 64-byte rows.
-template <typename T>
+template <int CPL, typename T>
 static __global__ __launch_bounds__(kBlock) void kb_up0(int n, RowIdx rows, const int* __restrict__ ci,
                                                  const T* __restrict__ av, const T* __restrict__ zp,
                                                  const T* __restrict__ r, const T* __restrict__ dinv,
                                                  T* __restrict__ z_out, const double* __restrict__ dv,
                                                  double* __restrict__ partial, const int* __restrict__ done) {
     if (*done) return;
-    constexpr int CPL = up0_cols<T>(), LPR = kW / CPL, GPB = kBlock / LPR;
-    __shared__ double s_dot[GPB][kW];
-    const int g = threadIdx.x / LPR, col0 = (threadIdx.x % LPR) * CPL;
-    const TileWalk w = unit_walk(n, GPB, g);
+    constexpr int lw = CPL == 4 ? 4 : CPL == 2 ? 3 : 2, W = 1 << lw;
+    __shared__ double s_dot[kFixedRows][W];
+    const int g = threadIdx.x / kFixedLanes, col0 = (threadIdx.x % kFixedLanes) * CPL;
+    const TileWalk w = unit_walk(n, kFixedRows, g);
     double dot[CPL];
 #pragma unroll
     for (int q = 0; q < CPL; ++q) dot[q] = 0.0;
@@ -241,8 +251,8 @@ static __global__ __launch_bounds__(kBlock) void kb_up0(int n, RowIdx rows, cons
         T s[CPL];
 #pragma unroll
         for (int q = 0; q < CPL; ++q) s[q] = 0;
-        row_accumulate<8, CPL, T, T>(rows, i, ci, av, zp, col0, s);
-        const size_t e = (size_t)i * kW + col0;
+        row_accumulate<8, CPL, T, T>(rows, i, ci, av, zp, lw, col0, s);
+        const size_t e = ((size_t)i << lw) + col0;
         const Vec<T, CPL> zv = vload<T, CPL>(zp + e);
         const T di = dinv[i];
 #pragma unroll
@@ -255,26 +265,27 @@ static __global__ __launch_bounds__(kBlock) void kb_up0(int n, RowIdx rows, cons
 #pragma unroll
     for (int q = 0; q < CPL; ++q) s_dot[g][col0 + q] = dot[q];
     __syncthreads();
-    if (threadIdx.x < kW) {
+    if (threadIdx.x < W) {
         double t = 0.0;
-        for (int q = 0; q < GPB; ++q) t += s_dot[q][threadIdx.x];
-        partial[(size_t)blockIdx.x * kW + threadIdx.x] = t;
+        for (int q = 0; q < kFixedRows; ++q) t += s_dot[q][threadIdx.x];
+        partial[(size_t)blockIdx.x * W + threadIdx.x] = t;
     }
 }
 
-// Coarsest level: Z = A_L^-1 R (nL x nL times nL x 16), then prolongation
+// Coarsest level: Z = A_L^-1 R (nL x nL times nL x W), then prolongation
 // into level L-1 or (single level) z out with per-column partials of z . dv.
 // FP64 uses the matrix cores: v_mfma_f64_16x16x4_f64 on 16-row blocks, one
-// wave per block.  Z goes through the scratch zc (nL x 16).
+// wave per block.  Z goes through the scratch zc (nL x W).
 template <typename T, typename RT, typename RTF, bool OUT>
 static __global__ __launch_bounds__(kCoarseThreads) void kb_coarse(
-    int nL, const T* __restrict__ ainv, const RT* __restrict__ r, T* __restrict__ zc,
+    int nL, int lw, const T* __restrict__ ainv, const RT* __restrict__ r, T* __restrict__ zc,
     const int* __restrict__ aggptr_f, const RTF* __restrict__ r_f, const T* __restrict__ dinv_f,
     const T* __restrict__ p_f, T* __restrict__ zp_f, double* __restrict__ z_out, const double* __restrict__ dv,
     double* __restrict__ partial, const int* __restrict__ done) {
     if (*done) return;
     const int tid = threadIdx.x, wave = tid / 64, l = tid % 64;
     constexpr int kWaves = kCoarseThreads / 64;
+    const int W = 1 << lw;
     if constexpr (std::is_same<T, double>::value) {
         // A tile (16 x 4): lane l holds A[l % 16][l / 16]; B tile (4 x 16):
         // lane l holds B[l / 16][l % 16]; D (16 x 16): result register i of
@@ -287,135 +298,162 @@ static __global__ __launch_bounds__(kCoarseThreads) void kb_coarse(
             for (int k0 = 0; k0 < nL; k0 += 4) {
                 const int k = k0 + l / 16;
                 const double a = (m < nL && k < nL) ? ainv[(size_t)m * nL + k] : 0.0;
-                const double b = (k < nL) ? (double)r[(size_t)k * kW + (l % 16)] : 0.0;
+                const double b = (k < nL && l % 16 < W) ? (double)r[((size_t)k << lw) + (l % 16)] : 0.0;
                 acc = __builtin_amdgcn_mfma_f64_16x16x4f64(a, b, acc, 0, 0, 0);
             }
 #pragma unroll
             for (int i = 0; i < 4; ++i) {
                 const int row = rb * 16 + 4 * i + (l / 16);
-                if (row < nL) zc[(size_t)row * kW + (l % 16)] = acc[i];
+                if (row < nL && l % 16 < W) zc[((size_t)row << lw) + (l % 16)] = acc[i];
             }
         }
     } else {
-        for (int e = tid; e < nL * kW; e += kCoarseThreads) {
-            const int I = e / kW, c = e % kW;
+        for (int e = tid; e < nL << lw; e += kCoarseThreads) {
+            const int I = e >> lw, c = e & (W - 1);
             T s = 0;
-            for (int j = 0; j < nL; ++j) s += ainv[(size_t)I * nL + j] * (T)r[(size_t)j * kW + c];
+            for (int j = 0; j < nL; ++j) s += ainv[(size_t)I * nL + j] * (T)r[((size_t)j << lw) + c];
             zc[e] = s;
         }
     }
     __threadfence_block();
     __syncthreads();
-    double dot = 0.0;
-    for (int e = tid; e < nL * kW; e += kCoarseThreads) {
-        const int I = e / kW, c = e % kW;
-        const T z = zc[e];
-        if constexpr (OUT) {
-            z_out[e] = (double)z;
-            dot += (double)z * dv[e];
-        } else {
-            for (int m = aggptr_f[I]; m < aggptr_f[I + 1]; ++m)
-                zp_f[(size_t)m * kW + c] = prolong_value(dinv_f[m], (T)r_f[(size_t)m * kW + c], p_f[m], z);
-        }
-    }
     if constexpr (OUT) {
-        __shared__ double s_dot[kCoarseThreads / kW][kW];
-        s_dot[tid / kW][tid % kW] = dot;
+        // thread t: column t mod W, rows t / W + 64 i (64 rows at every width,
+        // so that a column's dot product is the same bits at each)
+        __shared__ double s_dot[kCoarseThreads];
+        const int stride = (kCoarseThreads / kW) << lw;
+        double dot = 0.0;
+        if (tid < stride)
+            for (int e = tid; e < nL << lw; e += stride) {
+                const T z = zc[e];
+                z_out[e] = (double)z;
+                dot += (double)z * dv[e];
+            }
+        s_dot[tid] = dot;
         __syncthreads();
-        if (tid < kW) {
+        if (tid < W) {
             double t = 0.0;
-            for (int q = 0; q < kCoarseThreads / kW; ++q) t += s_dot[q][tid];
+            for (int q = tid; q < stride; q += W) t += s_dot[q];
             partial[tid] = t;
+        }
+    } else {
+        for (int e = tid; e < nL << lw; e += kCoarseThreads) {
+            const int I = e >> lw, c = e & (W - 1);
+            const T z = zc[e];
+            for (int m = aggptr_f[I]; m < aggptr_f[I + 1]; ++m)
+                zp_f[((size_t)m << lw) + c] = prolong_value(dinv_f[m], (T)r_f[((size_t)m << lw) + c], p_f[m], z);
         }
     }
 }
 
 // Large coarsest level (L >= 1): the product and the prolongation into level
-// L-1 spread over many workgroups of 256 threads (OUT: the product is written
-// to z_out instead, n_L x 16 in FP64, for the per-operator parity check).  FP64: one wave per 16-row
-// block on the matrix cores (four waves, 64 rows per workgroup), prolongated
-// straight from the result registers.  FP32: a workgroup owns 16 rows and its
-// threads split the columns j in 16 fixed ranges (one row and all 16
-// right-hand sides per thread), meeting in LDS in a fixed order; small row
-// blocks give ceil(n_L / 16) workgroups, enough to spread a coarsest level of
-// a few thousand rows over the chip.
-template <typename T>
-constexpr int coarse_rows_block_rows_b() { return std::is_same<T, double>::value ? 64 : 16; }
+// L-1 spread over many workgroups of 256 threads that own 16 rows each (OUT: the
+// product is written to z_out instead, n_L x W in FP64, for the per-operator
+// parity check).  FP64: the workgroup's four waves split the columns j in four
+// ranges on the matrix cores, the four tiles meeting in LDS in range order.
+// FP32: its threads split the columns j in 16 fixed ranges (one row and all W
+// right-hand sides per thread), meeting in LDS in a fixed order.  Both are bound
+// by the chain of their loads (a few MB from L2), so several steps' loads are
+// issued together: FP64 at 1096 rows 120 us with one wave over all columns and a
+// load per step, now 16; FP32 18.4 us with a load per step, now 12.5.
+constexpr int kCoarseBlockRows = 16;
 // Coarsest sizes from which the many-workgroup kernel replaces the single
-// workgroup: FP64 keeps the single-workgroup matrix-core product up to the
-// single-right-hand-side threshold; FP32, whose single workgroup computes
-// each (row, column) entry as a serial loop over n_L, switches early.
+// workgroup, whose time is its chain of n_L / 4 loads: FP64 at 210 rows 26.9 us
+// against 5.2, so below 64 rows (8 us by that chain) there is little to split.
 template <typename T>
-constexpr int coarse_rows_min_b() { return std::is_same<T, double>::value ? kCoarseRowsMin : 32; }
-template <typename T>
-inline int coarse_rows_grid_b(int nL) {
-    return (nL + coarse_rows_block_rows_b<T>() - 1) / coarse_rows_block_rows_b<T>();
+constexpr int coarse_rows_min_b() { return std::is_same<T, double>::value ? 64 : 32; }
+inline int coarse_rows_grid_b(int nL) { return (nL + kCoarseBlockRows - 1) / kCoarseBlockRows; }
+
+// The FP32 ranges of kb_coarse_rows: row I's products over columns [j0, j1), one
+// after the other, for W right-hand sides in registers; the loads of U columns
+// are in flight together.
+template <int W, typename T, typename RT>
+static __device__ void coarse_range(int nL, int I, int j0, int j1, const T* __restrict__ ainv, const RT* __restrict__ r,
+                                    T* __restrict__ out) {
+    constexpr int U = 4;
+    T acc[W];
+#pragma unroll
+    for (int c = 0; c < W; ++c) acc[c] = 0;
+    if (I < nL) {
+        int j = j0;
+        for (; j + U <= j1; j += U) {
+            T a[U], v[U][W];
+#pragma unroll
+            for (int u = 0; u < U; ++u) {
+                a[u] = ainv[(size_t)(j + u) * nL + I];
+#pragma unroll
+                for (int c = 0; c < W; ++c) v[u][c] = (T)r[(size_t)(j + u) * W + c];
+            }
+#pragma unroll
+            for (int u = 0; u < U; ++u)
+#pragma unroll
+                for (int c = 0; c < W; ++c) acc[c] += a[u] * v[u][c];
+        }
+        for (; j < j1; ++j) {
+            const T a = ainv[(size_t)j * nL + I];
+#pragma unroll
+            for (int c = 0; c < W; ++c) acc[c] += a * (T)r[(size_t)j * W + c];
+        }
+    }
+#pragma unroll
+    for (int c = 0; c < W; ++c) out[c] = acc[c];
 }
 
 template <typename T, typename RT, typename RTF, bool OUT = false>
 static __global__ __launch_bounds__(kBlock) void kb_coarse_rows(
-    int nL, const T* __restrict__ ainv, const RT* __restrict__ r,
+    int nL, int lw, const T* __restrict__ ainv, const RT* __restrict__ r,
     const int* __restrict__ aggptr_f, const RTF* __restrict__ r_f, const T* __restrict__ dinv_f,
     const T* __restrict__ p_f, T* __restrict__ zp_f, double* __restrict__ z_out, const int* __restrict__ done) {
     if (*done) return;
-    const int tid = threadIdx.x, wave = tid / 64, l = tid % 64;
+    constexpr int R = kCoarseBlockRows, G = std::is_same<T, double>::value ? kBlock / 64 : kBlock / R;
+    __shared__ T s_part[G][R][kW + 1];
+    const int tid = threadIdx.x, W = 1 << lw;
     if constexpr (std::is_same<T, double>::value) {
         using d4 = __attribute__((__vector_size__(4 * sizeof(double)))) double;
-        const int rb = blockIdx.x * (kBlock / 64) + wave;        // 16-row block of this wave
-        if (rb * 16 >= nL) return;
+        constexpr int U = 8;                                // k steps whose loads are in flight together
+        const int wave = tid / 64, l = tid % 64, col = l % 16;
+        const int m = min((int)blockIdx.x * R + col, nL - 1);       // rows past the end repeat the last: not stored
+        const int steps = (nL + 3) / 4;
+        const int s0 = steps * wave / G, s1 = steps * (wave + 1) / G;
         d4 acc = {0.0, 0.0, 0.0, 0.0};
-        const int m = rb * 16 + (l % 16);
-        for (int k0 = 0; k0 < nL; k0 += 4) {
-            const int k = k0 + l / 16;
-            const double a = (m < nL && k < nL) ? ainv[(size_t)m * nL + k] : 0.0;
-            const double b = (k < nL) ? (double)r[(size_t)k * kW + (l % 16)] : 0.0;
-            acc = __builtin_amdgcn_mfma_f64_16x16x4f64(a, b, acc, 0, 0, 0);
-        }
-        const int c = l % 16;
+        for (int t = s0; t < s1; t += U) {
+            double a[U], b[U];
 #pragma unroll
-        for (int i = 0; i < 4; ++i) {
-            const int I = rb * 16 + 4 * i + (l / 16);
-            if (I >= nL) continue;
-            const T z = acc[i];
-            if constexpr (OUT) {
-                z_out[(size_t)I * kW + c] = (double)z;
-                continue;
+            for (int u = 0; u < U; ++u) {
+                const int k = 4 * (t + u) + l / 16;
+                const bool in = t + u < s1 && k < nL;
+                a[u] = in ? ainv[(size_t)m * nL + k] : 0.0;
+                b[u] = in && col < W ? (double)r[((size_t)k << lw) + col] : 0.0;
             }
-            for (int mm = aggptr_f[I]; mm < aggptr_f[I + 1]; ++mm)
-                zp_f[(size_t)mm * kW + c] = prolong_value(dinv_f[mm], (T)r_f[(size_t)mm * kW + c], p_f[mm], z);
+#pragma unroll
+            for (int u = 0; u < U; ++u) acc = __builtin_amdgcn_mfma_f64_16x16x4f64(a[u], b[u], acc, 0, 0, 0);
         }
+#pragma unroll
+        for (int i = 0; i < 4; ++i) s_part[wave][4 * i + l / 16][col] = acc[i];
     } else {
-        constexpr int R = coarse_rows_block_rows_b<T>(), G = kBlock / R;
-        __shared__ T s_part[G][R][kW + 1];
         const int g = tid / R, lt = tid % R;
         const int I = blockIdx.x * R + lt;
         const int j0 = (int)((long long)nL * g / G), j1 = (int)((long long)nL * (g + 1) / G);
-        T acc[kW];
-#pragma unroll
-        for (int c = 0; c < kW; ++c) acc[c] = 0;
-        if (I < nL) {
-            for (int j = j0; j < j1; ++j) {
-                const T a = ainv[(size_t)j * nL + I];
-#pragma unroll
-                for (int c = 0; c < kW; ++c) acc[c] += a * (T)r[(size_t)j * kW + c];
-            }
+        if (lw == 2)
+            coarse_range<4>(nL, I, j0, j1, ainv, r, s_part[g][lt]);
+        else if (lw == 3)
+            coarse_range<8>(nL, I, j0, j1, ainv, r, s_part[g][lt]);
+        else
+            coarse_range<16>(nL, I, j0, j1, ainv, r, s_part[g][lt]);
+    }
+    __syncthreads();
+    for (int e = tid; e < R << lw; e += kBlock) {
+        const int row = e >> lw, c = e & (W - 1);
+        const int II = blockIdx.x * R + row;
+        if (II >= nL) continue;
+        T z = s_part[0][row][c];
+        for (int q = 1; q < G; ++q) z += s_part[q][row][c];
+        if constexpr (OUT) {
+            z_out[((size_t)II << lw) + c] = (double)z;
+            continue;
         }
-#pragma unroll
-        for (int c = 0; c < kW; ++c) s_part[g][lt][c] = acc[c];
-        __syncthreads();
-        for (int e = tid; e < R * kW; e += kBlock) {
-            const int row = e / kW, c = e % kW;
-            const int II = blockIdx.x * R + row;
-            if (II >= nL) continue;
-            T z = s_part[0][row][c];
-            for (int q = 1; q < G; ++q) z += s_part[q][row][c];
-            if constexpr (OUT) {
-                z_out[(size_t)II * kW + c] = (double)z;
-                continue;
-            }
-            for (int mm = aggptr_f[II]; mm < aggptr_f[II + 1]; ++mm)
-                zp_f[(size_t)mm * kW + c] = prolong_value(dinv_f[mm], (T)r_f[(size_t)mm * kW + c], p_f[mm], z);
-        }
+        for (int mm = aggptr_f[II]; mm < aggptr_f[II + 1]; ++mm)
+            zp_f[((size_t)mm << lw) + c] = prolong_value(dinv_f[mm], (T)r_f[((size_t)mm << lw) + c], p_f[mm], z);
     }
 }
 
@@ -436,12 +474,8 @@ static __global__ __launch_bounds__(kBlock) void kb_narrow(long long cnt, const 
 // gathered, one line per entry instead of two), and per-column partials of
 // p.q and p.r.  A column on its first iteration, or finished, takes q = A z
 // (an idle column's q stays bounded).  q holds q_old on entry; each element
-// is read before it is overwritten, by the same lane.  Fixed shape: unroll 8,
-// four columns per lane (two 16-byte loads).
-constexpr int kKrylovCols = 4;
-constexpr int kKrylovRowsPerBlock = kBlock / (kW / kKrylovCols);
-
-template <typename ZT>
+// is read before it is overwritten, by the same lane.  Fixed shape, as kb_up0.
+template <int CPL, typename ZT>
 static __global__ __launch_bounds__(kBlock) void kb_krylov_pq(int n, RowIdx rows, const int* __restrict__ ci,
                                                        const double* __restrict__ av, const ZT* __restrict__ z,
                                                        const double* __restrict__ p_old, double* __restrict__ p_new,
@@ -449,9 +483,9 @@ static __global__ __launch_bounds__(kBlock) void kb_krylov_pq(int n, RowIdx rows
                                                        const BatchState* __restrict__ st, double* __restrict__ partial,
                                                        const int* __restrict__ done) {
     if (*done) return;
-    constexpr int CPL = kKrylovCols, LPR = kW / CPL, GPB = kBlock / LPR;
-    __shared__ double s_pq[GPB][kW], s_pr[GPB][kW];
-    const int g = threadIdx.x / LPR, col0 = (threadIdx.x % LPR) * CPL;
+    constexpr int lw = CPL == 4 ? 4 : CPL == 2 ? 3 : 2, W = 1 << lw, GPB = kFixedRows;
+    __shared__ double s_pq[GPB][W], s_pr[GPB][W];
+    const int g = threadIdx.x / kFixedLanes, col0 = (threadIdx.x % kFixedLanes) * CPL;
     bool first[CPL], fresh[CPL];
     double beta[CPL], pq[CPL], pr[CPL];
 #pragma unroll
@@ -468,8 +502,8 @@ static __global__ __launch_bounds__(kBlock) void kb_krylov_pq(int n, RowIdx rows
         double s[CPL];
 #pragma unroll
         for (int c = 0; c < CPL; ++c) s[c] = 0.0;
-        row_accumulate<8, CPL, double, ZT>(rows, i, ci, av, z, col0, s);
-        const size_t e = (size_t)i * kW + col0;
+        row_accumulate<8, CPL, double, ZT>(rows, i, ci, av, z, lw, col0, s);
+        const size_t e = ((size_t)i << lw) + col0;
         const Vec<ZT, CPL> zi = vload<ZT, CPL>(z + e);
         const Vec<double, CPL> po = vload<double, CPL>(p_old + e);
         const Vec<double, CPL> qo = vload<double, CPL>(q + e), ri = vload<double, CPL>(r + e);
@@ -491,31 +525,36 @@ static __global__ __launch_bounds__(kBlock) void kb_krylov_pq(int n, RowIdx rows
         s_pr[g][col0 + c] = pr[c];
     }
     __syncthreads();
-    if (threadIdx.x < kW) {
+    if (threadIdx.x < W) {
         double a = 0.0, b = 0.0;
         for (int t = 0; t < GPB; ++t) { a += s_pq[t][threadIdx.x]; b += s_pr[t][threadIdx.x]; }
-        partial[((size_t)blockIdx.x * kW + threadIdx.x) * 2] = a;
-        partial[((size_t)blockIdx.x * kW + threadIdx.x) * 2 + 1] = b;
+        partial[((size_t)blockIdx.x * W + threadIdx.x) * 2] = a;
+        partial[((size_t)blockIdx.x * W + threadIdx.x) * 2 + 1] = b;
     }
 }
+
+// The vector kernels below take kRowGroups rows a workgroup, one lane per
+// column (kRowGroups W threads), whatever the width.
+constexpr int kRowGroups = kBlock / kW;
 
 // x += alpha_c p, r -= alpha_c q for the active columns; partials of r.r.
 // r32 (the FP32 cycle): r rounded to FP32 beside it, the cycle's level-0
 // right-hand side.
-static __global__ __launch_bounds__(kBlock) void kb_update(int n, double* __restrict__ x, double* __restrict__ r,
+static __global__ __launch_bounds__(kBlock) void kb_update(int n, int lw, double* __restrict__ x, double* __restrict__ r,
                                                     float* __restrict__ r32, const double* __restrict__ p,
                                                     const double* __restrict__ q, const BatchState* __restrict__ st,
                                                     double* __restrict__ partial, const int* __restrict__ done) {
     if (*done) return;
-    constexpr int GPB = kBlock / kW;
+    constexpr int GPB = kRowGroups;
+    const int W = 1 << lw;
     __shared__ double s_rr[GPB][kW];
-    const int g = threadIdx.x / kW, lane = threadIdx.x % kW;
+    const int g = threadIdx.x >> lw, lane = threadIdx.x & (W - 1);
     const bool live = st->col[lane].done == 0;
     const double alpha = st->col[lane].alpha;
     double rr = 0.0;
     const int stride = gridDim.x * GPB;
     for (int i = blockIdx.x * GPB + g; i < n; i += stride) {
-        const size_t e = (size_t)i * kW + lane;
+        const size_t e = ((size_t)i << lw) + lane;
         double ri = r[e];
         if (live) {
             x[e] += alpha * p[e];
@@ -527,38 +566,39 @@ static __global__ __launch_bounds__(kBlock) void kb_update(int n, double* __rest
     }
     s_rr[g][lane] = rr;
     __syncthreads();
-    if (threadIdx.x < kW) {
+    if ((int)threadIdx.x < W) {
         double t = 0.0;
         for (int q2 = 0; q2 < GPB; ++q2) t += s_rr[q2][threadIdx.x];
-        partial[(size_t)blockIdx.x * kW + threadIdx.x] = t;
+        partial[(size_t)blockIdx.x * W + threadIdx.x] = t;
     }
 }
 
 // Fixed-order per-column sums of `count` partials (partial gi of column c at
-// ((gi * kW + c) * stride + off)) by one workgroup of kFinThreads: thread t
-// takes column t % kW and the partials gi = t / kW, + kFinParts, ...
+// ((gi * W + c) * stride + off)) by one workgroup of kFinParts W threads: thread
+// t takes column t mod W and the partials gi = t / W, + kFinParts, ...
 // (neighbouring threads read neighbouring columns of one partial), four loads
 // in flight; the kFinParts part sums of a column then meet in LDS in part
-// order.  The result is valid in threads 0 .. kW-1 (thread c: column c).
-constexpr int kFinThreads = 1024;
-constexpr int kFinParts = kFinThreads / kW;
+// order.  The result is valid in threads 0 .. W-1 (thread c: column c).
+constexpr int kFinParts = 64;
+constexpr int kFinThreads = kFinParts * kW;
 
-__device__ __forceinline__ double col_sum(const double* __restrict__ partial, int count, int stride, int off,
+__device__ __forceinline__ double col_sum(const double* __restrict__ partial, int count, int stride, int off, int lw,
                                           double (*s_part)[kW]) {
-    const int c = threadIdx.x % kW, part = threadIdx.x / kW;
+    const int c = threadIdx.x & ((1 << lw) - 1), part = threadIdx.x >> lw;
     double s0 = 0.0, s1 = 0.0, s2 = 0.0, s3 = 0.0;
     int gi = part;
+    const auto at = [&](int g) { return partial[(((size_t)g << lw) + c) * stride + off]; };
     for (; gi + 3 * kFinParts < count; gi += 4 * kFinParts) {
-        s0 += partial[((size_t)gi * kW + c) * stride + off];
-        s1 += partial[((size_t)(gi + kFinParts) * kW + c) * stride + off];
-        s2 += partial[((size_t)(gi + 2 * kFinParts) * kW + c) * stride + off];
-        s3 += partial[((size_t)(gi + 3 * kFinParts) * kW + c) * stride + off];
+        s0 += at(gi);
+        s1 += at(gi + kFinParts);
+        s2 += at(gi + 2 * kFinParts);
+        s3 += at(gi + 3 * kFinParts);
     }
-    for (; gi < count; gi += kFinParts) s0 += partial[((size_t)gi * kW + c) * stride + off];
+    for (; gi < count; gi += kFinParts) s0 += at(gi);
     s_part[part][c] = (s0 + s1) + (s2 + s3);
     __syncthreads();
     double t = 0.0;
-    if (threadIdx.x < kW)
+    if (threadIdx.x < (1u << lw))
         for (int q = 0; q < kFinParts; ++q) t += s_part[q][threadIdx.x];
     __syncthreads();
     return t;
@@ -577,13 +617,13 @@ __device__ __forceinline__ void update_all_done(BatchState* st) {
 }
 
 // beta (and rho for PCG) from the partials of z.dv.
-static __global__ __launch_bounds__(kFinThreads) void kb_fin_beta(BatchState* __restrict__ st,
+static __global__ __launch_bounds__(kFinThreads) void kb_fin_beta(int lw, BatchState* __restrict__ st,
                                                                   const double* __restrict__ partial, int count) {
     if (st->all_done) return;
     __shared__ double s_part[kFinParts][kW];
     const int c = threadIdx.x;
-    const double d = col_sum(partial, count, 1, 0, s_part);
-    if (c < kW) {
+    const double d = col_sum(partial, count, 1, 0, lw, s_part);
+    if (c < 1 << lw) {
         BatchCol& C = st->col[c];
         if (C.active && !C.done) {
             if (st->krylov == PAMG_KRYLOV_CG) {
@@ -596,14 +636,14 @@ static __global__ __launch_bounds__(kFinThreads) void kb_fin_beta(BatchState* __
     }
 }
 
-static __global__ __launch_bounds__(kFinThreads) void kb_fin_alpha(BatchState* __restrict__ st,
+static __global__ __launch_bounds__(kFinThreads) void kb_fin_alpha(int lw, BatchState* __restrict__ st,
                                                                    const double* __restrict__ partial, int count) {
     if (st->all_done) return;
     __shared__ double s_part[kFinParts][kW];
     const int c = threadIdx.x;
-    const double pq = col_sum(partial, count, 2, 0, s_part);
-    const double pr = col_sum(partial, count, 2, 1, s_part);
-    if (c < kW) {
+    const double pq = col_sum(partial, count, 2, 0, lw, s_part);
+    const double pr = col_sum(partial, count, 2, 1, lw, s_part);
+    if (c < 1 << lw) {
         BatchCol& C = st->col[c];
         if (C.active && !C.done) {
             if (!(pq > 0.0)) {
@@ -622,13 +662,13 @@ static __global__ __launch_bounds__(kFinThreads) void kb_fin_alpha(BatchState* _
     update_all_done(st);
 }
 
-static __global__ __launch_bounds__(kFinThreads) void kb_fin_norm(BatchState* __restrict__ st,
+static __global__ __launch_bounds__(kFinThreads) void kb_fin_norm(int lw, BatchState* __restrict__ st,
                                                                   const double* __restrict__ partial, int count) {
     if (st->all_done) return;
     __shared__ double s_part[kFinParts][kW];
     const int c = threadIdx.x;
-    const double rr = col_sum(partial, count, 1, 0, s_part);
-    if (c < kW) {
+    const double rr = col_sum(partial, count, 1, 0, lw, s_part);
+    if (c < 1 << lw) {
         BatchCol& C = st->col[c];
         if (C.active && !C.done) {
             const double rn = sqrt(rr);
@@ -654,15 +694,15 @@ static __global__ __launch_bounds__(kFinThreads) void kb_fin_norm(BatchState* __
 
 // Start (or restart) the columns in `mask`: ||b|| and ||r|| from partials
 // (bb_count == 0: keep bnorm), first iteration next, stopping state.
-static __global__ __launch_bounds__(kFinThreads) void kb_fin_init(BatchState* __restrict__ st,
+static __global__ __launch_bounds__(kFinThreads) void kb_fin_init(int lw, BatchState* __restrict__ st,
                                                                   const double* __restrict__ bb_part, int bb_count,
                                                                   const double* __restrict__ rr_part, int rr_count,
                                                                   int mask) {
     __shared__ double s_part[kFinParts][kW];
     const int c = threadIdx.x;
-    const double bb = bb_count > 0 ? col_sum(bb_part, bb_count, 1, 0, s_part) : 0.0;
-    const double rr = col_sum(rr_part, rr_count, 1, 0, s_part);
-    if (c < kW && ((mask >> c) & 1)) {
+    const double bb = bb_count > 0 ? col_sum(bb_part, bb_count, 1, 0, lw, s_part) : 0.0;
+    const double rr = col_sum(rr_part, rr_count, 1, 0, lw, s_part);
+    if (c < 1 << lw && ((mask >> c) & 1)) {
         BatchCol& C = st->col[c];
         if (bb_count > 0) C.bnorm = sqrt(bb);
         C.rnorm = sqrt(rr);
@@ -687,18 +727,19 @@ static __global__ __launch_bounds__(kFinThreads) void kb_fin_init(BatchState* __
 // Load columns from caller buffers (src[c] != nullptr: column c of b in the
 // caller's numbering): B[:, c] = b_c (hierarchical order), R[:, c] = B[:, c],
 // X[:, c] = 0; per-column partials of b.b (also r.r).
-static __global__ __launch_bounds__(kBlock) void kb_load(int n, const int* __restrict__ iperm,
+static __global__ __launch_bounds__(kBlock) void kb_load(int n, int lw, const int* __restrict__ iperm,
                                                   const double* const* __restrict__ src, double* __restrict__ B,
                                                   double* __restrict__ R, float* __restrict__ R32,
                                                   double* __restrict__ X, double* __restrict__ partial) {
-    constexpr int GPB = kBlock / kW;
+    constexpr int GPB = kRowGroups;
+    const int W = 1 << lw;
     __shared__ double s_bb[GPB][kW];
-    const int g = threadIdx.x / kW, lane = threadIdx.x % kW;
+    const int g = threadIdx.x >> lw, lane = threadIdx.x & (W - 1);
     const double* sc = src[lane];
     double bb = 0.0;
     const int stride = gridDim.x * GPB;
     for (int i = blockIdx.x * GPB + g; i < n; i += stride) {
-        const size_t e = (size_t)i * kW + lane;
+        const size_t e = ((size_t)i << lw) + lane;
         if (sc) {
             const double v = sc[iperm[i]];
             B[e] = v;
@@ -710,43 +751,45 @@ static __global__ __launch_bounds__(kBlock) void kb_load(int n, const int* __res
     }
     s_bb[g][lane] = bb;
     __syncthreads();
-    if (threadIdx.x < kW) {
+    if ((int)threadIdx.x < W) {
         double t = 0.0;
         for (int q = 0; q < GPB; ++q) t += s_bb[q][threadIdx.x];
-        partial[(size_t)blockIdx.x * kW + threadIdx.x] = t;
+        partial[(size_t)blockIdx.x * W + threadIdx.x] = t;
     }
 }
 
 // Store columns (dst[c] != nullptr): dst_c[i] = X[perm[i], c] (caller order);
 // a column whose right-hand side was zero gets x = 0.
-static __global__ __launch_bounds__(kBlock) void kb_store(int n, const int* __restrict__ perm, double* const* __restrict__ dst,
+static __global__ __launch_bounds__(kBlock) void kb_store(int n, int lw, const int* __restrict__ perm, double* const* __restrict__ dst,
                                                    const double* __restrict__ X, const BatchState* __restrict__ st) {
-    constexpr int GPB = kBlock / kW;
-    const int g = threadIdx.x / kW, lane = threadIdx.x % kW;
+    constexpr int GPB = kRowGroups;
+    const int W = 1 << lw;
+    const int g = threadIdx.x >> lw, lane = threadIdx.x & (W - 1);
     double* dc = dst[lane];
     if (!dc) return;
     const bool zero = st->col[lane].done == 2;
     const int stride = gridDim.x * GPB;
-    for (int i = blockIdx.x * GPB + g; i < n; i += stride) dc[i] = zero ? 0.0 : X[(size_t)perm[i] * kW + lane];
+    for (int i = blockIdx.x * GPB + g; i < n; i += stride) dc[i] = zero ? 0.0 : X[((size_t)perm[i] << lw) + lane];
 }
 
 // Y = B - A X (all columns) and per-column partials of y.y; with `commit`
 // set, columns in `mask` also take Y as their recurrence residual R.
-static __global__ __launch_bounds__(kBlock) void kb_resid(int n, RowIdx rows, const int* __restrict__ ci,
+static __global__ __launch_bounds__(kBlock) void kb_resid(int n, int lw, RowIdx rows, const int* __restrict__ ci,
                                                    const double* __restrict__ av, const double* __restrict__ X,
                                                    const double* __restrict__ B, double* __restrict__ Y,
                                                    double* __restrict__ R, float* __restrict__ R32, int mask,
                                                    double* __restrict__ partial) {
-    constexpr int GPB = kBlock / kW;
+    constexpr int GPB = kRowGroups;
+    const int W = 1 << lw;
     __shared__ double s_yy[GPB][kW];
-    const int g = threadIdx.x / kW, lane = threadIdx.x % kW;
+    const int g = threadIdx.x >> lw, lane = threadIdx.x & (W - 1);
     const TileWalk w = unit_walk(n, GPB, g);
     double yy = 0.0;
     const bool commit = R != nullptr && ((mask >> lane) & 1);
     for (int i = w.first; i < w.end; i += w.stride) {
         double s[1] = {0.0};
-        row_accumulate<4, 1, double, double>(rows, i, ci, av, X, lane, s);
-        const size_t e = (size_t)i * kW + lane;
+        row_accumulate<4, 1, double, double>(rows, i, ci, av, X, lw, lane, s);
+        const size_t e = ((size_t)i << lw) + lane;
         const double y = B[e] - s[0];
         Y[e] = y;
         if (commit) {
@@ -757,10 +800,10 @@ static __global__ __launch_bounds__(kBlock) void kb_resid(int n, RowIdx rows, co
     }
     s_yy[g][lane] = yy;
     __syncthreads();
-    if (threadIdx.x < kW) {
+    if ((int)threadIdx.x < W) {
         double t = 0.0;
         for (int q = 0; q < GPB; ++q) t += s_yy[q][threadIdx.x];
-        partial[(size_t)blockIdx.x * kW + threadIdx.x] = t;
+        partial[(size_t)blockIdx.x * W + threadIdx.x] = t;
     }
 }
 
