@@ -143,11 +143,13 @@ typedef struct {
                                  pattern is not symmetric and small inputs are built on the
                                  host).  The hierarchy is bitwise the host-built one: the
                                  matching is the greedy matching under the same strict order,
-                                 computed as locally dominant edges in parallel rounds (Sec.
-                                 3.1, eq. (approximatematch)), and every Galerkin entry sums its
+                                 computed by concurrent proposals along every vertex's ordered
+                                 list (Sec. 3.1, eq. (approximatematch)), and every Galerkin entry sums its
                                  terms in the same order.  Default 1 (0: host only). */
     int32_t device_min_rows;  /* device_setup: levels with at most this many rows (or max_dense or
-                                 max_coarse, if larger) are built on the host (0: 65536) */
+                                 max_coarse, if larger) are built on the host (0: inputs with at
+                                 most 8192 rows, and levels with at most 1024 below a larger
+                                 input; or max_coarse, if larger) */
     int32_t reserved[2];
 } pamg_params;
 

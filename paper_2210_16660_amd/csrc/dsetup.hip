@@ -1,12 +1,11 @@
 // Device construction of the large levels of the AMG hierarchy (arXiv
 // 2210.16660, Sec. 3.1), bitwise the host construction (setup.cpp):
 //   * l1 diagonal, edge weights of eq. (weights) and the eligibility c > 1;
-//   * the matching: locally dominant edges in parallel rounds (every alive
-//     vertex points at its heaviest eligible unmatched neighbour under the
-//     strict order (c desc, lo asc, hi asc); mutual pointers are matched; a
-//     vertex without such a neighbour stays single).  For a strict total order
-//     on the edges this is the greedy matching, the one the host's Suitor
-//     algorithm computes and eq. (approximatematch) approximates;
+//   * the matching: concurrent proposals along every vertex's eligible
+//     neighbours under the strict order (c desc, lo asc, hi asc), a better
+//     proposal displacing a worse one (the Suitor algorithm, as on the host).
+//     For a strict total order on the edges this is the greedy matching, which
+//     eq. (approximatematch) approximates;
 //   * aggregates numbered by smallest member and the tentative prolongator of
 //     eq. (prolongator);
 //   * the Galerkin product with every coarse entry summed in the canonical
@@ -16,9 +15,9 @@
 //     over the s pairwise steps (p multiplied finest first);
 //   * the hierarchical numbering, the permuted rows (columns ascending), the
 //     column-scaled values and the tiles' column dictionaries.
-// A level is built here while it is large (more rows than the dense limit,
-// the coarsening limit and a size floor) and its rows are short (at most
-// kRowCap entries); the first level that is not, and every coarser one, is
+// A level is built here while it has more rows than a size floor (and the
+// coarsening limit) and short rows (at most kRowCap entries); the first level
+// that is not, that reduces too little or has no pair, and every coarser one, is
 // built on the host from that level's matrix and near-null vector.
 //
 // Compiled with -ffp-contract=off: each written floating-point operation is
@@ -225,12 +224,6 @@ __device__ inline double edge_weight(double a_lohi, double a_lolo, double a_hihi
     return 1.0 - num / den;
 }
 
-__device__ inline bool heavier(double c1, int lo1, int hi1, double c2, int lo2, int hi2) {
-    if (c1 != c2) return c1 > c2;
-    if (lo1 != lo2) return lo1 < lo2;
-    return hi1 < hi2;
-}
-
 __device__ inline int find_col(const int* ci, int b, int e, int col) {
     while (b < e) {
         const int m = (b + e) >> 1;
@@ -242,22 +235,25 @@ __device__ inline int find_col(const int* ci, int b, int e, int col) {
 // Weight of every off-diagonal entry from the upper entry (lo, hi) of its
 // edge (both directions carry the same value); 0 on the diagonal.  Flags an
 // entry whose transposed entry is not stored (the device matching scans rows,
-// so the pattern must be symmetric).
+// so the pattern must be symmetric); tr: the transposed entry's position.
 __global__ void k_weights(int n, const int* rp, const int* ci, const double* v, const double* diag, const double* w,
-                          double* c, int* asym) {
+                          double* c, int* tr, int* asym) {
     GRID_STRIDE(i, n) {
         for (int k = rp[i]; k < rp[i + 1]; ++k) {
             const int j = ci[k];
             if (j == (int)i) {
                 c[k] = 0.0;
+                tr[k] = k;
                 continue;
             }
             const int t = find_col(ci, rp[j], rp[j + 1], (int)i);
             if (t >= rp[j + 1] || ci[t] != (int)i) {
                 atomicOr(asym, 1);
                 c[k] = 0.0;
+                tr[k] = k;
                 continue;
             }
+            tr[k] = t;
             const int lo = min((int)i, j), hi = max((int)i, j);
             const double a = j > (int)i ? v[k] : v[t];
             c[k] = edge_weight(a, diag[lo], diag[hi], w[lo], w[hi]);
@@ -284,21 +280,20 @@ __device__ inline void lds_bitonic(K* key, int P) {
         }
 }
 
-constexpr unsigned char kAlive = 0, kMatched = 1, kSingle = 2;
-
 // A neighbour of vertex i in the matching order: heavier first; for equal
 // weights the edge with the smaller (lo, hi) first, which for a fixed i is
 // the smaller neighbour index.  x > y: x comes after y.
 struct Nbr {
     double c;
-    int j;
+    int j, t;               // t: the entry's place in its row
     __device__ bool operator>(const Nbr& y) const { return c < y.c || (c == y.c && j > y.j); }
 };
 
 // Every vertex's eligible neighbours (c > 1) in the matching order, at its
-// row's positions in adj; their number in ecnt.  One wavefront per row.
+// row's positions in adj; their number in ecnt; pos: an eligible entry's place
+// in adj, -1 for the others.  One wavefront per row.
 __global__ __launch_bounds__(64) void k_sort_adj(int n, const int* rp, const int* ci, const double* c, int* adj,
-                                                 int* ecnt) {
+                                                 int* pos, int* ecnt) {
     __shared__ Nbr key[kRowCap];
     const int lane = threadIdx.x;
     for (int i = blockIdx.x; i < n; i += gridDim.x) {
@@ -307,13 +302,15 @@ __global__ __launch_bounds__(64) void k_sort_adj(int n, const int* rp, const int
         while (P < len) P <<= 1;
         int cnt = 0;
         for (int t = lane; t < P; t += 64) {
-            Nbr x{-1.0, INT_MAX};
+            Nbr x{-1.0, INT_MAX, 0};
             if (t < len) {
                 const int j = ci[b + t];
                 const double cc = c[b + t];
                 if (j != i && cc > 1.0) {
-                    x = Nbr{cc, j};
+                    x = Nbr{cc, j, t};
                     ++cnt;
+                } else {
+                    pos[b + t] = -1;
                 }
             }
             key[t] = x;
@@ -321,61 +318,72 @@ __global__ __launch_bounds__(64) void k_sort_adj(int n, const int* rp, const int
         for (int off = 32; off > 0; off >>= 1) cnt += __shfl_xor(cnt, off);
         __syncthreads();
         lds_bitonic(key, P);
-        for (int t = lane; t < cnt; t += 64) adj[b + t] = key[t].j;
+        for (int t = lane; t < cnt; t += 64) {
+            adj[b + t] = key[t].j;
+            pos[b + key[t].t] = b + t;
+        }
         if (lane == 0) ecnt[i] = cnt;
         __syncthreads();
     }
 }
 
-// One round, first half: every alive vertex picks its heaviest eligible
-// neighbour that is not matched (the first unmatched one in its sorted list;
-// matched vertices stay matched, so the cursor only moves forward); none
-// left: it stays single.
-__global__ void k_pick(int n, const int* rp, const int* ecnt, const int* adj, const int* mate, unsigned char* state,
-                       int* cur, int* cand) {
+// mirror[e]: the place of edge e of adj in its other endpoint's list (both
+// directions of an edge carry the same weight, so both lists hold it).
+__global__ void k_mirror(long long nnz, const int* pos, const int* tr, int* mirror) {
+    GRID_STRIDE(k, nnz) {
+        const int e = pos[k];
+        if (e >= 0) mirror[e] = pos[tr[k]];
+    }
+}
+
+// The matching by proposals: a vertex proposes along its list, heaviest edge
+// first, to the first neighbour whose best proposal so far is lighter; a
+// vertex whose proposal is displaced goes on from its place in its own list.
+// The edges are totally ordered, so the outcome is the one matching in which
+// every unmatched edge has a heavier matched neighbour, whatever the order of
+// the proposals: bitwise the host's.  best[j] is the place, in j's own list, of
+// the edge over which j's best proposal came (smaller is heavier), so that one
+// atomic minimum is the whole proposal, and the displaced vertex and its place
+// follow from the value it returns through adj and mirror, which do not change:
+// nothing else is shared and no thread waits for another.  A plain look at best
+// first: its values only fall, so an old one rejects nothing wrongly.  Every
+// pass moves one vertex's place forward, so the proposals end.
+// Bound by the longest chain of displacements (dependent trips to memory);
+// rounds of mutual picks before, three launches each, took 89 rounds a level
+// and 7.5 of the 17 ms of kernels of a 64^3 trilinear setup.
+constexpr unsigned kNoProposal = 0xffffffffu;
+__global__ __launch_bounds__(kSB) void k_propose(int n, const int* __restrict__ rp, const int* __restrict__ ecnt,
+                                                 const int* __restrict__ adj, const int* __restrict__ mirror,
+                                                 unsigned* best) {
     GRID_STRIDE(i, n) {
-        if (state[i] != kAlive) continue;
-        int q = cur[i];
-        const int e = rp[i] + ecnt[i];
-        while (q < e && mate[adj[q]] >= 0) ++q;
-        cur[i] = q;
-        if (q < e) {
-            cand[i] = adj[q];
-        } else {
-            cand[i] = -1;
-            state[i] = kSingle;
+        int u = (int)i, at = rp[i];
+        for (;;) {
+            const int end = rp[u] + ecnt[u];
+            unsigned old = kNoProposal;
+            for (; at < end; ++at) {
+                const int j = adj[at];
+                const unsigned m = (unsigned)mirror[at];
+                if (__hip_atomic_load(best + j, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT) < m) continue;
+                old = atomicMin(best + j, m);
+                if (m < old) break;
+                old = kNoProposal;
+            }
+            if (old == kNoProposal) break;      // accepted by a free vertex, or the list is through
+            u = adj[old];
+            at = mirror[old] + 1;
         }
     }
 }
 
-__global__ void k_cursor(int n, const int* rp, int* cur) { GRID_STRIDE(i, n) cur[i] = rp[i]; }
-
-// Second half: mutual picks are matched.  flag[0] = 1 if a vertex is still
-// alive after the round, flag[1] = 1 if a vertex was matched (plain stores of
-// 1, one per workgroup that has one; the caller clears them).
-constexpr int kCommitGrid = 2048;
-__global__ __launch_bounds__(kSB) void k_commit(int n, const int* cand, int* mate, unsigned char* state, int* flag) {
-    __shared__ int any[2];
-    if (threadIdx.x < 2) any[threadIdx.x] = 0;
-    __syncthreads();
-    bool alive = false, matched = false;
+// mate[i]: the vertex whose proposal i holds, if that one holds i's.
+__global__ void k_mates(int n, const int* adj, const unsigned* best, int* mate) {
     GRID_STRIDE(i, n) {
-        if (state[i] != kAlive) continue;
-        const int j = cand[i];
-        if (cand[j] == (int)i) {
-            mate[i] = j;
-            state[i] = kMatched;
-            matched = true;
-        } else {
-            alive = true;
+        int m = -1;
+        if (best[i] != kNoProposal) {
+            const int u = adj[best[i]];
+            if (best[u] != kNoProposal && adj[best[u]] == (int)i) m = u;
         }
-    }
-    if (alive) any[0] = 1;
-    if (matched) any[1] = 1;
-    __syncthreads();
-    if (threadIdx.x == 0) {
-        if (any[0]) flag[0] = 1;
-        if (any[1]) flag[1] = 1;
+        mate[i] = m;
     }
 }
 
@@ -836,16 +844,17 @@ enum Coarsened { kCoarsened, kNoPairs, kAsymmetric };
 // next level's matrix and near-null vector.  kNoPairs: the level is left to
 // the host; kAsymmetric: the pattern is not symmetric (only the input level
 // can be), the whole build is left to the host.
-Coarsened coarsen(Temps& T, CanLevel& L, CanLevel& C, hipStream_t s) {
+Coarsened coarsen(Temps& T, CanLevel& L, CanLevel& C, const pamg_params& prm, hipStream_t s) {
     const int n = L.n;
     double* diag = T.get<double>(n);
     double* c = T.get<double>(L.nnz);
+    int* tr = T.get<int>(L.nnz);
     int* flag = T.get<int>(4);
     HIP_CHECK(hipMemsetAsync(flag, 0, 4 * sizeof(int), s));
     hipLaunchKernelGGL(k_l1diag, dim3(grid_for(n, kSB)), dim3(kSB), 0, s, n, (const int*)L.rp, (const int*)L.ci,
                        (const double*)L.v, L.dinv, diag, flag + 2);
     hipLaunchKernelGGL(k_weights, dim3(grid_for(n, kSB)), dim3(kSB), 0, s, n, (const int*)L.rp, (const int*)L.ci,
-                       (const double*)L.v, (const double*)diag, (const double*)L.w, c, flag);
+                       (const double*)L.v, (const double*)diag, (const double*)L.w, c, tr, flag);
     int head[3];
     HIP_CHECK(hipMemcpyAsync(head, flag, 3 * sizeof(int), hipMemcpyDeviceToHost, s));
     HIP_CHECK(hipStreamSynchronize(s));
@@ -853,42 +862,27 @@ Coarsened coarsen(Temps& T, CanLevel& L, CanLevel& C, hipStream_t s) {
     T.release(diag);
     // eligible neighbours in the matching order
     int* adj = T.get<int>(L.nnz);
+    int* pos = T.get<int>(L.nnz);
     int* ecnt = T.get<int>(n);
     hipLaunchKernelGGL(k_sort_adj, dim3(grid_rows(n)), dim3(64), 0, s, n, (const int*)L.rp, (const int*)L.ci,
-                       (const double*)c, adj, ecnt);
+                       (const double*)c, adj, pos, ecnt);
     T.release(c);
-    // matching rounds, kRoundsPerCheck between looks at the counters (a
-    // round with nothing alive changes nothing); every round with an alive
-    // vertex matches at least the heaviest picked edge
-    constexpr int kRoundsPerCheck = 8;
+    int* mirror = T.get<int>(L.nnz);
+    unsigned* best = T.get<unsigned>(n);
     int* mate = T.get<int>(n);
-    int* cand = T.get<int>(n);
-    int* cur = T.get<int>(n);
-    unsigned char* state = T.get<unsigned char>(n);
-    HIP_CHECK(hipMemsetAsync(mate, 0xff, sizeof(int) * n, s));
-    HIP_CHECK(hipMemsetAsync(state, 0, n, s));
-    hipLaunchKernelGGL(k_cursor, dim3(grid_for(n, kSB)), dim3(kSB), 0, s, n, (const int*)L.rp, cur);
-    int* cnt = flag + 2;
-    const int gc = std::min(grid_for(n, kSB), kCommitGrid);
-    for (long long round = 0;; round += kRoundsPerCheck) {
-        HIP_CHECK(hipMemsetAsync(cnt, 0, 2 * sizeof(int), s));
-        for (int r = 0; r < kRoundsPerCheck; ++r) {
-            HIP_CHECK(hipMemsetAsync(cnt, 0, sizeof(int), s));
-            hipLaunchKernelGGL(k_pick, dim3(grid_for(n, kSB)), dim3(kSB), 0, s, n, (const int*)L.rp,
-                               (const int*)ecnt, (const int*)adj, (const int*)mate, state, cur, cand);
-            hipLaunchKernelGGL(k_commit, dim3(gc), dim3(kSB), 0, s, n, (const int*)cand, mate, state, cnt);
-        }
-        int rc[2];
-        HIP_CHECK(hipMemcpyAsync(rc, cnt, 2 * sizeof(int), hipMemcpyDeviceToHost, s));
-        HIP_CHECK(hipStreamSynchronize(s));
-        if (rc[0] == 0) break;
-        if (rc[1] == 0 || round > n) throw Error(PAMG_E_DEVICE, "device matching made no progress");
-    }
+    HIP_CHECK(hipMemsetAsync(best, 0xff, sizeof(unsigned) * n, s));
+    hipLaunchKernelGGL(k_mirror, dim3(grid_for(L.nnz, kSB)), dim3(kSB), 0, s, L.nnz, (const int*)pos, (const int*)tr,
+                       mirror);
+    hipLaunchKernelGGL(k_propose, dim3(grid_for(n, kSB)), dim3(kSB), 0, s, n, (const int*)L.rp, (const int*)ecnt,
+                       (const int*)adj, (const int*)mirror, best);
+    hipLaunchKernelGGL(k_mates, dim3(grid_for(n, kSB)), dim3(kSB), 0, s, n, (const int*)adj, (const unsigned*)best,
+                       mate);
     T.release(adj);
+    T.release(pos);
+    T.release(tr);
+    T.release(mirror);
     T.release(ecnt);
-    T.release(cur);
-    T.release(cand);
-    T.release(state);
+    T.release(best);
     // aggregates
     int* lead = T.get<int>(n);
     int* size = T.get<int>(n);
@@ -901,7 +895,8 @@ Coarsened coarsen(Temps& T, CanLevel& L, CanLevel& C, hipStream_t s) {
     T.release(size);
     L.nc = (int)nc;
     L.pairs = (int)(n - nc);
-    if (L.pairs == 0) {
+    // (too little reduction on a level the dense solve can take: coarsest)
+    if (L.pairs == 0 || (n <= prm.max_dense && (double)n < prm.min_ratio * (double)nc)) {
         T.release(mate);
         T.release(aid);
         T.release(msz);
@@ -1054,9 +1049,11 @@ std::unique_ptr<DeviceBuild> device_build(pamg_hierarchy* h, const pamg_csr& A, 
                                           hipStream_t s) {
     std::unique_ptr<DeviceBuild> out(new DeviceBuild());
     Temps T{h->ctx, s, {}};
-    const int floor_rows = prm.device_min_rows > 0 ? prm.device_min_rows : kDeviceMinRows;
-    const int limit = std::max({floor_rows, prm.max_dense, prm.max_coarse});
+    const int given = std::max({prm.device_min_rows, prm.max_dense, prm.max_coarse});
+    const int first = prm.device_min_rows > 0 ? given : std::max(kDeviceMinRows, prm.max_coarse);
+    const int rest = prm.device_min_rows > 0 ? given : std::max(kDeviceStopRows, prm.max_coarse);
     auto dev_level = [&](const CanLevel& L, int l) {
+        const int limit = l == 0 ? first : rest;
         return L.n > limit && l + 1 < prm.max_levels && L.maxrow <= kRowCap;
     };
     // level 0: the input matrix (its header checked by the caller), w = 1
@@ -1099,7 +1096,7 @@ std::unique_ptr<DeviceBuild> device_build(pamg_hierarchy* h, const pamg_csr& A, 
         CanLevel& L = lev[built];
         L.dinv = T.get<double>(L.n);
         CanLevel C;
-        const Coarsened r = coarsen(T, L, C, s);
+        const Coarsened r = coarsen(T, L, C, prm, s);
         if (r == kAsymmetric) return nullptr;
         if (r == kNoPairs) break;          // the host takes this level
         lev.push_back(C);
