@@ -145,12 +145,20 @@ static void launch_down_b(const DevLevelIdx& I, int v, int lw, const T* vd, cons
     with_variant_at(v, lw, [&](auto u, auto c, int rows) {
         constexpr int U = decltype(u)::value, CPL = decltype(c)::value;
         const int grid = unit_grid(I.nc, rows);
-        if (r_is_f64)
-            hipLaunchKernelGGL((kb_down<U, CPL, T, double>), dim3(grid), dim3(kBlock), 0, s, I.nc, lw, I.row_idx(),
-                               (const int*)I.ci, vd, (const double*)r, p, (const int*)I.aggptr, rc, done);
+        const bool pair = I.sell && I.nnz >= kPairRow * (long long)I.n;
+        auto go = [&](auto two, auto rt) {
+            using RT = decltype(rt);
+            hipLaunchKernelGGL((kb_down<U, CPL, decltype(two)::value, T, RT>), dim3(grid), dim3(kBlock), 0, s, I.nc, lw,
+                               I.row_idx(), (const int*)I.ci, vd, (const RT*)r, p, (const int*)I.aggptr, rc, done);
+        };
+        if (pair && r_is_f64)
+            go(std::true_type{}, double{});
+        else if (pair)
+            go(std::true_type{}, T{});
+        else if (r_is_f64)
+            go(std::false_type{}, double{});
         else
-            hipLaunchKernelGGL((kb_down<U, CPL, T, T>), dim3(grid), dim3(kBlock), 0, s, I.nc, lw, I.row_idx(),
-                               (const int*)I.ci, vd, (const T*)r, p, (const int*)I.aggptr, rc, done);
+            go(std::false_type{}, T{});
     });
 }
 
@@ -295,25 +303,32 @@ static void enqueue_block_b(BatchEngine* E, DevVals<T>& V, int krylov, int k, hi
 // ---------------------------------------------------------------- autotuner
 
 template <typename F>
-static float time_variant(F&& launch, hipStream_t s) {
+static float time_variant(F&& launch, int reps, hipStream_t s) {
     hipEvent_t e0, e1;
     HIP_CHECK(hipEventCreate(&e0));
     HIP_CHECK(hipEventCreate(&e1));
     launch();
     HIP_CHECK(hipEventRecord(e0, s));
-    for (int i = 0; i < 3; ++i) launch();
+    for (int i = 0; i < reps; ++i) launch();
     HIP_CHECK(hipEventRecord(e1, s));
     HIP_CHECK(hipEventSynchronize(e1));
     float ms = 0;
     HIP_CHECK(hipEventElapsedTime(&ms, e0, e1));
     (void)hipEventDestroy(e0);
     (void)hipEventDestroy(e1);
-    return ms;
+    return ms / reps;
 }
 
 // Pick, per level, the fastest down-sweep and up-sweep variant (unroll depth
 // x columns per lane) by timing each on the real level.  The variants do not
-// change any column's arithmetic, only how it is scheduled.
+// change any column's arithmetic, only how it is scheduled.  A launch on a level
+// of at most kTuneFewRows rows takes 6 to 20 us, within what three launches from
+// the host vary by (a choice of 13.7 us where the best took 9.8): there the five
+// variants that can win (unroll 4 or 8, and few columns per lane to fill the
+// chip) are timed over twelve launches each, as many launches as before.
+constexpr int kTuneFewRows = 32768;
+static bool tune_few(int v) { return v == 2 || v == 3 || v == 7 || v == 8 || v == 12; }
+
 template <typename T>
 static void autotune(BatchEngine* E, DevVals<T>& V, hipStream_t s) {
     pamg_hierarchy* h = E->h;
@@ -325,20 +340,24 @@ static void autotune(BatchEngine* E, DevVals<T>& V, hipStream_t s) {
     const void* r0 = L > 0 ? level0_rhs<T>(E, nodone, s) : E->R;
     for (int l = 0; l < L; ++l) {
         const DevLevelIdx& I = h->idx[l];
+        const bool few = I.n <= kTuneFewRows;
+        const int reps = few ? 12 : 3;
         float best = 1e30f;
         for (int v = 0; v < kNumVariants; ++v) {
+            if (few && !tune_few(v)) continue;
             const float t = time_variant([&]() {
                 if (l == 0)
                     launch_down_b<T>(I, v, 4, V.vd[0], r0, r0_f64, V.p[0], (T*)E->r[1], nodone, s);
                 else
                     launch_down_b<T>(I, v, 4, V.vd[l], E->r[l], false, V.p[l], (T*)E->r[l + 1], nodone, s);
-            }, s);
+            }, reps, s);
             if (t < best) { best = t; E->cfg_down[l] = v; }
         }
         if (l == 0) continue;
         const DevLevelIdx& Fi = h->idx[l - 1];
         best = 1e30f;
         for (int v = 0; v < kNumVariants; ++v) {
+            if (few && !tune_few(v)) continue;
             const float t = time_variant([&]() {
                 if (l - 1 == 0)
                     launch_up_b<T>(I, Fi, v, 4, V.v[l], (const T*)E->zp[l], (const T*)E->r[l], V.dinv[l], r0, r0_f64,
@@ -346,7 +365,7 @@ static void autotune(BatchEngine* E, DevVals<T>& V, hipStream_t s) {
                 else
                     launch_up_b<T>(I, Fi, v, 4, V.v[l], (const T*)E->zp[l], (const T*)E->r[l], V.dinv[l], E->r[l - 1],
                                    false, V.dinv[l - 1], V.p[l - 1], (T*)E->zp[l - 1], nodone, s);
-            }, s);
+            }, reps, s);
             if (t < best) { best = t; E->cfg_up[l] = v; }
         }
     }

@@ -122,43 +122,114 @@ inline int unit_grid(long long nunits, int gpb) {
     return g < 1 ? 1 : (int)g;
 }
 
-// s[q] += sum over row i's entries, in entry order, of a_k x[c_k][col0 + q].
-// (The lanes of a group load the same index and value; plain loads keep the
-// line in L2 for the group's next entries: non-temporal loads made the
-// 16-column engine 1.6x slower.)
+// s[q] += the next U entries of a row, in entry order, of a_k x[c_k][col0 + q],
+// all their loads in flight together; TAIL: only the first rem of them (the
+// others repeat the last one's loads and are left out of the sum).
+template <int U, bool TAIL, int CPL, typename T, typename XT>
+__device__ __forceinline__ void entries_accumulate(int o, int st, int rem, const int* __restrict__ ci,
+                                                   const T* __restrict__ av, const XT* __restrict__ x, int lw,
+                                                   int col0, T (&s)[CPL]) {
+    int c[U];
+    T a[U];
+#pragma unroll
+    for (int u = 0; u < U; ++u) c[u] = ci[o + (TAIL ? min(u, rem - 1) : u) * st];
+#pragma unroll
+    for (int u = 0; u < U; ++u) a[u] = av[o + (TAIL ? min(u, rem - 1) : u) * st];
+    Vec<XT, CPL> xv[U];
+#pragma unroll
+    for (int u = 0; u < U; ++u) xv[u] = vload<XT, CPL>(x + ((size_t)c[u] << lw) + col0);
+#pragma unroll
+    for (int u = 0; u < U; ++u)
+#pragma unroll
+        for (int q = 0; q < CPL; ++q) {
+            const T t = s[q] + a[u] * (T)xv[u].v[q];
+            s[q] = !TAIL || u < rem ? t : s[q];
+        }
+}
+
+// The last rem < U entries of a row, one trip to memory for the columns and one
+// for the values: the smallest power of two of loads that holds them.  (One
+// entry after the other before: rows of 7 at unroll 8 were a chain of 7 trips;
+// the Krylov pass over 227 thousand such rows, FP64, 8 columns, 28.7 us, now
+// 20.6, level 0's up-sweep 20.0 and 15.4.)
+template <int U, int CPL, typename T, typename XT>
+__device__ __forceinline__ void tail_accumulate(int o, int st, int rem, const int* __restrict__ ci,
+                                                const T* __restrict__ av, const XT* __restrict__ x, int lw, int col0,
+                                                T (&s)[CPL]) {
+    if constexpr (U == 1) {
+        if (rem > 0) entries_accumulate<1, false, CPL, T, XT>(o, st, 1, ci, av, x, lw, col0, s);
+    } else {
+        if (rem > U / 2)
+            entries_accumulate<U, true, CPL, T, XT>(o, st, rem, ci, av, x, lw, col0, s);
+        else
+            tail_accumulate<U / 2, CPL, T, XT>(o, st, rem, ci, av, x, lw, col0, s);
+    }
+}
+
+// s[q] += sum over row i's entries, in entry order, of a_k x[c_k][col0 + q], U
+// entries at a time.  (The lanes of a group load the same index and value;
+// plain loads keep the line in L2 for the group's next entries: non-temporal
+// loads made the 16-column engine 1.6x slower.)
 template <int U, int CPL, typename T, typename XT>
 __device__ __forceinline__ void row_accumulate(const RowIdx& R, int i, const int* __restrict__ ci,
                                                const T* __restrict__ av, const XT* __restrict__ x, int lw, int col0,
                                                T (&s)[CPL]) {
     const int len = R.len(i), st = R.stride();
     int o = R.start(i), k = 0;
-    for (; k + U <= len; k += U, o += U * st) {
-        int c[U];
-        T a[U];
+    for (; k + U <= len; k += U, o += U * st) entries_accumulate<U, false, CPL, T, XT>(o, st, U, ci, av, x, lw, col0, s);
+    tail_accumulate<U, CPL, T, XT>(o, st, len - k, ci, av, x, lw, col0, s);
+}
+
+// Two rows at once (i and the next one): s0 and s1 as row_accumulate computes
+// them, H entries of each in flight together.  For long sliced rows: entry k of
+// two neighbouring rows shares a line of columns and of values, and the rows of
+// an aggregate share most of the lines they gather, which then are still in L1
+// (128^3 trilinear, 16 columns, level 0: FP32 403 us one row after the other,
+// 326 in pairs, FP64 639 and 596; level 1: 222 and 191, 387 and 345).  Short
+// rows share little (1.33 million rows of 7, FP64: 140 and 151), and with a
+// row's entries contiguous a pair only widens the spread of the loads (550
+// thousand rows, FP32: 100 and 120; 227 thousand rows of 7, FP64: 21 and 27).
+constexpr int kPairRow = 16;                            // mean entries per row
+template <int H, int CPL, typename T, typename XT>
+__device__ __forceinline__ void row_pair_accumulate(const RowIdx& R, int i, const int* __restrict__ ci,
+                                                    const T* __restrict__ av, const XT* __restrict__ x, int lw,
+                                                    int col0, T (&s0)[CPL], T (&s1)[CPL]) {
+    const int len0 = R.len(i), len1 = R.len(i + 1), st = R.stride();
+    const int o0 = R.start(i), o1 = R.start(i + 1);
+    const int most = max(len0, len1);
+    for (int k = 0; k < most; k += H) {
+        int c0[H], c1[H];
+        T a0[H], a1[H];
 #pragma unroll
-        for (int u = 0; u < U; ++u) c[u] = ci[o + u * st];
+        for (int u = 0; u < H; ++u) {
+            const int k0 = min(k + u, len0 - 1), k1 = min(k + u, len1 - 1);
+            c0[u] = ci[o0 + k0 * st];
+            c1[u] = ci[o1 + k1 * st];
+            a0[u] = av[o0 + k0 * st];
+            a1[u] = av[o1 + k1 * st];
+        }
+        Vec<XT, CPL> x0[H], x1[H];
 #pragma unroll
-        for (int u = 0; u < U; ++u) a[u] = av[o + u * st];
-        Vec<XT, CPL> xv[U];
+        for (int u = 0; u < H; ++u) {
+            x0[u] = vload<XT, CPL>(x + ((size_t)c0[u] << lw) + col0);
+            x1[u] = vload<XT, CPL>(x + ((size_t)c1[u] << lw) + col0);
+        }
 #pragma unroll
-        for (int u = 0; u < U; ++u) xv[u] = vload<XT, CPL>(x + ((size_t)c[u] << lw) + col0);
+        for (int u = 0; u < H; ++u)
 #pragma unroll
-        for (int u = 0; u < U; ++u)
-#pragma unroll
-            for (int q = 0; q < CPL; ++q) s[q] += a[u] * (T)xv[u].v[q];
-    }
-    for (; k < len; ++k, o += st) {
-        const Vec<XT, CPL> xv = vload<XT, CPL>(x + ((size_t)ci[o] << lw) + col0);
-        const T a = av[o];
-#pragma unroll
-        for (int q = 0; q < CPL; ++q) s[q] += a * (T)xv.v[q];
+            for (int q = 0; q < CPL; ++q) {
+                const T t0 = s0[q] + a0[u] * (T)x0[u].v[q], t1 = s1[q] + a1[u] * (T)x1[u].v[q];
+                s0[q] = k + u < len0 ? t0 : s0[q];
+                s1[q] = k + u < len1 ? t1 : s1[q];
+            }
     }
 }
 
 // ---------------------------------------------------------------- V-cycle
 
 // Down-sweep: rc[I] = sum_{m in G_I} p_m (r_m - (A D^-1 r)_m), per column.
-template <int U, int CPL, typename T, typename RT>
+// PAIR: two members at a time (row_pair_accumulate).
+template <int U, int CPL, bool PAIR, typename T, typename RT>
 static __global__ __launch_bounds__(kBlock) void kb_down(int nc, int lw, RowIdx rows, const int* __restrict__ ci,
                                                   const T* __restrict__ vd, const RT* __restrict__ r,
                                                   const T* __restrict__ p, const int* __restrict__ aggptr,
@@ -172,7 +243,22 @@ static __global__ __launch_bounds__(kBlock) void kb_down(int nc, int lw, RowIdx 
         T acc[CPL];
 #pragma unroll
         for (int q = 0; q < CPL; ++q) acc[q] = 0;
-        for (int m = m0; m < m1; ++m) {
+        int m = m0;
+        if constexpr (PAIR && U > 1)
+            for (; m + 1 < m1; m += 2) {
+                T s0[CPL], s1[CPL];
+#pragma unroll
+                for (int q = 0; q < CPL; ++q) s0[q] = s1[q] = 0;
+                const Vec<RT, CPL> rm0 = vload<RT, CPL>(r + ((size_t)m << lw) + col0);
+                const Vec<RT, CPL> rm1 = vload<RT, CPL>(r + ((size_t)(m + 1) << lw) + col0);
+                const T p0 = p[m], p1 = p[m + 1];
+                row_pair_accumulate<U / 2, CPL, T, RT>(rows, m, ci, vd, r, lw, col0, s0, s1);
+#pragma unroll
+                for (int q = 0; q < CPL; ++q) acc[q] += p0 * ((T)rm0.v[q] - s0[q]);
+#pragma unroll
+                for (int q = 0; q < CPL; ++q) acc[q] += p1 * ((T)rm1.v[q] - s1[q]);
+            }
+        for (; m < m1; ++m) {
             T s[CPL];
 #pragma unroll
             for (int q = 0; q < CPL; ++q) s[q] = 0;
