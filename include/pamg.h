@@ -148,7 +148,7 @@ typedef struct {
                                  terms in the same order.  Default 1 (0: host only). */
     int32_t device_min_rows;  /* device_setup: levels with at most this many rows (or max_dense or
                                  max_coarse, if larger) are built on the host (0: inputs with at
-                                 most 8192 rows, and levels with at most 1024 below a larger
+                                 most 8192 rows, and levels with at most 256 below a larger
                                  input; or max_coarse, if larger) */
     int32_t reserved[2];
 } pamg_params;

@@ -52,7 +52,7 @@ inline int grid_for(long long n, int per) {
 struct Temps {
     pamg_context* ctx;
     hipStream_t s;
-    std::vector<DevAlloc> list;
+    std::vector<DevAlloc> list, pending;
     template <typename T>
     T* get(size_t count) {
         const size_t bytes = std::max<size_t>(1, count) * sizeof(T);
@@ -60,17 +60,30 @@ struct Temps {
         list.push_back({p, bytes});
         return static_cast<T*>(p);
     }
+    // Given back at the next drain(): the kernels launched so far may still use
+    // it.  (A wait of its own for each left the device idle for a launch's
+    // latency, about 250 times in a setup of nine levels.)  What is pending in
+    // coarsen() is below what the layout of the level takes later, and large
+    // arrays there are given back at once, so the peak is the same.
     void release(void* p) {
         for (size_t i = 0; i < list.size(); ++i)
             if (list[i].p == p) {
-                HIP_CHECK(hipStreamSynchronize(s));
-                ctx_free(ctx, p, list[i].bytes, s);
+                pending.push_back(list[i]);
                 list.erase(list.begin() + i);
                 return;
             }
     }
+    // The stream has been waited for since the last release.
+    void drain() { ctx_free_all(ctx, pending); }
+    void release_now(void* p, void* q) {
+        release(p);
+        release(q);
+        HIP_CHECK(hipStreamSynchronize(s));
+        drain();
+    }
     ~Temps() {
         (void)hipStreamSynchronize(s);
+        ctx_free_all(ctx, pending);
         ctx_free_all(ctx, list);
     }
 };
@@ -149,7 +162,9 @@ long long scan(Temps& T, long long n, const TIn* in, long long* out, hipStream_t
         T.release(off);
     }
     T.release(blk);
-    return read1(out + n, s);
+    const long long total = read1(out + n, s);
+    T.drain();
+    return total;
 }
 
 __global__ void k_to_int(long long n, const long long* in, int* out) { GRID_STRIDE(i, n) out[i] = (int)in[i]; }
@@ -157,6 +172,14 @@ __global__ void k_to_int(long long n, const long long* in, int* out) { GRID_STRI
 __global__ void k_fill_d(long long n, double* x, double v) { GRID_STRIDE(i, n) x[i] = v; }
 
 // ---------------------------------------------------------- level kernels
+
+// *m = max(*m, x).  Most callers find a value that is large enough and leave:
+// one atomic per wavefront on one address held the count pass of the Galerkin
+// product over 1.07 million coarse rows to 7.5 ms where the fill pass takes 1.8
+// (64^3 trilinear, both passes, all levels: 3.9 ms, now 1.4).
+__device__ inline void raise_max(int* m, int x) {
+    if (__hip_atomic_load(m, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT) < x) atomicMax(m, x);
+}
 
 // d_i = sum_j |a_ij| (ascending columns), a_ii, dinv = 1/d; the longest row.
 __global__ void k_l1diag(int n, const int* rp, const int* ci, const double* v, double* dinv, double* diag,
@@ -172,7 +195,7 @@ __global__ void k_l1diag(int n, const int* rp, const int* ci, const double* v, d
         diag[i] = dg;
         mx = max(mx, rp[i + 1] - rp[i]);
     }
-    atomicMax(maxrow, mx);
+    raise_max(maxrow, mx);
 }
 
 // validate_csr's row checks, one thread per row, in the same order (no
@@ -235,11 +258,18 @@ __device__ inline int find_col(const int* ci, int b, int e, int col) {
 // Weight of every off-diagonal entry from the upper entry (lo, hi) of its
 // edge (both directions carry the same value); 0 on the diagonal.  Flags an
 // entry whose transposed entry is not stored (the device matching scans rows,
-// so the pattern must be symmetric); tr: the transposed entry's position.
-__global__ void k_weights(int n, const int* rp, const int* ci, const double* v, const double* diag, const double* w,
-                          double* c, int* tr, int* asym) {
-    GRID_STRIDE(i, n) {
-        for (int k = rp[i]; k < rp[i + 1]; ++k) {
+// so the pattern must be symmetric); tr: the transposed entry's position.  A
+// search per entry: eight lanes share a row, so that the entries are read in
+// runs and a row's searches overlap (64^3 trilinear, all levels: a lane
+// per row 1.55 ms, now 0.41).
+constexpr int kWeightLanes = 8;
+__global__ __launch_bounds__(kSB) void k_weights(int n, const int* rp, const int* ci, const double* v,
+                                                 const double* diag, const double* w, double* c, int* tr, int* asym) {
+    const int lane = threadIdx.x % kWeightLanes;
+    const long long stride = (long long)gridDim.x * (kSB / kWeightLanes);
+    for (long long i = (long long)blockIdx.x * (kSB / kWeightLanes) + threadIdx.x / kWeightLanes; i < n; i += stride) {
+        const int e = rp[i + 1];
+        for (int k = rp[i] + lane; k < e; k += kWeightLanes) {
             const int j = ci[k];
             if (j == (int)i) {
                 c[k] = 0.0;
@@ -504,7 +534,7 @@ __global__ __launch_bounds__(64) void k_galerkin(int nc, const int* mem_ptr, con
         longest = max(longest, runs);
         __syncthreads();
     }
-    if (!FILL && lane == 0) atomicMax(bad + 1, longest);
+    if (!FILL && lane == 0) raise_max(bad + 1, longest);
 }
 
 // ------------------------------------------------------------ layout kernels
@@ -621,7 +651,7 @@ __global__ __launch_bounds__(kSB) void k_dict(int ntiles, const int4* tiles, con
         if (!FILL) {
             if (threadIdx.x == 0) {
                 dlen[t] = total;
-                atomicMax(maxlen, total);
+                raise_max(maxlen, total);
             }
         } else {
             for (int u = threadIdx.x; u < m; u += kSB) {
@@ -822,7 +852,7 @@ __global__ void k_sort_members(int nc, const long long* mptr, int* mem, int* mem
         if (I == nc - 1) mem_ptr[nc] = e;
         mx = max(mx, e - b);
     }
-    atomicMax(longest, mx);
+    raise_max(longest, mx);
 }
 
 // ------------------------------------------------------------------ driver
@@ -853,13 +883,14 @@ Coarsened coarsen(Temps& T, CanLevel& L, CanLevel& C, const pamg_params& prm, hi
     HIP_CHECK(hipMemsetAsync(flag, 0, 4 * sizeof(int), s));
     hipLaunchKernelGGL(k_l1diag, dim3(grid_for(n, kSB)), dim3(kSB), 0, s, n, (const int*)L.rp, (const int*)L.ci,
                        (const double*)L.v, L.dinv, diag, flag + 2);
-    hipLaunchKernelGGL(k_weights, dim3(grid_for(n, kSB)), dim3(kSB), 0, s, n, (const int*)L.rp, (const int*)L.ci,
+    hipLaunchKernelGGL(k_weights, dim3(grid_for(n, kSB / kWeightLanes)), dim3(kSB), 0, s, n, (const int*)L.rp, (const int*)L.ci,
                        (const double*)L.v, (const double*)diag, (const double*)L.w, c, tr, flag);
     int head[3];
     HIP_CHECK(hipMemcpyAsync(head, flag, 3 * sizeof(int), hipMemcpyDeviceToHost, s));
     HIP_CHECK(hipStreamSynchronize(s));
-    if (head[0]) return kAsymmetric;
     T.release(diag);
+    T.drain();
+    if (head[0]) return kAsymmetric;
     // eligible neighbours in the matching order
     int* adj = T.get<int>(L.nnz);
     int* pos = T.get<int>(L.nnz);
@@ -940,6 +971,7 @@ Coarsened coarsen(Temps& T, CanLevel& L, CanLevel& C, const pamg_params& prm, hi
     C.maxrow = head[1];
     T.release(ccnt);
     T.release(crp);
+    T.drain();
     return kCoarsened;
 }
 
@@ -1033,7 +1065,7 @@ void device_gs_schedule(pamg_hierarchy* h, DevLevelOut& D, int nb, hipStream_t s
     D.gs_df = dalloc<uint8_t>(h, n, s);
     D.gs_db = dalloc<uint8_t>(h, n, s);
     D.gs_maxd = dalloc<int>(h, 2 * (size_t)nblk, s);
-    Temps T{h->ctx, s, {}};
+    Temps T{h->ctx, s, {}, {}};
     int* bad = T.get<int>(1);
     HIP_CHECK(hipMemsetAsync(bad, 0, sizeof(int), s));
     const RowIdx R{D.rp, D.sell.rowpos};
@@ -1048,7 +1080,7 @@ void device_gs_schedule(pamg_hierarchy* h, DevLevelOut& D, int nb, hipStream_t s
 std::unique_ptr<DeviceBuild> device_build(pamg_hierarchy* h, const pamg_csr& A, const pamg_params& prm,
                                           hipStream_t s) {
     std::unique_ptr<DeviceBuild> out(new DeviceBuild());
-    Temps T{h->ctx, s, {}};
+    Temps T{h->ctx, s, {}, {}};
     const int given = std::max({prm.device_min_rows, prm.max_dense, prm.max_coarse});
     const int first = prm.device_min_rows > 0 ? given : std::max(kDeviceMinRows, prm.max_coarse);
     const int rest = prm.device_min_rows > 0 ? given : std::max(kDeviceStopRows, prm.max_coarse);
@@ -1169,6 +1201,16 @@ std::unique_ptr<DeviceBuild> device_build(pamg_hierarchy* h, const pamg_csr& A, 
         T.release(mptr);
         T.release(cagg);
     }
+    // canonical levels a .. b-1 have been laid out (or downloaded)
+    auto drop_levels = [&](int a, int b) {
+        for (int l = a; l < b; ++l) {
+            const CanLevel& L = lev[l];
+            void* const all[] = {L.rp, L.ci, L.v, L.w, L.dinv, L.p, L.agg, L.mem_ptr, L.mem};
+            for (void* p : all)
+                if (p) T.release(p);
+        }
+    };
+    drop_levels(m, (int)lev.size());
     // device layouts of the kept levels K-1 .. 0 (their arrays belong to the hierarchy)
     out->dev.resize(K);
     const int* cip = nullptr;   // hierarchical -> canonical of the coarser level
@@ -1221,6 +1263,7 @@ std::unique_ptr<DeviceBuild> device_build(pamg_hierarchy* h, const pamg_csr& A, 
         std::vector<int32_t> rp_h, ap_h;
         to_host(rp_h, D.rp, (size_t)n + 1, s);
         to_host(ap_h, D.aggptr, (size_t)nc + 1, s);
+        T.drain();
         for (int32_t c = 0; c < nc; ++c) D.max_agg = std::max(D.max_agg, ap_h[c + 1] - ap_h[c]);
         D.nent = L.nnz;
         if (sell) {
@@ -1283,8 +1326,7 @@ std::unique_ptr<DeviceBuild> device_build(pamg_hierarchy* h, const pamg_csr& A, 
                 HIP_CHECK(hipMemcpyAsync(D.ci, ci2, sizeof(int) * L.nnz, hipMemcpyDeviceToDevice, s));
                 HIP_CHECK(hipMemcpyAsync(D.v, v2, sizeof(double) * L.nnz, hipMemcpyDeviceToDevice, s));
             }
-            T.release(ci2);
-            T.release(v2);
+            T.release_now(ci2, v2);
         } else {
             D.ci = ci2;
             D.v = v2;
@@ -1295,6 +1337,7 @@ std::unique_ptr<DeviceBuild> device_build(pamg_hierarchy* h, const pamg_csr& A, 
         D.items = first_tile_items(L.nnz);
         if (sell) {
             cip = D.iperm;
+            drop_levels(kp[j], kp[j] + steps);
             continue;
         }
         // tiles (host partition of the row pointer) and dictionaries
@@ -1361,6 +1404,7 @@ std::unique_ptr<DeviceBuild> device_build(pamg_hierarchy* h, const pamg_csr& A, 
         to_device(D.down_tiles, down.data(), down.size(), s);
         D.n_down = (int)(down.size() / 4);
         cip = D.iperm;
+        drop_levels(kp[j], kp[j] + steps);
     }
     HIP_CHECK(hipStreamSynchronize(s));
     return out;

@@ -9,9 +9,10 @@ namespace pamg {
 // single level) is built on the host; below a larger one every level of more
 // than kDeviceStopRows rows (or max_coarse, if larger) is built on the device.
 // Whole setups with the stop at 65536 rows, 8192 and 1024: 64^3 trilinear 45.3,
-// 28.1 and 23.4 ms, 61^3 varying coefficients 42.2, 19.2 and 14.2; of an input
-// of 13,824 rows on the host 11.9 ms, on the device 6.7.
-constexpr int kDeviceMinRows = 8192, kDeviceStopRows = 1024;
+// 28.1 and 23.4 ms, 61^3 varying coefficients 42.2, 19.2 and 14.2; with the stop
+// at 1024 and 256 (after other changes) 30^3 trilinear 9.5 and 7.9, 40^3 Laplacian
+// 8.5 and 7.8.  An input of 13,824 rows: on the host 11.9 ms, on the device 5.4.
+constexpr int kDeviceMinRows = 8192, kDeviceStopRows = 256;
 
 // Column dictionaries of a level's tiles (TileDict on the device).
 struct DevDict {

@@ -43,7 +43,8 @@ def test_variants_sum_rows_alike(case, prec):
     make, kw, variants = CASES[case]
     A = make()
     H = pamg.Hierarchy(A, build_f32=1, **kw)
-    for nrhs in (16, 3):
+    full = None
+    for nrhs in (16, 3, 7):
         B = torch.from_numpy(np.stack([uniform_rhs(A.n, 80 + c) for c in range(nrhs)])).cuda()
         ref = None
         for v in variants:
@@ -54,3 +55,5 @@ def test_variants_sum_rows_alike(case, prec):
             if ref is None:
                 ref = X
             assert torch.equal(X.view(torch.int64), ref.view(torch.int64)), (v, nrhs)
+        full = ref if full is None else full
+        assert torch.equal(ref.view(torch.int64), full[:nrhs].view(torch.int64)), nrhs
