@@ -79,8 +79,8 @@ struct BatchEngine {
     double** dst_dev = nullptr;
     void** ptr_host = nullptr;                // pinned staging for the pointer tables (2 * kW)
     hipStream_t cap_stream = nullptr;
-    hipGraphExec_t graph[2] = {nullptr, nullptr};
-    int graph_k[2] = {0, 0}, graph_lw[2] = {0, 0};
+    hipGraphExec_t graph[2][3] = {};          // per recurrence and width (log2 less 2), with the iterations
+    int graph_k[2][3] = {};                   // it was captured for
     std::vector<int> cfg_down, cfg_up;        // variant per level
     std::vector<DevAlloc> allocs;             // from the hierarchy's context
     uint64_t bytes = 0;
@@ -89,8 +89,9 @@ struct BatchEngine {
 void destroy_batch(BatchEngine* E) {
     if (!E) return;
     (void)hipDeviceSynchronize();
-    for (auto& g : E->graph)
-        if (g) (void)hipGraphExecDestroy(g);
+    for (auto& row : E->graph)
+        for (auto& g : row)
+            if (g) (void)hipGraphExecDestroy(g);
     if (E->cap_stream) (void)hipStreamDestroy(E->cap_stream);
     if (E->h) ctx_free_all(E->h->ctx, E->allocs);
     if (E->st_host) (void)hipHostFree(E->st_host);
@@ -441,8 +442,9 @@ BatchEngine* get_engine(pamg_hierarchy* h, int prec, hipStream_t s) {
 }
 
 static hipGraphExec_t block_graph(BatchEngine* E, int krylov, int k) {
-    hipGraphExec_t& ex = E->graph[krylov];
-    if (ex && E->graph_k[krylov] == k && E->graph_lw[krylov] == E->lw) return ex;
+    hipGraphExec_t& ex = E->graph[krylov][E->lw - 2];
+    int& captured = E->graph_k[krylov][E->lw - 2];
+    if (ex && captured == k) return ex;
     if (ex) {
         HIP_CHECK(hipGraphExecDestroy(ex));
         ex = nullptr;
@@ -456,12 +458,9 @@ static hipGraphExec_t block_graph(BatchEngine* E, int krylov, int k) {
     HIP_CHECK(hipStreamEndCapture(E->cap_stream, &g));
     HIP_CHECK(hipGraphInstantiate(&ex, g, nullptr, nullptr, 0));
     HIP_CHECK(hipGraphDestroy(g));
-    E->graph_k[krylov] = k;
-    E->graph_lw[krylov] = E->lw;
+    captured = k;
     return ex;
 }
-
-void batch_prepare_graph(BatchEngine* E, int krylov, int k) { (void)block_graph(E, krylov, k); }
 
 void release_engine(pamg_hierarchy* h, int prec) { h->batch[prec].reset(); }   // destroy_batch synchronizes
 
@@ -479,6 +478,28 @@ uint64_t engine_bytes(const pamg_hierarchy* h, int prec) {
     b += (uint64_t)h->idx[L].n * kW * s + 8 * n0 * 8 + (prec == PAMG_PREC_F32 ? 2 * n0 * 4 : 0);
     b += 2 * (uint64_t)kMaxGrid * kW * 2 * 8 + sizeof(BatchState) + 2 * kW * sizeof(void*);
     return b;
+}
+
+int batch_width(const BatchEngine* E) { return 1 << E->lw; }
+
+// The narrowest width that holds `columns`: taken as it is when no column runs
+// (keep false), and otherwise never below the running one; wider, the running
+// columns' vectors move to their places in the longer rows.
+void batch_set_width(BatchEngine* E, int columns, bool keep, hipStream_t s) {
+    const int lw = keep ? std::max(E->lw, width_log(columns)) : width_log(columns);
+    if (keep && lw != E->lw) {
+        const int n = E->h->idx[0].n;
+        const long long cnt = (long long)n << lw;
+        for (double* v : {E->X, E->R, E->B, E->P[0], E->P[1], E->Q}) {
+            hipLaunchKernelGGL(kb_widen, dim3(vec_grid(cnt)), dim3(kBlock), 0, s, cnt, E->lw, lw, (const double*)v, E->Y);
+            HIP_CHECK(hipMemcpyAsync(v, E->Y, sizeof(double) * cnt, hipMemcpyDeviceToDevice, s));
+        }
+        if (E->R32)
+            hipLaunchKernelGGL(kb_narrow, dim3(vec_grid(cnt)), dim3(kBlock), 0, s, cnt, (const double*)E->R, E->R32,
+                               (const int*)E->h->zero_flag);
+        HIP_CHECK(hipGetLastError());
+    }
+    E->lw = lw;
 }
 
 // One block of k iterations (graph replay or direct launches).
@@ -773,12 +794,12 @@ void batch_set_config(pamg_hierarchy* h, int prec, const int32_t* cfg) {
     }
     BatchEngine* E = get_engine(h, prec, nullptr);
     HIP_CHECK(hipDeviceSynchronize());
-    for (int k = 0; k < 2; ++k)
-        if (E->graph[k]) {
-            HIP_CHECK(hipGraphExecDestroy(E->graph[k]));
-            E->graph[k] = nullptr;
-            E->graph_k[k] = 0;
-        }
+    for (auto& row : E->graph)
+        for (auto& g : row)
+            if (g) {
+                HIP_CHECK(hipGraphExecDestroy(g));
+                g = nullptr;
+            }
     for (int l = 0; l < L; ++l) {
         E->cfg_down[l] = down[l];
         if (l > 0) E->cfg_up[l] = up[l];

@@ -21,11 +21,14 @@ void batch_load(BatchEngine* E, const double* const* src, const double* tol, con
 void batch_store(BatchEngine* E, double* const* dst, hipStream_t s);
 void batch_true_residual(BatchEngine* E, int restart_mask, double* relres, hipStream_t s);
 void batch_run_block(BatchEngine* E, int krylov, int k, bool use_graph, hipStream_t s);
-// Capture and instantiate the block graph batch_run_block replays (no launch).
-void batch_prepare_graph(BatchEngine* E, int krylov, int k);
 // Mark the columns in `mask` inactive in the host copy of the state (written
 // back by the next batch_write_state / batch_load).
 void batch_retire(BatchEngine* E, int mask);
+// Columns a row of the vectors holds (4, 8 or 16), and the change to the
+// narrowest width that holds `columns`, between blocks; keep: columns run, and
+// keep their values (the width then only grows).
+int batch_width(const BatchEngine* E);
+void batch_set_width(BatchEngine* E, int columns, bool keep, hipStream_t s);
 // Free the engine of this precision (synchronizes the device); the tuned
 // kernel variants stay with the hierarchy for the next engine.
 void release_engine(pamg_hierarchy* h, int prec);

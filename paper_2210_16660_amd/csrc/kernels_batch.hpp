@@ -553,6 +553,17 @@ static __global__ __launch_bounds__(kBlock) void kb_narrow(long long cnt, const 
     for (long long i = (long long)blockIdx.x * kBlock + threadIdx.x; i < cnt; i += stride) dst[i] = (float)src[i];
 }
 
+// Rows of 2^from values to rows of 2^to (more): each column at its place, zeros in
+// the new ones.  cnt: the values written.
+static __global__ __launch_bounds__(kBlock) void kb_widen(long long cnt, int from, int to,
+                                                          const double* __restrict__ src, double* __restrict__ dst) {
+    const long long stride = (long long)gridDim.x * kBlock;
+    for (long long i = (long long)blockIdx.x * kBlock + threadIdx.x; i < cnt; i += stride) {
+        const int c = (int)(i & ((1 << to) - 1));
+        dst[i] = c < 1 << from ? src[((i >> to) << from) + c] : 0.0;
+    }
+}
+
 // ---------------------------------------------------------------- Krylov
 
 // p = z + beta_c p_old (p = z on a column's first iteration), q = A p as
