@@ -1,7 +1,8 @@
 // Multi-right-hand-side solves: up to 16 independent FCG/PCG recurrences
 // share every pass over the hierarchy's matrices.  The engine owns the
-// n x 16 work vectors of one V-cycle precision, the per-level kernel variants
-// chosen by the autotuner, and a HIP graph of one block of iterations.
+// work vectors of one V-cycle precision (room for n x 16 values each, n x W in
+// use, W = 4, 8 or 16), the per-level kernel variants chosen by the autotuner,
+// and a HIP graph of one block of iterations per width.
 // Columns can be loaded and retired between blocks (the serving loop uses
 // this); a column's arithmetic never depends on the other columns.
 #include <hip/hip_runtime.h>

@@ -5,8 +5,7 @@
 // of a row are one 128-byte (FP64) or 64-byte (FP32) line, so every gathered
 // neighbour is one line and every matrix entry is read once per 16 columns.
 // The width is a launch argument (lw = log2 W): a batch of few right-hand sides
-// moves few columns (five columns of 227 thousand rows, FP64: 10.9 ms a solve
-// at width 16).  A row is handled by a group of W/CPL lanes, each lane owning
+// moves few columns.  A row is handled by a group of W/CPL lanes, each lane owning
 // CPL adjacent columns.  Per column the arithmetic is a fixed sequence (entries in CSR
 // order, members in order), independent of the unroll depth U, of CPL and
 // of the other columns: a column's result does not depend on what else is
@@ -543,9 +542,9 @@ static __global__ __launch_bounds__(kBlock) void kb_coarse_rows(
     }
 }
 
-// FP64 -> FP32 copy of n x 16 values (the FP32 cycle's level-0 right-hand
-// side, for the debug entry point; in the iteration every writer of R also
-// writes R32).
+// FP64 -> FP32 copy of cnt values (the FP32 cycle's level-0 right-hand side, for
+// the debug entry point and after widening; in the iteration every writer of R
+// also writes R32).
 static __global__ __launch_bounds__(kBlock) void kb_narrow(long long cnt, const double* __restrict__ src,
                                                     float* __restrict__ dst, const int* __restrict__ done) {
     if (*done) return;

@@ -128,7 +128,8 @@ static __global__ __launch_bounds__(MAXB) void k_hgs(
 // (backward: (U_pp + D_pp)^-1), and a sweep is one product d = W t, with no
 // chain and about the substitution's bytes (a row of W holds at most its
 // position in the block: 160 values on average, against 60 to 70 values and
-// columns).  On levels with short rows the substitution stays: level 0 of the
+// columns): 5.2 us a sweep on that level, the inversion 0.49 ms per direction.
+// On levels with short rows the substitution stays: level 0 of the
 // 27-point operator holds 3 to 4 in-block entries a row, so W would be twice
 // the whole matrix (45 us a sweep there, against 47 us for W's bytes alone).
 //

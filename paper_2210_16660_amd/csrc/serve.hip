@@ -13,7 +13,8 @@
 //     budget, freeing idle operators' 16-column engines and then evicting
 //     idle cached operators in least-recently-used order; otherwise it waits;
 //   * batching: every cached operator is a group with its own stream and 16
-//     columns; a waiting request takes a free column between iteration blocks
+//     columns; a batch is as wide as the columns in use need (4, 8 or 16); a
+//     waiting request takes a free column between iteration blocks
 //     and its recurrence starts there (columns are independent, so a result
 //     is the same whatever else is in the group);
 //   * overlap: every group with running columns has one iteration block in

@@ -4,7 +4,8 @@ displaces the next, the longest chain there is), a path of equal edges and a
 grid of them (ties by the numbers of the endpoints), a graph of hubs whose
 lists are long and mostly taken, random weights on a random graph, vertices
 without an eligible edge; and a hierarchy that stalls below the dense limit,
-whose last level is decided on the device."""
+whose last level is decided on the device.  The options that stop the coarsening
+there (levels, sizes, ratio, with and without composition) against the host."""
 import numpy as np
 import pytest
 import scipy.sparse as sp
@@ -76,3 +77,30 @@ def test_matching_is_the_oracles(case):
         orp, oci, ov = O.level(l)
         assert np.array_equal(rp, orp) and np.array_equal(ci, oci), f"level {l} pattern differs"
         assert np.array_equal(v.view(np.uint64), ov.view(np.uint64)), f"level {l} values differ"
+
+
+STOPS = [{"max_levels": 2}, {"max_levels": 4}, {"max_coarse": 3000}, {"min_ratio": 1.9}, {"min_ratio": 3.0},
+         {"max_levels": 3, "agg_steps": 2}, {"max_coarse": 700, "agg_steps": 3}, {"min_ratio": 1.9, "agg_steps": 2}]
+
+
+@pytest.mark.parametrize("kw", STOPS, ids=str)
+@pytest.mark.parametrize("make", [lambda: lap7(22), lambda: varcoef7(22, seed=11)], ids=["lap7", "varcoef"])
+def test_coarsening_stops_where_the_hosts_does(make, kw):
+    A = make()
+
+    def build(device):
+        try:
+            return pamg.Hierarchy(A, device_setup=device, **kw)
+        except pamg.PamgError as e:
+            return e.code
+
+    D, R = build(1), build(0)
+    if isinstance(R, int):
+        assert D == R
+        return
+    assert D.levels == R.levels and R.info().device_levels == 0
+    for l in range(D.levels):
+        for a, b in zip(D.level_csr(l), R.level_csr(l)):
+            assert np.array_equal(a.view(np.uint8), b.view(np.uint8)), l
+    for l in range(D.levels - 1):
+        assert np.array_equal(D.aggregates(l), R.aggregates(l)), l
