@@ -151,12 +151,22 @@ static uint64_t tail_bytes(const pamg_csr& A, int prec) {
     return std::min(entries, n * n) * (prec == PAMG_PREC_F32 ? 12 : 8);
 }
 
+// Bound of the unused room of sliced levels (setup.cpp, sell_tiles: equal tiles
+// for whole rounds of the chip, each with the room of a full one, so at most a
+// round of full tiles of a level's mean rows): values, scaled values (and their
+// FP32 copies), columns and positions.
+static double sell_room(double n, double nnz, int prec) {
+    double levels = 0;
+    for (double nl = n; nl >= kSellMinRows; nl /= 1.9) levels += 1;
+    return levels * kSellGrid * kSlice * (nnz / std::max(n, 1.0)) * (prec == PAMG_PREC_F32 ? 30 : 22);
+}
+
 static uint64_t estimate_core(const pamg_csr& A, int prec) {
     const double cx = 2.3;
     const double n = (double)A.n, nnz = (double)A.nnz;
     double hier = cx * (nnz * (4 + 8 + 8) + n * 80) + 96.0 * n + (1 << 18);
     if (prec == PAMG_PREC_F32) hier += cx * (nnz * 8 + n * 32) + 4.0 * n;
-    return (uint64_t)hier + tail_bytes(A, prec);
+    return (uint64_t)(hier + sell_room(n, nnz, prec)) + tail_bytes(A, prec);
 }
 
 // ... plus the dense inverse of a coarsest level of the usual size (at most

@@ -105,3 +105,21 @@ def test_new_coefficients_on_sliced_rows():
         K.solve(b, x, tol=1e-6)
         xs.append(x.cpu().numpy().view(np.uint64))
     assert np.array_equal(*xs)
+
+
+@pytest.mark.parametrize("name", sorted(OPERATORS))
+@pytest.mark.parametrize("prec", [pamg.PREC_F32, pamg.PREC_F64])
+def test_admission_estimate_covers_the_slices(matrices, name, prec):
+    # just above the least size the tiles' unused room is largest
+    A = matrices[name]
+    S = pamg.Server(precision=prec, single_path=1)
+    x = torch.zeros(A.n, dtype=torch.float64, device="cuda:0")
+    S.submit(1, A, dev(np.zeros(A.n)), x, tag=1)
+    done = []
+    while not done:
+        done = S.poll()
+    st = S.stats()
+    S.close()
+    assert done[0].status == pamg.OK and st.setups == 1
+    est = pamg.server_estimate_bytes(A, prec)
+    assert est // 16 <= st.bytes_in_use <= est
