@@ -93,17 +93,18 @@ __global__ __launch_bounds__(kDenseThreads) void k_dense_eye(int N, double* __re
 // This tile is the serial part of the factorization (one workgroup, one after
 // the other), so it is bound by the latency of its 64 column steps.  A thread
 // of the 16 x 16 grid holds 4 x 4 entries of the tile and of the inverse in
-// registers (rows ty + 16 a, columns tx + 16 b); a step exchanges only the
-// pivot column and one row of the inverse through LDS (two buffers, one
-// barrier), and both triangles are eliminated together: A_ic -= (a_ij / d_j)
-// a_cj and T_i -= (a_ij / d_j) T_j.  The square roots of the pivots stay out
-// of the chain and scale L and T at the end.  In LDS with three barriers a
-// step, and the inverse afterwards by one thread per column, the tile took
-// 126 us (5.3 of the 8.7 ms of n = 2675); now the update that contains it
-// takes 43 us.
+// registers (rows ty + 16 a, columns tx + 16 b); two steps exchange only their
+// two columns and two rows of the inverse through LDS (two buffers, one barrier;
+// every thread makes the second step's column and row from the first's itself),
+// and both triangles are eliminated together: A_ic -= (a_ij / d_j) a_cj and
+// T_i -= (a_ij / d_j) T_j.  The square roots of the pivots stay out of the chain
+// and scale L and T at the end.  In LDS with three barriers a step, and the
+// inverse afterwards by one thread per column, the tile took 126 us (5.3 of the
+// 8.7 ms of n = 2675); in registers with a barrier a step 28, now 22, and the
+// update that contains it 38 (43).
 __device__ __forceinline__ void potrf_tile(double* M, int N, int kb, double* Dinv, int* bad) {
-    __shared__ double s_col[2][kT];     // column j of the tile (rows >= j)
-    __shared__ double s_row[2][kT];     // row j of the inverse
+    __shared__ double s_col[2][2][kT];  // columns j and j + 1 of the tile
+    __shared__ double s_row[2][2][kT];  // rows j and j + 1 of the inverse
     __shared__ double s_piv[kT];
     const int tx = threadIdx.x % 16, ty = threadIdx.x / 16;
     double* G = M + (size_t)kb * kT * N + (size_t)kb * kT;
@@ -119,45 +120,62 @@ __device__ __forceinline__ void potrf_tile(double* M, int N, int kb, double* Din
 #pragma unroll
     for (int J = 0; J < 4; ++J) {
 #pragma unroll 1                        // (unrolled, the code outgrows the instruction cache)
-        for (int jj = 0; jj < 16; ++jj) {
-            const int j = 16 * J + jj, buf = j & 1;
-            if (tx == jj) {
+        for (int jj = 0; jj < 16; jj += 2) {
+            const int j = 16 * J + jj, buf = (jj >> 1) & 1;
+            if ((tx & ~1) == jj) {
 #pragma unroll
-                for (int a = 0; a < 4; ++a) s_col[buf][ty + 16 * a] = A[a][J];
+                for (int a = 0; a < 4; ++a) s_col[buf][tx & 1][ty + 16 * a] = A[a][J];
             }
-            if (ty == jj) {
+            if ((ty & ~1) == jj) {
 #pragma unroll
-                for (int b = 0; b < 4; ++b) s_row[buf][tx + 16 * b] = T[J][b];
+                for (int b = 0; b < 4; ++b) s_row[buf][ty & 1][tx + 16 * b] = T[J][b];
             }
             __syncthreads();
-            double d = s_col[buf][j];
-            const bool spd = d > 0.0;
-            if (!spd) d = 1.0;
+            // step j, and what it makes of the pivot of step j + 1
+            double d0 = s_col[buf][0][j], d1 = s_col[buf][1][j + 1];
+            const double m = s_col[buf][0][j + 1];
+            double r0[4], r1[4], c0[4], c1[4], t0[4], t1[4];
+#pragma unroll
+            for (int u = 0; u < 4; ++u) {
+                r0[u] = s_col[buf][0][ty + 16 * u];
+                r1[u] = s_col[buf][1][ty + 16 * u];
+                c0[u] = s_col[buf][0][tx + 16 * u];
+                c1[u] = s_col[buf][1][tx + 16 * u];
+                t0[u] = s_row[buf][0][tx + 16 * u];
+                t1[u] = s_row[buf][1][tx + 16 * u];
+            }
+            const bool spd0 = d0 > 0.0;
+            if (!spd0) d0 = 1.0;
+            const double rd0 = 1.0 / d0, lm = m * rd0;
+            d1 -= lm * m;
+            const bool spd1 = d1 > 0.0;
+            if (!spd1) d1 = 1.0;
+            const double rd1 = 1.0 / d1;
             if (threadIdx.x == 0) {
-                s_piv[j] = d;
-                if (!spd) *bad = 1;
+                s_piv[j] = d0;
+                s_piv[j + 1] = d1;
+                if (!spd0 || !spd1) *bad = 1;
             }
-            double li[4], ac[4], tr[4];
-            const double rd = 1.0 / d;
+            // columns and rows j + 1 after step j; an entry past its range
+            // contributes a zero factor (selected after the loads, which are
+            // issued together)
 #pragma unroll
             for (int u = 0; u < 4; ++u) {
-                li[u] = s_col[buf][ty + 16 * u];
-                ac[u] = s_col[buf][tx + 16 * u];
-                tr[u] = s_row[buf][tx + 16 * u];
-            }
-            // an entry past its range contributes a zero factor (selected
-            // after the loads, which are issued together)
-#pragma unroll
-            for (int u = 0; u < 4; ++u) {
-                li[u] = ty + 16 * u > j ? li[u] * rd : 0.0;
-                ac[u] = tx + 16 * u > j ? ac[u] : 0.0;
+                const double l0 = r0[u] * rd0;
+                r1[u] = ty + 16 * u > j + 1 ? (r1[u] - l0 * m) * rd1 : 0.0;
+                r0[u] = ty + 16 * u > j ? l0 : 0.0;
+                c1[u] = tx + 16 * u > j + 1 ? c1[u] - (c0[u] * rd0) * m : 0.0;
+                c0[u] = tx + 16 * u > j ? c0[u] : 0.0;
+                t1[u] -= lm * t0[u];
             }
 #pragma unroll
             for (int a = 0; a < 4; ++a)
 #pragma unroll
                 for (int b = 0; b < 4; ++b) {
-                    A[a][b] -= li[a] * ac[b];
-                    T[a][b] -= li[a] * tr[b];
+                    A[a][b] -= r0[a] * c0[b];
+                    T[a][b] -= r0[a] * t0[b];
+                    A[a][b] -= r1[a] * c1[b];
+                    T[a][b] -= r1[a] * t1[b];
                 }
             // no second barrier: the next step writes the other buffer, and
             // this one only after the next barrier
