@@ -63,8 +63,29 @@ __device__ __forceinline__ void zero(d4 (&acc)[4]) {
 __device__ __forceinline__ int res_row(int wave, int lane, int i) { return 16 * wave + 4 * i + lane / 16; }
 __device__ __forceinline__ int res_col(int lane, int ct) { return 16 * ct + lane % 16; }
 
-__device__ __forceinline__ void load_tile(double (*S)[kTP], const double* __restrict__ g, int ld) {
-    for (int e = threadIdx.x; e < kT * kT; e += kDenseThreads) S[e / kT][e % kT] = g[(size_t)(e / kT) * ld + e % kT];
+// Two tiles into LDS, all loads (two values each: tiles and their rows are 16-byte
+// aligned) in flight before the first is stored.  A load and its store at a time,
+// a launch waited on memory 32 times over: n = 2675, panel 13.3 us, now 5.9, update
+// with the diagonal tile 38, now 32.5, X^T X 512, now 211 (its flops take 185 at
+// the rate of a large FP64 product).
+__device__ __forceinline__ void load_tiles(double (*S0)[kTP], const double* __restrict__ g0, int ld0,
+                                           double (*S1)[kTP], const double* __restrict__ g1, int ld1) {
+    constexpr int P = kT * kT / 2 / kDenseThreads;
+    double2 x[P], y[P];
+#pragma unroll
+    for (int p = 0; p < P; ++p) {
+        const int e = 2 * ((int)threadIdx.x + p * kDenseThreads), r = e / kT, c = e % kT;
+        x[p] = *reinterpret_cast<const double2*>(g0 + (size_t)r * ld0 + c);
+        y[p] = *reinterpret_cast<const double2*>(g1 + (size_t)r * ld1 + c);
+    }
+#pragma unroll
+    for (int p = 0; p < P; ++p) {
+        const int e = 2 * ((int)threadIdx.x + p * kDenseThreads), r = e / kT, c = e % kT;
+        S0[r][c] = x[p].x;
+        S0[r][c + 1] = x[p].y;
+        S1[r][c] = y[p].x;
+        S1[r][c + 1] = y[p].y;
+    }
 }
 
 // M = 0 beforehand; scatter the CSR of the coarsest level, identity padding
@@ -101,7 +122,7 @@ __global__ __launch_bounds__(kDenseThreads) void k_dense_eye(int N, double* __re
 // and scale L and T at the end.  In LDS with three barriers a step, and the
 // inverse afterwards by one thread per column, the tile took 126 us (5.3 of the
 // 8.7 ms of n = 2675); in registers with a barrier a step 28, now 22, and the
-// update that contains it 38 (43).
+// update that contains it 32.5.
 __device__ __forceinline__ void potrf_tile(double* M, int N, int kb, double* Dinv, int* bad) {
     __shared__ double s_col[2][2][kT];  // columns j and j + 1 of the tile
     __shared__ double s_row[2][2][kT];  // rows j and j + 1 of the inverse
@@ -216,8 +237,7 @@ __global__ __launch_bounds__(kDenseThreads) void k_dense_panel(double* __restric
     const int u = blockIdx.x;
     double* G = u < t ? M + (size_t)(kb + 1 + u) * kT * N + (size_t)kb * kT
                       : X + (size_t)kb * kT * N + (size_t)(u - t) * kT;
-    load_tile(Dk, Dinv + (size_t)kb * kT * kT, kT);
-    load_tile(A, G, N);
+    load_tiles(Dk, Dinv + (size_t)kb * kT * kT, kT, A, G, N);
     __syncthreads();
     d4 acc[4];
     zero(acc);
@@ -257,16 +277,14 @@ __global__ __launch_bounds__(kDenseThreads) void k_dense_update(double* M, doubl
         int i, j;
         tri_index(blockIdx.x, i, j);
         const int ib = kb + 1 + i, jb = kb + 1 + j;
-        load_tile(P, M + (size_t)ib * kT * N + (size_t)kb * kT, N);
-        load_tile(Q, M + (size_t)jb * kT * N + (size_t)kb * kT, N);
+        load_tiles(P, M + (size_t)ib * kT * N + (size_t)kb * kT, N, Q, M + (size_t)jb * kT * N + (size_t)kb * kT, N);
         __syncthreads();
         strip_product(acc, wave, lane, [&](int r, int k) { return P[r][k]; }, [&](int k, int c) { return Q[c][k]; });
         G = M + (size_t)ib * kT * N + (size_t)jb * kT;
     } else {
         const int u = (int)(blockIdx.x - T);
         const int m = kb + 1 + u / (kb + 1), c0 = u % (kb + 1);
-        load_tile(P, M + (size_t)m * kT * N + (size_t)kb * kT, N);
-        load_tile(Q, X + (size_t)kb * kT * N + (size_t)c0 * kT, N);
+        load_tiles(P, M + (size_t)m * kT * N + (size_t)kb * kT, N, Q, X + (size_t)kb * kT * N + (size_t)c0 * kT, N);
         __syncthreads();
         strip_product(acc, wave, lane, [&](int r, int k) { return P[r][k]; }, [&](int k, int c) { return Q[k][c]; });
         G = X + (size_t)m * kT * N + (size_t)c0 * kT;
@@ -295,8 +313,7 @@ __global__ __launch_bounds__(kDenseThreads) void k_dense_xtx(const double* __res
     d4 acc[4];
     zero(acc);
     for (int k = a; k < nb; ++k) {
-        load_tile(Xa, X + (size_t)k * kT * N + (size_t)a * kT, N);
-        load_tile(Xb, X + (size_t)k * kT * N + (size_t)b * kT, N);
+        load_tiles(Xa, X + (size_t)k * kT * N + (size_t)a * kT, N, Xb, X + (size_t)k * kT * N + (size_t)b * kT, N);
         __syncthreads();
         strip_product(acc, wave, lane, [&](int r, int kk) { return Xa[kk][r]; }, [&](int kk, int c) { return Xb[kk][c]; });
         __syncthreads();
