@@ -146,6 +146,7 @@ constexpr int kSellStep = 8;         // entries of a row loaded together
 constexpr int kSellDict = 2048;      // longest dictionary of a tile (16 KB in FP64)
 constexpr int kSellMinRows = 2 * kSellGrid * kSlice;  // 786,432: two full rounds of the chip
 constexpr int kSellMaxRow = 128;     // longest row (a lane walks its row alone)
+constexpr int kSellRowSpread = 4;    // longest row over the mean row
 constexpr int kTileRows = kBlock;    // at most one row (or aggregate) per thread in a tile
 constexpr int kMaxAggSteps = 4;      // composed aggregates hold at most 2^4 fine rows
 constexpr int kTargetTiles = 1024;   // small levels shrink their tiles to keep >= this many
@@ -166,8 +167,10 @@ void make_tiles(const std::vector<int32_t>& rp, const std::vector<int32_t>& aggp
                 int32_t cap, std::vector<int32_t>& up, std::vector<int32_t>& down);
 
 // Whether a level of n rows, nnz entries and longest row maxrow is stored in
-// sliced rows.
+// sliced rows, if its tiles then store no more than sell_fits allows.
 bool sell_applies(int64_t n, int64_t nnz, int64_t maxrow);
+// Whether tiles that store `padded` entries for nnz are kept.
+bool sell_fits(int64_t padded, int64_t nnz);
 // Tiles of an n-row level (aggptr: aggregate boundaries they respect, nc = 0:
 // none), 4 ints each: first row, end row, first coarse row, end coarse row;
 // and the same with every tile halved whose dictionary (dlen) is too long
@@ -175,7 +178,7 @@ bool sell_applies(int64_t n, int64_t nnz, int64_t maxrow);
 std::vector<int32_t> sell_tiles(const std::vector<int32_t>& aggptr, int32_t n, int32_t nc);
 bool split_sell_tiles(std::vector<int32_t>& tiles, const std::vector<int32_t>& aggptr, int32_t nc,
                       const std::vector<int32_t>& dlen);
-// Empty when the padded entries exceed 32-bit positions.
+// Empty when the tiles would store too much padding (sell_fits).
 SellRows sell_rows(const std::vector<int32_t>& rp, const std::vector<int32_t>& ci, const std::vector<int32_t>& aggptr,
                    int32_t n, int32_t nc);
 // First tile of each of 8 equal shares of the n rows (tiles: stride ints per

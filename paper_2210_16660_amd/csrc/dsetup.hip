@@ -73,6 +73,16 @@ struct Temps {
                 return;
             }
     }
+    // An array that stays: it belongs to the hierarchy from here on.
+    void keep(pamg_hierarchy* h, void* p) {
+        for (size_t i = 0; i < list.size(); ++i)
+            if (list[i].p == p) {
+                h->allocs.push_back(list[i]);
+                h->info.device_bytes += list[i].bytes;
+                list.erase(list.begin() + i);
+                return;
+            }
+    }
     // The stream has been waited for since the last release.
     void drain() { ctx_free_all(ctx, pending); }
     void release_now(void* p, void* q) {
@@ -1267,42 +1277,43 @@ std::unique_ptr<DeviceBuild> device_build(pamg_hierarchy* h, const pamg_csr& A, 
         for (int32_t c = 0; c < nc; ++c) D.max_agg = std::max(D.max_agg, ap_h[c + 1] - ap_h[c]);
         D.nent = L.nnz;
         if (sell) {
-            // tiles (host partition of the aggregates), halved until every dictionary fits
-            DevSell& S = D.sell;
-            std::vector<int32_t> tiles = sell_tiles(ap_h, n, nc), dlen;
+            // tiles (host partition of the aggregates), halved until every
+            // dictionary fits, while they store no more than sell_fits allows
+            std::vector<int32_t> tiles = sell_tiles(ap_h, n, nc), dlen, size;
             for (;;) {
                 const int nt = (int)(tiles.size() / 4);
                 int4* td = T.get<int4>(nt);
                 int* dl = T.get<int>(nt);
+                int* sz2 = T.get<int>(nt);
                 to_device(reinterpret_cast<int*>(td), tiles.data(), tiles.size(), s);
-                hipLaunchKernelGGL(k_dict_count, dim3(grid_rows(nt)), dim3(kSB), 0, s, nt, (const int4*)td,
-                                   (const int*)D.rp, (const int*)ci2, dl);
-                to_host(dlen, dl, (size_t)nt, s);
+                hipLaunchKernelGGL(k_sell_sizes, dim3(grid_rows(nt)), dim3(kSB), 0, s, nt, (const int4*)td,
+                                   (const int*)D.rp, sz2);
+                to_host(size, sz2, (size_t)nt, s);
+                sell = sell_fits(std::accumulate(size.begin(), size.end(), 0ll), L.nnz);
+                if (sell) {
+                    hipLaunchKernelGGL(k_dict_count, dim3(grid_rows(nt)), dim3(kSB), 0, s, nt, (const int4*)td,
+                                       (const int*)D.rp, (const int*)ci2, dl);
+                    to_host(dlen, dl, (size_t)nt, s);
+                }
                 T.release(td);
                 T.release(dl);
-                if (!split_sell_tiles(tiles, ap_h, nc, dlen)) break;
+                T.release(sz2);
+                if (!sell || !split_sell_tiles(tiles, ap_h, nc, dlen)) break;
             }
-            const int nt = (int)dlen.size();
-            int4* td = T.get<int4>(nt);
-            int* size = T.get<int>(nt);
-            to_device(reinterpret_cast<int*>(td), tiles.data(), tiles.size(), s);
-            hipLaunchKernelGGL(k_sell_sizes, dim3(grid_rows(nt)), dim3(kSB), 0, s, nt, (const int4*)td,
-                               (const int*)D.rp, size);
-            std::vector<int32_t> size_h;
-            to_host(size_h, size, (size_t)nt, s);
-            T.release(td);
-            T.release(size);
-            std::vector<int32_t> full(8 * (size_t)nt, 0);
-            long long at = 0;
-            for (int t = 0; t < nt && at < (1ll << 31); ++t) {
-                const int32_t* q = &tiles[4 * (size_t)t];
-                const int32_t d[8] = {q[0], q[1], (int32_t)at, (int32_t)S.len, dlen[t], q[2], q[3], 0};
-                std::copy(d, d + 8, full.begin() + 8 * (size_t)t);
-                S.max_len = std::max(S.max_len, dlen[t]);
-                S.len += dlen[t];
-                at += size_h[t];
-            }
-            if (at < (1ll << 31)) {
+            T.drain();
+            if (sell) {
+                DevSell& S = D.sell;
+                const int nt = (int)dlen.size();
+                std::vector<int32_t> full(8 * (size_t)nt, 0);
+                long long at = 0;
+                for (int t = 0; t < nt; ++t) {
+                    const int32_t* q = &tiles[4 * (size_t)t];
+                    const int32_t d[8] = {q[0], q[1], (int32_t)at, (int32_t)S.len, dlen[t], q[2], q[3], 0};
+                    std::copy(d, d + 8, full.begin() + 8 * (size_t)t);
+                    S.max_len = std::max(S.max_len, dlen[t]);
+                    S.len += dlen[t];
+                    at += size[t];
+                }
                 S.n_tiles = nt;
                 D.nent = at;
                 sell_shares(full, 8, n, S.xcd);
@@ -1317,17 +1328,13 @@ std::unique_ptr<DeviceBuild> device_build(pamg_hierarchy* h, const pamg_csr& A, 
                 hipLaunchKernelGGL(k_sell_fill, dim3(grid_rows(nt)), dim3(kSB), 0, s, nt, (const int4*)S.tiles,
                                    (const int*)D.rp, (const int*)ci2, (const double*)v2, S.slot, S.rowpos, D.ci, D.v,
                                    S.col, S.loc);
+                T.release_now(ci2, v2);
             } else {
-                sell = false;                   // more padded entries than 32-bit positions
+                T.keep(h, ci2);
+                T.keep(h, v2);
             }
-            if (!sell) {
-                D.ci = dalloc<int>(h, L.nnz, s);
-                D.v = dalloc<double>(h, L.nnz, s);
-                HIP_CHECK(hipMemcpyAsync(D.ci, ci2, sizeof(int) * L.nnz, hipMemcpyDeviceToDevice, s));
-                HIP_CHECK(hipMemcpyAsync(D.v, v2, sizeof(double) * L.nnz, hipMemcpyDeviceToDevice, s));
-            }
-            T.release_now(ci2, v2);
-        } else {
+        }
+        if (!sell) {
             D.ci = ci2;
             D.v = v2;
         }

@@ -24,11 +24,14 @@
 // six such tiles a CU is slower: within 1 %), four or five workgroups per CU
 // with longer batches, seven or eight (spills), every load one batch ahead.
 //
-// Where it is used (sell_applies): levels of at least two rounds of the chip
-// (786,432 rows).  A tile waits on memory for its gather, its stream and its
-// finish one after the other, and only other tiles hide that: 1.07 M rows are
-// even in FP64 and 7 % faster in FP32, 534 thousand rows 4 to 8 % slower, 135
-// thousand 11.6 -> 16.8 us, so smaller levels keep the dictionary tiles.
+// Where it is used (sell_applies, sell_fits): levels of at least two rounds of
+// the chip (786,432 rows) whose padding stays within 1.4 times the entries.  A
+// tile waits on memory for its gather, its stream and its finish one after the
+// other, and only other tiles hide that.  Down- and up-sweep, dictionary tiles
+// -> sliced rows, us: 27-point rows, 1.05 million, FP64 65 -> 60 and 68 -> 64,
+// FP32 51 -> 43 and 49 -> 45; 528 thousand 34 -> 36 and 39 -> 41, FP32 24 -> 25
+// and 27 -> 30; 7-point rows, 1.06 million 29 -> 24 and 31 -> 25, FP32 24 -> 20
+// and 24 -> 20; 531 thousand 11 -> 13 and 16 -> 19, FP32 8 -> 11 and 12 -> 15.
 #pragma once
 
 #include "kernels.hpp"

@@ -151,14 +151,22 @@ static uint64_t tail_bytes(const pamg_csr& A, int prec) {
     return std::min(entries, n * n) * (prec == PAMG_PREC_F32 ? 12 : 8);
 }
 
-// Bound of the unused room of sliced levels (setup.cpp, sell_tiles: equal tiles
-// for whole rounds of the chip, each with the room of a full one, so at most a
-// round of full tiles of a level's mean rows): values, scaled values (and their
-// FP32 copies), columns and positions.
-static double sell_room(double n, double nnz, int prec) {
-    double levels = 0;
-    for (double nl = n; nl >= kSellMinRows; nl /= 1.9) levels += 1;
-    return levels * kSellGrid * kSlice * (nnz / std::max(n, 1.0)) * (prec == PAMG_PREC_F32 ? 30 : 22);
+// Bound of the bytes sliced levels hold beyond dictionary tiles: the padding
+// sell_fits allows in a level's values, scaled values (and their FP32 copies),
+// columns and positions, less the second position array of the tiles.  Level
+// 0 stores at most every row at its longest's length and one round of full
+// tiles (sell_tiles); of the levels below only the size is guessed.
+static double sell_room(const pamg_csr& A, int prec) {
+    const double n = (double)A.n, nnz = (double)A.nnz, entry = prec == PAMG_PREC_F32 ? 30 : 22;
+    if (A.n < kSellMinRows || !A.row_ptr) return 0.0;
+    int64_t maxrow = 0;
+    for (int32_t i = 0; i < A.n; ++i) maxrow = std::max<int64_t>(maxrow, (int64_t)A.row_ptr[i + 1] - A.row_ptr[i]);
+    double bytes = 0.0;
+    if (sell_applies(A.n, A.nnz, maxrow))
+        bytes = std::min(0.4 * nnz, (n + (double)kSellGrid * kSlice) * (double)maxrow - nnz) * entry - 2.0 * nnz;
+    double share = 1.0 / 1.9;
+    for (; n * share >= kSellMinRows; share /= 1.9) bytes += nnz * share * (0.4 * entry - 2.0);
+    return std::max(0.0, bytes);
 }
 
 static uint64_t estimate_core(const pamg_csr& A, int prec) {
@@ -166,7 +174,7 @@ static uint64_t estimate_core(const pamg_csr& A, int prec) {
     const double n = (double)A.n, nnz = (double)A.nnz;
     double hier = cx * (nnz * (4 + 8 + 8) + n * 80) + 96.0 * n + (1 << 18);
     if (prec == PAMG_PREC_F32) hier += cx * (nnz * 8 + n * 32) + 4.0 * n;
-    return (uint64_t)(hier + sell_room(n, nnz, prec)) + tail_bytes(A, prec);
+    return (uint64_t)(hier + sell_room(A, prec)) + tail_bytes(A, prec);
 }
 
 // ... plus the dense inverse of a coarsest level of the usual size (at most

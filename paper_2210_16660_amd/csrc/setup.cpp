@@ -1071,8 +1071,25 @@ void make_tiles(const std::vector<int32_t>& rp, const std::vector<int32_t>& aggp
     }
 }
 
+// The line for the size: kernels_sell.hpp.  A row that is long beside the
+// others keeps its tile waiting for one lane (about a microsecond per four of
+// its entries), where a dictionary tile spreads it over a workgroup: rows of
+// the grids' levels reach 1.0 to 1.8 times the mean.
 bool sell_applies(int64_t n, int64_t nnz, int64_t maxrow) {
-    return first_tile_items(nnz) >= kDictItems && n >= kSellMinRows && maxrow <= kSellMaxRow;
+    return first_tile_items(nnz) >= kDictItems && n >= kSellMinRows && maxrow <= kSellMaxRow &&
+           maxrow * n <= kSellRowSpread * nnz;
+}
+
+// At most 1.4 times the entries (and 32-bit positions): uneven rows, tiles cut
+// for their dictionaries and the rounding to whole rounds of the chip all end
+// in padding.  Down- and up-sweep, FP64, tiles over sliced rows: 1.07 and 1.07
+// at 1.37 times the entries (875 thousand 27-point rows), 1.08 and 1.03 at 1.33
+// (2.2 million rows of 9 on average), 1.01 and 0.96 at 1.49 (1.1 million rows
+// of 11), 0.76 and 0.77 at 1.92 (a tetrahedral mesh of a million points, rows
+// of 5 to 96).  Beside the dictionary tiles' 25 to 27 bytes an entry it is at
+// most a fifth more memory.
+bool sell_fits(int64_t padded, int64_t nnz) {
+    return 5 * padded <= 7 * nnz && padded < (int64_t(1) << 31);
 }
 
 // Equal tiles, their number a multiple of the workgroups the chip holds (a
@@ -1145,6 +1162,14 @@ SellRows sell_rows(const std::vector<int32_t>& rp, const std::vector<int32_t>& c
     std::vector<uint16_t> local(ci.size());
     for (;;) {
         const int64_t nt = (int64_t)tiles.size() / 4;
+        // (cutting a tile never stores less)
+        int64_t padded = 0;
+        for (int64_t t = 0; t < nt; ++t) {
+            int32_t longest = 0;
+            for (int32_t i = tiles[4 * t]; i < tiles[4 * t + 1]; ++i) longest = std::max(longest, rp[i + 1] - rp[i]);
+            padded += (int64_t)kSlice * longest;
+        }
+        if (!sell_fits(padded, rp[n])) return SellRows();
         dict.assign(nt, {});
         std::vector<int32_t> dlen(nt, 0);
         parallel_chunks(nt, 4, [&](int th, int64_t b, int64_t e) {
@@ -1179,7 +1204,6 @@ SellRows sell_rows(const std::vector<int32_t>& rp, const std::vector<int32_t>& c
         S.max_len = std::max(S.max_len, len);
         total += len;
         at += (int64_t)kSlice * longest;
-        if (at >= (int64_t(1) << 31)) return SellRows();
     }
     sell_shares(S.tiles, 8, n, S.xcd);
     S.col.resize(total);
