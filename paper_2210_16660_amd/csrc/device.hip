@@ -140,7 +140,16 @@ static int tail_level(const pamg_hierarchy* h);
 
 bool gs_dense_level(const pamg_hierarchy* h, int l) {
     const DevLevelIdx& I = h->idx[l];
-    return h->smoother == PAMG_SMOOTHER_HYBRID_GS && l < h->L && I.nnz >= (long long)kGsDenseRow * I.n;
+    if (h->smoother != PAMG_SMOOTHER_HYBRID_GS || l >= h->L || I.nnz < (long long)kGsDenseRow * I.n) return false;
+    const double m = (double)I.gs_inblock / I.n;
+    const double bytes = 8.0 * (double)I.gs_nblk * (double)gs_dense_block(h->gs_block);
+    return m >= kGsDenseInBlock || (m >= kGsDenseFew && bytes <= kGsDenseBytes);
+}
+
+static long long gs_inblock(const std::vector<int32_t>& fresh) {
+    long long c = 0;
+    for (size_t i = 1; i < fresh.size(); i += 2) c += fresh[i] & 0xff;
+    return c;
 }
 
 void build_gs_dense(pamg_hierarchy* h, int l, hipStream_t s) {
@@ -251,6 +260,13 @@ void upload_hierarchy(pamg_hierarchy* h, const std::vector<LayoutLevel>& lay, bo
             I.gs_maxd = D.gs_maxd;
             I.gs_fresh = reinterpret_cast<const int2*>(D.gs_fresh);
             I.gs_nblk = D.gs_nblk;
+            if (I.nnz >= (long long)kGsDenseRow * I.n) {
+                std::vector<int32_t> fresh(2 * (size_t)I.n);
+                HIP_CHECK(hipMemcpyAsync(fresh.data(), D.gs_fresh, sizeof(int32_t) * fresh.size(),
+                                         hipMemcpyDeviceToHost, s));
+                HIP_CHECK(hipStreamSynchronize(s));
+                I.gs_inblock = gs_inblock(fresh);
+            }
         }
     }
     for (int l = m; l < nl; ++l) {
@@ -318,6 +334,7 @@ void upload_hierarchy(pamg_hierarchy* h, const std::vector<LayoutLevel>& lay, bo
                 I.gs_maxd = upload<int>(h, Ly.gs.maxd, s);
                 I.gs_fresh = reinterpret_cast<const int2*>(upload<int>(h, Ly.gs.fresh, s));
                 I.gs_nblk = (int)Ly.gs.maxd.size() / 2;
+                I.gs_inblock = gs_inblock(Ly.gs.fresh);
             }
         }
     }

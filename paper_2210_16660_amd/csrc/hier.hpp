@@ -110,6 +110,7 @@ struct DevLevelIdx {
     const int* gs_maxd = nullptr;
     const int2* gs_fresh = nullptr;     // per row: first in-block entry, counts (GsLevel::fresh)
     int gs_nblk = 0;
+    long long gs_inblock = 0;           // levels with long rows: entries before a row in its block, all rows
     // smoothed prolongator (l < L): P and P^T patterns, hierarchical numbering
     DevTiled sa_p, sa_t;
     long long sa_nnz = 0;

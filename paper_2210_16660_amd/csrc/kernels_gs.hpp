@@ -25,7 +25,13 @@ constexpr int kGsSmallBlock = 64;     // blocks of <= 64 rows run one wave per w
 constexpr int kGsFresh = 16;          // in-block entries of a row held in registers
 static_assert(kGsFresh % 4 == 0, "the substitution reads its slots in groups of four");
 constexpr int kGsBatch = 8;           // entries past those loaded together in a depth step
-constexpr int kGsDenseRow = 64;       // mean row length from which a level's blocks are inverted (k_hgs_dense)
+// Levels whose blocks are inverted (gs_dense_level; the figures are at k_hgs_dense):
+// rows of kGsDenseRow entries or more on average, and before a row in its block
+// kGsDenseInBlock on average, kGsDenseFew where the inverses of a direction
+// take at most kGsDenseBytes.
+constexpr int kGsDenseRow = 64;
+constexpr double kGsDenseInBlock = 8.0, kGsDenseFew = 6.0;
+constexpr double kGsDenseBytes = 64 << 20;
 
 // One sweep from t = r - A x_old (ZERO: x_old = 0 and t = r, the first
 // pre-smoothing sweep).  Row i of the block: d_i = (t_i - sum_{fresh j}
@@ -119,19 +125,35 @@ static __global__ __launch_bounds__(MAXB) void k_hgs(
 }
 
 // ----------------------------------------------------------------------------
-// Levels with long rows (kGsDenseRow entries or more on average: smoothed
-// Galerkin levels).  A block of 256 such rows is almost a dense triangle (59
-// to 72 in-block entries before a row, mean depth 188 to 202 of 255), so its
-// substitution is a chain of about 200 steps, each waiting on memory for the
-// row's entries: 780 us a sweep on a level of 23,032 rows, whatever its size.
-// The triangles are inverted instead, once at setup: W = (L_pp + D_pp)^-1
-// (backward: (U_pp + D_pp)^-1), and a sweep is one product d = W t, with no
-// chain and about the substitution's bytes (a row of W holds at most its
-// position in the block: 160 values on average, against 60 to 70 values and
-// columns): 5.2 us a sweep on that level, the inversion 0.49 ms per direction.
+// Levels with long rows (smoothed Galerkin levels, wide stencils).  The rows of a
+// block of 256 then hold tens of entries in it (23, 42 and 104 before a row on
+// the three levels of the 56^3 trilinear operator's smoothed hierarchy), so its
+// substitution is a chain of some 200 steps, each waiting on memory for the
+// row's entries: 417, 592 and 1516 us a sweep on those levels of 23,032, 2,912
+// and 369 rows (FP64, with the residual's pass).  The triangles are inverted
+// instead, once at setup: W = (L_pp + D_pp)^-1 (backward: (U_pp + D_pp)^-1), and
+// a sweep is one product d = W t, with no chain (a row of W holds at most its
+// position in the block: 160 values on average): 17, 12 and 8 us there, the
+// inversion 0.49 ms per direction.
 // On levels with short rows the substitution stays: level 0 of the
 // 27-point operator holds 3 to 4 in-block entries a row, so W would be twice
 // the whole matrix (45 us a sweep there, against 47 us for W's bytes alone).
+//
+// Where the line lies (gs_dense_level).  The chain costs with the entries a row
+// has in its block, once they are more than the registers hold; W costs with
+// its tiles, which a block of less than 64 rows fills badly (32 KB a block, 4 KB
+// a row at nb = 8).  A sweep, substitution -> product, us (both with the
+// residual's pass), m the mean entries before a row in its block:
+//   23,032 rows of 121:   nb 16, m 5.4, FP64 16 -> 19, FP32 14 -> 12;
+//                         nb 24, m 7.5, 21 -> 15; nb 64, m 15, 76 -> 13
+//   262 thousand of 118:  nb 8, m 2.7, 105 -> 238; nb 24, m 6.7, 95 -> 127;
+//                         nb 32, m 8.3, 101 -> 108, FP32 83 -> 68;
+//                         nb 48, m 10.5, 126 -> 91; nb 256, m 22, 564 -> 137
+//   1.33 million of 121:  nb 8, 537 -> 1205; nb 24, m 6.7, 549 -> 634;
+//                         nb 32, m 8.2, 574 -> 560, FP32 443 -> 319;
+//                         nb 48, m 10.5, 652 -> 488; nb 256, 2346 -> 679
+//   100 thousand of 81, columns anywhere: nb 256, m 1.3, 62 -> 73.
+// With m >= 8 (blocks of 17 rows or more) W holds at most 241 values a row.
 //
 // W is stored in 64 x 64 tiles, column-major inside a tile, so that the 64
 // lanes of a wave (one row each) read 512 consecutive bytes per column; only
