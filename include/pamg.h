@@ -430,8 +430,10 @@ typedef struct {
 int pamg_server_opts_default(pamg_server_opts *o);
 /* An upper estimate of the device bytes an operator can hold in a server
  * (A: host CSR; precision: the V-cycle's): its hierarchy plus its 16-column
- * engine.  Admission charges the hierarchy part of it for an uncached
- * operator, then the exact figure once the hierarchy exists; the engine is
+ * engine, with either setting of single_path.  Admission charges the
+ * hierarchy part of it for an uncached operator (less the dense operator of
+ * the cycle's last levels, which only single_path solves use, where that is
+ * 0), then the exact figure once the hierarchy exists; the engine is
  * built (and charged, exactly) only when the operator's requests first run
  * as a batch.  Under budget pressure the engines of idle operators are freed
  * before idle operators are evicted; an engine that can never fit beside its

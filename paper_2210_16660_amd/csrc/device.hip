@@ -605,7 +605,7 @@ static void launch_coarse(int nL, const T* ainv, const RT* r, const int* aggptr_
 // for the two launches of a level.  (serve.hip charges the bound.)
 
 static int tail_level(const pamg_hierarchy* h) {
-    if (h->smoother != PAMG_SMOOTHER_L1_JACOBI || h->smoothed_p) return h->L;
+    if (!h->with_tail || h->smoother != PAMG_SMOOTHER_L1_JACOBI || h->smoothed_p) return h->L;
     int t = h->L;
     while (t > 1) {
         const long long n = h->idx[t - 1].n;
@@ -1568,6 +1568,7 @@ pamg_hierarchy* finish_build(std::unique_ptr<HostBuild> b, hipStream_t stream, p
     pamg_hierarchy* h = new_hierarchy(b->prm.host_only != 0, ctx);
     h->smoother = b->prm.smoother;
     h->smoothed_p = b->prm.smooth_prolongator != 0;
+    h->with_tail = b->with_tail;
     if (h->smoother == PAMG_SMOOTHER_HYBRID_GS) {
         h->sweeps = b->prm.sweeps > 0 ? b->prm.sweeps : 4;
         h->gs_block = b->prm.gs_block > 0 ? b->prm.gs_block : 256;
@@ -1601,11 +1602,12 @@ pamg_hierarchy* finish_build(std::unique_ptr<HostBuild> b, hipStream_t stream, p
 }
 
 pamg_hierarchy* device_setup_build(const pamg_csr& A, const pamg_params& prm, hipStream_t stream,
-                                   pamg_context* ctx) {
+                                   pamg_context* ctx, bool with_tail) {
     auto t0 = std::chrono::steady_clock::now();
     set_num_threads(prm.num_threads > 0 ? prm.num_threads : 0);
     validate_csr_header(A);   // the rows are checked on the device (or by the host build)
     pamg_hierarchy* h = new_hierarchy(false, ctx);
+    h->with_tail = with_tail;
     try {
         std::unique_ptr<DeviceBuild> db = device_build(h, A, prm, stream);
         if (!db) {

@@ -144,6 +144,7 @@ struct pamg_hierarchy {
     int sweeps = 1, gs_block = 256;
     double omega = 1.0;
     bool smoothed_p = false;                  // smoothed prolongators (general sparse P)
+    bool with_tail = true;                    // false: only the batch engine runs on it, which goes to the coarsest level
     int tail = 0;                             // level from which the l1-Jacobi cycle is one dense product (<= L)
     std::vector<pamg::DevLevelIdx> idx;
     pamg::DevVals<double> f64;
@@ -204,6 +205,7 @@ struct HostBuild {
     HostHierarchy H;
     std::vector<LayoutLevel> lay;
     pamg_params prm{};
+    bool with_tail = true;             // pamg_hierarchy::with_tail
     double host_ms = 0.0;
 };
 std::unique_ptr<HostBuild> host_build(const pamg_csr& A, const pamg_params& prm);
@@ -213,7 +215,8 @@ pamg_hierarchy* finish_build(std::unique_ptr<HostBuild> b, hipStream_t stream, p
 // The hierarchy with its large levels built on the device, or null when the
 // device construction does not apply (prm already checked; A's rows are
 // validated on the device, as validate_csr would).
-pamg_hierarchy* device_setup_build(const pamg_csr& A, const pamg_params& prm, hipStream_t stream, pamg_context* ctx);
+pamg_hierarchy* device_setup_build(const pamg_csr& A, const pamg_params& prm, hipStream_t stream, pamg_context* ctx,
+                                   bool with_tail = true);
 // Host copies (canonical numbering) of the device-built levels, made once
 // from the device arrays: matrix, l1 inverse diagonal, aggregates and
 // prolongator entries (no near-null vector).

@@ -143,8 +143,12 @@ static double ms_between(Clock::time_point a, Clock::time_point b) {
 // as a batch, and is charged then.
 static uint64_t dense_bytes(uint64_t nL, int prec) { return nL * nL * (prec == PAMG_PREC_F32 ? 12 : 8); }
 
-// Bound of the dense operator of the cycle's last levels (device.hip,
-// tail_level), whose size the hierarchy fixes.
+// Whether the operators of S get the dense operator of the cycle's last levels:
+// only the single-right-hand-side solver runs it.
+static bool with_tail(const pamg_server* S) { return S->opts.single_path != 0; }
+
+// Bound of that operator (device.hip, tail_level), whose size the hierarchy
+// fixes.
 static uint64_t tail_bytes(const pamg_csr& A, int prec) {
     const uint64_t n = (uint64_t)A.n, nnz = (uint64_t)A.nnz, rows = kTailRows;
     const uint64_t entries = std::max(std::min(kTailShare * nnz, rows * rows), std::min(nnz, 4 * rows * rows));
@@ -169,19 +173,19 @@ static double sell_room(const pamg_csr& A, int prec) {
     return std::max(0.0, bytes);
 }
 
-static uint64_t estimate_core(const pamg_csr& A, int prec) {
+static uint64_t estimate_core(const pamg_csr& A, int prec, bool tail) {
     const double cx = 2.3;
     const double n = (double)A.n, nnz = (double)A.nnz;
     double hier = cx * (nnz * (4 + 8 + 8) + n * 80) + 96.0 * n + (1 << 18);
     if (prec == PAMG_PREC_F32) hier += cx * (nnz * 8 + n * 32) + 4.0 * n;
-    return (uint64_t)(hier + sell_room(A, prec)) + tail_bytes(A, prec);
+    return (uint64_t)(hier + sell_room(A, prec)) + (tail ? tail_bytes(A, prec) : 0);
 }
 
 // ... plus the dense inverse of a coarsest level of the usual size (at most
 // the default max_coarse rows); a stalled coarsening can leave a larger one,
 // which admission charges once the host phase has fixed n_L.
-static uint64_t hierarchy_estimate(const pamg_csr& A, int prec) {
-    return estimate_core(A, prec) + dense_bytes(std::min<uint64_t>((uint64_t)A.n, 200), prec);
+static uint64_t hierarchy_estimate(const pamg_csr& A, int prec, bool tail) {
+    return estimate_core(A, prec, tail) + dense_bytes(std::min<uint64_t>((uint64_t)A.n, 200), prec);
 }
 
 // Upper estimate of the 16-column engine before the hierarchy exists (the
@@ -196,9 +200,9 @@ static uint64_t engine_estimate(uint64_t n, int prec) {
 }
 
 // What an operator can hold in the server: its hierarchy and, once its
-// requests run as a batch, its engine.
+// requests run as a batch, its engine (either setting of single_path).
 uint64_t estimate_bytes(const pamg_csr& A, int prec) {
-    return hierarchy_estimate(A, prec) + engine_estimate((uint64_t)A.n, prec);
+    return hierarchy_estimate(A, prec, true) + engine_estimate((uint64_t)A.n, prec);
 }
 
 // Bytes of one batched iteration at a width of `columns`.
@@ -319,8 +323,8 @@ static bool ensure_engine(pamg_server* S, ServeGroup* g, bool evict_operators) {
 
 // Upper bound of the device bytes of an operator whose host phase is done:
 // the estimate with the dense coarsest inverse at its actual size.
-static uint64_t bound_bytes(const SetupJob& j, int prec) {
-    return estimate_core(j.A, prec) + dense_bytes((uint64_t)coarsest_n(*j.built), prec);
+static uint64_t bound_bytes(const SetupJob& j, int prec, bool tail) {
+    return estimate_core(j.A, prec, tail) + dense_bytes((uint64_t)coarsest_n(*j.built), prec);
 }
 
 static void fail_key(pamg_server* S, uint64_t key, int status) {
@@ -340,7 +344,7 @@ static void request_setup(pamg_server* S, ServeRequest* q) {
     const uint64_t key = q->r.op_key;
     if (S->groups.count(key) || S->setups.count(key)) return;
     if (!q->r.A) throw Error(PAMG_E_INVALID, "request for an uncached operator carries no matrix");
-    if (hierarchy_estimate(*q->r.A, S->opts.precision) > S->opts.hbm_budget_bytes) throw Error(PAMG_E_BUSY, "");
+    if (hierarchy_estimate(*q->r.A, S->opts.precision, with_tail(S)) > S->opts.hbm_budget_bytes) throw Error(PAMG_E_BUSY, "");
     SetupJob* j = new SetupJob();
     j->key = key;
     j->A = *q->r.A;
@@ -439,7 +443,7 @@ static void admit_ready(pamg_server* S) {
             continue;
         }
         if (j->reserved) release_reservation(S, j);   // the device construction did not apply
-        const uint64_t need = bound_bytes(*j, prec);
+        const uint64_t need = bound_bytes(*j, prec, with_tail(S));
         if (need > budget) {
             it = S->setups.erase(it);
             fail_key(S, j->key, PAMG_E_BUSY);
@@ -486,8 +490,8 @@ static void admit_ready(pamg_server* S) {
 // the canonical levels and per-level scratch of the construction (about 40
 // bytes per stored entry and 128 per row of the input, with the coarse
 // levels' share).
-static uint64_t device_build_bound(const pamg_csr& A, int prec) {
-    return hierarchy_estimate(A, prec) + 40ull * (uint64_t)A.nnz + 128ull * (uint64_t)A.n + (1ull << 20);
+static uint64_t device_build_bound(const pamg_csr& A, int prec, bool tail) {
+    return hierarchy_estimate(A, prec, tail) + 40ull * (uint64_t)A.nnz + 128ull * (uint64_t)A.n + (1ull << 20);
 }
 
 // Ask the scheduler for `need` bytes of the budget; false if refused (more
@@ -522,13 +526,13 @@ static void setup_main(pamg_server* S, int threads) {
         try {
             if (device_setup_applies(prm) && j->A.n > std::max({kDeviceMinRows, prm.max_dense, prm.max_coarse})) {
                 validate_csr_header(j->A);   // the rows are checked by the build
-                j->need = device_build_bound(j->A, S->opts.precision);
+                j->need = device_build_bound(j->A, S->opts.precision, with_tail(S));
                 // refused (the build's bound exceeds the whole budget): the
                 // host construction, whose admission needs only the hierarchy
                 if (wait_for_room(S, j)) {
                     HIP_CHECK(hipStreamCreateWithFlags(&j->stream, hipStreamNonBlocking));
                     const auto t0 = Clock::now();
-                    j->h = device_setup_build(j->A, prm, j->stream, S->ctx);
+                    j->h = device_setup_build(j->A, prm, j->stream, S->ctx, with_tail(S));
                     j->build_ms = ms_between(t0, Clock::now());
                     if (!j->h) {
                         (void)hipStreamDestroy(j->stream);
@@ -536,7 +540,10 @@ static void setup_main(pamg_server* S, int threads) {
                     }
                 }
             }
-            if (!j->h) j->built = host_build(j->A, prm);
+            if (!j->h) {
+                j->built = host_build(j->A, prm);
+                j->built->with_tail = with_tail(S);
+            }
         } catch (const Error& e) {
             j->status = e.code;
             j->error = e.what();
