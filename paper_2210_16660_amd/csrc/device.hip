@@ -1602,14 +1602,14 @@ pamg_hierarchy* finish_build(std::unique_ptr<HostBuild> b, hipStream_t stream, p
 }
 
 pamg_hierarchy* device_setup_build(const pamg_csr& A, const pamg_params& prm, hipStream_t stream,
-                                   pamg_context* ctx, bool with_tail) {
+                                   pamg_context* ctx, bool with_tail, int max_coarsest) {
     auto t0 = std::chrono::steady_clock::now();
     set_num_threads(prm.num_threads > 0 ? prm.num_threads : 0);
     validate_csr_header(A);   // the rows are checked on the device (or by the host build)
     pamg_hierarchy* h = new_hierarchy(false, ctx);
     h->with_tail = with_tail;
     try {
-        std::unique_ptr<DeviceBuild> db = device_build(h, A, prm, stream);
+        std::unique_ptr<DeviceBuild> db = device_build(h, A, prm, max_coarsest, stream);
         if (!db) {
             destroy_hierarchy(h);
             return nullptr;

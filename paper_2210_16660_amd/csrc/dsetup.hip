@@ -1087,7 +1087,7 @@ void device_gs_schedule(pamg_hierarchy* h, DevLevelOut& D, int nb, hipStream_t s
     if (read1(bad, s)) throw Error(PAMG_E_NOT_SPD, "non-positive diagonal on a coarse level (Gauss-Seidel smoother)");
 }
 
-std::unique_ptr<DeviceBuild> device_build(pamg_hierarchy* h, const pamg_csr& A, const pamg_params& prm,
+std::unique_ptr<DeviceBuild> device_build(pamg_hierarchy* h, const pamg_csr& A, const pamg_params& prm, int max_coarsest,
                                           hipStream_t s) {
     std::unique_ptr<DeviceBuild> out(new DeviceBuild());
     Temps T{h->ctx, s, {}, {}};
@@ -1161,6 +1161,7 @@ std::unique_ptr<DeviceBuild> device_build(pamg_hierarchy* h, const pamg_csr& A, 
         if (AL.n > prm.max_dense)
             throw Error(PAMG_E_STALLED, "coarsening stalled at " + std::to_string(AL.n) +
                                             " unknowns, above the dense-solve limit");
+        if (AL.n > max_coarsest) return nullptr;
         if (steps > 1) compose_levels(Hs, steps);
         out->host_lay = build_layout(Hs);
     }

@@ -73,7 +73,7 @@ bool device_setup_applies(const pamg_params& prm);
 // device; device arrays are allocated on h.  Null: nothing to build on the
 // device (a small or asymmetric-pattern input, or long rows): the host build
 // applies.
-std::unique_ptr<DeviceBuild> device_build(pamg_hierarchy* h, const pamg_csr& A, const pamg_params& prm,
+std::unique_ptr<DeviceBuild> device_build(pamg_hierarchy* h, const pamg_csr& A, const pamg_params& prm, int max_coarsest,
                                           hipStream_t s);
 
 }  // namespace pamg

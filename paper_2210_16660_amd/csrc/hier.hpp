@@ -198,6 +198,9 @@ inline int vec_grid(long long n) {
 }
 void require_device(const pamg_hierarchy* h);
 
+// Dense limit of the coarsest level (its FP64 inverse is n_L^2 doubles).
+constexpr int kMaxDense = 8192;
+
 // Setup in two phases: the host phase (validation, hierarchy, layout) needs
 // no device; the device phase uploads it, factorizes the coarsest level and
 // returns the hierarchy (or, with host_only, keeps it on the host).
@@ -214,17 +217,16 @@ int coarsest_n(const HostBuild& b);
 pamg_hierarchy* finish_build(std::unique_ptr<HostBuild> b, hipStream_t stream, pamg_context* ctx);
 // The hierarchy with its large levels built on the device, or null when the
 // device construction does not apply (prm already checked; A's rows are
-// validated on the device, as validate_csr would).
+// validated on the device, as validate_csr would) or the coarsest level has more
+// than max_coarsest rows (found before its dense inverse is allocated).
 pamg_hierarchy* device_setup_build(const pamg_csr& A, const pamg_params& prm, hipStream_t stream, pamg_context* ctx,
-                                   bool with_tail = true);
+                                   bool with_tail = true, int max_coarsest = kMaxDense);
 // Host copies (canonical numbering) of the device-built levels, made once
 // from the device arrays: matrix, l1 inverse diagonal, aggregates and
 // prolongator entries (no near-null vector).
 void ensure_host_levels(pamg_hierarchy* h);
 void check_params(const pamg_params& prm);
 
-// Dense limit of the coarsest level (its FP64 inverse is n_L^2 doubles).
-constexpr int kMaxDense = 8192;
 // A_L^{-1} (FP64, n x n row-major, symmetric) of the coarsest level from its
 // device CSR: Cholesky and inverse on the matrix cores (dense.hip).  Throws
 // PAMG_E_NOT_SPD on a non-positive pivot.  Synchronizes the stream.

@@ -30,6 +30,7 @@
 
 #include <algorithm>
 #include <chrono>
+#include <cmath>
 #include <condition_variable>
 #include <cstring>
 #include <deque>
@@ -494,6 +495,16 @@ static uint64_t device_build_bound(const pamg_csr& A, int prec, bool tail) {
     return hierarchy_estimate(A, prec, tail) + 40ull * (uint64_t)A.nnz + 128ull * (uint64_t)A.n + (1ull << 20);
 }
 
+// The largest coarsest level whose dense inverse that covers once the
+// construction's scratch is given back: the exact bytes of the operator then
+// stay within the reservation they replace.  An operator with a larger one
+// (coarsening stalled on vertices without strong couplings) is built on the
+// host, whose admission charges the inverse at its size.
+static int max_coarsest(const pamg_csr& A, int prec) {
+    const double room = (double)(device_build_bound(A, prec, false) - estimate_core(A, prec, false));
+    return (int)std::min((double)kMaxDense, std::sqrt(room / (double)dense_bytes(1, prec)));
+}
+
 // Ask the scheduler for `need` bytes of the budget; false if refused (more
 // than the budget) or if the server ended.
 static bool wait_for_room(pamg_server* S, SetupJob* j) {
@@ -532,7 +543,8 @@ static void setup_main(pamg_server* S, int threads) {
                 if (wait_for_room(S, j)) {
                     HIP_CHECK(hipStreamCreateWithFlags(&j->stream, hipStreamNonBlocking));
                     const auto t0 = Clock::now();
-                    j->h = device_setup_build(j->A, prm, j->stream, S->ctx, with_tail(S));
+                    j->h = device_setup_build(j->A, prm, j->stream, S->ctx, with_tail(S),
+                                              max_coarsest(j->A, S->opts.precision));
                     j->build_ms = ms_between(t0, Clock::now());
                     if (!j->h) {
                         (void)hipStreamDestroy(j->stream);
