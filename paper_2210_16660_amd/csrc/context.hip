@@ -67,8 +67,8 @@ void ctx_free(pamg_context* c, void* p, size_t bytes, hipStream_t s) {
     c->live.fetch_sub(bytes == 0 ? 1 : bytes);
 }
 
-void ctx_free_all(pamg_context* c, std::vector<DevAlloc>& list) {
-    for (const DevAlloc& a : list) ctx_free(c, a.p, a.bytes, nullptr);
+void ctx_free_all(pamg_context* c, std::vector<DevAlloc>& list, hipStream_t s) {
+    for (const DevAlloc& a : list) ctx_free(c, a.p, a.bytes, s);
     list.clear();
 }
 

@@ -337,6 +337,7 @@ std::unique_ptr<DenseWork> dense_work(pamg_context* ctx, int n, hipStream_t s) {
     const size_t NN = (size_t)N * N;
     std::unique_ptr<DenseWork> w(new DenseWork());
     w->ctx = ctx;
+    w->s = s;
     auto get = [&](size_t bytes) {
         void* p = ctx_alloc(ctx, bytes, s);
         w->bufs.push_back({p, bytes});

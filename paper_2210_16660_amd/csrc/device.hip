@@ -619,6 +619,7 @@ std::unique_ptr<TailWork> tail_work(pamg_hierarchy* h, hipStream_t s) {
     std::unique_ptr<TailWork> w(new TailWork());
     if (h->tail >= h->L) return w;
     w->ctx = h->ctx;
+    w->s = s;
     auto get = [&](size_t bytes) {
         void* p = ctx_alloc(h->ctx, bytes, s);
         w->bufs.push_back({p, bytes});

@@ -84,7 +84,7 @@ struct Temps {
             }
     }
     // The stream has been waited for since the last release.
-    void drain() { ctx_free_all(ctx, pending); }
+    void drain() { ctx_free_all(ctx, pending, s); }
     void release_now(void* p, void* q) {
         release(p);
         release(q);
@@ -93,8 +93,8 @@ struct Temps {
     }
     ~Temps() {
         (void)hipStreamSynchronize(s);
-        ctx_free_all(ctx, pending);
-        ctx_free_all(ctx, list);
+        ctx_free_all(ctx, pending, s);
+        ctx_free_all(ctx, list, s);
     }
 };
 

@@ -43,7 +43,7 @@ pamg_context* default_context(int device);
 void* ctx_alloc(pamg_context* c, size_t bytes, hipStream_t s);
 void ctx_free(pamg_context* c, void* p, size_t bytes, hipStream_t s);
 // Free a list of buffers (the device must be idle) and clear it.
-void ctx_free_all(pamg_context* c, std::vector<DevAlloc>& list);
+void ctx_free_all(pamg_context* c, std::vector<DevAlloc>& list, hipStream_t s = nullptr);
 
 template <typename T>
 struct DevVals {
@@ -237,8 +237,9 @@ struct DenseWork {
     std::vector<DevAlloc> bufs;
     double *M = nullptr, *X = nullptr, *D = nullptr;
     int* flag = nullptr;
+    hipStream_t s = nullptr;
     ~DenseWork() {
-        if (ctx) ctx_free_all(ctx, bufs);
+        if (ctx) ctx_free_all(ctx, bufs, s);
     }
 };
 constexpr int kTailRows = 1024;       // the dense operator of the cycle's last levels (tail_level)
@@ -251,8 +252,9 @@ struct TailWork {
     std::vector<DevAlloc> bufs;
     double *B[2] = {nullptr, nullptr}, *G = nullptr;
     int* own = nullptr;
+    hipStream_t s = nullptr;
     ~TailWork() {
-        if (ctx) ctx_free_all(ctx, bufs);
+        if (ctx) ctx_free_all(ctx, bufs, s);
     }
 };
 std::unique_ptr<TailWork> tail_work(pamg_hierarchy* h, hipStream_t s);
