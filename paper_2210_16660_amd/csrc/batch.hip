@@ -463,6 +463,12 @@ static hipGraphExec_t block_graph(BatchEngine* E, int krylov, int k) {
     return ex;
 }
 
+void batch_prepare_graphs(BatchEngine* E, int krylov, int k) {
+    const int lw = E->lw;
+    for (E->lw = 2; E->lw <= 4; ++E->lw) (void)block_graph(E, krylov, k);
+    E->lw = lw;
+}
+
 void release_engine(pamg_hierarchy* h, int prec) { h->batch[prec].reset(); }   // destroy_batch synchronizes
 
 // Device bytes of the 16-column engine of h (the allocations create_engine makes).

@@ -13,7 +13,8 @@
 //     budget, freeing idle operators' 16-column engines and then evicting
 //     idle cached operators in least-recently-used order; otherwise it waits;
 //   * batching: every cached operator is a group with its own stream and 16
-//     columns; a batch is as wide as the columns in use need (4, 8 or 16); a
+//     columns; a batch starts as wide as its columns need (4, 8 or 16) and is
+//     widened for columns that join, never narrowed while one runs; a
 //     waiting request takes a free column between iteration blocks
 //     and its recurrence starts there (columns are independent, so a result
 //     is the same whatever else is in the group);
@@ -314,6 +315,9 @@ static bool ensure_engine(pamg_server* S, ServeGroup* g, bool evict_operators) {
     const uint64_t need = engine_bytes(g->h, prec);
     if (need > S->opts.hbm_budget_bytes || !make_room(S, need, g, evict_operators)) return false;
     g->E = get_engine(g->h, prec, g->stream);
+    // every width's graph now: a capture makes the application's device-wide
+    // calls fail, so none is left for a width's first block in mid-traffic
+    if (S->opts.use_graph) batch_prepare_graphs(g->E, PAMG_KRYLOV_FCG, S->opts.block_iters);
     g->engine = batch_bytes(g->E);
     g->bytes += g->engine;
     std::lock_guard<std::mutex> lk(S->mu);
