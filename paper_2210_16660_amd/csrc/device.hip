@@ -1441,11 +1441,16 @@ static void time_op_impl(pamg_hierarchy* h, DevVals<T>& V, int op, int l, int re
                                   h->partial_b, nodone, s);
         };
     } else if (op == PAMG_OP_SMOOTH) {
-        // one backward hybrid Gauss-Seidel sweep: CSR (int32 columns), own r,
-        // x_old, 1/a_ii, depth, x_new; per block its largest depths
+        // one backward hybrid Gauss-Seidel sweep by substitution: CSR (int32
+        // columns), own r, x_old, 1/a_ii, depth, x_new; per block its largest
+        // depths.  With inverted blocks: the residual's pass (matrix, x_old, r,
+        // t), then the inverses, t, x_old, x_new
         if (h->smoother != PAMG_SMOOTHER_HYBRID_GS || l >= h->L)
             throw Error(PAMG_E_INVALID, "SMOOTH needs a hybrid Gauss-Seidel hierarchy and level < L");
         *bytes = I.nnz * (4 + sz) + 4 * (n + 1) + n * ((l == 0 ? 8 : sz) + 3 * sz + 1) + 8 * (uint64_t)I.gs_nblk;
+        if (V.gsw_b[l])
+            *bytes = M + (uint64_t)I.gs_nblk * (uint64_t)gs_dense_block(h->gs_block) * sz +
+                     n * ((l == 0 ? 8 : sz) + 5 * sz);
         DevVals<T>* Vp = &V;
         const bool small = h->gs_block <= kGsSmallBlock;
         if (l == 0)

@@ -523,7 +523,6 @@ static __global__ __launch_bounds__(kBlock, 4) void k_up(
 // over the chip (one workgroup took 13 us at 130 rows, this form about 5).  The
 // prolongation's operands are loaded ahead of the product.
 constexpr int kCoarseThreads = 1024;         // the 16-column engine's single-workgroup product
-constexpr int kCoarseRowsMin = 512;          // above this size that engine's runs on many workgroups
 constexpr int kCoarseRowsPerBlock = kBlock / 64;
 static_assert((1 << kMaxAggSteps) <= 64, "one lane per member of an aggregate");
 inline int coarse_rows_grid(int nL) { return (nL + kCoarseRowsPerBlock - 1) / kCoarseRowsPerBlock; }

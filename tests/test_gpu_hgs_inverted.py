@@ -104,6 +104,21 @@ def test_inverted_blocks_follow_new_coefficients(n, nb):
     assert np.array_equal(*xs)
 
 
+@pytest.mark.parametrize("nb,strips", [(8, 0), (40, 1), (256, 4)])
+def test_a_timed_sweep_counts_the_bytes_of_its_kernel(nb, strips):
+    # strips: 64-row strips of an inverted block (0: substitution)
+    A = stencil125(12, 7)
+    H = pamg.Hierarchy(A, smoother="hgs", gs_block=nb, build_f32=1)
+    n, nnz, blocks = A.n, len(A.col), -(-A.n // nb)
+    for prec, sz in ((pamg.PREC_F64, 8), (pamg.PREC_F32, 4)):
+        matrix = H.time_op(pamg.OP_SPMV, 0, 1, prec)[1] - n * (sz + 8)
+        if strips:
+            want = matrix + blocks * strips * (strips + 1) // 2 * 64 * 64 * sz + n * (8 + 5 * sz)
+        else:
+            want = nnz * (4 + sz) + 4 * (n + 1) + n * (8 + 3 * sz + 1) + 8 * blocks
+        assert H.time_op(pamg.OP_SMOOTH, 0, 1, prec)[1] == want
+
+
 def hierarchical_order(H):
     """Position of every level-0 row in nested-aggregate order."""
     sizes = H.level_sizes()[0]
