@@ -41,7 +41,8 @@ matrix bytes (16-bit dictionary positions), reported beside it.  The
 roofline "traffic" figure comes from profiles/traffic_q1_<n>.json (HBM bytes
 per launch from FETCH_SIZE/WRITE_SIZE counter runs, calibrated on a plain
 copy); it is reported only for the workload, precision and kernel source it
-was measured on (SHA-256 of csrc/kernels.hpp), else null.
+was measured on (SHA-256 of csrc/kernels.hpp and csrc/kernels_sell.hpp), else
+null.
 
 The CPU baseline runs the oracle in a child process started at once: its
 hierarchy setup (minutes at 256^3) overlaps the GPU work, and its solve
@@ -61,11 +62,11 @@ ROOT = os.path.dirname(os.path.abspath(__file__))
 sys.path.insert(0, ROOT)
 
 HBM_PEAK_GBS = 8000.0
-KERNELS_SRC = os.path.join(ROOT, "paper_2210_16660_amd", "csrc", "kernels.hpp")
+KERNELS_SRC = [os.path.join(ROOT, "paper_2210_16660_amd", "csrc", f) for f in ("kernels.hpp", "kernels_sell.hpp")]
 
 
 def kernels_hash() -> str:
-    return hashlib.sha256(open(KERNELS_SRC, "rb").read()).hexdigest()
+    return hashlib.sha256(b"".join(open(f, "rb").read() for f in KERNELS_SRC)).hexdigest()
 
 
 def traffic_for(kernel: str, n: int, precision: str, agg_steps: int):
@@ -77,7 +78,7 @@ def traffic_for(kernel: str, n: int, precision: str, agg_steps: int):
     except (OSError, ValueError):
         return None
     cfg = rec.get("config", {})
-    if (rec.get("kernels_hpp_sha256") != kernels_hash() or cfg.get("n_elements") != n
+    if (rec.get("kernels_sha256") != kernels_hash() or cfg.get("n_elements") != n
             or cfg.get("precision") != precision or cfg.get("agg_steps") != agg_steps):
         return None
     k = rec.get("kernels", {}).get(kernel)

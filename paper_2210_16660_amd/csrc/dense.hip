@@ -17,7 +17,7 @@
 //   then     A^{-1} = X^T X on the lower block triangle, mirrored.
 // The two halves need the same panel, so they share its launches (with five
 // launches a block column the substitution alone took 34 us of them).
-// n = 2675: 8.7 -> 2.8 ms (a block column: panel 13 us, update 43 us, of
+// n = 2675: 8.7 -> 1.9 ms (a block column: panel 5.9 us, update 32.5 us, of
 // which the next diagonal tile's serial factorization is the longer part).
 // Every tile product runs on the matrix cores (v_mfma_f64_16x16x4_f64): one
 // wave per 16-row strip of the 64 x 64 output tile, four 16-column tiles.

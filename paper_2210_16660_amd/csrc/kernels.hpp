@@ -71,9 +71,10 @@ struct RowIdx {
 };
 
 // a and b (uniform) have both been asked for when either is waited for: their
-// loads are not moved behind a branch below.  (The converged flag and the first descriptor, row or partials of a kernel are
-// loads of their own, written by other XCDs; waiting for one after the other
-// cost 0.6 us of the 4 us that a launch on a small level takes.)
+// loads are not moved behind a branch below.  (The converged flag and the first
+// descriptor, row or partials of a kernel are loads of their own, written by
+// other XCDs; waiting for one after the other cost 0.6 us of the 4 us that a
+// launch on a small level takes.)
 __device__ __forceinline__ void issued(int& a, int& b) { asm volatile("" : "+s"(a), "+s"(b)); }
 
 // Tiles handled by this workgroup: first, first+stride, ... < end.

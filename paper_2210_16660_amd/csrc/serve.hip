@@ -141,8 +141,8 @@ static double ms_between(Clock::time_point a, Clock::time_point b) {
 // and the restriction values (plus their FP32 copies), vectors; coarse levels
 // add at most 1.3x the finest (pairwise coarsening), fixed buffers ~0.2 MB.
 // The 16-column engine (eight n x 16 FP64 vectors at level 0 and two
-// n_l x 16 vectors per level, allocated for the widest batch) is built only when the operator's requests run
-// as a batch, and is charged then.
+// n_l x 16 vectors per level, allocated for the widest batch) is built only
+// when the operator's requests run as a batch, and is charged then.
 static uint64_t dense_bytes(uint64_t nL, int prec) { return nL * nL * (prec == PAMG_PREC_F32 ? 12 : 8); }
 
 // Whether the operators of S get the dense operator of the cycle's last levels:
