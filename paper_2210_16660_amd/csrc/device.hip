@@ -643,8 +643,10 @@ void build_tail(pamg_hierarchy* h, TailWork& w, hipStream_t s) {
         const int n = I.n, nc = I.nc;
         double* Bl = l == h->tail ? V.tail : w.B[l & 1];
         LAUNCH(k_tail_owners, vec_grid(nc), 0, s, nc, (const int*)I.aggptr, w.own);
-        LAUNCH(k_tail_g, nc, nc * sizeof(double), s, n, nc, (const int*)I.rp, (const int*)I.ci, (const double*)V.v[l],
-               (const double*)V.dinv[l], (const double*)V.p[l], (const int*)w.own, Bc, w.G);
+        hipLaunchKernelGGL(k_tail_g, dim3((nc + kTailRowsG - 1) / kTailRowsG, kTailParts), dim3(kBlock),
+                           kTailRowsG * nc * sizeof(double), s, n, nc,
+                           (const int*)I.rp, (const int*)I.ci, (const double*)V.v[l], (const double*)V.dinv[l],
+                           (const double*)V.p[l], (const int*)w.own, Bc, w.G);
         LAUNCH(k_tail_b, n, 0, s, n, (const int*)I.rp, (const int*)I.ci, (const double*)V.v[l],
                (const double*)V.dinv[l], (const double*)V.p[l], (const int*)w.own, (const double*)w.G, Bl);
         Bc = Bl;
@@ -1693,8 +1695,9 @@ void ensure_host_levels(pamg_hierarchy* h) {
         H.agg.resize(n);
         parallel_ranges(n, [&](int, int64_t b, int64_t e) {
             std::vector<std::pair<int32_t, double>> row;
-            for (int64_t i = b; i < e; ++i) {
-                const int32_t ip = perm[i];
+            // in the stored order: the rows of a sliced tile share their lines
+            for (int64_t ip = b; ip < e; ++ip) {
+                const int32_t i = iperm[ip];
                 row.clear();
                 const int64_t o0 = I.sell ? rowpos[ip] : rp[ip];
                 for (int32_t k = 0; k < rp[ip + 1] - rp[ip]; ++k)
