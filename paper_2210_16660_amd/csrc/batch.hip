@@ -147,20 +147,24 @@ static void launch_down_b(const DevLevelIdx& I, int v, int lw, const T* vd, cons
     with_variant_at(v, lw, [&](auto u, auto c, int rows) {
         constexpr int U = decltype(u)::value, CPL = decltype(c)::value;
         const int grid = unit_grid(I.nc, rows);
-        const bool pair = I.sell && I.nnz >= kPairRow * (long long)I.n;
-        auto go = [&](auto two, auto rt) {
+        auto go = [&](auto two, auto rt, auto where) {
             using RT = decltype(rt);
-            hipLaunchKernelGGL((kb_down<U, CPL, decltype(two)::value, T, RT>), dim3(grid), dim3(kBlock), 0, s, I.nc, lw,
-                               I.row_idx(), (const int*)I.ci, vd, (const RT*)r, p, (const int*)I.aggptr, rc, done);
+            hipLaunchKernelGGL((kb_down<U, CPL, decltype(two)::value, T, RT, decltype(where)>), dim3(grid), dim3(kBlock),
+                               0, s, I.nc, lw, where, (const int*)I.ci, vd, (const RT*)r, p, (const int*)I.aggptr, rc,
+                               done);
         };
-        if (pair && r_is_f64)
-            go(std::true_type{}, double{});
-        else if (pair)
-            go(std::true_type{}, T{});
-        else if (r_is_f64)
-            go(std::false_type{}, double{});
+        auto of = [&](auto two, auto where) {
+            if (r_is_f64)
+                go(two, double{}, where);
+            else
+                go(two, T{}, where);
+        };
+        if (!I.sell)
+            of(std::false_type{}, CsrRows{I.rp});
+        else if (I.nnz >= kPairRow * (long long)I.n)
+            of(std::true_type{}, SlicedRows{I.rp, I.rowpos});
         else
-            go(std::false_type{}, T{});
+            of(std::false_type{}, SlicedRows{I.rp, I.rowpos});
     });
 }
 
@@ -171,14 +175,17 @@ static void launch_up_b(const DevLevelIdx& I, const DevLevelIdx& F, int v, int l
     with_variant_at(v, lw, [&](auto u, auto c, int rows) {
         constexpr int U = decltype(u)::value, CPL = decltype(c)::value;
         const int grid = unit_grid(I.n, rows);
-        if (rf_is_f64)
-            hipLaunchKernelGGL((kb_up<U, CPL, T, T, double>), dim3(grid), dim3(kBlock), 0, s, I.n, lw, I.row_idx(),
-                               (const int*)I.ci, av, zp, r, dinv, (const int*)F.aggptr, (const double*)r_f, dinv_f,
-                               p_f, zp_f, done);
-        else
-            hipLaunchKernelGGL((kb_up<U, CPL, T, T, T>), dim3(grid), dim3(kBlock), 0, s, I.n, lw, I.row_idx(),
-                               (const int*)I.ci, av, zp, r, dinv, (const int*)F.aggptr, (const T*)r_f, dinv_f, p_f,
-                               zp_f, done);
+        with_rows(I, [&](auto where) {
+            using W = decltype(where);
+            if (rf_is_f64)
+                hipLaunchKernelGGL((kb_up<U, CPL, T, T, double, W>), dim3(grid), dim3(kBlock), 0, s, I.n, lw, where,
+                                   (const int*)I.ci, av, zp, r, dinv, (const int*)F.aggptr, (const double*)r_f, dinv_f,
+                                   p_f, zp_f, done);
+            else
+                hipLaunchKernelGGL((kb_up<U, CPL, T, T, T, W>), dim3(grid), dim3(kBlock), 0, s, I.n, lw, where,
+                                   (const int*)I.ci, av, zp, r, dinv, (const int*)F.aggptr, (const T*)r_f, dinv_f, p_f,
+                                   zp_f, done);
+        });
     });
 }
 
@@ -258,9 +265,11 @@ static int enqueue_vcycle_b(BatchEngine* E, DevVals<T>& V, const double* dv, con
     if constexpr (std::is_same<T, float>::value) zout = E->Z32; else zout = E->Z;
     with_fixed(E->lw, [&](auto c) {
         constexpr int CPL = decltype(c)::value;
-        hipLaunchKernelGGL((kb_up0<CPL, T>), dim3(g), dim3(kBlock), 0, s, I0.n, I0.row_idx(), (const int*)I0.ci,
-                           (const T*)V.v[0], (const T*)E->zp[0], (const T*)r0, (const T*)V.dinv[0], zout, dv,
-                           E->partial, done);
+        with_rows(I0, [&](auto where) {
+            hipLaunchKernelGGL((kb_up0<CPL, T, decltype(where)>), dim3(g), dim3(kBlock), 0, s, I0.n, where,
+                               (const int*)I0.ci, (const T*)V.v[0], (const T*)E->zp[0], (const T*)r0,
+                               (const T*)V.dinv[0], zout, dv, E->partial, done);
+        });
     });
     return g;
 }
@@ -278,16 +287,19 @@ static void enqueue_iteration_b(BatchEngine* E, DevVals<T>& V, int krylov, int p
     const int gk = unit_grid(I0.n, kFixedRows);
     with_fixed(lw, [&](auto c) {
         constexpr int CPL = decltype(c)::value;
-        if (std::is_same<T, float>::value && h->L > 0)
-            hipLaunchKernelGGL((kb_krylov_pq<CPL, float>), dim3(gk), dim3(kBlock), 0, s, I0.n, I0.row_idx(),
-                               (const int*)I0.ci, (const double*)h->f64.v[0], (const float*)E->Z32,
-                               (const double*)E->P[parity], E->P[1 - parity], E->Q, (const double*)E->R,
-                               (const BatchState*)E->st, E->partial, done);
-        else
-            hipLaunchKernelGGL((kb_krylov_pq<CPL, double>), dim3(gk), dim3(kBlock), 0, s, I0.n, I0.row_idx(),
-                               (const int*)I0.ci, (const double*)h->f64.v[0], (const double*)E->Z,
-                               (const double*)E->P[parity], E->P[1 - parity], E->Q, (const double*)E->R,
-                               (const BatchState*)E->st, E->partial, done);
+        with_rows(I0, [&](auto where) {
+            using W = decltype(where);
+            if (std::is_same<T, float>::value && h->L > 0)
+                hipLaunchKernelGGL((kb_krylov_pq<CPL, float, W>), dim3(gk), dim3(kBlock), 0, s, I0.n, where,
+                                   (const int*)I0.ci, (const double*)h->f64.v[0], (const float*)E->Z32,
+                                   (const double*)E->P[parity], E->P[1 - parity], E->Q, (const double*)E->R,
+                                   (const BatchState*)E->st, E->partial, done);
+            else
+                hipLaunchKernelGGL((kb_krylov_pq<CPL, double, W>), dim3(gk), dim3(kBlock), 0, s, I0.n, where,
+                                   (const int*)I0.ci, (const double*)h->f64.v[0], (const double*)E->Z,
+                                   (const double*)E->P[parity], E->P[1 - parity], E->Q, (const double*)E->R,
+                                   (const BatchState*)E->st, E->partial, done);
+        });
     });
     hipLaunchKernelGGL(kb_fin_alpha, dim3(1), fin, 0, s, lw, E->st, (const double*)E->partial, gk);
     const int g = unit_grid(I0.n, kRowGroups);
@@ -587,10 +599,12 @@ void batch_true_residual(BatchEngine* E, int restart_mask, double* relres, hipSt
     pamg_hierarchy* h = E->h;
     const DevLevelIdx& I0 = h->idx[0];
     const int g = unit_grid(I0.n, kRowGroups), W = 1 << E->lw;
-    hipLaunchKernelGGL(kb_resid, dim3(g), dim3(kRowGroups << E->lw), 0, s, I0.n, E->lw, I0.row_idx(), (const int*)I0.ci,
-                       (const double*)h->f64.v[0], (const double*)E->X, (const double*)E->B, E->Y,
-                       restart_mask ? E->R : (double*)nullptr, restart_mask ? E->R32 : (float*)nullptr, restart_mask,
-                       E->partial_b);
+    with_rows(I0, [&](auto where) {
+        hipLaunchKernelGGL((kb_resid<decltype(where)>), dim3(g), dim3(kRowGroups << E->lw), 0, s, I0.n, E->lw, where,
+                           (const int*)I0.ci, (const double*)h->f64.v[0], (const double*)E->X, (const double*)E->B,
+                           E->Y, restart_mask ? E->R : (double*)nullptr, restart_mask ? E->R32 : (float*)nullptr,
+                           restart_mask, E->partial_b);
+    });
     std::vector<double> part((size_t)g * W);
     HIP_CHECK(hipMemcpyAsync(part.data(), E->partial_b, part.size() * sizeof(double), hipMemcpyDeviceToHost, s));
     HIP_CHECK(hipStreamSynchronize(s));

@@ -191,6 +191,15 @@ inline T* dalloc(pamg_hierarchy* h, size_t count, hipStream_t s = nullptr) {
 bool gs_dense_level(const pamg_hierarchy* h, int l);
 void build_gs_dense(pamg_hierarchy* h, int l, hipStream_t s);
 
+// f(where I stores a row's entries): CsrRows or SlicedRows.
+template <typename F>
+inline void with_rows(const DevLevelIdx& I, F&& f) {
+    if (I.sell)
+        f(SlicedRows{I.rp, I.rowpos});
+    else
+        f(CsrRows{I.rp});
+}
+
 inline int vec_grid(long long n) {
     long long g = (n + kBlock - 1) / kBlock;
     if (g > kMaxGrid) g = kMaxGrid;

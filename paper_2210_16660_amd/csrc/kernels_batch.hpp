@@ -124,16 +124,16 @@ inline int unit_grid(long long nunits, int gpb) {
 // s[q] += the next U entries of a row, in entry order, of a_k x[c_k][col0 + q],
 // all their loads in flight together; TAIL: only the first rem of them (the
 // others repeat the last one's loads and are left out of the sum).
-template <int U, bool TAIL, int CPL, typename T, typename XT>
-__device__ __forceinline__ void entries_accumulate(int o, int st, int rem, const int* __restrict__ ci,
+template <int U, bool TAIL, int ST, int CPL, typename T, typename XT>
+__device__ __forceinline__ void entries_accumulate(int o, int rem, const int* __restrict__ ci,
                                                    const T* __restrict__ av, const XT* __restrict__ x, int lw,
                                                    int col0, T (&s)[CPL]) {
     int c[U];
     T a[U];
 #pragma unroll
-    for (int u = 0; u < U; ++u) c[u] = ci[o + (TAIL ? min(u, rem - 1) : u) * st];
+    for (int u = 0; u < U; ++u) c[u] = ci[o + (TAIL ? min(u, rem - 1) : u) * ST];
 #pragma unroll
-    for (int u = 0; u < U; ++u) a[u] = av[o + (TAIL ? min(u, rem - 1) : u) * st];
+    for (int u = 0; u < U; ++u) a[u] = av[o + (TAIL ? min(u, rem - 1) : u) * ST];
     Vec<XT, CPL> xv[U];
 #pragma unroll
     for (int u = 0; u < U; ++u) xv[u] = vload<XT, CPL>(x + ((size_t)c[u] << lw) + col0);
@@ -151,17 +151,17 @@ __device__ __forceinline__ void entries_accumulate(int o, int st, int rem, const
 // entry after the other before: rows of 7 at unroll 8 were a chain of 7 trips;
 // the Krylov pass over 227 thousand such rows, FP64, 8 columns, 28.7 us, now
 // 20.6, level 0's up-sweep 20.0 and 15.4.)
-template <int U, int CPL, typename T, typename XT>
-__device__ __forceinline__ void tail_accumulate(int o, int st, int rem, const int* __restrict__ ci,
+template <int U, int ST, int CPL, typename T, typename XT>
+__device__ __forceinline__ void tail_accumulate(int o, int rem, const int* __restrict__ ci,
                                                 const T* __restrict__ av, const XT* __restrict__ x, int lw, int col0,
                                                 T (&s)[CPL]) {
     if constexpr (U == 1) {
-        if (rem > 0) entries_accumulate<1, false, CPL, T, XT>(o, st, 1, ci, av, x, lw, col0, s);
+        if (rem > 0) entries_accumulate<1, false, ST, CPL, T, XT>(o, 1, ci, av, x, lw, col0, s);
     } else {
         if (rem > U / 2)
-            entries_accumulate<U, true, CPL, T, XT>(o, st, rem, ci, av, x, lw, col0, s);
+            entries_accumulate<U, true, ST, CPL, T, XT>(o, rem, ci, av, x, lw, col0, s);
         else
-            tail_accumulate<U / 2, CPL, T, XT>(o, st, rem, ci, av, x, lw, col0, s);
+            tail_accumulate<U / 2, ST, CPL, T, XT>(o, rem, ci, av, x, lw, col0, s);
     }
 }
 
@@ -169,14 +169,16 @@ __device__ __forceinline__ void tail_accumulate(int o, int st, int rem, const in
 // entries at a time.  (The lanes of a group load the same index and value;
 // plain loads keep the line in L2 for the group's next entries: non-temporal
 // loads made the 16-column engine 1.6x slower.)
-template <int U, int CPL, typename T, typename XT>
-__device__ __forceinline__ void row_accumulate(const RowIdx& R, int i, const int* __restrict__ ci,
+template <int U, int CPL, typename T, typename XT, class ROWS>
+__device__ __forceinline__ void row_accumulate(const ROWS& R, int i, const int* __restrict__ ci,
                                                const T* __restrict__ av, const XT* __restrict__ x, int lw, int col0,
                                                T (&s)[CPL]) {
-    const int len = R.len(i), st = R.stride();
+    constexpr int ST = ROWS::kStride;
+    const int len = R.len(i);
     int o = R.start(i), k = 0;
-    for (; k + U <= len; k += U, o += U * st) entries_accumulate<U, false, CPL, T, XT>(o, st, U, ci, av, x, lw, col0, s);
-    tail_accumulate<U, CPL, T, XT>(o, st, len - k, ci, av, x, lw, col0, s);
+    for (; k + U <= len; k += U, o += U * ST)
+        entries_accumulate<U, false, ST, CPL, T, XT>(o, U, ci, av, x, lw, col0, s);
+    tail_accumulate<U, ST, CPL, T, XT>(o, len - k, ci, av, x, lw, col0, s);
 }
 
 // Two rows at once (i and the next one): s0 and s1 as row_accumulate computes
@@ -189,11 +191,12 @@ __device__ __forceinline__ void row_accumulate(const RowIdx& R, int i, const int
 // row's entries contiguous a pair only widens the spread of the loads (550
 // thousand rows, FP32: 100 and 120; 227 thousand rows of 7, FP64: 21 and 27).
 constexpr int kPairRow = 16;                            // mean entries per row
-template <int H, int CPL, typename T, typename XT>
-__device__ __forceinline__ void row_pair_accumulate(const RowIdx& R, int i, const int* __restrict__ ci,
+template <int H, int CPL, typename T, typename XT, class ROWS>
+__device__ __forceinline__ void row_pair_accumulate(const ROWS& R, int i, const int* __restrict__ ci,
                                                     const T* __restrict__ av, const XT* __restrict__ x, int lw,
                                                     int col0, T (&s0)[CPL], T (&s1)[CPL]) {
-    const int len0 = R.len(i), len1 = R.len(i + 1), st = R.stride();
+    constexpr int st = ROWS::kStride;
+    const int len0 = R.len(i), len1 = R.len(i + 1);
     const int o0 = R.start(i), o1 = R.start(i + 1);
     const int most = max(len0, len1);
     for (int k = 0; k < most; k += H) {
@@ -228,8 +231,8 @@ __device__ __forceinline__ void row_pair_accumulate(const RowIdx& R, int i, cons
 
 // Down-sweep: rc[I] = sum_{m in G_I} p_m (r_m - (A D^-1 r)_m), per column.
 // PAIR: two members at a time (row_pair_accumulate).
-template <int U, int CPL, bool PAIR, typename T, typename RT>
-static __global__ __launch_bounds__(kBlock) void kb_down(int nc, int lw, RowIdx rows, const int* __restrict__ ci,
+template <int U, int CPL, bool PAIR, typename T, typename RT, class ROWS>
+static __global__ __launch_bounds__(kBlock) void kb_down(int nc, int lw, ROWS rows, const int* __restrict__ ci,
                                                   const T* __restrict__ vd, const RT* __restrict__ r,
                                                   const T* __restrict__ p, const int* __restrict__ aggptr,
                                                   T* __restrict__ rc, const int* __restrict__ done) {
@@ -276,8 +279,8 @@ static __global__ __launch_bounds__(kBlock) void kb_down(int nc, int lw, RowIdx 
 
 // Up-sweep at level l > 0: z = zp + D^-1 (r - A zp), prolongated into level
 // l-1: zp_f[m] = dinv_f[m] r_f[m] + p_f[m] z for the members m of row i.
-template <int U, int CPL, typename T, typename RT, typename RTF>
-static __global__ __launch_bounds__(kBlock) void kb_up(int n, int lw, RowIdx rows, const int* __restrict__ ci,
+template <int U, int CPL, typename T, typename RT, typename RTF, class ROWS>
+static __global__ __launch_bounds__(kBlock) void kb_up(int n, int lw, ROWS rows, const int* __restrict__ ci,
                                                 const T* __restrict__ av, const T* __restrict__ zp,
                                                 const RT* __restrict__ r, const T* __restrict__ dinv,
                                                 const int* __restrict__ aggptr_f, const RTF* __restrict__ r_f,
@@ -318,8 +321,8 @@ static __global__ __launch_bounds__(kBlock) void kb_up(int n, int lw, RowIdx row
 constexpr int kFixedLanes = 4;
 constexpr int kFixedRows = kBlock / kFixedLanes;
 
-template <int CPL, typename T>
-static __global__ __launch_bounds__(kBlock) void kb_up0(int n, RowIdx rows, const int* __restrict__ ci,
+template <int CPL, typename T, class ROWS>
+static __global__ __launch_bounds__(kBlock) void kb_up0(int n, ROWS rows, const int* __restrict__ ci,
                                                  const T* __restrict__ av, const T* __restrict__ zp,
                                                  const T* __restrict__ r, const T* __restrict__ dinv,
                                                  T* __restrict__ z_out, const double* __restrict__ dv,
@@ -571,8 +574,8 @@ static __global__ __launch_bounds__(kBlock) void kb_widen(long long cnt, int fro
 // p.q and p.r.  A column on its first iteration, or finished, takes q = A z
 // (an idle column's q stays bounded).  q holds q_old on entry; each element
 // is read before it is overwritten, by the same lane.  Fixed shape, as kb_up0.
-template <int CPL, typename ZT>
-static __global__ __launch_bounds__(kBlock) void kb_krylov_pq(int n, RowIdx rows, const int* __restrict__ ci,
+template <int CPL, typename ZT, class ROWS>
+static __global__ __launch_bounds__(kBlock) void kb_krylov_pq(int n, ROWS rows, const int* __restrict__ ci,
                                                        const double* __restrict__ av, const ZT* __restrict__ z,
                                                        const double* __restrict__ p_old, double* __restrict__ p_new,
                                                        double* __restrict__ q, const double* __restrict__ r,
@@ -870,7 +873,8 @@ static __global__ __launch_bounds__(kBlock) void kb_store(int n, int lw, const i
 
 // Y = B - A X (all columns) and per-column partials of y.y; with `commit`
 // set, columns in `mask` also take Y as their recurrence residual R.
-static __global__ __launch_bounds__(kBlock) void kb_resid(int n, int lw, RowIdx rows, const int* __restrict__ ci,
+template <class ROWS>
+static __global__ __launch_bounds__(kBlock) void kb_resid(int n, int lw, ROWS rows, const int* __restrict__ ci,
                                                    const double* __restrict__ av, const double* __restrict__ X,
                                                    const double* __restrict__ B, double* __restrict__ Y,
                                                    double* __restrict__ R, float* __restrict__ R32, int mask,
