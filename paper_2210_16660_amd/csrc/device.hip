@@ -691,18 +691,21 @@ static void launch_hgs(pamg_hierarchy* h, DevVals<T>& V, int l, const RT* r, con
         return;
     }
     const dim3 g(I.gs_nblk), blk(MAXB);
-    if (zero)
-        hipLaunchKernelGGL((k_hgs<MAXB, T, RT, false, true>), g, blk, 0, s, I.n, h->gs_block, I.row_idx(), (const int*)I.ci,
-                           (const T*)V.v[l], I.gs_fresh, (const T*)V.gsa[l], I.gs_df, I.gs_maxd, r,
-                           (const T*)nullptr, x_new, winv, done);
-    else if (backward)
-        hipLaunchKernelGGL((k_hgs<MAXB, T, T, true, false>), g, blk, 0, s, I.n, h->gs_block, I.row_idx(), (const int*)I.ci,
-                           (const T*)V.v[l], I.gs_fresh, (const T*)V.gsa[l], I.gs_db, I.gs_maxd, t, x_old, x_new,
-                           winv, done);
-    else
-        hipLaunchKernelGGL((k_hgs<MAXB, T, T, false, false>), g, blk, 0, s, I.n, h->gs_block, I.row_idx(), (const int*)I.ci,
-                           (const T*)V.v[l], I.gs_fresh, (const T*)V.gsa[l], I.gs_df, I.gs_maxd, t, x_old, x_new,
-                           winv, done);
+    with_rows(I, [&](auto where) {
+        using W = decltype(where);
+        if (zero)
+            hipLaunchKernelGGL((k_hgs<MAXB, T, RT, false, true, W>), g, blk, 0, s, I.n, h->gs_block, where,
+                               (const int*)I.ci, (const T*)V.v[l], I.gs_fresh, (const T*)V.gsa[l], I.gs_df, I.gs_maxd,
+                               r, (const T*)nullptr, x_new, winv, done);
+        else if (backward)
+            hipLaunchKernelGGL((k_hgs<MAXB, T, T, true, false, W>), g, blk, 0, s, I.n, h->gs_block, where,
+                               (const int*)I.ci, (const T*)V.v[l], I.gs_fresh, (const T*)V.gsa[l], I.gs_db, I.gs_maxd,
+                               t, x_old, x_new, winv, done);
+        else
+            hipLaunchKernelGGL((k_hgs<MAXB, T, T, false, false, W>), g, blk, 0, s, I.n, h->gs_block, where,
+                               (const int*)I.ci, (const T*)V.v[l], I.gs_fresh, (const T*)V.gsa[l], I.gs_df, I.gs_maxd,
+                               t, x_old, x_new, winv, done);
+    });
 }
 
 // `sweeps` hybrid Gauss-Seidel sweeps at level l on A_l x = r: forward from

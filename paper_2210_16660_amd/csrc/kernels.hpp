@@ -79,6 +79,8 @@ struct CsrRows {
     const int* rp;
     __device__ __forceinline__ int len(int i) const { return rp[i + 1] - rp[i]; }
     __device__ __forceinline__ int start(int i) const { return rp[i]; }
+    // where the row's entry of CSR index k is
+    __device__ __forceinline__ int entry(int, int k) const { return k; }
 };
 struct SlicedRows {
     static constexpr int kStride = kSlice;
@@ -86,6 +88,7 @@ struct SlicedRows {
     const int* pos;
     __device__ __forceinline__ int len(int i) const { return rp[i + 1] - rp[i]; }
     __device__ __forceinline__ int start(int i) const { return pos[i]; }
+    __device__ __forceinline__ int entry(int i, int k) const { return pos[i] + (k - rp[i]) * kStride; }
 };
 
 // a and b (uniform) have both been asked for when either is waited for: their

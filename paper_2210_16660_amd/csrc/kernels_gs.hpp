@@ -37,9 +37,9 @@ constexpr double kGsDenseBytes = 64 << 20;
 // pre-smoothing sweep).  Row i of the block: d_i = (t_i - sum_{fresh j}
 // a_ij d_j) / a_ii with fresh = in the block and earlier (forward) / later
 // (backward), in column order; x_new = x_old + d / omega.
-template <int MAXB, typename T, typename TT, bool BACKWARD, bool ZERO>
+template <int MAXB, typename T, typename TT, bool BACKWARD, bool ZERO, class ROWS>
 static __global__ __launch_bounds__(MAXB) void k_hgs(
-    int n, int nb, RowIdx R, const int* __restrict__ ci, const T* __restrict__ av, const int2* __restrict__ fr,
+    int n, int nb, ROWS R, const int* __restrict__ ci, const T* __restrict__ av, const int2* __restrict__ fr,
     const T* __restrict__ ainv, const uint8_t* __restrict__ depth, const int* __restrict__ maxd,
     const TT* __restrict__ tin, const T* __restrict__ x_old, T* __restrict__ x_new, T omega_inv,
     const int* __restrict__ done) {
@@ -49,16 +49,14 @@ static __global__ __launch_bounds__(MAXB) void k_hgs(
     const int b0 = p * nb, b1 = min(n, b0 + nb);
     const int i = b0 + t;
     const bool own = t < nb && i < b1;
-    const int st = R.stride();
+    constexpr int st = ROWS::kStride;
     int dep = -1, nf = 0, kf = 0;
     T ti = 0, xi = 0, ai = 0;
     if (own) {
         const int2 f = fr[i];
         const int before = f.y & 0xff, after = (f.y >> 8) & 0xff, diag = (f.y >> 16) & 1;
         nf = BACKWARD ? after : before;
-        // in-block entries of the row: kf, kf + st, ...
-        const int k = f.x - R.rp[i] + (BACKWARD ? before + diag : 0);
-        kf = R.start(i) + k * st;
+        kf = R.entry(i, f.x + (BACKWARD ? before + diag : 0));     // in-block entries: kf, kf + st, ...
         ti = (T)tin[i];
         ai = ainv[i];
         dep = depth[i];
