@@ -143,7 +143,7 @@ bool gs_dense_level(const pamg_hierarchy* h, int l) {
     if (h->smoother != PAMG_SMOOTHER_HYBRID_GS || l >= h->L || I.nnz < (long long)kGsDenseRow * I.n) return false;
     const double m = (double)I.gs_inblock / I.n;
     const double bytes = 8.0 * (double)I.gs_nblk * (double)gs_dense_block(h->gs_block);
-    return m >= kGsDenseInBlock || (m >= kGsDenseFew && bytes <= kGsDenseBytes);
+    return m >= kGsDenseInBlock || bytes <= std::pow(4.0, m - 3.0) * (1 << 20);
 }
 
 static long long gs_inblock(const std::vector<int32_t>& fresh) {

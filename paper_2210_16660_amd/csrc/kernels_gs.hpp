@@ -27,11 +27,10 @@ static_assert(kGsFresh % 4 == 0, "the substitution reads its slots in groups of 
 constexpr int kGsBatch = 8;           // entries past those loaded together in a depth step
 // Levels whose blocks are inverted (gs_dense_level; the figures are at k_hgs_dense):
 // rows of kGsDenseRow entries or more on average, and before a row in its block
-// kGsDenseInBlock on average, kGsDenseFew where the inverses of a direction
-// take at most kGsDenseBytes.
+// kGsDenseInBlock on average, or m < kGsDenseInBlock where the inverses of a
+// direction take at most 4^(m - 3) MB (m = 5: 16 MB, 6: 64 MB).
 constexpr int kGsDenseRow = 64;
-constexpr double kGsDenseInBlock = 8.0, kGsDenseFew = 6.0;
-constexpr double kGsDenseBytes = 64 << 20;
+constexpr double kGsDenseInBlock = 8.0;
 
 // One sweep from t = r - A x_old (ZERO: x_old = 0 and t = r, the first
 // pre-smoothing sweep).  Row i of the block: d_i = (t_i - sum_{fresh j}
@@ -142,6 +141,8 @@ static __global__ __launch_bounds__(MAXB) void k_hgs(
 // its tiles, which a block of less than 64 rows fills badly (32 KB a block, 4 KB
 // a row at nb = 8).  A sweep, substitution -> product, us (both with the
 // residual's pass), m the mean entries before a row in its block:
+//   2,912 rows of 339:    nb 8, m 3.1, 12 -> 11; nb 16, m 5.6, 13 -> 11;
+//                         nb 32, m 10, 28 -> 10
 //   23,032 rows of 121:   nb 16, m 5.4, FP64 16 -> 19, FP32 14 -> 12;
 //                         nb 24, m 7.5, 21 -> 15; nb 64, m 15, 76 -> 13
 //   262 thousand of 118:  nb 8, m 2.7, 105 -> 238; nb 24, m 6.7, 95 -> 127;

@@ -63,14 +63,15 @@ def wide_band(n, reach, seed):
 
 @pytest.mark.parametrize("device", [0, 1])
 def test_blocks_that_do_not_pay_are_not_inverted(device):
-    """Device bytes beyond the block schedule (8 bytes a block) do not grow as blocks shrink."""
+    """Device bytes beyond the block schedule (8 bytes a block) do not grow as blocks shrink, but
+    for small inverses (16 MB a level at five entries before a row)."""
     for A, kw in ((stencil125(22, 5), {}), (q1_stretched(16, 1.05), dict(agg_steps=3, smooth_prolongator=1))):
         size = {}
         for nb in (1, 8, 16, 256):
             H = pamg.Hierarchy(A, smoother="hgs", gs_block=nb, build_f32=1, device_setup=device, **kw)
             rows = sum(H.level_sizes()[0])
             size[nb] = H.info().device_bytes
-        assert max(size[1], size[8], size[16]) <= size[256] + 16 * rows, size
+        assert max(size[1], size[8], size[16]) <= size[256] + 16 * rows + (20 << 20), size
     B = scattered(12000, 6)                       # half a coupling in the block on average
     size = {nb: pamg.Hierarchy(B, smoother="hgs", gs_block=nb, max_levels=2, device_setup=device).info().device_bytes
             for nb in (1, 64, 256)}
