@@ -73,12 +73,11 @@ struct SellRows {
                                     // dictionary length, first coarse row, end coarse row, 0
     std::vector<uint32_t> slot;     // per sorted position: row - first row of its tile | length << 16
     std::vector<int32_t> rowpos;    // per row: its first entry (entry k: rowpos + kSlice k)
-    std::vector<int32_t> ci;        // columns, padded
     std::vector<int32_t> col;       // the dictionaries, tile after tile
-    std::vector<uint16_t> local;    // per (padded) entry: position of its column in its tile's dictionary
+    std::vector<uint16_t> local;    // per CSR entry: position of its column in its tile's dictionary
+    int64_t entries = 0;            // stored, with the padding (the upload places the entries, ks_fill)
     int32_t max_len = 0;            // longest dictionary
     int32_t xcd[9] = {};            // first tile of each of 8 equal shares of the rows, and the end
-    int64_t entries() const { return (int64_t)ci.size(); }
 };
 
 // A CSR matrix's row tiles (<= kTileRows rows and <= items * kBlock entries,
@@ -184,8 +183,6 @@ SellRows sell_rows(const std::vector<int32_t>& rp, const std::vector<int32_t>& c
 // First tile of each of 8 equal shares of the n rows (tiles: stride ints per
 // tile, the first row first).
 void sell_shares(const std::vector<int32_t>& tiles, int stride, int32_t n, int32_t xcd[9]);
-// Values in CSR order as the slices store them.
-std::vector<double> sell_values(const SellRows& S, const std::vector<int32_t>& rp, const std::vector<double>& v);
 
 // Smoothed prolongator of level l in hierarchical numbering (P and P^T).
 void sa_layout(const HostCSR& P, const LayoutLevel& fine, const LayoutLevel& coarse, LayoutLevel& out);

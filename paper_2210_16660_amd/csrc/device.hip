@@ -33,6 +33,30 @@ static T* upload(pamg_hierarchy* h, const std::vector<S>& src, hipStream_t s) {
     return d;
 }
 
+// Entries of a host-built level in CSR order, placed in its sliced rows (padding:
+// zero) on the device.
+template <typename T, typename S>
+static T* upload_slices(pamg_hierarchy* h, const DevLevelIdx& I, const std::vector<S>& src, hipStream_t s) {
+    T* d = dalloc<T>(h, I.nent, s);
+    const std::vector<T> conv = std::is_same<T, S>::value ? std::vector<T>() : std::vector<T>(src.begin(), src.end());
+    const void* from = std::is_same<T, S>::value ? (const void*)src.data() : (const void*)conv.data();
+    const size_t bytes = src.size() * sizeof(T);
+    struct Csr {
+        pamg_context* ctx;
+        hipStream_t s;
+        void* p;
+        size_t bytes;
+        ~Csr() { ctx_free(ctx, p, bytes, s); }
+    } csr{h->ctx, s, ctx_alloc(h->ctx, bytes, s), bytes};
+    HIP_CHECK(hipMemcpyAsync(csr.p, from, bytes, hipMemcpyHostToDevice, s));
+    HIP_CHECK(hipMemsetAsync(d, 0, I.nent * sizeof(T), s));
+    hipLaunchKernelGGL((ks_fill<T, false>), dim3(sell_fill_grid(I.sv.ntiles)), dim3(64), 0, s, I.sv, (const int*)I.rp,
+                       (const int*)nullptr, (const T*)csr.p, d);
+    HIP_CHECK(hipGetLastError());
+    HIP_CHECK(hipStreamSynchronize(s));
+    return d;
+}
+
 // A device array converted to another precision (the FP32 copy of a
 // device-built level: each value rounded as on the host).
 template <typename D, typename S>
@@ -72,10 +96,10 @@ static void upload_values(pamg_hierarchy* h, DevVals<T>& V, const std::vector<La
         } else {
             const LayoutLevel& Ly = lay[l - m];
             const bool sell = !Ly.sell.tiles.empty();
-            V.v[l] = sell ? upload<T>(h, sell_values(Ly.sell, Ly.rp, Ly.v), s) : upload<T>(h, Ly.v, s);
+            V.v[l] = sell ? upload_slices<T>(h, h->idx[l], Ly.v, s) : upload<T>(h, Ly.v, s);
             V.dinv[l] = upload<T>(h, Ly.dinv, s);
             if (l + 1 < nl) {
-                V.vd[l] = sell ? upload<T>(h, sell_values(Ly.sell, Ly.rp, Ly.vd), s) : upload<T>(h, Ly.vd, s);
+                V.vd[l] = sell ? upload_slices<T>(h, h->idx[l], Ly.vd, s) : upload<T>(h, Ly.vd, s);
                 V.p[l] = upload<T>(h, Ly.p, s);
             }
         }
@@ -277,16 +301,20 @@ void upload_hierarchy(pamg_hierarchy* h, const std::vector<LayoutLevel>& lay, bo
         I.nc = (l + 1 < nl) ? (int)lay[l + 1 - m].dinv.size() : 0;
         I.items = Ly.items;
         I.rp = upload<int>(h, Ly.rp, s);
-        I.ci = upload<int>(h, Ly.sell.tiles.empty() ? Ly.ci : Ly.sell.ci, s);
-        I.nent = Ly.sell.tiles.empty() ? I.nnz : Ly.sell.entries();
+        I.nent = I.nnz;
         I.perm = upload<int>(h, Ly.perm, s);
         I.iperm = upload<int>(h, Ly.iperm, s);
-        if (!Ly.sell.tiles.empty()) {
+        if (Ly.sell.tiles.empty()) {
+            I.ci = upload<int>(h, Ly.ci, s);
+        } else {
             const SellRows& S = Ly.sell;
             I.sell = true;
+            I.nent = S.entries;
             I.sv = {reinterpret_cast<const int4*>(upload<int>(h, S.tiles, s)), (int)(S.tiles.size() / 8), {},
-                    upload<uint32_t>(h, S.slot, s), upload<int>(h, S.col, s), upload<uint16_t>(h, S.local, s)};
+                    upload<uint32_t>(h, S.slot, s), upload<int>(h, S.col, s), nullptr};
             std::copy(S.xcd, S.xcd + 9, I.sv.xcd);
+            I.sv.loc = upload_slices<uint16_t>(h, I, S.local, s);
+            I.ci = upload_slices<int>(h, I, Ly.ci, s);
             I.rowpos = upload<int>(h, S.rowpos, s);
             I.sell_dmax = std::max(1, (int)S.max_len);
             I.sell_dlen = (long long)S.col.size();

@@ -84,53 +84,6 @@ static __global__ __launch_bounds__(kBlock) void k_diag_inverse(int n, RowIdx R,
     }
 }
 
-// Values of a level in sliced rows, from the canonical entry of every entry in
-// row order (the padding keeps the setup's zeros).  A wave takes 64 sorted rows
-// of a tile: a whole row at a time (kGatherStep entries of a longer one) is read
-// by 8, 16 or 32 lanes, so that its entries, neighbours in vc, cost their lines
-// once; the values turn in LDS and are written step by step, coalesced.  Level 0
-// of 56.6 million entries: 1010 us step by step over the whole level with an
-// index per stored entry, 430 to 480 with 8 or 16 entries of 256 rows at a time
-// (a row's lines are gone from L2 by its next step), now 265.
-constexpr int kGatherStep = 32;
-static __global__ __launch_bounds__(64) void k_gather_slices(SellView V, const int* __restrict__ rp,
-                                                             const int* __restrict__ idx,
-                                                             const double* __restrict__ vc, double* __restrict__ v) {
-    constexpr int W = kSlice / 64, U = 8;
-    __shared__ double s_v[kGatherStep][64 + 1];
-    const int lane = threadIdx.x;
-    for (int w = blockIdx.x; w < W * V.ntiles; w += gridDim.x) {
-        const int4 d = V.tiles[2 * (w / W)];
-        const int p0 = w % W * 64, m = min(64, d.y - d.x - p0);
-        if (m <= 0) continue;
-        const uint32_t q = V.slot[d.x + p0 + min(lane, m - 1)];                 // lanes past the rows repeat the last
-        const int len = (int)(q >> 16), b = rp[d.x + (int)(q & 0xffff)];
-        const int longest = __builtin_amdgcn_readfirstlane(len);
-        const int lg = longest > 16 ? 5 : longest > 8 ? 4 : 3, rows = 64 >> lg;
-        const int u = lane & ((1 << lg) - 1), g = lane >> lg;
-        for (int k0 = 0; k0 < longest; k0 += kGatherStep) {
-            for (int r0 = g; r0 < 64; r0 += U * rows) {
-                int c[U], n[U];
-                double x[U];
-#pragma unroll
-                for (int y = 0; y < U; ++y) {
-                    n[y] = __shfl(len, r0 + y * rows);
-                    c[y] = idx[__shfl(b, r0 + y * rows) + min(k0 + u, n[y] - 1)];
-                }
-#pragma unroll
-                for (int y = 0; y < U; ++y) x[y] = vc[c[y]];
-#pragma unroll
-                for (int y = 0; y < U; ++y)
-                    if (k0 + u < n[y]) s_v[u][r0 + y * rows] = x[y];
-            }
-            __syncthreads();
-            for (int k = 0; k < min(kGatherStep, longest - k0); ++k)
-                if (lane < m && k0 + k < len) v[(size_t)d.z + (size_t)(k0 + k) * kSlice + p0 + lane] = s_v[k][lane];
-            __syncthreads();
-        }
-    }
-}
-
 // The pairwise chain behind the kept levels: pattern, aggregates and p of
 // pairwise level m.
 struct ChainView {
@@ -255,8 +208,8 @@ static void update_values(pamg_hierarchy* h, const double* val, bool on_device, 
         hipLaunchKernelGGL((k_gather<double, double>), dim3(vec_grid(I.n)), dim3(kBlock), 0, s, I.n,
                            (const int*)I.iperm, (const double*)R.dcan[j], V.dinv[j]);
         if (I.sell)
-            hipLaunchKernelGGL(k_gather_slices, dim3(std::min(kSlice / 64 * I.sv.ntiles, 16 * kMaxGrid)), dim3(64), 0, s,
-                               I.sv, (const int*)I.rp, (const int*)R.hperm[j], vc, V.v[j]);
+            hipLaunchKernelGGL((ks_fill<double, true>), dim3(sell_fill_grid(I.sv.ntiles)), dim3(64), 0, s, I.sv,
+                               (const int*)I.rp, (const int*)R.hperm[j], vc, V.v[j]);
         else
             hipLaunchKernelGGL((k_gather<double, double>), dim3(vec_grid(I.nnz)), dim3(kBlock), 0, s, (int)I.nnz,
                                (const int*)R.hperm[j], vc, V.v[j]);

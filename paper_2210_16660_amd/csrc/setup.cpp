@@ -1159,17 +1159,20 @@ SellRows sell_rows(const std::vector<int32_t>& rp, const std::vector<int32_t>& c
     };
     std::vector<PosBuf> pbuf(num_threads());
     std::vector<std::vector<int32_t>> dict;
-    std::vector<uint16_t> local(ci.size());
+    S.local.resize(ci.size());
+    std::vector<int32_t> size;
     for (;;) {
         const int64_t nt = (int64_t)tiles.size() / 4;
         // (cutting a tile never stores less)
-        int64_t padded = 0;
-        for (int64_t t = 0; t < nt; ++t) {
-            int32_t longest = 0;
-            for (int32_t i = tiles[4 * t]; i < tiles[4 * t + 1]; ++i) longest = std::max(longest, rp[i + 1] - rp[i]);
-            padded += (int64_t)kSlice * longest;
-        }
-        if (!sell_fits(padded, rp[n])) return SellRows();
+        size.assign(nt, 0);
+        parallel_ranges(nt, [&](int, int64_t b, int64_t e) {
+            for (int64_t t = b; t < e; ++t) {
+                int32_t longest = 0;
+                for (int32_t i = tiles[4 * t]; i < tiles[4 * t + 1]; ++i) longest = std::max(longest, rp[i + 1] - rp[i]);
+                size[t] = kSlice * longest;
+            }
+        });
+        if (!sell_fits(std::accumulate(size.begin(), size.end(), (int64_t)0), rp[n])) return SellRows();
         dict.assign(nt, {});
         std::vector<int32_t> dlen(nt, 0);
         parallel_chunks(nt, 4, [&](int th, int64_t b, int64_t e) {
@@ -1185,7 +1188,7 @@ SellRows sell_rows(const std::vector<int32_t>& rp, const std::vector<int32_t>& c
                     }
                 std::sort(u.begin(), u.end());
                 for (size_t j = 0; j < u.size(); ++j) pos[u[j]] = (int32_t)j;
-                for (int32_t k = k0; k < k1; ++k) local[k] = (uint16_t)pos[ci[k]];
+                for (int32_t k = k0; k < k1; ++k) S.local[k] = (uint16_t)pos[ci[k]];
                 for (int32_t c : u) pos[c] = -1;
                 dlen[t] = (int32_t)u.size();
             }
@@ -1193,24 +1196,22 @@ SellRows sell_rows(const std::vector<int32_t>& rp, const std::vector<int32_t>& c
         if (!split_sell_tiles(tiles, aggptr, nc, dlen)) break;
     }
     const int64_t nt = (int64_t)tiles.size() / 4;
-    int64_t total = 0, at = 0;
+    int64_t total = 0;
     S.tiles.resize(8 * nt);
     for (int64_t t = 0; t < nt; ++t) {
-        const int32_t r0 = tiles[4 * t], r1 = tiles[4 * t + 1], len = (int32_t)dict[t].size();
-        int32_t longest = 0;
-        for (int32_t i = r0; i < r1; ++i) longest = std::max(longest, rp[i + 1] - rp[i]);
-        const int32_t d[8] = {r0, r1, (int32_t)at, (int32_t)total, len, tiles[4 * t + 2], tiles[4 * t + 3], 0};
+        const int32_t len = (int32_t)dict[t].size();
+        const int32_t d[8] = {tiles[4 * t],   tiles[4 * t + 1], (int32_t)S.entries,
+                              (int32_t)total, len,              tiles[4 * t + 2],
+                              tiles[4 * t + 3], 0};
         std::copy(d, d + 8, S.tiles.begin() + 8 * t);
         S.max_len = std::max(S.max_len, len);
         total += len;
-        at += (int64_t)kSlice * longest;
+        S.entries += size[t];
     }
     sell_shares(S.tiles, 8, n, S.xcd);
     S.col.resize(total);
     S.slot.resize(n);
     S.rowpos.resize(n);
-    S.ci.assign(at, 0);
-    S.local.assign(at, 0);
     parallel_ranges(nt, [&](int, int64_t b, int64_t e) {
         std::vector<int32_t> order;
         for (int64_t t = b; t < e; ++t) {
@@ -1221,26 +1222,12 @@ SellRows sell_rows(const std::vector<int32_t>& rp, const std::vector<int32_t>& c
             const auto len = [&](int32_t j) { return rp[r0 + j + 1] - rp[r0 + j]; };
             std::stable_sort(order.begin(), order.end(), [&](int32_t x, int32_t y) { return len(x) > len(y); });
             for (int32_t q = 0; q < rows; ++q) {
-                const int32_t i = r0 + order[q], o = S.tiles[8 * t + 2] + q;
                 S.slot[r0 + q] = (uint32_t)order[q] | (uint32_t)len(order[q]) << 16;
-                S.rowpos[i] = o;
-                for (int32_t k = rp[i]; k < rp[i + 1]; ++k) {
-                    S.ci[o + (int64_t)(k - rp[i]) * kSlice] = ci[k];
-                    S.local[o + (int64_t)(k - rp[i]) * kSlice] = local[k];
-                }
+                S.rowpos[r0 + order[q]] = S.tiles[8 * t + 2] + q;
             }
         }
     });
     return S;
-}
-
-std::vector<double> sell_values(const SellRows& S, const std::vector<int32_t>& rp, const std::vector<double>& v) {
-    std::vector<double> out(S.entries(), 0.0);
-    parallel_ranges((int64_t)S.rowpos.size(), [&](int, int64_t b, int64_t e) {
-        for (int64_t i = b; i < e; ++i)
-            for (int32_t k = rp[i]; k < rp[i + 1]; ++k) out[S.rowpos[i] + (int64_t)(k - rp[i]) * kSlice] = v[k];
-    });
-    return out;
 }
 
 // Row tiles of an n-row matrix with ncols columns, capacity chosen as for a

@@ -3,8 +3,9 @@
 // which levels are stored that way:
 //  * even rows: the tiles cover the rows in order, whole aggregates, at most
 //    256 rows; inside a tile the rows are sorted by length, ties in row order;
-//    every entry is at rowpos + 256 k with its column, and its position names
-//    that column in the tile's dictionary (sorted, no longer than 2048);
+//    every row's entries start at its position in the tile, and an entry's
+//    position names its column in the tile's dictionary (sorted, no longer than
+//    2048);
 //  * the same with scattered rows, whose tiles are cut for their dictionaries;
 //  * never more than 1.4 times the entries: uneven rows and badly scattered
 //    ones are not stored this way at all;
@@ -69,8 +70,8 @@ static void check_tiles(const char* name, const Case& c, const SellRows& S, int*
     const int64_t nt = (int64_t)S.tiles.size() / 8;
     CHECK(nt > 0, "%s: not stored in sliced rows", name);
     if (nt == 0) return;
-    CHECK(5 * S.entries() <= 7 * (int64_t)c.ci.size(), "%s: %lld stored for %zu entries", name,
-          (long long)S.entries(), c.ci.size());
+    CHECK(5 * S.entries <= 7 * (int64_t)c.ci.size(), "%s: %lld stored for %zu entries", name,
+          (long long)S.entries, c.ci.size());
     int32_t row = 0, coarse = 0;
     int64_t at = 0, dict = 0;
     *most = 0;
@@ -99,15 +100,14 @@ static void check_tiles(const char* name, const Case& c, const SellRows& S, int*
             lastrow = i;
             longest = std::max(longest, len);
             for (int32_t k = 0; k < len; ++k) {
-                const int64_t e = S.rowpos[i] + (int64_t)kSlice * k;
-                CHECK(S.ci[e] == c.ci[c.rp[i] + k] && S.local[e] < d[4] && S.col[d[3] + S.local[e]] == S.ci[e],
-                      "%s row %d entry %d", name, i, k);
+                const int32_t e = c.rp[i] + k;
+                CHECK(S.local[e] < d[4] && S.col[d[3] + S.local[e]] == c.ci[e], "%s row %d entry %d", name, i, k);
             }
         }
         at += (int64_t)kSlice * longest;
         dict += d[4];
     }
-    CHECK(row == c.n && at == S.entries() && dict == (int64_t)S.col.size(), "%s: covered", name);
+    CHECK(row == c.n && at == S.entries && dict == (int64_t)S.col.size(), "%s: covered", name);
 }
 
 int main() {
