@@ -124,7 +124,7 @@ inline int unit_grid(long long nunits, int gpb) {
 // s[q] += the next U entries of a row, in entry order, of a_k x[c_k][col0 + q],
 // all their loads in flight together; TAIL: only the first rem of them (the
 // others repeat the last one's loads and are left out of the sum).
-template <int U, bool TAIL, int ST, int CPL, typename T, typename XT>
+template <int U, bool TAIL, int ST, int CPL, typename T, typename XT, bool APART = false>
 __device__ __forceinline__ void entries_accumulate(int o, int rem, const int* __restrict__ ci,
                                                    const T* __restrict__ av, const XT* __restrict__ x, int lw,
                                                    int col0, T (&s)[CPL]) {
@@ -137,6 +137,7 @@ __device__ __forceinline__ void entries_accumulate(int o, int rem, const int* __
     Vec<XT, CPL> xv[U];
 #pragma unroll
     for (int u = 0; u < U; ++u) xv[u] = vload<XT, CPL>(x + ((size_t)c[u] << lw) + col0);
+    if constexpr (APART) __builtin_amdgcn_sched_barrier(0);   // every gather is issued before the first sum
 #pragma unroll
     for (int u = 0; u < U; ++u)
 #pragma unroll
@@ -169,7 +170,9 @@ __device__ __forceinline__ void tail_accumulate(int o, int rem, const int* __res
 // entries at a time.  (The lanes of a group load the same index and value;
 // plain loads keep the line in L2 for the group's next entries: non-temporal
 // loads made the 16-column engine 1.6x slower.)
-template <int U, int CPL, typename T, typename XT, class ROWS>
+// APART keeps the compiler from moving sums in between the gathers to save
+// registers.
+template <int U, int CPL, typename T, typename XT, bool APART = false, class ROWS>
 __device__ __forceinline__ void row_accumulate(const ROWS& R, int i, const int* __restrict__ ci,
                                                const T* __restrict__ av, const XT* __restrict__ x, int lw, int col0,
                                                T (&s)[CPL]) {
@@ -177,7 +180,7 @@ __device__ __forceinline__ void row_accumulate(const ROWS& R, int i, const int* 
     const int len = R.len(i);
     int o = R.start(i), k = 0;
     for (; k + U <= len; k += U, o += U * ST)
-        entries_accumulate<U, false, ST, CPL, T, XT>(o, U, ci, av, x, lw, col0, s);
+        entries_accumulate<U, false, ST, CPL, T, XT, APART>(o, U, ci, av, x, lw, col0, s);
     tail_accumulate<U, ST, CPL, T, XT>(o, len - k, ci, av, x, lw, col0, s);
 }
 
@@ -574,6 +577,10 @@ static __global__ __launch_bounds__(kBlock) void kb_widen(long long cnt, int fro
 // p.q and p.r.  A column on its first iteration, or finished, takes q = A z
 // (an idle column's q stays bounded).  q holds q_old on entry; each element
 // is read before it is overwritten, by the same lane.  Fixed shape, as kb_up0.
+// Bound by the gathered rows of z.  With four columns a lane eight gathers take
+// 64 registers, and the compiler put sums between them to stay within 128: one
+// to three gathers in flight, 907 us (128^3 trilinear, 16 columns, FP64 z; FP32
+// 629); kept apart 132 registers, all eight in flight, 755 us (590).
 template <int CPL, typename ZT, class ROWS>
 static __global__ __launch_bounds__(kBlock) void kb_krylov_pq(int n, ROWS rows, const int* __restrict__ ci,
                                                        const double* __restrict__ av, const ZT* __restrict__ z,
@@ -601,7 +608,7 @@ static __global__ __launch_bounds__(kBlock) void kb_krylov_pq(int n, ROWS rows, 
         double s[CPL];
 #pragma unroll
         for (int c = 0; c < CPL; ++c) s[c] = 0.0;
-        row_accumulate<8, CPL, double, ZT>(rows, i, ci, av, z, lw, col0, s);
+        row_accumulate<8, CPL, double, ZT, CPL == 4>(rows, i, ci, av, z, lw, col0, s);
         const size_t e = ((size_t)i << lw) + col0;
         const Vec<ZT, CPL> zi = vload<ZT, CPL>(z + e);
         const Vec<double, CPL> po = vload<double, CPL>(p_old + e);
