@@ -12,8 +12,8 @@
 // The vector is gathered once per tile, at the tile's distinct columns (its
 // dictionary), into LDS; an entry reads its value through a 16-bit position.
 // These passes are bound by HBM traffic, the matrix stream and the gathers that
-// miss L2 (5.8 GB a Krylov pass of 16.9 M rows and 453 M entries, 6.6 GB in the
-// dictionary tiles of the smaller levels): in those, 4096 entries are staged
+// miss L2 (counters: 6.4 GB a Krylov pass of 16.9 M rows and 453 M entries, 6.9 GB
+// in the dictionary tiles of the smaller levels): in those, 4096 entries are staged
 // through LDS as products, so about 150 rows of the 27-point operator share a
 // dictionary, 4.9 gathers a row; 256 rows take 4.1.  Without the products the
 // kernels need 80 registers and 18 KB of LDS, six workgroups per CU in place of
